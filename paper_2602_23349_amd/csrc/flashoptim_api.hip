@@ -270,7 +270,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     std::memset(&a, 0, sizeof(a));
     a.c = c;
     a.sqrt_min_word = sqrt_min_word;
-    const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems : fo::chunk_elems(kind);
+    const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems : fo::chunk_elems(kind, split, quant);
     // one workgroup per chunk: the launch grid is a 31-bit count
     int64_t total_chunks = 0;
     for (const TensorDev& d : live) total_chunks += (d.numel + ce - 1) / ce;
@@ -1080,7 +1080,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     if (!adamw_consts(hp, c)) return FLASHOPTIM_ERR_INVALID_ARG;
     int rc = validate_tensors(tensors, n_tensors, true);
     if (rc != FLASHOPTIM_OK) return rc;
-    const int64_t ce = fo::chunk_elems(FLASHOPTIM_ADAMW);
+    const int64_t ce = fo::chunk_elems(FLASHOPTIM_ADAMW, true, true);
     int64_t n_live = 0, total_tiles = 0, only = -1;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (tensors[i].numel == 0) continue;
@@ -1169,7 +1169,7 @@ int flashoptim_last_hip_error(void) { return g_last_hip_error; }
 
 int64_t flashoptim_step_launch_count(int kind, const int64_t* numels, int64_t n_tensors) {
     if (kind < 0 || kind > 2 || n_tensors < 0 || (n_tensors > 0 && !numels)) return FLASHOPTIM_ERR_INVALID_ARG;
-    const int64_t ce = fo::chunk_elems(kind);
+    const int64_t ce = fo::chunk_elems(kind, true, true);
     int64_t tiles = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (numels[i] < 0 || numels[i] >= kMaxNumel) return FLASHOPTIM_ERR_NUMEL_RANGE;

@@ -93,8 +93,8 @@ __device__ __forceinline__ void st128(void* p, uint32_t a, uint32_t b, uint32_t 
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 
-// Maximum over the lanes that share a 32-element group: a lane pair (16 elements per lane)
-// or a lane quad (8 per lane).  Each step is ONE instruction, v_max_f32 with its first operand taken
+// Maximum over the lanes that share a 32-element group: a lane pair (16 elements per lane),
+// a lane quad (8 per lane) or two quads (4 per lane).  Each step is ONE instruction, v_max_f32 with its first operand taken
 // from the neighbouring lane through a DPP quad permute (written as inline assembly: from the
 // builtin the compiler makes a DPP move, two canonicalising maxima and the maximum itself).  The
 // s_nop covers the two wait states a DPP read needs after the instruction that wrote its source.
@@ -109,10 +109,19 @@ __device__ __forceinline__ float max_across_pair_of_pairs(float x) {
     asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x));
     return r;
 }
+// After the first two steps the four lanes of a quad agree, so mirroring each run of eight lanes brings every
+// lane the other quad's value.
+__device__ __forceinline__ float max_across_two_quads(float x) {
+    float r;
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(x));
+    return r;
+}
 template <int VEC>
 __device__ __forceinline__ float group_max(float x) {
+    static_assert(VEC == 4 || VEC == 8 || VEC == 16, "lanes per group: 8, 4 or 2");
     x = max_across_lane_pair(x);
-    if (VEC == 8) x = max_across_pair_of_pairs(x);
+    if (VEC <= 8) x = max_across_pair_of_pairs(x);
+    if (VEC == 4) x = max_across_two_quads(x);
     return x;
 }
 
@@ -429,7 +438,7 @@ __device__ __forceinline__ uint32_t block_local(uint32_t v) {
 // 4 * N bytes from / to base + byte_off (4N-byte aligned, N <= 4)
 template <int N>
 __device__ __forceinline__ void gld(uint32_t (&w)[N], gcptr_t base, uint32_t byte_off) {
-    static_assert(N == 2 || N == 4, "");
+    static_assert(N == 1 || N == 2 || N == 4, "");
     typedef uint32_t vec_t __attribute__((ext_vector_type(N)));
     typedef const __attribute__((address_space(1))) vec_t* vptr_t;
 #if FO_NT_LOAD
@@ -442,7 +451,7 @@ __device__ __forceinline__ void gld(uint32_t (&w)[N], gcptr_t base, uint32_t byt
 }
 template <int N>
 __device__ __forceinline__ void gst(gptr_t base, uint32_t byte_off, const uint32_t (&w)[N]) {
-    static_assert(N == 2 || N == 4, "");
+    static_assert(N == 1 || N == 2 || N == 4, "");
     typedef uint32_t vec_t __attribute__((ext_vector_type(N)));
     typedef __attribute__((address_space(1))) vec_t* vptr_t;
     vec_t v;
@@ -482,29 +491,23 @@ __device__ __forceinline__ void gst_words(gptr_t base, uint32_t byte_off, const 
         }
     }
 }
-// FP32 streams (ablation variants): VEC floats per lane are two or more 16-byte accesses, each of
-// which covers only part of every cache line the wavefront touches.  These go without the
-// non-temporal hint: with it the line is not kept between the two accesses and is fetched
-// twice (measured 26.8 vs 19.9 ms for the variant with FP32 weights on the Llama list).
-template <int VEC>
-__device__ __forceinline__ void gld_floats(float (&f)[VEC], gcptr_t base, uint32_t byte_off) {
-    static_assert(VEC % 4 == 0, "");
-    typedef float vec_t __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int k = 0; k < VEC / 4; ++k) {
-        const vec_t v = *(const __attribute__((address_space(1))) vec_t*)(base + byte_off + 16u * k);
-        f[4 * k] = v[0]; f[4 * k + 1] = v[1]; f[4 * k + 2] = v[2]; f[4 * k + 3] = v[3];
-    }
+// FP32 streams: four floats per lane, so that one access of a wavefront covers 1 KB of consecutive bytes.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void gld_floats(float (&f)[4], gcptr_t base, uint32_t byte_off) {
+#if FO_NT_LOAD
+    const f32x4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) f32x4_t*)(base + byte_off));
+#else
+    const f32x4_t v = *(const __attribute__((address_space(1))) f32x4_t*)(base + byte_off);
+#endif
+    f[0] = v[0]; f[1] = v[1]; f[2] = v[2]; f[3] = v[3];
 }
-template <int VEC>
-__device__ __forceinline__ void gst_floats(gptr_t base, uint32_t byte_off, const float (&f)[VEC]) {
-    static_assert(VEC % 4 == 0, "");
-    typedef float vec_t __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int k = 0; k < VEC / 4; ++k) {
-        const vec_t v = {f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]};
-        *(__attribute__((address_space(1))) vec_t*)(base + byte_off + 16u * k) = v;
-    }
+__device__ __forceinline__ void gst_floats(gptr_t base, uint32_t byte_off, const float (&f)[4]) {
+    const f32x4_t v = {f[0], f[1], f[2], f[3]};
+#if FO_NT_STORE
+    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) f32x4_t*)(base + byte_off));
+#else
+    *(__attribute__((address_space(1))) f32x4_t*)(base + byte_off) = v;
+#endif
 }
 __device__ __forceinline__ uint32_t gld_u16(gcptr_t base, uint32_t byte_off) {
     return *(const __attribute__((address_space(1))) uint16_t*)(base + byte_off);
@@ -518,14 +521,14 @@ __device__ __forceinline__ void gst_u16(gptr_t base, uint32_t byte_off, uint32_t
 template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_full(LaneIO<VEC>& x, const TensorDev& T, int64_t tile0, uint32_t lane_el) {
     lane_el = block_local(lane_el);
-    if (SPLIT) {
+    if constexpr (SPLIT) {
         gld_words(x.p, gbase(T.param, 2 * tile0), 2u * lane_el);
         gld_words(x.r, gbase(T.rho, tile0), lane_el);
     } else {
         gld_floats(x.th32, gbase(T.theta32, 4 * tile0), 4u * lane_el);
     }
     gld_words(x.g, gbase(T.grad, 2 * tile0), 2u * lane_el);
-    if (QUANT) {
+    if constexpr (QUANT) {
         const uint32_t scale_off = (lane_el >> 5) * 2u;
         gld_words(x.mq, gbase(T.m_q, tile0), lane_el);
         x.ms = gld_u16(gbase(T.m_scale, (tile0 >> 5) * 2), scale_off);
@@ -535,7 +538,7 @@ __device__ __forceinline__ void load_full(LaneIO<VEC>& x, const TensorDev& T, in
         }
     } else {
         gld_floats(x.m32, gbase(T.m32, 4 * tile0), 4u * lane_el);
-        if (HAS_V) gld_floats(x.v32, gbase(T.v32, 4 * tile0), 4u * lane_el);
+        if constexpr (HAS_V) gld_floats(x.v32, gbase(T.v32, 4 * tile0), 4u * lane_el);
     }
 }
 
@@ -587,13 +590,13 @@ template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void store_full(const LaneIO<VEC>& y, const TensorDev& T, int64_t tile0, uint32_t lane_el,
                                            bool group_leader) {
     lane_el = block_local(lane_el);
-    if (SPLIT) {
+    if constexpr (SPLIT) {
         gst_words(gbase(T.param, 2 * tile0), 2u * lane_el, y.p);
         gst_words(gbase(T.rho, tile0), lane_el, y.r);
     } else {
         gst_floats(gbase(T.theta32, 4 * tile0), 4u * lane_el, y.th32);
     }
-    if (QUANT) {
+    if constexpr (QUANT) {
         gst_words(gbase(T.m_q, tile0), lane_el, y.mq);
         if (HAS_V) gst_words(gbase(T.v_q, tile0), lane_el, y.vq);
         if (group_leader) {
@@ -603,7 +606,7 @@ __device__ __forceinline__ void store_full(const LaneIO<VEC>& y, const TensorDev
         }
     } else {
         gst_floats(gbase(T.m32, 4 * tile0), 4u * lane_el, y.m32);
-        if (HAS_V) gst_floats(gbase(T.v32, 4 * tile0), 4u * lane_el, y.v32);
+        if constexpr (HAS_V) gst_floats(gbase(T.v32, 4 * tile0), 4u * lane_el, y.v32);
     }
 }
 
@@ -896,8 +899,10 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& 
     LaneIO<VEC> x, y;
     if (FULL || cnt == VEC) load_full<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0, lane_el);
     else load_tail<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0 + lane_el, cnt);
-    store_table_entries<THREADS>(tab, entries, tid);
-    __syncthreads();
+    if constexpr (SPLIT || QUANT) {        // the plain FP32 step decodes nothing
+        store_table_entries<THREADS>(tab, entries, tid);
+        __syncthreads();
+    }
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
     update_lane<KIND, VEC, SPLIT, QUANT, EXACT>(x, y, tab, c, T.lr, T.wd);
@@ -915,7 +920,7 @@ __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
     __shared__ DecodeTables tab;
     const int tid = (int)threadIdx.x;
     TableEntries entries;
-    load_table_entries<THREADS>(entries, tid);
+    if constexpr (SPLIT || QUANT) load_table_entries<THREADS>(entries, tid);
     TensorDev T;
     const int64_t chunk = locate_tile<DIRECT>(a, T);
     const int64_t tile0 = chunk * (int64_t)kTile;              // first element of the tile (wave-uniform)
@@ -932,7 +937,7 @@ __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
 
 template <int KIND, bool SPLIT, bool QUANT, bool EXACT>
 static hipError_t launch_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    constexpr int VEC = step_vec(KIND), THREADS = step_threads(KIND);
+    constexpr int VEC = step_vec(KIND, SPLIT, QUANT), THREADS = step_threads(KIND, SPLIT, QUANT);
     const dim3 grid((unsigned)n_blocks), block(THREADS);
     if (direct) hipLaunchKernelGGL((step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT>), grid, block, 0, s, a);
@@ -992,8 +997,8 @@ __global__ __launch_bounds__(THREADS) void probe_kernel(StepArgs a) {
 
 hipError_t launch_probe(int kind, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     const dim3 grid((unsigned)n_blocks);
-#define FO_PROBE(K, DR) hipLaunchKernelGGL((probe_kernel<K, step_vec(K), step_threads(K), DR>), grid, \
-                                           dim3(step_threads(K)), 0, s, a)
+#define FO_PROBE(K, DR) hipLaunchKernelGGL((probe_kernel<K, step_vec(K, true, true), step_threads(K, true, true), DR>), grid, \
+                                           dim3(step_threads(K, true, true)), 0, s, a)
     if (kind == 0) { if (direct) FO_PROBE(0, true); else FO_PROBE(0, false); }
     else if (kind == 1) { if (direct) FO_PROBE(1, true); else FO_PROBE(1, false); }
     else { if (direct) FO_PROBE(2, true); else FO_PROBE(2, false); }
@@ -1028,33 +1033,38 @@ hipError_t launch_clock_monitor(unsigned long long* samples, int n_samples, unsi
 
 // -------------------------------------------------------- standalone codecs --
 //
-// Not on the per-step path (used at initialisation, for inspection and by tests).  They share
-// the lane layout of the step kernels: a workgroup of 256 lanes covers a tile of 2048 consecutive
-// elements, 8 per lane, so that BF16 data moves as 128-bit, byte data as 64-bit and FP32 data as
-// two 128-bit accesses per lane, and a quantisation group is a lane quad.  The arithmetic is the
-// plain exact form of each operation.
+// Not on the per-step path (used at initialisation, for inspection and by tests).  Every one of them has an FP32
+// array on one side, and that array is most of the traffic, so the lane layout follows it: a lane owns four
+// consecutive elements per pass, one 128-bit FP32 access, 64 bits of BF16 or 32 bits of codes, and a wavefront's
+// access covers whole cache lines of every stream.  A quantisation group is eight lanes.  A workgroup of 256 lanes
+// covers kCodecTile consecutive elements in passes of 1024, all of whose loads are issued before the first use.
+// Bound: HBM.  150 M elements, before (eight consecutive elements per lane: two FP32 accesses that each cover half
+// of every line, so no non-temporal hint) and now: split 174 -> 163 us (6.4 TB/s), reconstruct 191 -> 163, quantize
+// 123 -> 117, dequantize 146 -> 119.  Two passes: with one, dequantize stays at 147 us (the table is staged twice as
+// often), with four at 136.
 
-constexpr int kCodecVec = 8;
-constexpr int kCodecTile = kThreads * kCodecVec;
+constexpr int kCodecVec = 4;
+constexpr int kCodecPass = kThreads * kCodecVec;          // elements per pass
+constexpr int kCodecPasses = 2;
+constexpr int kCodecTile = kCodecPass * kCodecPasses;     // elements per workgroup
 
 struct LanePos {
-    int64_t tile0;       // first element of the workgroup's tile (wave-uniform)
-    uint32_t lane_el;    // first element of the lane inside the tile
+    int64_t tile0;       // first element of the pass (wave-uniform)
+    uint32_t lane_el;    // first element of the lane inside the pass
     int cnt;             // elements of the lane that exist: kCodecVec, or fewer at the ragged end
 };
+// FULL: every element of the pass exists (known at compile time, so that no case distinction is left).
+template <bool FULL>
 __device__ __forceinline__ LanePos lane_pos_at(int64_t tile0, int64_t n) {
     LanePos L;
     L.tile0 = tile0;
     L.lane_el = (uint32_t)threadIdx.x * kCodecVec;
-    const int64_t rem = n - tile0;
-    const int tile_cnt = rem >= kCodecTile ? kCodecTile : (rem > 0 ? (int)rem : 0);
-    const int left = tile_cnt - (int)L.lane_el;
-    L.cnt = left >= kCodecVec ? kCodecVec : (left > 0 ? left : 0);
+    const int64_t left = n - tile0 - (int64_t)L.lane_el;
+    L.cnt = (FULL || left >= kCodecVec) ? kCodecVec : (left > 0 ? (int)left : 0);
     return L;
 }
-__device__ __forceinline__ LanePos lane_pos(int64_t n) { return lane_pos_at((int64_t)blockIdx.x * kCodecTile, n); }
 
-// Eight elements of a lane from / to an array of 4-, 2- or 1-byte elements.  Full lanes use
+// The elements of a lane from / to an array of 4-, 2- or 1-byte elements.  Full lanes use
 // vector accesses; ragged lanes go element by element and read missing elements as zero.
 __device__ __forceinline__ void load_f32(float (&f)[kCodecVec], const float* p, const LanePos& L) {
     if (L.cnt == kCodecVec) {
@@ -1194,52 +1204,82 @@ __device__ __forceinline__ void stage_table(float* lds, const float* table) {
     __syncthreads();
 }
 
-template <int N, typename RHO>
-__global__ __launch_bounds__(kThreads) void split_kernel(const float* theta, uint16_t* param, RHO* rho, int64_t n) {
-    const LanePos L = lane_pos(n);
-    if (L.cnt == 0) return;
-    float th[kCodecVec];
-    load_f32(th, theta, L);
-    uint32_t pw[kCodecVec / 2], c[kCodecVec];
-#pragma unroll
-    for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[2 * j], th[2 * j + 1]);
-#pragma unroll
-    for (int i = 0; i < kCodecVec; ++i) c[i] = (uint32_t)split_rho<N>(th[i], half_of(pw, i));
-    store_u16(param, L, pw);
-    if constexpr (sizeof(RHO) == 1) {
-        uint32_t rw[kCodecVec / 4];
-        pack_u8(rw, c);
-        store_u8(rho, L, rw);
-    } else {
-        uint32_t rw[kCodecVec / 2];
-        pack_u16(rw, c);
-        store_u16(rho, L, rw);
-    }
+// The rho half of C without the tables: the same three operations as split_rho, of which the clamp is the
+// identity for a finite theta' (|e| <= half an ULP under round-to-nearest), with Round() as one addition.
+// For N = 127 the product with N is exact (at most 16 + 7 significant bits).  A non-finite theta' gives 0.
+template <int N>
+__device__ __forceinline__ uint32_t split_rho_bits(float theta, uint32_t b) {
+    const int E = (int)((b >> 7) & 0xffu);
+    const float e = theta - u2f(b << 16);
+    const float y = ldexpf(e, 135 - (E < 1 ? 1 : E)) * (float)N;
+    return E == 255 ? 0u : round_to_int_bits(y);
 }
 
+template <int N, typename RHO, bool FULL>
+__device__ __forceinline__ void split_tile(const float* theta, uint16_t* param, RHO* rho, int64_t n, int64_t tile0) {
+    float th[kCodecPasses][kCodecVec];
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) load_f32(th[r], theta, lane_pos_at<FULL>(tile0 + r * kCodecPass, n));
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        uint32_t pw[kCodecVec / 2], c[kCodecVec];
+#pragma unroll
+        for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[r][2 * j], th[r][2 * j + 1]);
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<N>(th[r][i], half_of(pw, i));
+        store_u16(param, L, pw);
+        if constexpr (sizeof(RHO) == 1) {
+            uint32_t rw[kCodecVec / 4];
+            pack_u8(rw, c);
+            store_u8(rho, L, rw);
+        } else {
+            uint32_t rw[kCodecVec / 2];
+            pack_u16(rw, c);
+            store_u16(rho, L, rw);
+        }
+    }
+}
+template <int N, typename RHO>
+__global__ __launch_bounds__(kThreads) void split_kernel(const float* theta, uint16_t* param, RHO* rho, int64_t n) {
+    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
+    if (n - tile0 >= kCodecTile) split_tile<N, RHO, true>(theta, param, rho, n, tile0);
+    else split_tile<N, RHO, false>(theta, param, rho, n, tile0);
+}
+
+template <int N, typename RHO, bool FULL>
+__device__ __forceinline__ void reconstruct_tile(const uint16_t* param, const RHO* rho, float* theta, int64_t n,
+                                                 int64_t tile0, float* rho_over_n) {
+    constexpr int kRhoWords = sizeof(RHO) == 1 ? kCodecVec / 4 : kCodecVec / 2;
+    uint32_t pw[kCodecPasses][kCodecVec / 2], rw[kCodecPasses][kRhoWords];
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        load_u16(pw[r], param, L);
+        if constexpr (sizeof(RHO) == 1) load_u8(rw[r], rho, L);
+        else load_u16(rw[r], rho, L);
+    }
+    if constexpr (sizeof(RHO) == 1) stage_table(rho_over_n, g_decode_tables.rho);
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        float th[kCodecVec];
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) {
+            if constexpr (sizeof(RHO) == 1) th[i] = reconstruct_tab(rho_over_n, half_of(pw[r], i), byte_of(rw[r], i));
+            else th[i] = reconstruct_n<N>(half_of(pw[r], i), (int)(int16_t)half_of(rw[r], i));
+        }
+        store_f32(theta, L, th);
+    }
+}
 template <int N, typename RHO>
 __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const uint16_t* param, const RHO* rho, float* theta,
                                                                int64_t n) {
-    const LanePos L = lane_pos(n);
+    static_assert(sizeof(RHO) != 1 || N == 127, "the table holds rho / 127");
     __shared__ float rho_over_n[sizeof(RHO) == 1 ? 256 : 1];
-    if constexpr (sizeof(RHO) == 1) stage_table(rho_over_n, g_decode_tables.rho);
-    if (L.cnt == 0) return;
-    uint32_t pw[kCodecVec / 2];
-    load_u16(pw, param, L);
-    float th[kCodecVec];
-    if constexpr (sizeof(RHO) == 1) {
-        static_assert(sizeof(RHO) != 1 || N == 127, "the table holds rho / 127");
-        uint32_t rw[kCodecVec / 4];
-        load_u8(rw, rho, L);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) th[i] = reconstruct_tab(rho_over_n, half_of(pw, i), byte_of(rw, i));
-    } else {
-        uint32_t rw[kCodecVec / 2];
-        load_u16(rw, rho, L);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) th[i] = reconstruct_n<N>(half_of(pw, i), (int)(int16_t)half_of(rw, i));
-    }
-    store_f32(theta, L, th);
+    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
+    if (n - tile0 >= kCodecTile) reconstruct_tile<N, RHO, true>(param, rho, theta, n, tile0, rho_over_n);
+    else reconstruct_tile<N, RHO, false>(param, rho, theta, n, tile0, rho_over_n);
 }
 
 // The data-independent experiment of Section 4.4: FP32 bit patterns first, first + stride, ...
@@ -1322,32 +1362,61 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(uint64_t first, uint64_
     }
 }
 
-// Group quantizers written out plainly.  LINEAR drops the compander (the plain absmax-scaled integer
-// quantisation that Section 4.5 takes as its baseline): momentum code = Round(127 m / s), variance
-// code = Round(255 v / s) with s the group maximum of v itself.
-// quantize_lane: the eight codes of a lane and the FP16 scale bits of its group.  All four lanes of
+// Group quantizers.  LINEAR drops the compander (the plain absmax-scaled integer quantisation that Section 4.5
+// takes as its baseline): momentum code = Round(127 m / s), variance code = Round(255 v / s) with s the group
+// maximum of v itself.
+//
+// The companded codes are decided from an estimate, as in the step kernels: with their exact form (an IEEE division
+// or square root per element) throughout, 150 M elements of m / v took 120 / 125 us, with the estimate 117 / 118
+// (6.5 TB/s).  Momentum: m_code_bracket.  Variance: y* = v_sqrt_f32(v) * RN(255 r), where the hardware root is
+// within one ulp.  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and the exact argument of Round()
+// by 3 (root, * r, * 255): 6 * 2^-24 * 255.5 < 9.2e-5, and the fused multiply-add that forms y* -+ w rounds by at
+// most 2^-17 = 7.7e-6, so w = 1.1e-4 decides.  A subnormal v has y below 1e-9 for every FP16 scale, far from a tie.
+constexpr float kTieWindowCodecV = 1.1e-4f;
+
+// quantize_lane: the codes of a lane, one byte each, and the FP16 scale bits of its group.  All eight lanes of
 // a group must call it together; elements past the end are zero and do not raise the maximum.
 // The group maximum of sqrt(v) is the square root of the maximum of v (the root is monotone).
 template <bool VARIANCE, bool LINEAR>
-__device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], uint32_t (&codes)[kCodecVec]) {
+__device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], uint32_t (&w)[kCodecVec / 4]) {
+    static_assert(kCodecVec == 4, "one word of codes");
     float a = 0.0f;
 #pragma unroll
     for (int i = 0; i < kCodecVec; ++i) a = fmaxf(a, VARIANCE ? x[i] : fabsf(x[i]));
     a = group_max<kCodecVec>(a);
     if (VARIANCE && !LINEAR) a = sqrtf(a);
     float r;
-    const uint32_t sbits = group_scale(a, &r);
+    const uint32_t sbits = group_scale_fast(a, &r);
+    uint32_t c[kCodecVec];
+    if (!LINEAR) {
+        uint32_t lo_w = 0, hi_w = 0;
+        const float r255 = 255.0f * r;
 #pragma unroll
-    for (int i = 0; i < kCodecVec; ++i) {
-        uint32_t c;
-        if (!LINEAR) {
-            c = VARIANCE ? v_code_exact(x[i], r) : m_code_exact(x[i], r);
-        } else if (VARIANCE) {
-            c = round_to_int_bits(__builtin_amdgcn_fmed3f((x[i] * r) * 255.0f, 0.0f, 255.0f));
-        } else {
-            c = round_to_int_bits(__builtin_amdgcn_fmed3f((x[i] * r) * 127.0f, -127.0f, 127.0f));
+        for (int i = 0; i < kCodecVec; ++i) {
+            float lo, hi;
+            if (VARIANCE) {
+                const float root = __builtin_amdgcn_sqrtf(x[i]);
+                lo = fmaf(root, r255, -kTieWindowCodecV);
+                hi = fmaf(root, r255, kTieWindowCodecV);
+            } else {
+                m_code_bracket(x[i], r, &lo, &hi);
+            }
+            lo_w = put_u8(lo, i, lo_w);
+            hi_w = put_u8(hi, i, hi_w);
         }
-        codes[i] = c & 0xffu;
+        w[0] = VARIANCE ? lo_w : lo_w ^ 0x80808080u;
+        if (any_lane(lo_w != hi_w)) {
+#pragma unroll
+            for (int i = 0; i < kCodecVec; ++i) c[i] = VARIANCE ? v_code_exact(x[i], r) : m_code_exact(x[i], r);
+            w[0] = pack_low_bytes(c[0], c[1], c[2], c[3]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) {
+            c[i] = VARIANCE ? round_to_int_bits(__builtin_amdgcn_fmed3f((x[i] * r) * 255.0f, 0.0f, 255.0f))
+                            : round_to_int_bits(__builtin_amdgcn_fmed3f((x[i] * r) * 127.0f, -127.0f, 127.0f));
+        }
+        w[0] = pack_low_bytes(c[0], c[1], c[2], c[3]);
     }
     return sbits;
 }
@@ -1369,61 +1438,95 @@ __device__ __forceinline__ bool group_leader(const LanePos& L) {
     return (threadIdx.x & (kGroup / kCodecVec - 1)) == 0 && L.cnt > 0;
 }
 
+template <bool VARIANCE, bool LINEAR, bool FULL>
+__device__ __forceinline__ void quantize_tile(const float* x, uint8_t* q, uint16_t* scale, int64_t n, int64_t tile0) {
+    float v[kCodecPasses][kCodecVec];
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) load_f32(v[r], x, lane_pos_at<FULL>(tile0 + r * kCodecPass, n));
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        uint32_t w[kCodecVec / 4];
+        const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v[r], w);
+        if (L.cnt > 0) store_u8(q, L, w);
+        if (group_leader(L)) scale[(L.tile0 + L.lane_el) >> 5] = (uint16_t)sbits;
+    }
+}
 template <bool VARIANCE, bool LINEAR>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* x, uint8_t* q, uint16_t* scale,
                                                             int64_t n) {
-    const LanePos L = lane_pos(n);
-    float v[kCodecVec];
-    load_f32(v, x, L);
-    uint32_t codes[kCodecVec], w[kCodecVec / 4];
-    const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v, codes);
-    pack_u8(w, codes);
-    if (L.cnt > 0) store_u8(q, L, w);
-    if (group_leader(L)) scale[(L.tile0 + L.lane_el) >> 5] = (uint16_t)sbits;
+    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
+    if (n - tile0 >= kCodecTile) quantize_tile<VARIANCE, LINEAR, true>(x, q, scale, n, tile0);
+    else quantize_tile<VARIANCE, LINEAR, false>(x, q, scale, n, tile0);
 }
 
+__device__ __forceinline__ float load_scale(const uint16_t* scale, const LanePos& L) {
+    return L.cnt > 0 ? (float)__builtin_bit_cast(_Float16, scale[(L.tile0 + L.lane_el) >> 5]) : 0.0f;
+}
+
+template <bool VARIANCE, bool LINEAR, bool FULL>
+__device__ __forceinline__ void dequantize_tile(const uint8_t* q, const uint16_t* scale, float* x, int64_t n,
+                                                int64_t tile0, float* tab) {
+    uint32_t w[kCodecPasses][kCodecVec / 4];
+    float s[kCodecPasses];
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        load_u8(w[r], q, L);
+        s[r] = load_scale(scale, L);
+    }
+    stage_table(tab, decode_table<VARIANCE, LINEAR>());
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
+        float v[kCodecVec];
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) v[i] = dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w[r], i), s[r]);
+        store_f32(x, L, v);
+    }
+}
 template <bool VARIANCE, bool LINEAR>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, const uint16_t* scale, float* x,
                                                               int64_t n) {
-    const LanePos L = lane_pos(n);
     __shared__ float tab[256];
-    stage_table(tab, decode_table<VARIANCE, LINEAR>());
-    if (L.cnt == 0) return;
-    uint32_t w[kCodecVec / 4];
-    load_u8(w, q, L);
-    const float s = (float)__builtin_bit_cast(_Float16, scale[(L.tile0 + L.lane_el) >> 5]);
-    float v[kCodecVec];
-#pragma unroll
-    for (int i = 0; i < kCodecVec; ++i) v[i] = dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w, i), s);
-    store_f32(x, L, v);
+    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
+    if (n - tile0 >= kCodecTile) dequantize_tile<VARIANCE, LINEAR, true>(q, scale, x, n, tile0, tab);
+    else dequantize_tile<VARIANCE, LINEAR, false>(q, scale, x, n, tile0, tab);
 }
 
 // Quantisation error of a buffer (Section 4.5): sums[0] += sum (Q^-1(Q(x)) - x)^2 and
 // sums[1] += sum x^2, in double.  A workgroup walks over tiles blockIdx.x, blockIdx.x + gridDim.x,
 // ... and adds its partial sums once at the end (wavefront reduction, one atomic pair per
 // wavefront), so the number of atomics on the two accumulators stays small.
+template <bool VARIANCE, bool LINEAR, bool FULL>
+__device__ __forceinline__ void nmse_tile(const float* x, int64_t n, int64_t tile0, const float* tab, double& err,
+                                          double& ref) {
+    float v[kCodecPasses][kCodecVec];
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) load_f32(v[r], x, lane_pos_at<FULL>(tile0 + r * kCodecPass, n));
+#pragma unroll
+    for (int r = 0; r < kCodecPasses; ++r) {
+        uint32_t w[kCodecVec / 4];
+        const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v[r], w);
+        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
+        // (elements past the end are zero: their code decodes to zero and they add nothing)
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) {
+            const double xi = (double)v[r][i];
+            const double d = (double)dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w, i), s) - xi;
+            err += d * d;
+            ref += xi * xi;
+        }
+    }
+}
 template <bool VARIANCE, bool LINEAR>
 __global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t n, double* sums) {
-    const int64_t n_tiles = (n + kCodecTile - 1) / kCodecTile;
     __shared__ float tab[256];
     stage_table(tab, decode_table<VARIANCE, LINEAR>());
     double err = 0.0, ref = 0.0;
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const LanePos L = lane_pos_at(tile * kCodecTile, n);
-        float v[kCodecVec];
-        load_f32(v, x, L);
-        uint32_t codes[kCodecVec];
-        const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v, codes);
-        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) {
-            if (i < L.cnt) {
-                const double xi = (double)v[i];
-                const double d = (double)dequantize_one<VARIANCE, LINEAR>(tab, codes[i], s) - xi;
-                err += d * d;
-                ref += xi * xi;
-            }
-        }
+    for (int64_t tile0 = (int64_t)blockIdx.x * kCodecTile; tile0 < n; tile0 += (int64_t)gridDim.x * kCodecTile) {
+        if (n - tile0 >= kCodecTile) nmse_tile<VARIANCE, LINEAR, true>(x, n, tile0, tab, err, ref);
+        else nmse_tile<VARIANCE, LINEAR, false>(x, n, tile0, tab, err, ref);
     }
     for (int off = 32; off > 0; off >>= 1) {
         err += __shfl_down(err, off);
@@ -1438,7 +1541,6 @@ __global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t 
 constexpr unsigned kNmseMaxBlocks = 256 * 8;     // eight resident workgroups per compute unit
 
 static inline unsigned tiles_for(int64_t n) { return (unsigned)((n + kCodecTile - 1) / kCodecTile); }
-
 void launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
     if (bits == 8) hipLaunchKernelGGL((split_kernel<127, int8_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s, theta,
                                       (uint16_t*)param, (int8_t*)rho, n);
@@ -1469,8 +1571,7 @@ static void launch_codec(int op, const void* in, const uint16_t* scale_in, void*
     else if (op == 1) hipLaunchKernelGGL((dequantize_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
                                          (const uint8_t*)in, scale_in, (float*)out, n);
     else hipLaunchKernelGGL((nmse_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n) < kNmseMaxBlocks ? tiles_for(n) : kNmseMaxBlocks),
-                            dim3(kThreads), 0, s,
-                            (const float*)in, n, sums);
+                            dim3(kThreads), 0, s, (const float*)in, n, sums);
 }
 static void dispatch_codec(bool variance, bool linear, int op, const void* in, const uint16_t* scale_in, void* out,
                            uint16_t* scale_out, int64_t n, double* sums, hipStream_t s) {
@@ -1498,71 +1599,96 @@ void launch_nmse(bool variance, bool linear, const float* x, int64_t n, double* 
 // Migration between a standard FP32 optimizer state (theta, m, v: 12 B/param for AdamW) and
 // the compressed layout: COMPRESS applies C, Q_m, Q_v (Algorithms 1-3) in one pass over a list;
 // the other direction applies the inverses (its per-code factors from staged tables of the defining
-// divisions).  Written with the plain exact forms; same tile
-// look-up and lane layout (8 elements per lane, a lane quad per group) as the step kernels.
-static_assert(kCodecTile == kConvChunkElems, "the host builds the conversion's tables for tiles of this size");
+// divisions).  Tile look-up of the step kernels, lane layout and arithmetic of the standalone codecs.
+constexpr int kConvPasses = kConvChunkElems / kCodecPass;
+static_assert(kConvPasses * kCodecPass == kConvChunkElems, "the host builds the conversion's tables for tiles of this size");
+
+template <bool HAS_V, bool FULL>
+__device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0) {
+    float th[kConvPasses][kCodecVec], m[kConvPasses][kCodecVec], v[kConvPasses][kCodecVec];
+#pragma unroll
+    for (int r = 0; r < kConvPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
+        load_f32(th[r], T.theta32, L);
+        load_f32(m[r], T.m32, L);
+        if (HAS_V) load_f32(v[r], T.v32, L);
+    }
+    // every lane of a group takes part in the group maxima, also those past the end
+#pragma unroll
+    for (int r = 0; r < kConvPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
+        const int64_t group = (L.tile0 + L.lane_el) >> 5;
+        uint32_t pw[kCodecVec / 2], c[kCodecVec], w[kCodecVec / 4];
+#pragma unroll
+        for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[r][2 * j], th[r][2 * j + 1]);
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<127>(th[r][i], half_of(pw, i));
+        pack_u8(w, c);
+        if (L.cnt > 0) {
+            store_u16(T.param, L, pw);
+            store_u8(T.rho, L, w);
+        }
+        const uint32_t ms = quantize_lane<false, false>(m[r], w);
+        if (L.cnt > 0) store_u8(T.m_q, L, w);
+        if (group_leader(L)) T.m_scale[group] = (uint16_t)ms;
+        if (HAS_V) {
+            const uint32_t vs = quantize_lane<true, false>(v[r], w);
+            if (L.cnt > 0) store_u8(T.v_q, L, w);
+            if (group_leader(L)) T.v_scale[group] = (uint16_t)vs;
+        }
+    }
+}
+
+template <bool HAS_V, bool FULL>
+__device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0, float (&tab)[3][256]) {
+    uint32_t pw[kConvPasses][kCodecVec / 2], rw[kConvPasses][kCodecVec / 4], mw[kConvPasses][kCodecVec / 4],
+        vw[kConvPasses][kCodecVec / 4];
+    float sm[kConvPasses], sv[kConvPasses];
+#pragma unroll
+    for (int r = 0; r < kConvPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
+        load_u16(pw[r], T.param, L);
+        load_u8(rw[r], T.rho, L);
+        load_u8(mw[r], T.m_q, L);
+        sm[r] = load_scale(T.m_scale, L);
+        if (HAS_V) {
+            load_u8(vw[r], T.v_q, L);
+            sv[r] = load_scale(T.v_scale, L);
+        }
+    }
+    tab[0][threadIdx.x] = g_decode_tables.rho[threadIdx.x];
+    tab[1][threadIdx.x] = g_decode_tables.m[threadIdx.x];
+    stage_table(tab[2], g_decode_tables.v);
+#pragma unroll
+    for (int r = 0; r < kConvPasses; ++r) {
+        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
+        float f[kCodecVec];
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_tab(tab[0], half_of(pw[r], i), byte_of(rw[r], i));
+        store_f32(T.theta32, L, f);
+#pragma unroll
+        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw[r], i), sm[r]);
+        store_f32(T.m32, L, f);
+        if (HAS_V) {
+#pragma unroll
+            for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(vw[r], i), sv[r]);
+            store_f32(T.v32, L, f);
+        }
+    }
+}
 
 template <bool HAS_V, bool COMPRESS, bool DIRECT>
 __global__ __launch_bounds__(kThreads) void convert_kernel(StepArgs a) {
     TensorDev T;
-    const int64_t chunk = locate_tile<DIRECT>(a, T);
-    const LanePos L = lane_pos_at(chunk * (int64_t)kCodecTile, T.numel);
-    const int64_t group = (L.tile0 + L.lane_el) >> 5;
-    if (COMPRESS) {
-        // every lane of a group takes part in the group maxima, also those past the end
-        float th[kCodecVec], m[kCodecVec], v[kCodecVec];
-        load_f32(th, T.theta32, L);
-        load_f32(m, T.m32, L);
-        uint32_t pw[kCodecVec / 2], c[kCodecVec], w[kCodecVec / 4];
-#pragma unroll
-        for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[2 * j], th[2 * j + 1]);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) c[i] = (uint32_t)split_rho<127>(th[i], half_of(pw, i));
-        if (L.cnt > 0) {
-            store_u16(T.param, L, pw);
-            pack_u8(w, c);
-            store_u8(T.rho, L, w);
-        }
-        const uint32_t ms = quantize_lane<false, false>(m, c);
-        if (L.cnt > 0) {
-            pack_u8(w, c);
-            store_u8(T.m_q, L, w);
-        }
-        if (group_leader(L)) T.m_scale[group] = (uint16_t)ms;
-        if (HAS_V) {
-            load_f32(v, T.v32, L);
-            const uint32_t vs = quantize_lane<true, false>(v, c);
-            if (L.cnt > 0) {
-                pack_u8(w, c);
-                store_u8(T.v_q, L, w);
-            }
-            if (group_leader(L)) T.v_scale[group] = (uint16_t)vs;
-        }
+    const int64_t tile0 = locate_tile<DIRECT>(a, T) * (int64_t)kConvChunkElems;
+    const bool full = T.numel - tile0 >= kConvChunkElems;
+    if constexpr (COMPRESS) {
+        if (full) compress_tile<HAS_V, true>(T, tile0);
+        else compress_tile<HAS_V, false>(T, tile0);
     } else {
         __shared__ float tab[3][256];        // rho / 127, phi_m^-1(q / 127), q / 255
-        tab[0][threadIdx.x] = g_decode_tables.rho[threadIdx.x];
-        tab[1][threadIdx.x] = g_decode_tables.m[threadIdx.x];
-        stage_table(tab[2], g_decode_tables.v);
-        if (L.cnt == 0) return;
-        uint32_t pw[kCodecVec / 2], w[kCodecVec / 4];
-        float f[kCodecVec];
-        load_u16(pw, T.param, L);
-        load_u8(w, T.rho, L);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_tab(tab[0], half_of(pw, i), byte_of(w, i));
-        store_f32(T.theta32, L, f);
-        const float s_m = (float)__builtin_bit_cast(_Float16, T.m_scale[group]);
-        load_u8(w, T.m_q, L);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(w, i), s_m);
-        store_f32(T.m32, L, f);
-        if (HAS_V) {
-            const float s_v = (float)__builtin_bit_cast(_Float16, T.v_scale[group]);
-            load_u8(w, T.v_q, L);
-#pragma unroll
-            for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(w, i), s_v);
-            store_f32(T.v32, L, f);
-        }
+        if (full) decompress_tile<HAS_V, true>(T, tile0, tab);
+        else decompress_tile<HAS_V, false>(T, tile0, tab);
     }
 }
 

@@ -164,6 +164,33 @@ def test_ragged_ends_write_nothing_past_the_end(n):
     assert tail_intact(th, 5.0)
 
 
+@pytest.mark.parametrize("n", [3, 4, 5, 1023, 1024, 1025, 2048, 2051, 3071, 3073])
+def test_codecs_at_the_edges_of_a_pass_and_of_a_tile(n):
+    # four elements per lane, 1024 per pass of a workgroup, 2048 per workgroup
+    test_ragged_ends_write_nothing_past_the_end(n)
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -14, 0.0009765625 * 1.2373046875, 65504.0, 2.0 ** -24])
+def test_codes_next_to_rounding_ties(scale):
+    # the encoders decide a code from an estimate unless it lies within a window around a tie: values on both sides
+    # of every tie, from neighbours in FP32 to beyond the window, get the oracle's codes
+    k = np.arange(0, 255) + 0.5
+    near = np.concatenate([np.arange(-8, 9) * 2.0 ** -24, np.linspace(-1.5e-6, 1.5e-6, 61)])
+    root = (k[:, None] / 255.0 * (1.0 + near[None, :])).ravel() * scale
+    a = np.concatenate([kk / (254.0 - kk) * (1.0 + near) for kk in np.arange(0, 127) + 0.5]) * scale
+    for vals, quant_gpu, quant_cpu, dt, top in (
+            (root * root, fo.quantize_variance, oracle.quantize_variance, torch.uint8, scale * scale),
+            (a, fo.quantize_momentum, oracle.quantize_momentum, torch.int8, scale),
+            (-a, fo.quantize_momentum, oracle.quantize_momentum, torch.int8, scale)):
+        vals = np.concatenate([vals, np.zeros(-vals.size % 31)]).reshape(-1, 31)
+        x = np.concatenate([np.full((vals.shape[0], 1), top), vals], axis=1).astype(np.float32).ravel()
+        q = torch.empty(x.size, dtype=dt, device="cuda")
+        s = torch.empty(x.size // 32, dtype=torch.float16, device="cuda")
+        quant_gpu(_dev(x), q, s)
+        wq, ws = quant_cpu(x)
+        assert np.array_equal(bits16(s), ws) and np.array_equal(q.cpu().numpy(), wq)
+
+
 def test_exact_rounding_ties_take_the_even_code():
     # inputs whose FP32 value before Round() is exactly k + 1/2 (scale 1.0): the device rounds them as the
     # oracle does, in the standalone quantisers
