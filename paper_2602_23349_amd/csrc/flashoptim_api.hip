@@ -597,6 +597,57 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
     return FLASHOPTIM_OK;
 }
 
+// ------------------------------------------------- workspaces of the quantisation error --
+//
+// A call needs device memory for the workgroups' partial sums and two doubles of pinned memory that the last kernel
+// writes and the host reads after waiting for the stream.  Both are kept from call to call (allocating and freeing
+// them cost ~20 us a call); a call takes a pair out of the pool for as long as it runs, so calls of several threads
+// and streams never share one, and a pair goes back only once its stream has been waited for.
+struct NmseSpace {
+    int device = 0;
+    double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs
+    double* sums = nullptr;         // pinned
+};
+std::mutex g_nmse_mu;
+constexpr int kMaxIdleNmse = 16;        // 32 KB of device memory each; a pair beyond that is freed after its call
+NmseSpace g_nmse_idle[kMaxIdleNmse];
+int g_nmse_n_idle = 0;
+
+void destroy_nmse(NmseSpace& w) {
+    if (w.partial) (void)hipFree(w.partial);
+    if (w.sums) (void)hipHostFree(w.sums);
+    w.partial = nullptr; w.sums = nullptr;
+}
+
+int take_nmse(NmseSpace& w) {
+    FO_HIP(hipGetDevice(&w.device));
+    {
+        std::lock_guard<std::mutex> lock(g_nmse_mu);
+        for (int i = 0; i < g_nmse_n_idle; ++i) {
+            if (g_nmse_idle[i].device != w.device) continue;
+            w = g_nmse_idle[i];
+            g_nmse_idle[i] = g_nmse_idle[--g_nmse_n_idle];
+            return FLASHOPTIM_OK;
+        }
+    }
+    hipError_t e = hipMalloc((void**)&w.partial, fo::kNmseMaxBlocks * sizeof(double2));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&w.sums, 2 * sizeof(double), hipHostMallocDefault);
+    if (e != hipSuccess) {
+        destroy_nmse(w);
+        g_last_hip_error = (int)e;
+        (void)hipGetLastError();
+        return FLASHOPTIM_ERR_HIP;
+    }
+    return FLASHOPTIM_OK;
+}
+
+// Takes a pair back whose work is known to have finished.
+void give_nmse(NmseSpace& w) {
+    std::lock_guard<std::mutex> lock(g_nmse_mu);
+    if (g_nmse_n_idle < kMaxIdleNmse) g_nmse_idle[g_nmse_n_idle++] = w;
+    else destroy_nmse(w);
+}
+
 // ------------------------------------------ the step entry point that allocates nothing --
 //
 // For callers that cannot allocate device memory (stream capture, tight serving loops): the two device
@@ -885,18 +936,20 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     if (!x) return FLASHOPTIM_ERR_INVALID_ARG;
     if (!aligned16(x)) return FLASHOPTIM_ERR_MISALIGNED;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    double* d = nullptr;
-    FO_HIP(hipMalloc((void**)&d, 2 * sizeof(double)));
-    hipError_t e = hipMemsetAsync(d, 0, 2 * sizeof(double), stream);
-    if (e == hipSuccess) { fo::launch_nmse(state == 1, linear == 1, x, n, d, stream); e = hipGetLastError(); }
-    if (e == hipSuccess) e = hipMemcpyAsync(sums, d, 2 * sizeof(double), hipMemcpyDeviceToHost, stream);
+    NmseSpace w;
+    const int rc = take_nmse(w);
+    if (rc != FLASHOPTIM_OK) return rc;
+    hipError_t e = fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, w.sums, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    (void)hipFree(d);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
         (void)hipGetLastError();
+        destroy_nmse(w);            // hipFree waits for whatever may still use it
         return FLASHOPTIM_ERR_HIP;
     }
+    sums[0] = w.sums[0];
+    sums[1] = w.sums[1];
+    give_nmse(w);
     return FLASHOPTIM_OK;
 }
 
@@ -1184,6 +1237,8 @@ int flashoptim_release_cache(void) {
     for (auto& kv : g_plans) destroy_plan(kv.second);
     g_plans.clear();
     g_index.clear();
+    std::lock_guard<std::mutex> nmse_lock(g_nmse_mu);
+    while (g_nmse_n_idle > 0) destroy_nmse(g_nmse_idle[--g_nmse_n_idle]);
     return FLASHOPTIM_OK;
 }
 

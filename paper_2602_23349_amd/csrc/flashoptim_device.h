@@ -128,7 +128,10 @@ hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t str
 void launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s);
 void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                        hipStream_t s);
-void launch_nmse(bool variance, bool linear, const float* x, int64_t n, double* sums, hipStream_t s);
+constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per compute unit
+// partial: device memory for kNmseMaxBlocks pairs; sums: two doubles that the device can write and the host reads
+hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
+                       hipStream_t s);
 void launch_copy(const CopySegment* segs, const uint2* chunks, int64_t n_chunks, hipStream_t s);
 constexpr int kSelftestSectionCount = 7;
 constexpr unsigned long long kSelftestSqrtValues = 0x7f800000ull - 0x0f800000ull;   // section 2: every FP32 value in [2^-96, FLT_MAX]

@@ -1494,10 +1494,27 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, 
     else dequantize_tile<VARIANCE, LINEAR, false>(q, scale, x, n, tile0, tab);
 }
 
-// Quantisation error of a buffer (Section 4.5): sums[0] += sum (Q^-1(Q(x)) - x)^2 and
-// sums[1] += sum x^2, in double.  A workgroup walks over tiles blockIdx.x, blockIdx.x + gridDim.x,
-// ... and adds its partial sums once at the end (wavefront reduction, one atomic pair per
-// wavefront), so the number of atomics on the two accumulators stays small.
+// Quantisation error of a buffer (Section 4.5): sum (Q^-1(Q(x)) - x)^2 and sum x^2, in double.  A workgroup walks
+// over tiles blockIdx.x, blockIdx.x + gridDim.x, ... and writes its pair of partial sums; a second kernel of one
+// workgroup adds the pairs up in a fixed order and writes the result to memory that the host reads.
+// (With one pair of FP64 atomics per wavefront on the two totals, 2^24 elements took 206 us, nearly all of it
+// those 16,384 updates of two addresses.)
+__device__ __forceinline__ void block_sum_pair(double& a, double& b) {
+    __shared__ double part[2][kThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_down(a, off);
+        b += __shfl_down(b, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = a;
+        part[1][threadIdx.x >> 6] = b;
+    }
+    __syncthreads();
+    a = b = 0.0;
+#pragma unroll
+    for (int k = 0; k < kThreads / 64; ++k) { a += part[0][k]; b += part[1][k]; }
+}
+
 template <bool VARIANCE, bool LINEAR, bool FULL>
 __device__ __forceinline__ void nmse_tile(const float* x, int64_t n, int64_t tile0, const float* tab, double& err,
                                           double& ref) {
@@ -1514,13 +1531,13 @@ __device__ __forceinline__ void nmse_tile(const float* x, int64_t n, int64_t til
         for (int i = 0; i < kCodecVec; ++i) {
             const double xi = (double)v[r][i];
             const double d = (double)dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w, i), s) - xi;
-            err += d * d;
-            ref += xi * xi;
+            err = fma(d, d, err);
+            ref = fma(xi, xi, ref);
         }
     }
 }
 template <bool VARIANCE, bool LINEAR>
-__global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t n, double* sums) {
+__global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t n, double2* partial) {
     __shared__ float tab[256];
     stage_table(tab, decode_table<VARIANCE, LINEAR>());
     double err = 0.0, ref = 0.0;
@@ -1528,19 +1545,29 @@ __global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t 
         if (n - tile0 >= kCodecTile) nmse_tile<VARIANCE, LINEAR, true>(x, n, tile0, tab, err, ref);
         else nmse_tile<VARIANCE, LINEAR, false>(x, n, tile0, tab, err, ref);
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        err += __shfl_down(err, off);
-        ref += __shfl_down(ref, off);
+    block_sum_pair(err, ref);
+    if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(err, ref);
+}
+__global__ __launch_bounds__(kThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums) {
+    double err = 0.0, ref = 0.0;
+    for (int i = (int)threadIdx.x; i < n_partial; i += kThreads) {
+        const double2 p = partial[i];
+        err += p.x;
+        ref += p.y;
     }
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&sums[0], err);
-        atomicAdd(&sums[1], ref);
+    block_sum_pair(err, ref);
+    if (threadIdx.x == 0) {
+        sums[0] = err;
+        sums[1] = ref;
     }
 }
 
-constexpr unsigned kNmseMaxBlocks = 256 * 8;     // eight resident workgroups per compute unit
-
 static inline unsigned tiles_for(int64_t n) { return (unsigned)((n + kCodecTile - 1) / kCodecTile); }
+static inline unsigned nmse_blocks(int64_t n) {
+    const int64_t tiles = (n + kCodecTile - 1) / kCodecTile;
+    return (unsigned)(tiles < kNmseMaxBlocks ? tiles : kNmseMaxBlocks);
+}
+
 void launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
     if (bits == 8) hipLaunchKernelGGL((split_kernel<127, int8_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s, theta,
                                       (uint16_t*)param, (int8_t*)rho, n);
@@ -1565,22 +1592,22 @@ hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t str
 }
 template <bool VARIANCE, bool LINEAR>
 static void launch_codec(int op, const void* in, const uint16_t* scale_in, void* out, uint16_t* scale_out, int64_t n,
-                         double* sums, hipStream_t s) {
+                         double2* partial, hipStream_t s) {
     if (op == 0) hipLaunchKernelGGL((quantize_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
                                     (const float*)in, (uint8_t*)out, scale_out, n);
     else if (op == 1) hipLaunchKernelGGL((dequantize_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
                                          (const uint8_t*)in, scale_in, (float*)out, n);
-    else hipLaunchKernelGGL((nmse_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n) < kNmseMaxBlocks ? tiles_for(n) : kNmseMaxBlocks),
-                            dim3(kThreads), 0, s, (const float*)in, n, sums);
+    else hipLaunchKernelGGL((nmse_kernel<VARIANCE, LINEAR>), dim3(nmse_blocks(n)), dim3(kThreads), 0, s, (const float*)in,
+                            n, partial);
 }
 static void dispatch_codec(bool variance, bool linear, int op, const void* in, const uint16_t* scale_in, void* out,
-                           uint16_t* scale_out, int64_t n, double* sums, hipStream_t s) {
+                           uint16_t* scale_out, int64_t n, double2* partial, hipStream_t s) {
     if (variance) {
-        if (linear) launch_codec<true, true>(op, in, scale_in, out, scale_out, n, sums, s);
-        else launch_codec<true, false>(op, in, scale_in, out, scale_out, n, sums, s);
+        if (linear) launch_codec<true, true>(op, in, scale_in, out, scale_out, n, partial, s);
+        else launch_codec<true, false>(op, in, scale_in, out, scale_out, n, partial, s);
     } else {
-        if (linear) launch_codec<false, true>(op, in, scale_in, out, scale_out, n, sums, s);
-        else launch_codec<false, false>(op, in, scale_in, out, scale_out, n, sums, s);
+        if (linear) launch_codec<false, true>(op, in, scale_in, out, scale_out, n, partial, s);
+        else launch_codec<false, false>(op, in, scale_in, out, scale_out, n, partial, s);
     }
 }
 void launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
@@ -1590,8 +1617,13 @@ void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t
                        hipStream_t s) {
     dispatch_codec(variance, linear, 1, q, scale, x, nullptr, n, nullptr, s);
 }
-void launch_nmse(bool variance, bool linear, const float* x, int64_t n, double* sums, hipStream_t s) {
-    dispatch_codec(variance, linear, 2, x, nullptr, nullptr, nullptr, n, sums, s);
+hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
+                       hipStream_t s) {
+    dispatch_codec(variance, linear, 2, x, nullptr, nullptr, nullptr, n, partial, s);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kThreads), 0, s, partial, (int)nmse_blocks(n), sums);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------ layout conversion --

@@ -85,6 +85,46 @@ def test_nmse_of_a_buffer_larger_than_one_pass_of_the_grid():
     assert err / ref == pytest.approx(want, rel=1e-9)
 
 
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 2048 * 2048, 2048 * 2048 + 1])
+@pytest.mark.parametrize("state", ["momentum", "variance"])
+def test_nmse_at_the_edges_of_a_tile_and_of_the_grid(state, n):
+    rng = np.random.default_rng(n)
+    x = (rng.standard_normal(n) * 1e-3).astype(np.float32)
+    x = x * x if state == "variance" else x
+    err, ref = fo.quantization_nmse(state, False, _dev(x))
+    qf, df = ((oracle.quantize_momentum, oracle.dequantize_momentum) if state == "momentum" else
+              (oracle.quantize_variance, oracle.dequantize_variance))
+    q, s = qf(x)
+    x64 = x.astype(np.float64)
+    # n FP64 additions in another order: relative error below n * 2^-53 < 5e-10 (every term is non-negative)
+    assert ref == pytest.approx(float(np.dot(x64, x64)), rel=1e-9)
+    assert err == pytest.approx(float(((df(q, s).astype(np.float64) - x64) ** 2).sum()), rel=1e-9, abs=0.0)
+
+
+def test_nmse_calls_of_several_threads_do_not_share_their_sums():
+    import threading
+    xs = [torch.full((4096 * (i + 1) + i,), float(i + 1), device="cuda") for i in range(6)]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        want = float(xs[i].numel()) * (i + 1) ** 2            # every value is the group maximum: no error, exact sums
+        for _ in range(20):
+            got = fo.quantization_nmse("momentum", False, xs[i], stream=stream)
+            if got != (0.0, want):
+                wrong.append((i, got, want))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong[:3]
+    fo.release_cache()                                          # the idle workspaces are given back ...
+    assert fo.quantization_nmse("momentum", False, xs[0])[1] == float(xs[0].numel())       # ... and made anew
+
+
 def test_nmse_argument_validation_and_empty():
     assert fo.quantization_nmse("momentum", False, torch.empty(0, dtype=torch.float32, device="cuda")) == (0.0, 0.0)
     L = fo.load_library()
