@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstdint>
@@ -15,6 +16,7 @@
 #include <list>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -45,6 +47,7 @@ thread_local int g_last_hip_error = 0;
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int64_t n_groups(int64_t n) { return (n + fo::kGroup - 1) / fo::kGroup; }
+inline size_t round16(size_t x) { return (x + 15) & ~(size_t)15; }
 inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 
 // ----------------------------------------------------- cached device tables --
@@ -56,23 +59,26 @@ inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 // The tensor table is re-uploaded (104 B per tensor, through pinned staging, in stream
 // order) only when its content differs from what the device already holds.
 
-struct Staging {          // pinned host buffer + the event that marks its last copy done
-    void* host = nullptr;
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;
-    bool in_flight = false;
-};
+constexpr uint32_t kRingSlots = 4;
+constexpr size_t kFlagStride = 64;      // bytes: each slot's flag has a cache line of its own
 
 struct Plan {
     int device = 0;
+    void* d_mem = nullptr;         // one allocation: the table, then the index
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
-    size_t table_bytes = 0;
-    void* d_index = nullptr;       // uint32 coarse table (steps, conversions) or uint2 chunk table (copies)
-    void* h_index = nullptr;       // pinned source of the index table's one upload (kept until the plan is freed)
+    void* d_index = nullptr;       // uint32 coarse table (steps, conversions) or uint2 piece table (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     std::string uploaded;          // bytes of the table the device currently holds
-    Staging ring[4];
-    int next_slot = 0;
+    // Pinned memory, one allocation: the slots' flags, the source of the index table's one upload (kept until the plan
+    // is freed), and kRingSlots slots of slot_bytes through which tables and headers reach the device.  The kernel that
+    // reads slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
+    uint8_t* h_mem = nullptr;
+    uint8_t* h_slots = nullptr;
+    size_t slot_bytes = 0;
+    uint32_t n_uploads = 0;
+    uint32_t in_slot[kRingSlots] = {};     // number of the upload last put into each slot (0: none)
+
+    uint32_t* flag(uint32_t slot) const { return reinterpret_cast<uint32_t*>(h_mem + slot * kFlagStride); }
 };
 
 std::mutex g_mu;
@@ -86,52 +92,64 @@ void destroy_plan(Plan& p) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p.device);
-    if (p.d_table || p.d_index) (void)hipDeviceSynchronize();
-    for (auto& s : p.ring) {
-        if (s.done) { if (s.in_flight) (void)hipEventSynchronize(s.done); (void)hipEventDestroy(s.done); }
-        if (s.host) (void)hipHostFree(s.host);
-        s = Staging();
-    }
-    if (p.d_table) (void)hipFree(p.d_table);
-    if (p.d_index) (void)hipFree(p.d_index);
-    if (p.h_index) (void)hipHostFree(p.h_index);
-    p.d_table = nullptr; p.d_index = nullptr; p.h_index = nullptr;
+    if (p.d_mem) (void)hipDeviceSynchronize();
+    if (p.d_mem) (void)hipFree(p.d_mem);
+    if (p.h_mem) (void)hipHostFree(p.h_mem);
+    p.d_mem = nullptr; p.h_mem = nullptr;
     (void)hipSetDevice(cur);
 }
 
-// Puts `bytes` of `src` (host memory that the caller may reuse at once) into device memory `dst` in stream
-// order, via one of the plan's pinned ring slots.  Never waits for the stream: a slot is waited for only
-// when its own copy of four uploads ago is still in flight.
-int stage_and_copy(Plan& p, void* dst, const void* src, size_t bytes, hipStream_t stream) {
-    Staging& s = p.ring[p.next_slot];
-    p.next_slot = (p.next_slot + 1) % 4;
-    if (s.in_flight) { FO_HIP(hipEventSynchronize(s.done)); s.in_flight = false; }
-    if (s.bytes < bytes) {
-        if (s.host) { FO_HIP(hipHostFree(s.host)); s.host = nullptr; s.bytes = 0; }
-        FO_HIP(hipHostMalloc(&s.host, bytes, hipHostMallocDefault));
-        s.bytes = bytes;
+// Puts `bytes` of `src` (host memory that the caller may reuse at once; at most slot_bytes) into one of the plan's
+// pinned slots, for a kernel that the caller then launches with *flag and *seq.  Never waits for the stream: a slot is
+// waited for only when the kernel that reads it, of kRingSlots uploads ago, has not run yet.
+int stage(Plan& p, const void* src, size_t bytes, void** slot, uint32_t** flag, uint32_t* seq) {
+    const uint32_t i = p.n_uploads % kRingSlots;
+    if (p.in_slot[i]) {
+        const volatile uint32_t* f = p.flag(i);
+        // (bounded: a kernel that was captured into a graph and has not been replayed, or that a failed stream dropped,
+        // never sets the flag; once the device has drained nothing reads the slot)
+        const auto t0 = std::chrono::steady_clock::now();
+        for (uint32_t k = 0; *f != p.in_slot[i]; ++k) {
+            if (k < 1000) continue;
+            std::this_thread::yield();
+            if (std::chrono::steady_clock::now() - t0 < std::chrono::seconds(5)) continue;
+            FO_HIP(hipDeviceSynchronize());
+            break;
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        p.in_slot[i] = 0;
     }
-    if (!s.done) FO_HIP(hipEventCreateWithFlags(&s.done, hipEventDisableTiming));
-    std::memcpy(s.host, src, bytes);
-    FO_HIP(hipMemcpyAsync(dst, s.host, bytes, hipMemcpyHostToDevice, stream));
-    FO_HIP(hipEventRecord(s.done, stream));
-    s.in_flight = true;
+    *slot = p.h_slots + i * p.slot_bytes;
+    std::memcpy(*slot, src, bytes);
+    *flag = p.flag(i);
+    *seq = p.n_uploads + 1;
     return FLASHOPTIM_OK;
+}
+// The kernel that reads the slot of the last stage() call has been launched.
+void mark_in_flight(Plan& p) {
+    const uint32_t i = p.n_uploads % kRingSlots;
+    p.in_slot[i] = ++p.n_uploads;
 }
 
 // Puts `bytes` of `src` into p.d_table in stream order and remembers what the device now holds.
 int upload_table(Plan& p, const void* src, size_t bytes, hipStream_t stream) {
-    const int rc = stage_and_copy(p, p.d_table, src, bytes, stream);
-    if (rc == FLASHOPTIM_OK) p.uploaded.assign(static_cast<const char*>(src), bytes);
-    return rc;
+    void* slot = nullptr;
+    uint32_t *flag = nullptr, seq = 0;
+    const int rc = stage(p, src, bytes, &slot, &flag, &seq);
+    if (rc != FLASHOPTIM_OK) return rc;
+    FO_HIP(fo::launch_upload(slot, p.d_table, bytes, flag, seq, stream));
+    mark_in_flight(p);
+    p.uploaded.assign(static_cast<const char*>(src), bytes);
+    return FLASHOPTIM_OK;
 }
 
 // Finds or creates the plan for `key`.  The index table is consumed only on creation: it is copied to a
 // pinned buffer of the plan and uploaded in stream order on `stream`, ahead of the launch that the
 // creating call enqueues there (later calls with the same list touch the same tensors, so the caller
 // orders them after this one like any other work on those tensors).  Nothing here waits for the stream.
-int get_plan(const std::string& key, size_t table_bytes, const void* index, size_t index_bytes, int64_t n_chunks,
-             hipStream_t stream, Plan** out) {
+// slot_bytes: the most that stage() is asked to hold.
+int get_plan(const std::string& key, size_t table_bytes, const void* index, size_t index_bytes, size_t slot_bytes,
+             int64_t n_chunks, hipStream_t stream, Plan** out) {
     auto it = g_index.find(key);
     if (it != g_index.end()) {
         g_plans.splice(g_plans.begin(), g_plans, it->second);
@@ -140,14 +158,19 @@ int get_plan(const std::string& key, size_t table_bytes, const void* index, size
     }
     Plan p;
     FO_HIP(hipGetDevice(&p.device));
-    p.table_bytes = table_bytes;
     p.n_chunks = n_chunks;
-    hipError_t e = hipMalloc(&p.d_table, table_bytes);
-    if (e == hipSuccess) e = hipMalloc(&p.d_index, index_bytes);
-    if (e == hipSuccess) e = hipHostMalloc(&p.h_index, index_bytes, hipHostMallocDefault);
+    p.slot_bytes = (size_t)align64((int64_t)slot_bytes);
+    const size_t index_at = (size_t)align64((int64_t)table_bytes), h_index_at = kRingSlots * kFlagStride;
+    const size_t h_slots_at = h_index_at + (size_t)align64((int64_t)index_bytes);
+    hipError_t e = hipMalloc(&p.d_mem, index_at + round16(index_bytes));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, h_slots_at + kRingSlots * p.slot_bytes, hipHostMallocDefault);
     if (e == hipSuccess) {
-        std::memcpy(p.h_index, index, index_bytes);
-        e = hipMemcpyAsync(p.d_index, p.h_index, index_bytes, hipMemcpyHostToDevice, stream);
+        p.d_table = p.d_mem;
+        p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
+        p.h_slots = p.h_mem + h_slots_at;
+        std::memset(p.h_mem, 0, kRingSlots * kFlagStride);
+        std::memcpy(p.h_mem + h_index_at, index, index_bytes);
+        e = fo::launch_move(p.h_mem + h_index_at, p.d_index, index_bytes, stream);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -321,7 +344,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
         }
     }
     int rc = get_plan(key, live.size() * sizeof(TensorDev), coarse.data(), coarse.size() * sizeof(uint32_t),
-                      total_chunks, stream, &plan);
+                      live.size() * sizeof(TensorDev), total_chunks, stream, &plan);
     if (rc != FLASHOPTIM_OK) return rc;
 
     const size_t bytes = live.size() * sizeof(TensorDev);
@@ -509,7 +532,6 @@ int64_t tensor_payload(int64_t n, int kind) {
 void put_i64(uint8_t* p, int64_t v) { for (int i = 0; i < 8; ++i) p[i] = (uint8_t)((uint64_t)v >> (8 * i)); }
 void put_u32(uint8_t* p, uint32_t v) { for (int i = 0; i < 4; ++i) p[i] = (uint8_t)(v >> (8 * i)); }
 int64_t get_i64(const uint8_t* p) { uint64_t v = 0; for (int i = 0; i < 8; ++i) v |= (uint64_t)p[i] << (8 * i); return (int64_t)v; }
-uint32_t get_u32(const uint8_t* p) { uint32_t v = 0; for (int i = 0; i < 4; ++i) v |= (uint32_t)p[i] << (8 * i); return v; }
 
 std::vector<uint8_t> build_header(int kind, const flashoptim_tensor* t, int64_t n, int64_t step, int64_t total) {
     std::vector<uint8_t> h((size_t)(64 + align64(16 * n)), 0);
@@ -549,43 +571,47 @@ void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* bl
     }
 }
 
-// header (pack only): `header_bytes` of host memory that go to `header_dst` in stream order, ahead of the copy.
+// header (pack only): `header_bytes` of host memory that go to `header_dst` in stream order, with the copy.
 int run_copy(const std::vector<CopySegment>& segs, hipStream_t stream, const void* header = nullptr,
              size_t header_bytes = 0, void* header_dst = nullptr) {
     if (segs.empty() && !header) return FLASHOPTIM_OK;
-    std::vector<uint2> chunks;
+    int64_t total = 0;
+    for (const CopySegment& s : segs) total += s.pad_bytes;
+    const int piece = total < fo::kCopySmallBytes ? fo::kCopyPieceSmall : fo::kCopyPieceLarge;
+    std::vector<uint2> pieces;
     for (size_t si = 0; si < segs.size(); ++si) {
-        const int64_t nc = (segs[si].pad_bytes + fo::kCopyChunkBytes - 1) / fo::kCopyChunkBytes;
-        for (int64_t ci = 0; ci < nc; ++ci) chunks.push_back(make_uint2((unsigned)si, (unsigned)ci));
+        const int64_t nc = (segs[si].pad_bytes + piece - 1) / piece;
+        for (int64_t ci = 0; ci < nc; ++ci) pieces.push_back(make_uint2((unsigned)si, (unsigned)ci));
     }
     int device = 0;
     FO_HIP(hipGetDevice(&device));
     std::string key;
-    const int32_t tag[2] = {-1, device};
+    // (the header's length is part of the identity: it sizes the plan's slots, and tensors without elements lengthen it)
+    const int32_t tag[3] = {-1, device, (int32_t)(header_bytes / 16)};
     append(key, tag, sizeof(tag));
     append(key, segs.data(), segs.size() * sizeof(CopySegment));
     std::lock_guard<std::mutex> lock(g_mu);
     Plan* plan = nullptr;
     // (a list without any element still has a header: one dummy entry keeps the allocations non-empty)
     const uint2 none = make_uint2(0u, 0u);
-    const CopySegment no_seg = {nullptr, nullptr, 0, 0};
-    int rc = get_plan(key, segs.empty() ? sizeof(CopySegment) : segs.size() * sizeof(CopySegment),
-                      chunks.empty() ? &none : chunks.data(), (chunks.empty() ? 1 : chunks.size()) * sizeof(uint2),
-                      (int64_t)chunks.size(), stream, &plan);
+    const size_t table_bytes = segs.empty() ? sizeof(CopySegment) : segs.size() * sizeof(CopySegment);
+    int rc = get_plan(key, table_bytes, pieces.empty() ? &none : pieces.data(),
+                      (pieces.empty() ? 1 : pieces.size()) * sizeof(uint2),
+                      header_bytes > table_bytes ? header_bytes : table_bytes, (int64_t)pieces.size(), stream, &plan);
     if (rc != FLASHOPTIM_OK) return rc;
-    (void)no_seg;
-    if (header) {
-        rc = stage_and_copy(*plan, header_dst, header, header_bytes, stream);
-        if (rc != FLASHOPTIM_OK) return rc;
-    }
-    if (segs.empty()) return FLASHOPTIM_OK;
-    if (plan->uploaded.empty()) {
+    if (!segs.empty() && plan->uploaded.empty()) {
         rc = upload_table(*plan, segs.data(), segs.size() * sizeof(CopySegment), stream);
         if (rc != FLASHOPTIM_OK) return rc;
     }
-    fo::launch_copy(static_cast<const CopySegment*>(plan->d_table), static_cast<const uint2*>(plan->d_index), plan->n_chunks,
-                    stream);
-    FO_HIP(hipGetLastError());
+    void* slot = nullptr;
+    uint32_t *flag = nullptr, seq = 0;
+    if (header) {
+        rc = stage(*plan, header, header_bytes, &slot, &flag, &seq);
+        if (rc != FLASHOPTIM_OK) return rc;
+    }
+    FO_HIP(fo::launch_copy(piece, static_cast<const CopySegment*>(plan->d_table), static_cast<const uint2*>(plan->d_index),
+                           plan->n_chunks, slot, header_dst, (int64_t)header_bytes, flag, seq, stream));
+    if (slot) mark_in_flight(*plan);
     return FLASHOPTIM_OK;
 }
 
@@ -597,43 +623,47 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
     return FLASHOPTIM_OK;
 }
 
-// ------------------------------------------------- workspaces of the quantisation error --
+// ------------------------------------------------------------ workspaces of waiting calls --
 //
-// A call needs device memory for the workgroups' partial sums and two doubles of pinned memory that the last kernel
-// writes and the host reads after waiting for the stream.  Both are kept from call to call (allocating and freeing
-// them cost ~20 us a call); a call takes a pair out of the pool for as long as it runs, so calls of several threads
-// and streams never share one, and a pair goes back only once its stream has been waited for.
-struct NmseSpace {
+// The calls that return values to the host (quantisation error, unpack's header check) let a kernel write them to
+// pinned memory and wait for the stream; the quantisation error also needs device memory for the workgroups' partial
+// sums.  Both are kept from call to call (allocating and freeing them cost ~20 us a call); a call takes a workspace
+// out of the pool for as long as it runs, so calls of several threads and streams never share one, and a workspace
+// goes back only once its stream has been waited for.
+struct CallSpace {
     int device = 0;
     double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs
-    double* sums = nullptr;         // pinned
+    void* host = nullptr;           // pinned, host_bytes
+    size_t host_bytes = 0;
 };
-std::mutex g_nmse_mu;
-constexpr int kMaxIdleNmse = 16;        // 32 KB of device memory each; a pair beyond that is freed after its call
-NmseSpace g_nmse_idle[kMaxIdleNmse];
-int g_nmse_n_idle = 0;
+std::mutex g_space_mu;
+constexpr int kMaxIdleSpaces = 16;              // 32 KB of device and at least 64 KB of pinned memory each; beyond that
+constexpr size_t kMinSpaceHost = 64 * 1024;     // a workspace is freed after its call, like one that had to be larger
+CallSpace g_space_idle[kMaxIdleSpaces];
+int g_space_n_idle = 0;
 
-void destroy_nmse(NmseSpace& w) {
+void destroy_space(CallSpace& w) {
     if (w.partial) (void)hipFree(w.partial);
-    if (w.sums) (void)hipHostFree(w.sums);
-    w.partial = nullptr; w.sums = nullptr;
+    if (w.host) (void)hipHostFree(w.host);
+    w = CallSpace();
 }
 
-int take_nmse(NmseSpace& w) {
+int take_space(CallSpace& w, size_t host_bytes) {
     FO_HIP(hipGetDevice(&w.device));
-    {
-        std::lock_guard<std::mutex> lock(g_nmse_mu);
-        for (int i = 0; i < g_nmse_n_idle; ++i) {
-            if (g_nmse_idle[i].device != w.device) continue;
-            w = g_nmse_idle[i];
-            g_nmse_idle[i] = g_nmse_idle[--g_nmse_n_idle];
+    if (host_bytes <= kMinSpaceHost) {
+        std::lock_guard<std::mutex> lock(g_space_mu);
+        for (int i = 0; i < g_space_n_idle; ++i) {
+            if (g_space_idle[i].device != w.device) continue;
+            w = g_space_idle[i];
+            g_space_idle[i] = g_space_idle[--g_space_n_idle];
             return FLASHOPTIM_OK;
         }
     }
+    w.host_bytes = host_bytes > kMinSpaceHost ? round16(host_bytes) : kMinSpaceHost;
     hipError_t e = hipMalloc((void**)&w.partial, fo::kNmseMaxBlocks * sizeof(double2));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&w.sums, 2 * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&w.host, w.host_bytes, hipHostMallocDefault);
     if (e != hipSuccess) {
-        destroy_nmse(w);
+        destroy_space(w);
         g_last_hip_error = (int)e;
         (void)hipGetLastError();
         return FLASHOPTIM_ERR_HIP;
@@ -641,11 +671,22 @@ int take_nmse(NmseSpace& w) {
     return FLASHOPTIM_OK;
 }
 
-// Takes a pair back whose work is known to have finished.
-void give_nmse(NmseSpace& w) {
-    std::lock_guard<std::mutex> lock(g_nmse_mu);
-    if (g_nmse_n_idle < kMaxIdleNmse) g_nmse_idle[g_nmse_n_idle++] = w;
-    else destroy_nmse(w);
+// Takes a workspace back whose work is known to have finished.
+void give_space(CallSpace& w) {
+    std::lock_guard<std::mutex> lock(g_space_mu);
+    if (g_space_n_idle < kMaxIdleSpaces && w.host_bytes == kMinSpaceHost) g_space_idle[g_space_n_idle++] = w;
+    else destroy_space(w);
+}
+
+// Waits for the work that uses `w` (launched with result `e`); if anything failed the workspace is freed, which waits
+// for whatever may still use it.
+int wait_space(CallSpace& w, hipError_t e, hipStream_t stream) {
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess) return FLASHOPTIM_OK;
+    g_last_hip_error = (int)e;
+    (void)hipGetLastError();
+    destroy_space(w);
+    return FLASHOPTIM_ERR_HIP;
 }
 
 // ------------------------------------------ the step entry point that allocates nothing --
@@ -936,20 +977,13 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     if (!x) return FLASHOPTIM_ERR_INVALID_ARG;
     if (!aligned16(x)) return FLASHOPTIM_ERR_MISALIGNED;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    NmseSpace w;
-    const int rc = take_nmse(w);
+    CallSpace w;
+    int rc = take_space(w, 2 * sizeof(double));
     if (rc != FLASHOPTIM_OK) return rc;
-    hipError_t e = fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, w.sums, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
-        (void)hipGetLastError();
-        destroy_nmse(w);            // hipFree waits for whatever may still use it
-        return FLASHOPTIM_ERR_HIP;
-    }
-    sums[0] = w.sums[0];
-    sums[1] = w.sums[1];
-    give_nmse(w);
+    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, static_cast<double*>(w.host), stream), stream);
+    if (rc != FLASHOPTIM_OK) return rc;
+    std::memcpy(sums, w.host, 2 * sizeof(double));
+    give_space(w);
     return FLASHOPTIM_OK;
 }
 
@@ -998,18 +1032,24 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     if (blob_bytes < total) return FLASHOPTIM_ERR_BAD_BLOB;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const std::vector<uint8_t> want = build_header(kind, tensors, n_tensors, 0, total);
-    std::vector<uint8_t> got(want.size());
-    FO_HIP(hipStreamSynchronize(stream));
-    FO_HIP(hipMemcpy(got.data(), blob, got.size(), hipMemcpyDeviceToHost));
-    // everything but the step field must match what this (kind, list) would have written
-    if (std::memcmp(got.data(), want.data(), 16) != 0) return FLASHOPTIM_ERR_BAD_BLOB;
-    if (std::memcmp(got.data() + 24, want.data() + 24, got.size() - 24) != 0) return FLASHOPTIM_ERR_BAD_BLOB;
-    std::vector<CopySegment> segs;
+    CallSpace w;
+    rc = take_space(w, want.size());
+    if (rc != FLASHOPTIM_OK) return rc;
+    const hipError_t e = fo::launch_move(blob, w.host, want.size(), stream);
+    std::vector<CopySegment> segs;      // built while the header is on its way
     build_segments(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, segs);
+    rc = wait_space(w, e, stream);
+    if (rc != FLASHOPTIM_OK) return rc;
+    // everything but the step field must match what this (kind, list) would have written
+    const uint8_t* got = static_cast<const uint8_t*>(w.host);
+    const bool match = std::memcmp(got, want.data(), 16) == 0 &&
+                       std::memcmp(got + 24, want.data() + 24, want.size() - 24) == 0;
+    const int64_t step = get_i64(got + 16);
+    give_space(w);
+    if (!match) return FLASHOPTIM_ERR_BAD_BLOB;
     rc = run_copy(segs, stream);
     if (rc != FLASHOPTIM_OK) return rc;
-    *step_out = get_i64(got.data() + 16);
-    (void)get_u32;
+    *step_out = step;
     return FLASHOPTIM_OK;
 }
 
@@ -1237,8 +1277,8 @@ int flashoptim_release_cache(void) {
     for (auto& kv : g_plans) destroy_plan(kv.second);
     g_plans.clear();
     g_index.clear();
-    std::lock_guard<std::mutex> nmse_lock(g_nmse_mu);
-    while (g_nmse_n_idle > 0) destroy_nmse(g_nmse_idle[--g_nmse_n_idle]);
+    std::lock_guard<std::mutex> space_lock(g_space_mu);
+    while (g_space_n_idle > 0) destroy_space(g_space_idle[--g_space_n_idle]);
     return FLASHOPTIM_OK;
 }
 

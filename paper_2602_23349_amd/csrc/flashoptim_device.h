@@ -39,10 +39,9 @@ constexpr int step_threads(int kind, bool split, bool quant) {
 constexpr int chunk_elems(int kind, bool split, bool quant) {
     return step_threads(kind, split, quant) * step_vec(kind, split, quant);
 }
-#ifndef FO_COPY_CHUNK_KB
-#define FO_COPY_CHUNK_KB 128
-#endif
-constexpr int kCopyChunkBytes = FO_COPY_CHUNK_KB * 1024;   // checkpoint copy: bytes per workgroup
+constexpr int kCopyPieceLarge = 128 * 1024;        // checkpoint copy: bytes per workgroup ...
+constexpr int kCopyPieceSmall = 32 * 1024;         // ... when fewer than kCopySmallBytes are copied in all
+constexpr int64_t kCopySmallBytes = (int64_t)2048 * kCopyPieceLarge;
 
 // One tensor as the kernels see it (device pointers), 104 bytes.
 struct TensorDev {
@@ -132,7 +131,14 @@ constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per comp
 // partial: device memory for kNmseMaxBlocks pairs; sums: two doubles that the device can write and the host reads
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
                        hipStream_t s);
-void launch_copy(const CopySegment* segs, const uint2* chunks, int64_t n_chunks, hipStream_t s);
+// header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst, header_bytes a multiple of 16;
+// it sets *flag (pinned) to seq when it has read the slot
+hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pieces, int64_t n_pieces, const void* header,
+                       void* header_dst, int64_t header_bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
+// Moves `bytes` (rounded up to 16: both buffers must have room) between pinned host memory and device memory.
+hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
+// The same from a pinned slot, by one workgroup that sets *flag (pinned) to seq when it has read the slot.
+hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
 constexpr int kSelftestSectionCount = 7;
 constexpr unsigned long long kSelftestSqrtValues = 0x7f800000ull - 0x0f800000ull;   // section 2: every FP32 value in [2^-96, FLT_MAX]
 constexpr int kSelftestCounters = 15;   // two per section, then the inexact count of section 6

@@ -1892,50 +1892,111 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 
 // ----------------------------------------------------------- checkpoint copy --
 //
-// Gather / scatter of byte segments: each workgroup copies one kCopyChunkBytes piece of one
-// segment with 128-bit accesses (segment starts are 16-byte aligned on both sides), the
-// ragged end byte by byte, and - when packing - zero-fills the padding up to pad_bytes.
+// Tells the host that a workgroup has read all of a slot of pinned memory.  Called by every lane of the workgroup after
+// its last use of the values it read (its loads have returned by then); the word itself carries no other data.
+__device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
-#ifndef FO_COPY_BATCH
-#define FO_COPY_BATCH 16
-#endif
-#ifndef FO_COPY_THREADS
-#define FO_COPY_THREADS 512
-#endif
-constexpr int kCopyThreads = FO_COPY_THREADS;
-__global__ __launch_bounds__(kCopyThreads) void copy_kernel(const CopySegment* segs, const uint2* chunks) {
-    const uint2 ck = chunks[blockIdx.x];
+// Gather / scatter of byte segments: each workgroup copies one piece of one segment with 128-bit accesses
+// (segment starts are 16-byte aligned on both sides), the ragged end byte by byte, and - when packing -
+// zero-fills the padding up to pad_bytes.  Bound: HBM.
+//
+// A full piece is BATCH loads per lane, all issued before the first store.  Long copies take 16 (pieces of 128 KB:
+// GPT-2's 638 MB blob 228 us, 5.6 TB/s, against 233 with 32 KB; two Llama layers with embedding and head 2.75 ms
+// against 2.97).  Below kCopySmallBytes there are fewer than two generations of such pieces - 1024 workgroups are
+// resident at a time - and the last one is mostly empty; four loads per lane then do better (ResNet-50, 131 MB:
+// 59.6 -> 51.8 us; a tensor of 3 M elements: 19.2 -> 15.1 us).
+//
+// header: the blob's header and table when packing, in a pinned slot; the workgroup behind the last piece writes it to
+// header_dst.
+constexpr int kCopyThreads = 512;
+template <int BATCH>
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(const CopySegment* segs, const uint2* pieces, uint32_t n_pieces,
+                                                            const uint4* header, uint4* header_dst, uint32_t header_n16,
+                                                            uint32_t* flag, uint32_t seq) {
+    constexpr int64_t kStride = (int64_t)kCopyThreads * 16;
+    constexpr int64_t kPiece = kStride * BATCH;
+    if (blockIdx.x == n_pieces) {
+        for (uint32_t i = threadIdx.x; i < header_n16; i += kCopyThreads) header_dst[i] = header[i];
+        release_slot(flag, seq);
+        return;
+    }
+    const uint2 ck = pieces[blockIdx.x];
     const CopySegment sg = segs[ck.x];
-    const int64_t begin = (int64_t)ck.y * kCopyChunkBytes;
+    const int64_t begin = (int64_t)ck.y * kPiece;
     const int64_t total = sg.pad_bytes;                  // >= sg.bytes
-    const int64_t end = (total - begin < kCopyChunkBytes) ? total : begin + kCopyChunkBytes;
+    const int64_t end = (total - begin < kPiece) ? total : begin + kPiece;
     const uint8_t* src = sg.src;
     uint8_t* dst = sg.dst;
-    constexpr int kBatch = FO_COPY_BATCH;                 // 128-bit loads in flight per lane
-    constexpr int64_t kStride = (int64_t)kCopyThreads * 16;
-    int64_t o = begin + (int64_t)threadIdx.x * 16;
-    // whole batches inside the copied bytes: all loads of a batch are issued before its stores
-    for (; o + (kBatch - 1) * kStride + 16 <= sg.bytes && o + (kBatch - 1) * kStride < end; o += kBatch * kStride) {
-        uint4 v[kBatch];
+    const int64_t o = begin + (int64_t)threadIdx.x * 16;
+    uint4 v[BATCH];
+    if (begin + kPiece <= sg.bytes) {
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) v[k] = ld128(src + o + k * kStride);
+        for (int k = 0; k < BATCH; ++k) v[k] = ld128(src + o + k * kStride);
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) st128(dst + o + k * kStride, v[k].x, v[k].y, v[k].z, v[k].w);
+        for (int k = 0; k < BATCH; ++k) st128(dst + o + k * kStride, v[k].x, v[k].y, v[k].z, v[k].w);
+        return;
     }
-    for (; o < end; o += kStride) {
-        if (o + 16 <= sg.bytes) {
-            const uint4 v = ld128(src + o);
-            st128(dst + o, v.x, v.y, v.z, v.w);
-        } else {
-            for (int k = 0; k < 16 && o + k < end; ++k) dst[o + k] = (o + k < sg.bytes) ? src[o + k] : (uint8_t)0;
-        }
+    // a segment's last piece: the same batch with the accesses past its end left out, then its ragged end
+#pragma unroll
+    for (int k = 0; k < BATCH; ++k) if (o + k * kStride + 16 <= sg.bytes) v[k] = ld128(src + o + k * kStride);
+#pragma unroll
+    for (int k = 0; k < BATCH; ++k)
+        if (o + k * kStride + 16 <= sg.bytes) st128(dst + o + k * kStride, v[k].x, v[k].y, v[k].z, v[k].w);
+    for (int64_t e = o; e < end; e += kStride) {
+        if (e + 16 <= sg.bytes) continue;
+        for (int k = 0; k < 16 && e + k < end; ++k) dst[e + k] = (e + k < sg.bytes) ? src[e + k] : (uint8_t)0;
     }
 }
+static_assert(kCopyPieceLarge == kCopyThreads * 16 * 16 && kCopyPieceSmall == kCopyThreads * 16 * 4,
+              "the host cuts the segments into pieces of these sizes");
 
 // (Issuing the copy as several shorter launches, which helps the step kernels, changed its rate by
 // less than 2 %: it stays one launch.)
-void launch_copy(const CopySegment* segs, const uint2* chunks, int64_t n_chunks, hipStream_t s) {
-    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)n_chunks), dim3(kCopyThreads), 0, s, segs, chunks);
+hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pieces, int64_t n_pieces, const void* header,
+                       void* header_dst, int64_t header_bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
+    const dim3 grid((unsigned)(n_pieces + (header ? 1 : 0))), block(kCopyThreads);
+    if (piece_bytes == kCopyPieceLarge)
+        hipLaunchKernelGGL(copy_kernel<16>, grid, block, 0, s, segs, pieces, (uint32_t)n_pieces, (const uint4*)header,
+                           (uint4*)header_dst, (uint32_t)(header_bytes / 16), flag, seq);
+    else
+        hipLaunchKernelGGL(copy_kernel<4>, grid, block, 0, s, segs, pieces, (uint32_t)n_pieces, (const uint4*)header,
+                           (uint4*)header_dst, (uint32_t)(header_bytes / 16), flag, seq);
+    return hipGetLastError();
+}
+
+// Small transfers between pinned host memory and device memory, in either direction, by a kernel instead of a copy
+// command (16-byte multiples; bound by the link to the host).  A copy command and the event that marks its end cost
+// the host 17 us and the stream 6 us in front of a step whose descriptors changed; these kernels cost 8 and 3
+// (ResNet-50 list under a learning-rate schedule: 75 us a step -> 60).
+__global__ __launch_bounds__(256) void move_kernel(const uint4* src, uint4* dst, uint32_t n16) {
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n16; i += gridDim.x * 256u) dst[i] = src[i];
+}
+hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s) {
+    const uint32_t n16 = (uint32_t)((bytes + 15) / 16), blocks = (n16 + 255) / 256;
+    hipLaunchKernelGGL(move_kernel, dim3(blocks < 64 ? blocks : 64), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, n16);
+    return hipGetLastError();
+}
+
+// One workgroup takes a descriptor table (104 bytes per tensor) from a pinned slot: four loads per lane in flight.
+constexpr int kUploadThreads = 1024;
+__global__ __launch_bounds__(kUploadThreads) void upload_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,
+                                                                uint32_t seq) {
+    for (uint32_t i = threadIdx.x; i < n16; i += 4 * kUploadThreads) {
+        uint4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) if (i + k * kUploadThreads < n16) v[k] = src[i + k * kUploadThreads];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) if (i + k * kUploadThreads < n16) dst[i + k * kUploadThreads] = v[k];
+    }
+    release_slot(flag, seq);
+}
+hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
+    hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadThreads), 0, s, (const uint4*)src, (uint4*)dst,
+                       (uint32_t)((bytes + 15) / 16), flag, seq);
+    return hipGetLastError();
 }
 
 }  // namespace fo

@@ -67,6 +67,48 @@ def test_checkpoint_pack_does_not_wait_for_the_stream():
         assert torch.equal(a.param.view(torch.int16), b.param.view(torch.int16)) and torch.equal(a.v_q, b.v_q)
 
 
+def test_descriptor_uploads_behind_a_busy_stream_keep_their_order():
+    # every step uploads other learning rates through one of four pinned slots: four steps are enqueued without waiting,
+    # further ones wait for a slot and never overwrite one that a kernel has still to read
+    specs = W.odd_sizes()
+    bufs, _ = _state(specs, seed=25)
+    ref, _ = _state(specs, seed=25)
+    tl, tl_ref = fo.TensorList(bufs), fo.TensorList(ref)
+    fo.adamw_step_exact(tl_ref, 0.9, 0.999, 1e-8, 1)
+    fo.adamw_step_exact(tl, 0.9, 0.999, 1e-8, 1)
+    torch.cuda.synchronize()
+    mon = _busy_stream(0.4)
+    t0 = time.perf_counter()
+    for t in range(2, 14):
+        for i in range(tl.n):
+            tl.set_hyper(i, lr=1e-3 * t)
+        fo.adamw_step_exact(tl, 0.9, 0.999, 1e-8, t, stream=mon.stream)
+        if t == 5:
+            dt, still_busy = time.perf_counter() - t0, not mon.stream.query()
+    mon.stream.synchronize()
+    assert still_busy and dt < 0.3, f"four steps took {dt:.3f} s on the host; stream busy afterwards: {still_busy}"
+    for t in range(2, 14):
+        for i in range(tl_ref.n):
+            tl_ref.set_hyper(i, lr=1e-3 * t)
+        fo.adamw_step_exact(tl_ref, 0.9, 0.999, 1e-8, t)
+        torch.cuda.synchronize()
+    for a, b in zip(ref, bufs):
+        assert torch.equal(a.rho, b.rho) and torch.equal(a.param.view(torch.int16), b.param.view(torch.int16))
+
+
+def test_packing_lists_that_differ_in_empty_tensors_only():
+    # the header grows with every tensor of the list, also with those that have no element
+    one = fo.ParamBuffers(64, "sgd")
+    for empties in (0, 1, 40, 3):
+        bufs = [one] * bool(empties % 2) + [fo.ParamBuffers(0, "sgd") for _ in range(empties)]
+        numels = [b.numel for b in bufs]
+        blob = torch.full((fo.checkpoint_size("sgd", numels),), 0x5A, dtype=torch.uint8, device="cuda")
+        fo.checkpoint_pack("sgd", bufs, 9, blob)
+        states = [oracle.TensorState(np.zeros(n, np.float32), "sgd") for n in numels]
+        assert np.array_equal(blob.cpu().numpy(), oracle.checkpoint_pack("sgd", states, 9))
+        assert fo.checkpoint_unpack("sgd", blob, bufs) == 9
+
+
 def test_first_step_on_a_new_list_does_not_wait_for_the_stream():
     specs = W.odd_sizes()
     bufs, _ = _state(specs, seed=22)

@@ -378,6 +378,39 @@ def test_checkpoint_pack_unpack_small_lists():
             assert sum(r[1] for r in rep) == 0
 
 
+@pytest.mark.parametrize("kind,sizes", [
+    # sections of 1 or 2 bytes per element around the ends of a 32 KB piece, and of its 8 KB rows
+    ("adamw", [4095, 4096, 8191, 8192, 8200, 16383, 16384, 16385, 32767, 32768, 32769, 32784, 65536, 65551]),
+    # the same for the 128 KB pieces of a long copy (above 256 MB in all)
+    ("adamw", [65535, 65536, 65537, 131071, 131072, 131073, 131088, 53_000_000]),
+    ("sgd", [3]),
+])
+def test_checkpoint_at_the_edges_of_a_piece(kind, sizes):
+    rng = np.random.default_rng(len(sizes))
+    states, bufs = [], []
+    for n in sizes:
+        st, ng = oracle.TensorState(np.zeros(1, np.float32), kind), (n + 31) // 32
+        st.n = n
+        st.thp, st.ms = rng.integers(0, 1 << 16, n, dtype=np.uint16), rng.integers(0, 1 << 16, ng, dtype=np.uint16)
+        st.rho, st.mq = (rng.integers(-128, 128, n, dtype=np.int8) for _ in range(2))
+        if kind == "adamw":
+            st.vq, st.vs = rng.integers(0, 256, n, dtype=np.uint8), rng.integers(0, 1 << 16, ng, dtype=np.uint16)
+        states.append(st)
+        bufs.append(upload_state(st, with_grad=False))
+    size = fo.checkpoint_size(kind, sizes)
+    blob = torch.full((size + 64,), 0x5A, dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack(kind, bufs, 7, blob[:size])
+    got = blob.cpu().numpy()
+    assert np.array_equal(got[:size], oracle.checkpoint_pack(kind, states, 7)) and (got[size:] == 0x5A).all()
+    fresh = [fo.ParamBuffers(n, kind, with_grad=False) for n in sizes]
+    assert fo.checkpoint_unpack(kind, blob[:size], fresh) == 7
+    for f, b in zip(fresh, bufs):
+        for k in ("param", "rho", "m_q", "m_scale", "v_q", "v_scale"):
+            x, y = getattr(f, k), getattr(b, k)
+            assert x is None or torch.equal(x.view(torch.int16 if x.element_size() == 2 else x.dtype),
+                                            y.view(torch.int16 if y.element_size() == 2 else y.dtype)), (f.numel, k)
+
+
 def test_hyperparameters_and_gradient_buffers_may_change_between_steps():
     # lr follows a schedule, weight decay toggles, and gradients arrive in different buffers: the cached
     # device table of the list must follow (it is re-uploaded in stream order when its content changes)
