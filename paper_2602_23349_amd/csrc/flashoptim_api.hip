@@ -15,7 +15,6 @@
 #include <cstring>
 #include <list>
 #include <mutex>
-#include <string>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -54,23 +53,54 @@ inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 //
 // A "plan" is what a multi-tensor launch needs on the device: the tensor table and the index
 // table (for steps and conversions a coarse workgroup -> tensor table, for copies one entry
-// per workgroup).  It is keyed by the list's identity (device, kind, every state pointer and
+// per workgroup).  It belongs to the list's identity (device, operation, every state pointer and
 // numel; NOT the gradient pointers or lr/wd, which legitimately change from step to step).
 // The tensor table is re-uploaded (104 B per tensor, through pinned staging, in stream
 // order) only when its content differs from what the device already holds.
+//
+// A call finds its plan through a 64-bit hash of the identity and then compares the descriptors themselves, so a
+// collision costs time and nothing else.  (With the identity as a string key, built and hashed byte by byte on
+// every call, a step over 161 tensors spent 5 us on the host beyond the launch, a checkpoint pack 20.)
+
+struct PlanTag {
+    int32_t device, op, kind, flags;    // op: a LiveOp, or kOpPack / kOpUnpack
+    const void* blob;                   // copies: the blob
+};
+inline bool operator==(const PlanTag& a, const PlanTag& b) {
+    return a.device == b.device && a.op == b.op && a.kind == b.kind && a.flags == b.flags && a.blob == b.blob;
+}
+
+bool same_identity(const TensorDev& a, const TensorDev& b) {
+    return a.param == b.param && a.rho == b.rho && a.m_q == b.m_q && a.m_scale == b.m_scale && a.v_q == b.v_q &&
+           a.v_scale == b.v_scale && a.theta32 == b.theta32 && a.m32 == b.m32 && a.v32 == b.v32 && a.numel == b.numel;
+}
+
+uint64_t identity_hash(const PlanTag& tag, const std::vector<TensorDev>& t) {
+    const uint64_t k = 0x9e3779b97f4a7c15ull;
+    uint64_t h = ((uint64_t)(uint32_t)tag.device + ((uint64_t)(uint32_t)tag.op << 16) + ((uint64_t)(uint32_t)tag.kind << 32) +
+                  ((uint64_t)(uint32_t)tag.flags << 48)) * k + (uint64_t)reinterpret_cast<uintptr_t>(tag.blob);
+    auto w = [](const void* p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); };
+    for (const TensorDev& d : t) {
+        const uint64_t x = w(d.param) + 3 * w(d.rho) + 5 * w(d.m_q) + 7 * w(d.m_scale) + 11 * w(d.v_q) + 13 * w(d.v_scale);
+        const uint64_t y = 17 * w(d.theta32) + 19 * w(d.m32) + 23 * w(d.v32) + 29 * (uint64_t)d.numel;
+        h = (h ^ (h >> 29) ^ (x + y)) * k;
+    }
+    return h ^ (h >> 32);
+}
 
 constexpr uint32_t kRingSlots = 4;
 constexpr size_t kFlagStride = 64;      // bytes: each slot's flag has a cache line of its own
 
 struct Plan {
-    int device = 0;
+    PlanTag tag = {};
+    uint64_t hash = 0;
+    std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
     void* d_mem = nullptr;         // one allocation: the table, then the index
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
     void* d_index = nullptr;       // uint32 coarse table (steps, conversions) or uint2 piece table (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
-    std::string uploaded;          // bytes of the table the device currently holds
-    // Pinned memory, one allocation: the slots' flags, the source of the index table's one upload (kept until the plan
-    // is freed), and kRingSlots slots of slot_bytes through which tables and headers reach the device.  The kernel that
+    // Pinned memory, one allocation: the slots' flags, the source of the first upload of both tables (kept until the
+    // plan is freed), and kRingSlots slots of slot_bytes through which later tables and headers reach the device.  The kernel that
     // reads slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
     uint8_t* h_mem = nullptr;
     uint8_t* h_slots = nullptr;
@@ -82,8 +112,8 @@ struct Plan {
 };
 
 std::mutex g_mu;
-std::unordered_map<std::string, std::list<std::pair<std::string, Plan>>::iterator> g_index;
-std::list<std::pair<std::string, Plan>> g_plans;   // most recently used first
+std::list<Plan> g_plans;            // most recently used first
+std::unordered_multimap<uint64_t, std::list<Plan>::iterator> g_index;
 constexpr size_t kMaxPlans = 256;   // least recently used beyond this are freed (after a device synchronisation)
 
 // Frees a plan's device and pinned buffers.  Work that was enqueued with this plan may still read them, so
@@ -91,7 +121,7 @@ constexpr size_t kMaxPlans = 256;   // least recently used beyond this are freed
 void destroy_plan(Plan& p) {
     int cur = 0;
     (void)hipGetDevice(&cur);
-    (void)hipSetDevice(p.device);
+    (void)hipSetDevice(p.tag.device);
     if (p.d_mem) (void)hipDeviceSynchronize();
     if (p.d_mem) (void)hipFree(p.d_mem);
     if (p.h_mem) (void)hipHostFree(p.h_mem);
@@ -131,46 +161,46 @@ void mark_in_flight(Plan& p) {
     p.in_slot[i] = ++p.n_uploads;
 }
 
-// Puts `bytes` of `src` into p.d_table in stream order and remembers what the device now holds.
-int upload_table(Plan& p, const void* src, size_t bytes, hipStream_t stream) {
-    void* slot = nullptr;
-    uint32_t *flag = nullptr, seq = 0;
-    const int rc = stage(p, src, bytes, &slot, &flag, &seq);
-    if (rc != FLASHOPTIM_OK) return rc;
-    FO_HIP(fo::launch_upload(slot, p.d_table, bytes, flag, seq, stream));
-    mark_in_flight(p);
-    p.uploaded.assign(static_cast<const char*>(src), bytes);
-    return FLASHOPTIM_OK;
+// Finds the plan of a list and makes it the most recently used one; nullptr if there is none.
+Plan* find_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors) {
+    const auto range = g_index.equal_range(hash);
+    for (auto it = range.first; it != range.second; ++it) {
+        const Plan& p = *it->second;
+        if (!(p.tag == tag) || p.tensors.size() != tensors.size()) continue;
+        bool same = true;
+        for (size_t i = 0; i < tensors.size() && same; ++i) same = same_identity(p.tensors[i], tensors[i]);
+        if (!same) continue;
+        g_plans.splice(g_plans.begin(), g_plans, it->second);
+        return &g_plans.front();
+    }
+    return nullptr;
 }
 
-// Finds or creates the plan for `key`.  The index table is consumed only on creation: it is copied to a
-// pinned buffer of the plan and uploaded in stream order on `stream`, ahead of the launch that the
-// creating call enqueues there (later calls with the same list touch the same tensors, so the caller
-// orders them after this one like any other work on those tensors).  Nothing here waits for the stream.
-// slot_bytes: the most that stage() is asked to hold.
-int get_plan(const std::string& key, size_t table_bytes, const void* index, size_t index_bytes, size_t slot_bytes,
-             int64_t n_chunks, hipStream_t stream, Plan** out) {
-    auto it = g_index.find(key);
-    if (it != g_index.end()) {
-        g_plans.splice(g_plans.begin(), g_plans, it->second);
-        *out = &g_plans.front().second;
-        return FLASHOPTIM_OK;
-    }
+// Makes the plan of a list that has none.  Both tables are copied to pinned memory of the plan and uploaded in stream
+// order on `stream`, ahead of the launch that the creating call enqueues there (later calls with the same list touch
+// the same tensors, so the caller orders them after this one like any other work on those tensors).  Nothing here
+// waits for the stream.  slot_bytes: the most that stage() is asked to hold.
+int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors, const void* table,
+              size_t table_bytes, const void* index, size_t index_bytes, size_t slot_bytes, int64_t n_chunks,
+              hipStream_t stream, Plan** out) {
     Plan p;
-    FO_HIP(hipGetDevice(&p.device));
+    p.tag = tag;
+    p.hash = hash;
+    p.tensors = tensors;
     p.n_chunks = n_chunks;
     p.slot_bytes = (size_t)align64((int64_t)slot_bytes);
-    const size_t index_at = (size_t)align64((int64_t)table_bytes), h_index_at = kRingSlots * kFlagStride;
-    const size_t h_slots_at = h_index_at + (size_t)align64((int64_t)index_bytes);
-    hipError_t e = hipMalloc(&p.d_mem, index_at + round16(index_bytes));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, h_slots_at + kRingSlots * p.slot_bytes, hipHostMallocDefault);
+    const size_t index_at = (size_t)align64((int64_t)table_bytes), both = index_at + round16(index_bytes);
+    const size_t source_at = kRingSlots * kFlagStride, slots_at = source_at + (size_t)align64((int64_t)both);
+    hipError_t e = hipMalloc(&p.d_mem, both > 0 ? both : 16);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, slots_at + kRingSlots * p.slot_bytes, hipHostMallocDefault);
     if (e == hipSuccess) {
         p.d_table = p.d_mem;
         p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
-        p.h_slots = p.h_mem + h_slots_at;
-        std::memset(p.h_mem, 0, kRingSlots * kFlagStride);
-        std::memcpy(p.h_mem + h_index_at, index, index_bytes);
-        e = fo::launch_move(p.h_mem + h_index_at, p.d_index, index_bytes, stream);
+        p.h_slots = p.h_mem + slots_at;
+        std::memset(p.h_mem, 0, source_at);
+        if (table_bytes) std::memcpy(p.h_mem + source_at, table, table_bytes);
+        if (index_bytes) std::memcpy(p.h_mem + source_at + index_at, index, index_bytes);
+        if (both) e = fo::launch_move(p.h_mem + source_at, p.d_mem, both, stream);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -178,18 +208,33 @@ int get_plan(const std::string& key, size_t table_bytes, const void* index, size
         destroy_plan(p);
         return FLASHOPTIM_ERR_HIP;
     }
-    g_plans.emplace_front(key, p);
-    g_index[key] = g_plans.begin();
+    g_plans.push_front(std::move(p));
+    g_index.emplace(hash, g_plans.begin());
     while (g_plans.size() > kMaxPlans) {
-        destroy_plan(g_plans.back().second);
-        g_index.erase(g_plans.back().first);
+        Plan& old = g_plans.back();
+        destroy_plan(old);
+        const auto range = g_index.equal_range(old.hash);
+        for (auto it = range.first; it != range.second; ++it)
+            if (&*it->second == &old) { g_index.erase(it); break; }
         g_plans.pop_back();
     }
-    *out = &g_plans.front().second;
+    *out = &g_plans.front();
     return FLASHOPTIM_OK;
 }
 
-void append(std::string& k, const void* p, size_t n) { k.append(static_cast<const char*>(p), n); }
+// Brings a step's table up to date in stream order if any descriptor has changed since its last upload.
+int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, hipStream_t stream) {
+    const size_t bytes = tensors.size() * sizeof(TensorDev);
+    if (std::memcmp(p.tensors.data(), tensors.data(), bytes) == 0) return FLASHOPTIM_OK;
+    void* slot = nullptr;
+    uint32_t *flag = nullptr, seq = 0;
+    const int rc = stage(p, tensors.data(), bytes, &slot, &flag, &seq);
+    if (rc != FLASHOPTIM_OK) return rc;
+    FO_HIP(fo::launch_upload(slot, p.d_table, bytes, flag, seq, stream));
+    mark_in_flight(p);
+    p.tensors = tensors;
+    return FLASHOPTIM_OK;
+}
 
 // ------------------------------------------------------------------- steps --
 
@@ -262,6 +307,7 @@ int to_dev_ex(const flashoptim_tensor_ex* t, int64_t n, bool has_v, bool split, 
 // What a multi-tensor launch runs: an optimizer step (kOpStepExact: with the exactly rounded division of
 // the AdamW update), a layout conversion, or the stream probe.
 enum LiveOp { kOpStep = 0, kOpCompress = 1, kOpDecompress = 2, kOpProbe = 3, kOpStepExact = 4 };
+constexpr int32_t kOpPack = 5, kOpUnpack = 6;
 
 hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool quant, const StepArgs& a, int64_t blocks,
                           hipStream_t stream) {
@@ -295,63 +341,48 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     a.sqrt_min_word = sqrt_min_word;
     const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems : fo::chunk_elems(kind, split, quant);
     // one workgroup per chunk: the launch grid is a 31-bit count
+    uint32_t log2_ce = 0;
+    while (((int64_t)1 << log2_ce) < ce) ++log2_ce;        // every tile size is a power of two
     int64_t total_chunks = 0;
-    for (const TensorDev& d : live) total_chunks += (d.numel + ce - 1) / ce;
+    for (TensorDev& d : live) {
+        const int64_t tiles = (d.numel + ce - 1) >> log2_ce;
+        d.first_tile = (uint32_t)total_chunks;             // (in range once the total has been checked)
+        d.n_tiles = (uint32_t)tiles;
+        total_chunks += tiles;
+    }
     if (total_chunks > (int64_t)0x7fffffff) return FLASHOPTIM_ERR_NUMEL_RANGE;
 
     if (live.size() == 1) {
         // gradient-release call: no table, no allocation, no lock
         a.single = live[0];
-        const int64_t blocks = (live[0].numel + ce - 1) / ce;
-        FO_HIP(launch_op(op, kind, true, split, quant, a, blocks, ce, stream));
+        FO_HIP(launch_op(op, kind, true, split, quant, a, total_chunks, ce, stream));
         return FLASHOPTIM_OK;
     }
 
-    int device = 0;
-    FO_HIP(hipGetDevice(&device));
-    std::string key;
-    key.reserve(16 + live.size() * 80);
-    const int32_t tag[5] = {kind, device, (int32_t)split, (int32_t)quant, (int32_t)op};
-    append(key, tag, sizeof(tag));
-    for (const TensorDev& d : live) {
-        const void* ids[9] = {d.param, d.rho, d.m_q, d.m_scale, d.v_q, d.v_scale, d.theta32, d.m32, d.v32};
-        append(key, ids, sizeof(ids));
-        append(key, &d.numel, sizeof(d.numel));
-    }
-
-    // tile ranges of the tensors (part of the device table) and the coarse workgroup -> tensor table
+    PlanTag tag = {0, (int32_t)op, kind, (int32_t)(split ? 1 : 0) | (int32_t)(quant ? 2 : 0), nullptr};
+    FO_HIP(hipGetDevice(&tag.device));
+    const uint64_t hash = identity_hash(tag, live);
     uint32_t shift = 0;
     while ((total_chunks >> shift) > (int64_t)fo::kCoarseMaxEntries) ++shift;
-    {
-        int64_t first = 0;
-        for (TensorDev& d : live) {
-            d.first_tile = (uint32_t)first;
-            d.n_tiles = (uint32_t)((d.numel + ce - 1) / ce);
-            first += d.n_tiles;
-        }
-    }
     std::lock_guard<std::mutex> lock(g_mu);
-    Plan* plan = nullptr;
-    std::vector<uint32_t> coarse;
-    if (g_index.find(key) == g_index.end()) {
-        const int64_t n_coarse = ((total_chunks - 1) >> shift) + 1;
-        coarse.resize((size_t)n_coarse);
+    Plan* plan = find_plan(tag, hash, live);
+    int rc;
+    if (plan) {
+        rc = refresh_table(*plan, live, stream);
+    } else {
+        // the coarse workgroup -> tensor table
+        std::vector<uint32_t> coarse((size_t)(((total_chunks - 1) >> shift) + 1));
         size_t ti = 0;
-        for (int64_t j = 0; j < n_coarse; ++j) {
-            const int64_t b = j << shift;
+        for (size_t j = 0; j < coarse.size(); ++j) {
+            const int64_t b = (int64_t)j << shift;
             while ((int64_t)live[ti].first_tile + live[ti].n_tiles <= b) ++ti;
-            coarse[(size_t)j] = (uint32_t)ti;
+            coarse[j] = (uint32_t)ti;
         }
+        const size_t bytes = live.size() * sizeof(TensorDev);
+        rc = make_plan(tag, hash, live, live.data(), bytes, coarse.data(), coarse.size() * sizeof(uint32_t), bytes,
+                       total_chunks, stream, &plan);
     }
-    int rc = get_plan(key, live.size() * sizeof(TensorDev), coarse.data(), coarse.size() * sizeof(uint32_t),
-                      live.size() * sizeof(TensorDev), total_chunks, stream, &plan);
     if (rc != FLASHOPTIM_OK) return rc;
-
-    const size_t bytes = live.size() * sizeof(TensorDev);
-    if (plan->uploaded.size() != bytes || std::memcmp(plan->uploaded.data(), live.data(), bytes) != 0) {
-        rc = upload_table(*plan, live.data(), bytes, stream);
-        if (rc != FLASHOPTIM_OK) return rc;
-    }
     a.tensors = static_cast<const TensorDev*>(plan->d_table);
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = shift;
@@ -571,46 +602,49 @@ void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* bl
     }
 }
 
-// header (pack only): `header_bytes` of host memory that go to `header_dst` in stream order, with the copy.
-int run_copy(const std::vector<CopySegment>& segs, hipStream_t stream, const void* header = nullptr,
-             size_t header_bytes = 0, void* header_dst = nullptr) {
-    if (segs.empty() && !header) return FLASHOPTIM_OK;
-    int64_t total = 0;
-    for (const CopySegment& s : segs) total += s.pad_bytes;
-    const int piece = total < fo::kCopySmallBytes ? fo::kCopyPieceSmall : fo::kCopyPieceLarge;
-    std::vector<uint2> pieces;
-    for (size_t si = 0; si < segs.size(); ++si) {
-        const int64_t nc = (segs[si].pad_bytes + piece - 1) / piece;
-        for (int64_t ci = 0; ci < nc; ++ci) pieces.push_back(make_uint2((unsigned)si, (unsigned)ci));
+// Copies between the list's buffers and the blob.  header (pack only): `header_bytes` of host memory that go to the
+// blob's start in stream order, with the copy.
+int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, const void* header,
+             size_t header_bytes, hipStream_t stream) {
+    // the identity: every tensor, those without elements included (they lengthen the header and move the sections)
+    std::vector<TensorDev> list;
+    list.reserve((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+        TensorDev d = to_dev(t[i], kind == FLASHOPTIM_ADAMW);
+        d.grad = nullptr;
+        d.lr = d.wd = 0.0f;
+        list.push_back(d);
     }
-    int device = 0;
-    FO_HIP(hipGetDevice(&device));
-    std::string key;
-    // (the header's length is part of the identity: it sizes the plan's slots, and tensors without elements lengthen it)
-    const int32_t tag[3] = {-1, device, (int32_t)(header_bytes / 16)};
-    append(key, tag, sizeof(tag));
-    append(key, segs.data(), segs.size() * sizeof(CopySegment));
+    PlanTag tag = {0, pack ? kOpPack : kOpUnpack, kind, 0, blob};
+    FO_HIP(hipGetDevice(&tag.device));
+    const uint64_t hash = identity_hash(tag, list);
+    int64_t total = 0;
+    for (const TensorDev& d : list) total += tensor_payload(d.numel, kind);
+    if (total == 0 && !pack) return FLASHOPTIM_OK;
+    const int piece = total < fo::kCopySmallBytes ? fo::kCopyPieceSmall : fo::kCopyPieceLarge;
     std::lock_guard<std::mutex> lock(g_mu);
-    Plan* plan = nullptr;
-    // (a list without any element still has a header: one dummy entry keeps the allocations non-empty)
-    const uint2 none = make_uint2(0u, 0u);
-    const size_t table_bytes = segs.empty() ? sizeof(CopySegment) : segs.size() * sizeof(CopySegment);
-    int rc = get_plan(key, table_bytes, pieces.empty() ? &none : pieces.data(),
-                      (pieces.empty() ? 1 : pieces.size()) * sizeof(uint2),
-                      header_bytes > table_bytes ? header_bytes : table_bytes, (int64_t)pieces.size(), stream, &plan);
-    if (rc != FLASHOPTIM_OK) return rc;
-    if (!segs.empty() && plan->uploaded.empty()) {
-        rc = upload_table(*plan, segs.data(), segs.size() * sizeof(CopySegment), stream);
+    Plan* plan = find_plan(tag, hash, list);
+    if (!plan) {
+        std::vector<CopySegment> segs;
+        build_segments(kind, t, n, blob, pack, segs);
+        std::vector<uint2> pieces;
+        pieces.reserve((size_t)(total / piece) + segs.size());
+        for (size_t si = 0; si < segs.size(); ++si) {
+            const int64_t nc = (segs[si].pad_bytes + piece - 1) / piece;
+            for (int64_t ci = 0; ci < nc; ++ci) pieces.push_back(make_uint2((unsigned)si, (unsigned)ci));
+        }
+        const int rc = make_plan(tag, hash, list, segs.data(), segs.size() * sizeof(CopySegment), pieces.data(),
+                                 pieces.size() * sizeof(uint2), header_bytes, (int64_t)pieces.size(), stream, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
     }
     void* slot = nullptr;
     uint32_t *flag = nullptr, seq = 0;
     if (header) {
-        rc = stage(*plan, header, header_bytes, &slot, &flag, &seq);
+        const int rc = stage(*plan, header, header_bytes, &slot, &flag, &seq);
         if (rc != FLASHOPTIM_OK) return rc;
     }
     FO_HIP(fo::launch_copy(piece, static_cast<const CopySegment*>(plan->d_table), static_cast<const uint2*>(plan->d_index),
-                           plan->n_chunks, slot, header_dst, (int64_t)header_bytes, flag, seq, stream));
+                           plan->n_chunks, slot, blob, (int64_t)header_bytes, flag, seq, stream));
     if (slot) mark_in_flight(*plan);
     return FLASHOPTIM_OK;
 }
@@ -1016,9 +1050,7 @@ int flashoptim_checkpoint_pack(int kind, const flashoptim_tensor* tensors, int64
     // header and table: staged in pinned memory and copied in stream order, like the sections themselves
     // (the blob may still be in use by earlier work on the stream); the call does not wait
     const std::vector<uint8_t> header = build_header(kind, tensors, n_tensors, step, total);
-    std::vector<CopySegment> segs;
-    build_segments(kind, tensors, n_tensors, static_cast<uint8_t*>(blob), true, segs);
-    return run_copy(segs, stream, header.data(), header.size(), blob);
+    return run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(blob), true, header.data(), header.size(), stream);
 }
 
 int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes, const flashoptim_tensor* tensors,
@@ -1035,10 +1067,7 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     CallSpace w;
     rc = take_space(w, want.size());
     if (rc != FLASHOPTIM_OK) return rc;
-    const hipError_t e = fo::launch_move(blob, w.host, want.size(), stream);
-    std::vector<CopySegment> segs;      // built while the header is on its way
-    build_segments(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, segs);
-    rc = wait_space(w, e, stream);
+    rc = wait_space(w, fo::launch_move(blob, w.host, want.size(), stream), stream);
     if (rc != FLASHOPTIM_OK) return rc;
     // everything but the step field must match what this (kind, list) would have written
     const uint8_t* got = static_cast<const uint8_t*>(w.host);
@@ -1047,7 +1076,7 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     const int64_t step = get_i64(got + 16);
     give_space(w);
     if (!match) return FLASHOPTIM_ERR_BAD_BLOB;
-    rc = run_copy(segs, stream);
+    rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, nullptr, 0, stream);
     if (rc != FLASHOPTIM_OK) return rc;
     *step_out = step;
     return FLASHOPTIM_OK;
@@ -1274,7 +1303,7 @@ int64_t flashoptim_step_launch_count(int kind, const int64_t* numels, int64_t n_
 
 int flashoptim_release_cache(void) {
     std::lock_guard<std::mutex> lock(g_mu);
-    for (auto& kv : g_plans) destroy_plan(kv.second);
+    for (Plan& p : g_plans) destroy_plan(p);
     g_plans.clear();
     g_index.clear();
     std::lock_guard<std::mutex> space_lock(g_space_mu);

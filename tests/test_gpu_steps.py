@@ -436,6 +436,48 @@ def test_hyperparameters_and_gradient_buffers_may_change_between_steps():
         assert sum(r[1] for r in rep) == 0
 
 
+def test_lists_of_the_same_buffers_in_other_arrangements_have_their_own_tables():
+    # reversed, shortened, with two tensors' momenta exchanged, and shorter than their buffers: each list is stepped
+    # like its tensors one by one
+    specs = [W.ParamSpec(f"t{n}", (n,), "matrix") for n in (4096, 2048, 4096, 100, 6000)]
+    lists = []
+    for _ in range(2):
+        bufs = []
+        for i, sp in enumerate(specs):
+            rs = W.random_state(sp.numel, i, seed=51, device="cuda", with_variance=False)
+            b = fo.ParamBuffers(sp.numel, "sgd")
+            b.param.copy_(rs["thp"]); b.rho.copy_(rs["rho"]); b.m_q.copy_(rs["mq"]); b.m_scale.copy_(rs["ms"])
+            b.grad.copy_(W.grad_bf16(sp, i, 1, seed=51, device="cuda")); b.lr = 1e-2
+            bufs.append(b)
+        lists.append(bufs)
+
+    def arrangements(b):
+        swapped = [x.shard(0, x.numel) for x in (b[0], b[2])]
+        for k in ("m_q", "m_scale"):
+            x, y = getattr(swapped[0], k), getattr(swapped[1], k)
+            setattr(swapped[0], k, y); setattr(swapped[1], k, x)
+        return [b, b[::-1], b[:-1], swapped, [x.shard(0, x.numel - 1) for x in b], b]
+
+    for listed, single in zip(arrangements(lists[0]), arrangements(lists[1])):
+        fo.sgd_step(listed, 0.9)
+        for x in single:
+            fo.sgd_step([x], 0.9)
+    torch.cuda.synchronize()
+    for a, b in zip(*lists):
+        assert torch.equal(a.rho, b.rho) and torch.equal(a.m_q, b.m_q)
+        assert torch.equal(a.param.view(torch.int16), b.param.view(torch.int16))
+        assert torch.equal(a.m_scale.view(torch.int16), b.m_scale.view(torch.int16))
+
+
+def test_calls_without_a_stream_take_torchs_current_stream():
+    from paper_2602_23349_amd.binding import _stream
+    seen = []
+    with torch.cuda.stream(torch.cuda.Stream()) as _:
+        seen.append((_stream(None).value or 0, torch.cuda.current_stream().cuda_stream))
+    seen.append((_stream(None).value or 0, torch.cuda.current_stream().cuda_stream))
+    assert all(a == b for a, b in seen) and seen[0] != seen[1]
+
+
 def test_non_default_stream_and_two_lists_interleaved():
     specs = W.odd_sizes()[10:16]
     st_a = [oracle.TensorState(W.theta0(sp, i, seed=12).numpy(), "sgd") for i, sp in enumerate(specs)]
