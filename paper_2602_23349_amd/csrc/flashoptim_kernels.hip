@@ -542,47 +542,63 @@ __device__ __forceinline__ void load_full(LaneIO<VEC>& x, const TensorDev& T, in
     }
 }
 
-// Ragged end of a tensor: element-wise loads, missing elements read as zero (a zero
-// element yields zero moments and therefore never raises its group's absmax).
+// Ragged end of a tensor: the cnt < VEC elements that a lane still has, one by one, missing elements as zero (a zero
+// element yields zero moments and therefore never raises its group's absmax).  Every load is issued, those of missing
+// elements from the last existing one, so that all of a lane's loads are in flight together: written as "load it if it
+// exists", each became a branch with a wait behind its load, and the list of 25 small odd sizes spent most of its
+// kernel time in this chain of about 40 loads.  For cnt == 0 nothing is read.
+template <int N, typename T>
+__device__ __forceinline__ void load_elements(T (&e)[N], const T* p, int cnt) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = p[i < cnt ? i : cnt - 1];
+#pragma unroll
+    for (int i = 0; i < N; ++i) if (i >= cnt) e[i] = (T)0;
+}
+template <int N>
+__device__ __forceinline__ void pack_elements(uint32_t (&w)[N / 4], const uint8_t (&e)[N]) {
+#pragma unroll
+    for (int j = 0; j < N / 4; ++j)
+        w[j] = (uint32_t)e[4 * j] | ((uint32_t)e[4 * j + 1] << 8) | ((uint32_t)e[4 * j + 2] << 16) |
+               ((uint32_t)e[4 * j + 3] << 24);
+}
+template <int N>
+__device__ __forceinline__ void pack_elements(uint32_t (&w)[N / 2], const uint16_t (&e)[N]) {
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) w[j] = (uint32_t)e[2 * j] | ((uint32_t)e[2 * j + 1] << 16);
+}
+
 template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, int64_t off, int cnt) {
-    const uint16_t* p = reinterpret_cast<const uint16_t*>(T.param) + off;
-    const uint16_t* g = reinterpret_cast<const uint16_t*>(T.grad) + off;
-    const uint8_t* r = reinterpret_cast<const uint8_t*>(T.rho) + off;
-    const uint8_t* mq = reinterpret_cast<const uint8_t*>(T.m_q) + off;
-    const uint8_t* vq = T.v_q + off;
-#pragma unroll
-    for (int j = 0; j < VEC / 2; ++j) {
-        uint32_t lo = (2 * j < cnt) ? g[2 * j] : 0u, hi = (2 * j + 1 < cnt) ? g[2 * j + 1] : 0u;
-        x.g[j] = lo | (hi << 16);
-        if (SPLIT) {
-            lo = (2 * j < cnt) ? p[2 * j] : 0u; hi = (2 * j + 1 < cnt) ? p[2 * j + 1] : 0u;
-            x.p[j] = lo | (hi << 16);
-        }
+    x = LaneIO<VEC>{};
+    if (cnt == 0) return;
+    uint16_t g[VEC], p[VEC];
+    uint8_t r[VEC], mq[VEC], vq[VEC];
+    load_elements(g, reinterpret_cast<const uint16_t*>(T.grad) + off, cnt);
+    if constexpr (SPLIT) {
+        load_elements(p, reinterpret_cast<const uint16_t*>(T.param) + off, cnt);
+        load_elements(r, reinterpret_cast<const uint8_t*>(T.rho) + off, cnt);
+    } else {
+        load_elements(x.th32, T.theta32 + off, cnt);
     }
-#pragma unroll
-    for (int j = 0; j < VEC / 4; ++j) {
-        uint32_t w = 0, wm = 0, wv = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (4 * j + k < cnt) {
-                if (SPLIT) w |= (uint32_t)r[4 * j + k] << (8 * k);
-                if (QUANT) wm |= (uint32_t)mq[4 * j + k] << (8 * k);
-                if (QUANT && HAS_V) wv |= (uint32_t)vq[4 * j + k] << (8 * k);
-            }
-        }
-        x.r[j] = w; x.mq[j] = wm; x.vq[j] = wv;
-    }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-        if (!SPLIT) x.th32[i] = (i < cnt) ? T.theta32[off + i] : 0.0f;
-        if (!QUANT) x.m32[i] = (i < cnt) ? T.m32[off + i] : 0.0f;
-        if (!QUANT && HAS_V) x.v32[i] = (i < cnt) ? T.v32[off + i] : 0.0f;
-    }
-    x.ms = 0; x.vs = 0;
-    if (QUANT && cnt > 0) {
+    if constexpr (QUANT) {
+        load_elements(mq, reinterpret_cast<const uint8_t*>(T.m_q) + off, cnt);
         x.ms = T.m_scale[off >> 5];
-        if (HAS_V) x.vs = T.v_scale[off >> 5];
+        if constexpr (HAS_V) {
+            load_elements(vq, T.v_q + off, cnt);
+            x.vs = T.v_scale[off >> 5];
+        }
+    } else {
+        load_elements(x.m32, T.m32 + off, cnt);
+        if constexpr (HAS_V) load_elements(x.v32, T.v32 + off, cnt);
+    }
+    pack_elements(x.g, g);
+    if constexpr (SPLIT) {
+        pack_elements(x.p, p);
+        pack_elements(x.r, r);
+    }
+    if constexpr (QUANT) {
+        pack_elements(x.mq, mq);
+        if constexpr (HAS_V) pack_elements(x.vq, vq);
     }
 }
 
@@ -1069,10 +1085,11 @@ __device__ __forceinline__ LanePos lane_pos_at(int64_t tile0, int64_t n) {
 __device__ __forceinline__ void load_f32(float (&f)[kCodecVec], const float* p, const LanePos& L) {
     if (L.cnt == kCodecVec) {
         gld_floats(f, gbase(p, 4 * L.tile0), 4u * block_local(L.lane_el));
+    } else if (L.cnt > 0) {
+        load_elements(f, p + L.tile0 + L.lane_el, L.cnt);
     } else {
-        const float* q = p + L.tile0 + L.lane_el;
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = (i < L.cnt) ? q[i] : 0.0f;
+        for (int i = 0; i < kCodecVec; ++i) f[i] = 0.0f;
     }
 }
 __device__ __forceinline__ void store_f32(float* p, const LanePos& L, const float (&f)[kCodecVec]) {
@@ -1087,13 +1104,13 @@ __device__ __forceinline__ void store_f32(float* p, const LanePos& L, const floa
 __device__ __forceinline__ void load_u16(uint32_t (&w)[kCodecVec / 2], const void* p, const LanePos& L) {
     if (L.cnt == kCodecVec) {
         gld_words(w, gbase(p, 2 * L.tile0), 2u * block_local(L.lane_el));
+    } else if (L.cnt > 0) {
+        uint16_t e[kCodecVec];
+        load_elements(e, reinterpret_cast<const uint16_t*>(p) + L.tile0 + L.lane_el, L.cnt);
+        pack_elements(w, e);
     } else {
-        const uint16_t* q = reinterpret_cast<const uint16_t*>(p) + L.tile0 + L.lane_el;
 #pragma unroll
-        for (int j = 0; j < kCodecVec / 2; ++j) {
-            const uint32_t lo = (2 * j < L.cnt) ? q[2 * j] : 0u, hi = (2 * j + 1 < L.cnt) ? q[2 * j + 1] : 0u;
-            w[j] = lo | (hi << 16);
-        }
+        for (int j = 0; j < kCodecVec / 2; ++j) w[j] = 0;
     }
 }
 __device__ __forceinline__ void store_u16(void* p, const LanePos& L, const uint32_t (&w)[kCodecVec / 2]) {
@@ -1108,15 +1125,13 @@ __device__ __forceinline__ void store_u16(void* p, const LanePos& L, const uint3
 __device__ __forceinline__ void load_u8(uint32_t (&w)[kCodecVec / 4], const void* p, const LanePos& L) {
     if (L.cnt == kCodecVec) {
         gld_words(w, gbase(p, L.tile0), block_local(L.lane_el));
+    } else if (L.cnt > 0) {
+        uint8_t e[kCodecVec];
+        load_elements(e, reinterpret_cast<const uint8_t*>(p) + L.tile0 + L.lane_el, L.cnt);
+        pack_elements(w, e);
     } else {
-        const uint8_t* q = reinterpret_cast<const uint8_t*>(p) + L.tile0 + L.lane_el;
 #pragma unroll
-        for (int j = 0; j < kCodecVec / 4; ++j) {
-            uint32_t t = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) if (4 * j + k < L.cnt) t |= (uint32_t)q[4 * j + k] << (8 * k);
-            w[j] = t;
-        }
+        for (int j = 0; j < kCodecVec / 4; ++j) w[j] = 0;
     }
 }
 __device__ __forceinline__ void store_u8(void* p, const LanePos& L, const uint32_t (&w)[kCodecVec / 4]) {
@@ -1907,7 +1922,8 @@ __device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
 // GPT-2's 638 MB blob 228 us, 5.6 TB/s, against 233 with 32 KB; two Llama layers with embedding and head 2.75 ms
 // against 2.97).  Below kCopySmallBytes there are fewer than two generations of such pieces - 1024 workgroups are
 // resident at a time - and the last one is mostly empty; four loads per lane then do better (ResNet-50, 131 MB:
-// 59.6 -> 51.8 us; a tensor of 3 M elements: 19.2 -> 15.1 us).
+// 59.6 -> 51.8 us; a tensor of 3 M elements: 19.2 -> 15.1 us).  The last piece of every segment was a serial chain of
+// up to 16 load-store pairs; with its loads together as well the two take 46.7 and 7 us.
 //
 // header: the blob's header and table when packing, in a pinned slot; the workgroup behind the last piece writes it to
 // header_dst.
