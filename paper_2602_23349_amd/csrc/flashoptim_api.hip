@@ -309,23 +309,23 @@ int to_dev_ex(const flashoptim_tensor_ex* t, int64_t n, bool has_v, bool split, 
 enum LiveOp { kOpStep = 0, kOpCompress = 1, kOpDecompress = 2, kOpProbe = 3, kOpStepExact = 4 };
 constexpr int32_t kOpPack = 5, kOpUnpack = 6;
 
-hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool quant, const StepArgs& a, int64_t blocks,
+hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool quant, bool small, const StepArgs& a, int64_t blocks,
                           hipStream_t stream) {
     if (op == kOpStep || op == kOpStepExact)
-        return fo::launch_step(kind, direct, split, quant, op == kOpStepExact, a, blocks, stream);
-    if (op == kOpProbe) return fo::launch_probe(kind, direct, a, blocks, stream);
+        return fo::launch_step(kind, direct, split, quant, small, op == kOpStepExact, a, blocks, stream);
+    if (op == kOpProbe) return fo::launch_probe(kind, direct, small, a, blocks, stream);
     return fo::launch_convert(kind == FLASHOPTIM_ADAMW, op == kOpCompress, direct, a, blocks, stream);
 }
 
 // The workgroups 0 .. blocks-1 of one logical launch (each handles `tile_elems` elements), issued as
 // back-to-back launches on the same stream, each covering at most kSegmentElems elements.
-hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, StepArgs a, int64_t blocks,
+hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, bool small, StepArgs a, int64_t blocks,
                      int64_t tile_elems, hipStream_t stream) {
     const int64_t seg = fo::kSegmentElems / tile_elems > 0 ? fo::kSegmentElems / tile_elems : 1;
     for (int64_t first = 0; first < blocks; first += seg) {
         a.block_offset = (uint32_t)first;
         const int64_t n = blocks - first < seg ? blocks - first : seg;
-        const hipError_t e = launch_segment(op, kind, direct, split, quant, a, n, stream);
+        const hipError_t e = launch_segment(op, kind, direct, split, quant, small, a, n, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -339,7 +339,11 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     std::memset(&a, 0, sizeof(a));
     a.c = c;
     a.sqrt_min_word = sqrt_min_word;
-    const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems : fo::chunk_elems(kind, split, quant);
+    int64_t elems = 0;
+    for (const TensorDev& d : live) elems += d.numel;
+    const bool small = fo::step_small(split, quant, elems);
+    const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems
+                                                                  : fo::chunk_elems(kind, split, quant, small);
     // one workgroup per chunk: the launch grid is a 31-bit count
     uint32_t log2_ce = 0;
     while (((int64_t)1 << log2_ce) < ce) ++log2_ce;        // every tile size is a power of two
@@ -355,7 +359,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     if (live.size() == 1) {
         // gradient-release call: no table, no allocation, no lock
         a.single = live[0];
-        FO_HIP(launch_op(op, kind, true, split, quant, a, total_chunks, ce, stream));
+        FO_HIP(launch_op(op, kind, true, split, quant, small, a, total_chunks, ce, stream));
         return FLASHOPTIM_OK;
     }
 
@@ -387,7 +391,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)live.size();
-    FO_HIP(launch_op(op, kind, false, split, quant, a, plan->n_chunks, ce, stream));
+    FO_HIP(launch_op(op, kind, false, split, quant, small, a, plan->n_chunks, ce, stream));
     return FLASHOPTIM_OK;
 }
 
@@ -1202,7 +1206,10 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     if (!adamw_consts(hp, c)) return FLASHOPTIM_ERR_INVALID_ARG;
     int rc = validate_tensors(tensors, n_tensors, true);
     if (rc != FLASHOPTIM_OK) return rc;
-    const int64_t ce = fo::chunk_elems(FLASHOPTIM_ADAMW, true, true);
+    int64_t elems = 0;
+    for (int64_t i = 0; i < n_tensors; ++i) elems += tensors[i].numel;
+    const bool small = fo::step_small(true, true, elems);
+    const int64_t ce = fo::chunk_elems(FLASHOPTIM_ADAMW, true, true, small);
     int64_t n_live = 0, total_tiles = 0, only = -1;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (tensors[i].numel == 0) continue;
@@ -1230,7 +1237,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     a.sqrt_min_word = word;
     if (n_live == 1) {          // one tensor: no table at all
         a.single = to_dev(tensors[only], true);
-        FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, true, true, true, a, total_tiles, ce, stream));
+        FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, true, true, true, small, a, total_tiles, ce, stream));
         return FLASHOPTIM_OK;
     }
     unsigned char* base = nullptr;
@@ -1269,7 +1276,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     a.coarse = coarse;
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)n_live;
-    FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, a, total_tiles, ce, stream));
+    FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, small, a, total_tiles, ce, stream));
     return FLASHOPTIM_OK;
 }
 
@@ -1291,10 +1298,13 @@ int flashoptim_last_hip_error(void) { return g_last_hip_error; }
 
 int64_t flashoptim_step_launch_count(int kind, const int64_t* numels, int64_t n_tensors) {
     if (kind < 0 || kind > 2 || n_tensors < 0 || (n_tensors > 0 && !numels)) return FLASHOPTIM_ERR_INVALID_ARG;
-    const int64_t ce = fo::chunk_elems(kind, true, true);
-    int64_t tiles = 0;
+    int64_t tiles = 0, elems = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (numels[i] < 0 || numels[i] >= kMaxNumel) return FLASHOPTIM_ERR_NUMEL_RANGE;
+        elems += numels[i];
+    }
+    const int64_t ce = fo::chunk_elems(kind, true, true, fo::step_small(true, true, elems));
+    for (int64_t i = 0; i < n_tensors; ++i) {
         tiles += (numels[i] + ce - 1) / ce;
     }
     const int64_t seg = fo::kSegmentElems / ce > 0 ? fo::kSegmentElems / ce : 1;

@@ -30,14 +30,20 @@ constexpr int kThreads = 256;                      // lanes per workgroup (codec
 // of every line: the plain FP32 AdamW step over a decoder layer of Llama-3.1-8B, 218 M parameters, took 1034 us
 // against 963 now).  256 lanes where the states are FP32 (512: 1004 us), 512 where they are quantized and the decode
 // tables have to be staged (AdamW, same layer: 509 us against 519 with 256).
-constexpr int step_vec(int kind, bool split, bool quant) {
-    return !(split && quant) ? 4 : kind == 0 ? FO_VEC_ADAMW : FO_VEC_SGD_LION;
+// Launches over fewer than kSmallElems elements fill less than half the chip with tiles of 2048: they take four elements
+// per lane and 256 lanes as well, twice to four times the workgroups with half the work per lane (kernel time, eight
+// -> four elements per lane: a flat tensor of 2^18 elements AdamW 3.9 -> 3.5 us, SGD 3.5 -> 2.8; 25 tensors of odd sizes
+// below 2^16, SGD 4.9 -> 3.8; at 2^20 elements the two are equal, from 2^22 on the larger tile wins by 2-8 %).
+constexpr int64_t kSmallElems = (int64_t)1 << 20;
+constexpr bool step_small(bool split, bool quant, int64_t elems) { return split && quant && elems < kSmallElems; }
+constexpr int step_vec(int kind, bool split, bool quant, bool small) {
+    return !(split && quant) || small ? 4 : kind == 0 ? FO_VEC_ADAMW : FO_VEC_SGD_LION;
 }
-constexpr int step_threads(int kind, bool split, bool quant) {
-    return !(split && quant) ? (quant ? 512 : 256) : kind == 0 ? FO_THREADS_ADAMW : FO_THREADS_SGD_LION;
+constexpr int step_threads(int kind, bool split, bool quant, bool small) {
+    return small ? 256 : !(split && quant) ? (quant ? 512 : 256) : kind == 0 ? FO_THREADS_ADAMW : FO_THREADS_SGD_LION;
 }
-constexpr int chunk_elems(int kind, bool split, bool quant) {
-    return step_threads(kind, split, quant) * step_vec(kind, split, quant);
+constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
+    return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);
 }
 constexpr int kCopyPieceLarge = 128 * 1024;        // checkpoint copy: bytes per workgroup ...
 constexpr int kCopyPieceSmall = 32 * 1024;         // ... when fewer than kCopySmallBytes are copied in all
@@ -112,11 +118,11 @@ struct CopySegment {
     int64_t pad_bytes;   // >= bytes; [bytes, pad_bytes) of dst is zero-filled
 };
 
-hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool exact, const StepArgs& a, int64_t n_blocks,
-                       hipStream_t s);
+hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,
+                       int64_t n_blocks, hipStream_t s);
 constexpr int kConvChunkElems = 1024;   // elements per workgroup of the layout-conversion kernel: one pass of its lanes
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);
-hipError_t launch_probe(int kind, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);
+hipError_t launch_probe(int kind, bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s);
 void launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s);
 void launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s);
 constexpr int kSweepStats = 8 + 3 * 256;

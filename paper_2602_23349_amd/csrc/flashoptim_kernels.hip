@@ -951,33 +951,39 @@ __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
     }
 }
 
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT>
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL>
 static hipError_t launch_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    constexpr int VEC = step_vec(KIND, SPLIT, QUANT), THREADS = step_threads(KIND, SPLIT, QUANT);
+    constexpr int VEC = step_vec(KIND, SPLIT, QUANT, SMALL), THREADS = step_threads(KIND, SPLIT, QUANT, SMALL);
     const dim3 grid((unsigned)n_blocks), block(THREADS);
     if (direct) hipLaunchKernelGGL((step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
+template <int KIND, bool EXACT>
+static hipError_t launch_packed(bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    return small ? launch_variant<KIND, true, true, EXACT, true>(direct, a, n_blocks, s)
+                 : launch_variant<KIND, true, true, EXACT, false>(direct, a, n_blocks, s);
+}
+
 template <int KIND>
-static hipError_t launch_kind(bool direct, bool split, bool quant, const StepArgs& a, int64_t n_blocks,
+static hipError_t launch_kind(bool direct, bool split, bool quant, bool small, const StepArgs& a, int64_t n_blocks,
                               hipStream_t s) {
-    if (split && quant) return launch_variant<KIND, true, true, true>(direct, a, n_blocks, s);
-    if (split) return launch_variant<KIND, true, false, true>(direct, a, n_blocks, s);
-    if (quant) return launch_variant<KIND, false, true, true>(direct, a, n_blocks, s);
-    return launch_variant<KIND, false, false, true>(direct, a, n_blocks, s);
+    if (split && quant) return launch_packed<KIND, true>(direct, small, a, n_blocks, s);
+    if (split) return launch_variant<KIND, true, false, true, false>(direct, a, n_blocks, s);
+    if (quant) return launch_variant<KIND, false, true, true, false>(direct, a, n_blocks, s);
+    return launch_variant<KIND, false, false, true, false>(direct, a, n_blocks, s);
 }
 
 // exact = false selects the faithful division; it exists for AdamW in the compressed
 // layout only (SGD and Lion have neither operation; the ablation variants are always exact).
-hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool exact, const StepArgs& a, int64_t n_blocks,
-                       hipStream_t s) {
+hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,
+                       int64_t n_blocks, hipStream_t s) {
     if (kind == 0 && !a.sqrt_min_word) return hipErrorInvalidValue;     // the AdamW kernels dereference it
-    if (kind == 0 && split && quant && !exact) return launch_variant<0, true, true, false>(direct, a, n_blocks, s);
-    if (kind == 0) return launch_kind<0>(direct, split, quant, a, n_blocks, s);
-    if (kind == 1) return launch_kind<1>(direct, split, quant, a, n_blocks, s);
-    return launch_kind<2>(direct, split, quant, a, n_blocks, s);
+    if (kind == 0 && split && quant && !exact) return launch_packed<0, false>(direct, small, a, n_blocks, s);
+    if (kind == 0) return launch_kind<0>(direct, split, quant, small, a, n_blocks, s);
+    if (kind == 1) return launch_kind<1>(direct, split, quant, small, a, n_blocks, s);
+    return launch_kind<2>(direct, split, quant, small, a, n_blocks, s);
 }
 
 // ------------------------------------------------------------- stream probe --
@@ -1011,14 +1017,17 @@ __global__ __launch_bounds__(THREADS) void probe_kernel(StepArgs a) {
     else store_tail<VEC, HAS_V, true, true>(x, T, tile0 + lane_el, cnt, leader);
 }
 
-hipError_t launch_probe(int kind, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    const dim3 grid((unsigned)n_blocks);
-#define FO_PROBE(K, DR) hipLaunchKernelGGL((probe_kernel<K, step_vec(K, true, true), step_threads(K, true, true), DR>), grid, \
-                                           dim3(step_threads(K, true, true)), 0, s, a)
-    if (kind == 0) { if (direct) FO_PROBE(0, true); else FO_PROBE(0, false); }
-    else if (kind == 1) { if (direct) FO_PROBE(1, true); else FO_PROBE(1, false); }
-    else { if (direct) FO_PROBE(2, true); else FO_PROBE(2, false); }
-#undef FO_PROBE
+template <int KIND, bool SMALL>
+static void launch_probe_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    constexpr int VEC = step_vec(KIND, true, true, SMALL), THREADS = step_threads(KIND, true, true, SMALL);
+    const dim3 grid((unsigned)n_blocks), block(THREADS);
+    if (direct) hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, false>), grid, block, 0, s, a);
+}
+hipError_t launch_probe(int kind, bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    if (kind == 0) { if (small) launch_probe_variant<0, true>(direct, a, n_blocks, s); else launch_probe_variant<0, false>(direct, a, n_blocks, s); }
+    else if (kind == 1) { if (small) launch_probe_variant<1, true>(direct, a, n_blocks, s); else launch_probe_variant<1, false>(direct, a, n_blocks, s); }
+    else { if (small) launch_probe_variant<2, true>(direct, a, n_blocks, s); else launch_probe_variant<2, false>(direct, a, n_blocks, s); }
     return hipGetLastError();
 }
 

@@ -90,6 +90,26 @@ def test_ragged_sizes_multi_tensor(kind, hp, mode):
     assert_parity(report, mode, f"ragged {kind}")
 
 
+@pytest.mark.parametrize("kind,hp,mode", [("adamw", ADAMW, "exact"), ("adamw", ADAMW, "default"), ("sgd", SGD, "exact"),
+                                          ("lion", LION, "exact")])
+@pytest.mark.parametrize("extra", ["above", "last_small", "first_large"])
+def test_launch_shapes_on_both_sides_of_their_limit(kind, hp, mode, extra, monkeypatch):
+    # fewer than 2^20 elements: four per lane, tiles of 1024; from there on eight, tiles of 2048 / 4096.  The odd sizes
+    # as they stand run in the small shape; here with a tensor that takes them past the limit, and single tensors
+    specs = {"above": W.odd_sizes() + [W.ParamSpec("big", (1 << 20,), "matrix")],
+             "last_small": [W.ParamSpec("s", ((1 << 20) - 1,), "matrix")],
+             "first_large": [W.ParamSpec("l", (1 << 20,), "matrix")]}[extra]
+    monkeypatch.setattr(W, "odd_sizes", lambda: specs)
+    test_ragged_sizes_multi_tensor(kind, hp, mode)
+
+
+@pytest.mark.parametrize("kind", ["adamw", "sgd", "lion"])
+def test_stream_probe_changes_nothing_in_the_large_shape(kind, monkeypatch):
+    specs = W.odd_sizes()[:4] + [W.ParamSpec("big", ((1 << 20) + 77,), "matrix")] + W.odd_sizes()[4:]
+    monkeypatch.setattr(W, "odd_sizes", lambda: specs)
+    test_stream_probe_changes_nothing(kind)
+
+
 @pytest.mark.parametrize("kind", ["adamw", "sgd", "lion"])
 def test_stream_probe_changes_nothing(kind):
     # the measurement aid moves a step's bytes and must leave every array as it was, ragged ends
