@@ -184,19 +184,25 @@ __device__ __forceinline__ float sqrt_rn_midrange(float x) {
     const float s = x * y, h = 0.5f * y;
     return fmaf(fmaf(-s, s, x), h, s);
 }
-// Correctly rounded n / d for operands well inside the normal range: 2^-60 <= |n|, d <= 2^60.
-// This is the usual refinement of the 1-ulp hardware reciprocal (one Newton step on the
-// reciprocal, two residual corrections of the quotient, every step one FMA); with the operands
-// in that range no intermediate result leaves the normal range, so the range scaling and the
-// special-case fix-up of the general division are not needed.  Callers check the range.
+// Correctly rounded n / d for operands well inside the normal range: 2^-60 <= |n|, d <= 2^60 (no intermediate result
+// leaves the normal range, so the range scaling and the special-case fix-up of the general division are not needed;
+// callers check the range).  Every step after the hardware reciprocal r0 (1 ulp) is one FMA or one product:
+//   e = 1 - d r0;  q1 = q0 + q0 e with q0 = n r0;  r1 = r0 + r0 e;  result q1 + (n - d q1) r1.
+// Why that is RN(n / d).  (1) r1 is the correctly rounded reciprocal: a property of the hardware estimate, which
+// scales with the exponent and holds for every mantissa (flashoptim_selftest, section 1).  (2) q0 e removes the error of
+// r0 down to its square (2^-46), so what separates q1 from n / d is the rounding of q0 and its own: at most one ulp
+// (plus 2^-22).  Hence n - d q1 is exact, and before the last rounding the result is off by |n / d - q1| |d r1 - 1|.
+// (3) With the mantissas of n and d as integers of 24 bits, n / d is never the middle of two FP32 numbers, and is at
+// least 2^-24 / b ulp away from one, b in [1, 2) being the mantissa of d.  Near a middle |n / d - q1| is half an
+// ulp, so by (1) the error is below 0.5 b 2^-25 < 2^-24 / b ulp, as b < 2: it cannot change the rounding.
+// (The classical form refines r first and corrects the quotient twice: one instruction more per element.)
 __device__ __forceinline__ float div_rn_midrange(float n, float d) {
-    float r = __builtin_amdgcn_rcpf(d);
-    const float e = fmaf(-d, r, 1.0f);
-    r = fmaf(e, r, r);
-    float q = n * r;
-    q = fmaf(fmaf(-d, q, n), r, q);
-    q = fmaf(fmaf(-d, q, n), r, q);
-    return q;
+    const float r0 = __builtin_amdgcn_rcpf(d);
+    const float e = fmaf(-d, r0, 1.0f);
+    const float q0 = n * r0;
+    const float q1 = fmaf(q0, e, q0);
+    const float r1 = fmaf(e, r0, r0);
+    return fmaf(fmaf(-d, q1, n), r1, q1);
 }
 
 // Faithful division: one residual correction of the quotient formed with the 1-ulp hardware reciprocal,
@@ -1769,7 +1775,7 @@ hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs
 // for the square root built on v_rsq_f32, as verified here value by value.  This kernel checks
 // those provisions on the device it runs on, against the plain IEEE operations:
 //   section 0: recip_of_fp16(s) == 1.0f / s for every positive finite FP16 value s;
-//   section 1: v_rcp_f32(d) within 1 ulp of 1.0f / d for every d in [1, 4);
+//   section 1: v_rcp_f32(d) within 1 ulp of 1.0f / d, and its Newton refinement equal to 1.0f / d, for every d in [1, 4);
 //   section 2: sqrt_rn_midrange(x) == sqrtf(x) for EVERY FP32 value x of its range [2^-96, FLT_MAX];
 //   section 3: momentum codes: wherever the two conversions of m_code_bracket agree, they agree with
 //              m_code_exact, for every m' in [2^-13, 2) of either sign;
@@ -1805,9 +1811,10 @@ __device__ __forceinline__ void selftest_one(int section, uint64_t gid, const St
     } else if (section == 1) {
         if (gid < (1ull << 24)) {
             const float d = u2f(0x3f800000u + (uint32_t)gid);            // [1, 4)
-            const int32_t diff = (int32_t)f2u(__builtin_amdgcn_rcpf(d)) - (int32_t)f2u(1.0f / d);
+            const float r0 = __builtin_amdgcn_rcpf(d);
+            const int32_t diff = (int32_t)f2u(r0) - (int32_t)f2u(1.0f / d);
             checked = true;
-            failed = diff > 1 || diff < -1;
+            failed = diff > 1 || diff < -1 || f2u(fmaf(fmaf(-d, r0, 1.0f), r0, r0)) != f2u(1.0f / d);
         }
     } else if (section == 2) {
         if (gid < kSelftestSqrtCount) {
