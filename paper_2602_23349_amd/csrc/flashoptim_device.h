@@ -28,8 +28,10 @@ constexpr int kThreads = 256;                      // lanes per workgroup (codec
 // The ablation variants (weights not split, states not quantized, or both) move FP32 arrays: four elements per lane,
 // so that a wavefront's 128-bit FP32 access covers whole cache lines (with eight, each of two accesses covered half
 // of every line: the plain FP32 AdamW step over a decoder layer of Llama-3.1-8B, 218 M parameters, took 1034 us
-// against 963 now).  256 lanes where the states are FP32 (512: 1004 us), 512 where they are quantized and the decode
-// tables have to be staged (AdamW, same layer: 509 us against 519 with 256).
+// against 963 with four).  The lanes per workgroup follow from the decode tables that it has to stage: none in the plain
+// FP32 step, whose workgroups are single wavefronts that start and retire on their own (same layer, with 256 / 128 /
+// 64 lanes: AdamW 974 / 955 / 928 us, SGD 639 / 629 / 599); 256 lanes where the weights are split (512: +3 %,
+// 128: +2 % on the GPT-2 list); 512 where the states are quantized (AdamW, same layer: 509 us against 519 with 256).
 // Launches over fewer than kSmallElems elements fill less than half the chip with tiles of 2048: they take four elements
 // per lane and 256 lanes as well, twice to four times the workgroups with half the work per lane (kernel time, eight
 // -> four elements per lane: a flat tensor of 2^18 elements AdamW 3.9 -> 3.5 us, SGD 3.5 -> 2.8; 25 tensors of odd sizes
@@ -40,7 +42,7 @@ constexpr int step_vec(int kind, bool split, bool quant, bool small) {
     return !(split && quant) || small ? 4 : kind == 0 ? FO_VEC_ADAMW : FO_VEC_SGD_LION;
 }
 constexpr int step_threads(int kind, bool split, bool quant, bool small) {
-    return small ? 256 : !(split && quant) ? (quant ? 512 : 256) : kind == 0 ? FO_THREADS_ADAMW : FO_THREADS_SGD_LION;
+    return small ? 256 : !(split && quant) ? (quant ? 512 : split ? 256 : 64) : kind == 0 ? FO_THREADS_ADAMW : FO_THREADS_SGD_LION;
 }
 constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
     return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);

@@ -81,8 +81,8 @@ def test_ablation_variants_match_oracle(kind, split, quant):
 @pytest.mark.parametrize("kind", ["adamw", "sgd", "lion"])
 @pytest.mark.parametrize("split,quant", [(True, False), (False, True), (False, False)])
 def test_ablation_variants_at_tile_edges(kind, split, quant, monkeypatch):
-    # four elements per lane, tiles of 1024 (FP32 states) and 2048 elements (quantized states)
-    sizes = [1021, 1024, 1027, 2045, 2048, 2051, 3, 4, 5, 4096]
+    # four elements per lane, tiles of 256 (plain FP32), 1024 (FP32 states) and 2048 elements (quantized states)
+    sizes = [253, 256, 259, 1021, 1024, 1027, 2045, 2048, 2051, 3, 4, 5, 4096]
     specs = [W.ParamSpec(f"edge{n}", (n,), "matrix") for n in sizes]
     monkeypatch.setattr(W, "odd_sizes", lambda: specs)
     test_ablation_variants_match_oracle(kind, split, quant)
