@@ -136,16 +136,19 @@ void launch_quantize(bool variance, bool linear, const float* x, void* q, uint16
 void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                        hipStream_t s);
 constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per compute unit
-// partial: device memory for kNmseMaxBlocks pairs; sums: two doubles that the device can write and the host reads
+// partial: device memory for kNmseMaxBlocks pairs; sums: two doubles of pinned memory; *flag (pinned) becomes seq once
+// they are there
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
-                       hipStream_t s);
+                       uint32_t* flag, uint32_t seq, hipStream_t s);
 // header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst, header_bytes a multiple of 16;
 // it sets *flag (pinned) to seq when it has read the slot
 hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pieces, int64_t n_pieces, const void* header,
                        void* header_dst, int64_t header_bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
-// Moves `bytes` (rounded up to 16: both buffers must have room) between pinned host memory and device memory.
+// Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
 // The same from a pinned slot, by one workgroup that sets *flag (pinned) to seq when it has read the slot.
+// Device to pinned memory; *flag (pinned) becomes seq once all of it is there.
+hipError_t launch_fetch(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
 hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
 constexpr int kSelftestSectionCount = 7;
 constexpr unsigned long long kSelftestSqrtValues = 0x7f800000ull - 0x0f800000ull;   // section 2: every FP32 value in [2^-96, FLT_MAX]

@@ -1578,7 +1578,15 @@ __global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t 
     block_sum_pair(err, ref);
     if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(err, ref);
 }
-__global__ __launch_bounds__(kThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums) {
+// Tells a waiting host that everything the workgroup has written to pinned memory is there.  Called by every lane.
+__device__ __forceinline__ void publish(uint32_t* flag, uint32_t seq) {
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(kThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums,
+                                                              uint32_t* flag, uint32_t seq) {
     double err = 0.0, ref = 0.0;
     for (int i = (int)threadIdx.x; i < n_partial; i += kThreads) {
         const double2 p = partial[i];
@@ -1590,6 +1598,7 @@ __global__ __launch_bounds__(kThreads) void nmse_total_kernel(const double2* par
         sums[0] = err;
         sums[1] = ref;
     }
+    publish(flag, seq);
 }
 
 static inline unsigned tiles_for(int64_t n) { return (unsigned)((n + kCodecTile - 1) / kCodecTile); }
@@ -1648,11 +1657,12 @@ void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t
     dispatch_codec(variance, linear, 1, q, scale, x, nullptr, n, nullptr, s);
 }
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
-                       hipStream_t s) {
+                       uint32_t* flag, uint32_t seq, hipStream_t s) {
     dispatch_codec(variance, linear, 2, x, nullptr, nullptr, nullptr, n, partial, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kThreads), 0, s, partial, (int)nmse_blocks(n), sums);
+    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kThreads), 0, s, partial, (int)nmse_blocks(n), sums, flag,
+                       seq);
     return hipGetLastError();
 }
 
@@ -1999,10 +2009,10 @@ hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pi
     return hipGetLastError();
 }
 
-// Small transfers between pinned host memory and device memory, in either direction, by a kernel instead of a copy
-// command (16-byte multiples; bound by the link to the host).  A copy command and the event that marks its end cost
-// the host 17 us and the stream 6 us in front of a step whose descriptors changed; these kernels cost 8 and 3
-// (ResNet-50 list under a learning-rate schedule: 75 us a step -> 60).
+// Small transfers between pinned host memory and device memory by a kernel instead of a copy command (16-byte
+// multiples; bound by the link to the host).  A copy command and the event that marks its end cost the host 17 us and
+// the stream 6 us in front of a step whose descriptors changed; these kernels cost 8 and 3 (ResNet-50 list under a
+// learning-rate schedule: 75 us a step -> 60).
 __global__ __launch_bounds__(256) void move_kernel(const uint4* src, uint4* dst, uint32_t n16) {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n16; i += gridDim.x * 256u) dst[i] = src[i];
 }
@@ -2024,6 +2034,17 @@ __global__ __launch_bounds__(kUploadThreads) void upload_kernel(const uint4* src
         for (int k = 0; k < 4; ++k) if (i + k * kUploadThreads < n16) dst[i + k * kUploadThreads] = v[k];
     }
     release_slot(flag, seq);
+}
+// The other way, for a host that waits for the flag.
+__global__ __launch_bounds__(kUploadThreads) void fetch_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,
+                                                               uint32_t seq) {
+    for (uint32_t i = threadIdx.x; i < n16; i += kUploadThreads) dst[i] = src[i];
+    publish(flag, seq);
+}
+hipError_t launch_fetch(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
+    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kUploadThreads), 0, s, (const uint4*)src, (uint4*)dst,
+                       (uint32_t)((bytes + 15) / 16), flag, seq);
+    return hipGetLastError();
 }
 hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
     hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadThreads), 0, s, (const uint4*)src, (uint4*)dst,

@@ -96,6 +96,24 @@ def test_descriptor_uploads_behind_a_busy_stream_keep_their_order():
         assert torch.equal(a.rho, b.rho) and torch.equal(a.param.view(torch.int16), b.param.view(torch.int16))
 
 
+def test_calls_that_return_values_wait_for_a_stream_that_stays_busy():
+    # behind 50 ms of other work: past the time for which the host watches the kernel's flag
+    bufs, _ = _state(W.odd_sizes(), seed=26)
+    blob = torch.zeros(fo.checkpoint_size("adamw", [b.numel for b in bufs]), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("adamw", bufs, 31, blob)
+    x = torch.full((5000,), 2.0, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(2):
+        mon = _busy_stream(0.05)
+        assert fo.quantization_nmse("momentum", False, x, stream=mon.stream) == (0.0, 20000.0)
+        fresh = [fo.ParamBuffers(b.numel, "adamw", with_grad=False) for b in bufs]
+        mon = _busy_stream(0.05)
+        assert fo.checkpoint_unpack("adamw", blob, fresh, stream=mon.stream) == 31
+        mon.stream.synchronize()
+        for a, b in zip(bufs, fresh):
+            assert torch.equal(a.rho, b.rho) and torch.equal(a.v_q, b.v_q)
+
+
 def test_packing_lists_that_differ_in_empty_tensors_only():
     # the header grows with every tensor of the list, also with those that have no element
     one = fo.ParamBuffers(64, "sgd")
