@@ -99,7 +99,9 @@ typedef struct flashoptim_lion_hp { float beta1, beta2; } flashoptim_lion_hp;
  * with a further distinct list frees the least recently used one after synchronising the device.  The grad pointers are not part of the
  * cached identity of a list, so gradients may live in different buffers each step.  A call whose descriptors
  * (pointers, grad pointers, numel, lr, weight_decay) equal those of the previous call on the same list enqueues
- * kernels only and may be captured into a HIP graph; changed descriptors are uploaded in stream order first.
+ * kernels only and may be captured into a HIP graph; changed descriptors are uploaded in stream order first.  A change
+ * of lr alone, to a value that all tensors share, needs no upload: it is an argument of the kernels (a captured call
+ * keeps the value it was captured with).
  *
  * flashoptim_adamw_step: Algorithm 4, the body of the loop after the gradient (reconstruct m, v, theta; AdamW
  *   update with bias correction and decoupled weight decay; quantize m, v; split theta).

@@ -56,7 +56,8 @@ inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 // per workgroup).  It belongs to the list's identity (device, operation, every state pointer and
 // numel; NOT the gradient pointers or lr/wd, which legitimately change from step to step).
 // The tensor table is re-uploaded (104 B per tensor, through pinned staging, in stream
-// order) only when its content differs from what the device already holds.
+// order) only when its content differs from what the device already holds; a learning rate that all
+// tensors share is not part of it.
 //
 // A call finds its plan through a 64-bit hash of the identity and then compares the descriptors themselves, so a
 // collision costs time and nothing else.  (With the identity as a string key, built and hashed byte by byte on
@@ -222,10 +223,18 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     return FLASHOPTIM_OK;
 }
 
-// Brings a step's table up to date in stream order if any descriptor has changed since its last upload.
-int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, hipStream_t stream) {
+// Brings a step's table up to date in stream order if any descriptor has changed since its last upload.  Where the
+// launch carries the learning rate, the table keeps the rates it was last uploaded with: an earlier launch that was
+// captured into a graph may still read them.
+int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr, hipStream_t stream) {
     const size_t bytes = tensors.size() * sizeof(TensorDev);
     if (std::memcmp(p.tensors.data(), tensors.data(), bytes) == 0) return FLASHOPTIM_OK;
+    if (ignore_lr) {
+        bool same = true;       // (the same list: what a call can change beside lr is the gradient and the weight decay)
+        for (size_t i = 0; i < tensors.size() && same; ++i)
+            same = p.tensors[i].grad == tensors[i].grad && std::memcmp(&p.tensors[i].wd, &tensors[i].wd, sizeof(float)) == 0;
+        if (same) return FLASHOPTIM_OK;
+    }
     void* slot = nullptr;
     uint32_t *flag = nullptr, seq = 0;
     const int rc = stage(p, tensors.data(), bytes, &slot, &flag, &seq);
@@ -363,6 +372,12 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
         return FLASHOPTIM_OK;
     }
 
+    // a learning rate that all tensors share goes with the launch, not through the table
+    bool shared_lr = true;
+    for (const TensorDev& d : live) shared_lr = shared_lr && std::memcmp(&d.lr, &live[0].lr, sizeof(float)) == 0;
+    a.table_lr_mask = shared_lr ? 0u : ~0u;
+    if (shared_lr) std::memcpy(&a.shared_lr_bits, &live[0].lr, sizeof(float));
+
     PlanTag tag = {0, (int32_t)op, kind, (int32_t)(split ? 1 : 0) | (int32_t)(quant ? 2 : 0), nullptr};
     FO_HIP(hipGetDevice(&tag.device));
     const uint64_t hash = identity_hash(tag, live);
@@ -372,7 +387,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     Plan* plan = find_plan(tag, hash, live);
     int rc;
     if (plan) {
-        rc = refresh_table(*plan, live, stream);
+        rc = refresh_table(*plan, live, shared_lr, stream);
     } else {
         // the coarse workgroup -> tensor table
         std::vector<uint32_t> coarse((size_t)(((total_chunks - 1) >> shift) + 1));
@@ -1296,6 +1311,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     a.coarse = coarse;
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)n_live;
+    a.table_lr_mask = ~0u;
     FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, small, a, total_tiles, ce, stream));
     return FLASHOPTIM_OK;
 }

@@ -947,6 +947,7 @@ __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
     const int64_t chunk = locate_tile<DIRECT>(a, T);
     const int64_t tile0 = chunk * (int64_t)kTile;              // first element of the tile (wave-uniform)
     const int64_t rem = T.numel - tile0;                       // elements from there to the tensor's end
+    if (!DIRECT) T.lr = u2f((f2u(T.lr) & a.table_lr_mask) | a.shared_lr_bits);     // (integers: stays on the scalar unit)
     StepConsts c = a.c;
     if (KIND == 0) c.sqrt_min = *a.sqrt_min_word;              // one scalar load, needed only after the streaming loads
     if (rem >= kTile) {

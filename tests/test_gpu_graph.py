@@ -74,3 +74,33 @@ def test_captured_steps_replay_like_eager_calls():
         for b in ref:
             b.grad.mul_(-0.5)
         torch.cuda.synchronize()
+
+
+def test_captured_learning_rates_are_kept_and_later_calls_do_not_reach_them():
+    # a rate that all tensors share is an argument of the captured kernels; rates that differ are read from the list's
+    # table, which an eager call with one common rate leaves alone
+    specs = W.odd_sizes()[4:14]
+    ref, got = _twins(specs, seed=43)
+    tl_ref, tl_got = fo.TensorList(ref), fo.TensorList(got)
+
+    def rates(tl, lrs):
+        for i in range(tl.n):
+            tl.set_hyper(i, lr=lrs[i % len(lrs)])
+
+    for common in (True, False):
+        captured = [2e-3] if common else [1e-3, 3e-3]
+        for tl in (tl_ref, tl_got):
+            rates(tl, captured)
+            fo.adamw_step_exact(tl, B1, B2, EPS, 1)            # tables and descriptors as the capture will find them
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            fo.adamw_step_exact(tl_got, B1, B2, EPS, 2)
+        for replay in range(3):
+            for tl in (tl_ref, tl_got):                        # an eager step at another common rate in between
+                rates(tl, [5e-4 * (replay + 1)])
+                fo.adamw_step_exact(tl, B1, B2, EPS, 3)
+            graph.replay()
+            rates(tl_ref, captured)
+            fo.adamw_step_exact(tl_ref, B1, B2, EPS, 2)
+            _assert_equal(ref, got, f"common={common} replay {replay}")

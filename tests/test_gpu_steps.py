@@ -456,6 +456,30 @@ def test_hyperparameters_and_gradient_buffers_may_change_between_steps():
         assert sum(r[1] for r in rep) == 0
 
 
+def test_common_and_differing_learning_rates_in_turn():
+    # a rate shared by all tensors goes with the launch, differing ones through the table; every order of the two, with
+    # weight decays and gradients changing beside them, follows the descriptors
+    specs = W.odd_sizes()[6:16]
+    states = [oracle.TensorState(W.theta0(sp, i, seed=61).numpy(), "lion") for i, sp in enumerate(specs)]
+    bufs = [upload_state(s) for s in states]
+    alt = [torch.empty_like(b.grad) for b in bufs]
+    tl = fo.TensorList(bufs)
+    plans = [[1e-4], [2e-4], [1e-4, 3e-4], [2e-4], [1e-4, 3e-4], [1e-4, 5e-4], [4e-4], [4e-4], [1e-4, 5e-4], [0.0], [1e-4]]
+    for t, lrs in enumerate(plans):
+        grads = grads_for(specs, t + 1, seed=61)
+        for i, (b, g) in enumerate(zip(bufs, grads)):
+            lr, wd = lrs[i % len(lrs)], (0.1 if (t // 3 + i) % 2 else 0.0)
+            dst = alt[i] if t in (3, 6) else b.grad
+            dst.copy_(g.cuda())
+            tl.set_grad(i, dst)
+            tl.set_hyper(i, lr=lr, weight_decay=wd)
+            oracle.lion_step(states[i], _g_bits(g), lr, wd, LION["beta1"], LION["beta2"])
+        fo.lion_step(tl, LION["beta1"], LION["beta2"])
+    for b, st, sp in zip(bufs, states, specs):
+        rep = compare_state(download(b), st, where=f"rates {sp.name}")
+        assert sum(r[1] for r in rep) == 0
+
+
 def test_lists_of_the_same_buffers_in_other_arrangements_have_their_own_tables():
     # reversed, shortened, with two tensors' momenta exchanged, and shorter than their buffers: each list is stepped
     # like its tensors one by one
