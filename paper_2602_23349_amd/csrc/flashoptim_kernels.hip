@@ -1530,8 +1530,9 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, 
 // workgroup adds the pairs up in a fixed order and writes the result to memory that the host reads.
 // (With one pair of FP64 atomics per wavefront on the two totals, 2^24 elements took 206 us, nearly all of it
 // those 16,384 updates of two addresses.)
+template <int THREADS>
 __device__ __forceinline__ void block_sum_pair(double& a, double& b) {
-    __shared__ double part[2][kThreads / 64];
+    __shared__ double part[2][THREADS / 64];
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_down(a, off);
         b += __shfl_down(b, off);
@@ -1543,7 +1544,7 @@ __device__ __forceinline__ void block_sum_pair(double& a, double& b) {
     __syncthreads();
     a = b = 0.0;
 #pragma unroll
-    for (int k = 0; k < kThreads / 64; ++k) { a += part[0][k]; b += part[1][k]; }
+    for (int k = 0; k < THREADS / 64; ++k) { a += part[0][k]; b += part[1][k]; }
 }
 
 template <bool VARIANCE, bool LINEAR, bool FULL>
@@ -1576,7 +1577,7 @@ __global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t 
         if (n - tile0 >= kCodecTile) nmse_tile<VARIANCE, LINEAR, true>(x, n, tile0, tab, err, ref);
         else nmse_tile<VARIANCE, LINEAR, false>(x, n, tile0, tab, err, ref);
     }
-    block_sum_pair(err, ref);
+    block_sum_pair<kThreads>(err, ref);
     if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(err, ref);
 }
 // Tells a waiting host that everything the workgroup has written to pinned memory is there.  Called by every lane.
@@ -1586,20 +1587,28 @@ __device__ __forceinline__ void publish(uint32_t* flag, uint32_t seq) {
     if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__global__ __launch_bounds__(kThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums,
-                                                              uint32_t* flag, uint32_t seq) {
-    double err = 0.0, ref = 0.0;
-    for (int i = (int)threadIdx.x; i < n_partial; i += kThreads) {
-        const double2 p = partial[i];
-        err += p.x;
-        ref += p.y;
+// One workgroup with all of its loads in flight, and one lane that orders the flag behind its own two stores (2^24
+// momentum values, a whole call: 27.4 us with eight rounds of loads and a system-wide fence by every lane, 25.6 now).
+constexpr int kTotalThreads = 512;
+constexpr int kTotalPairs = kNmseMaxBlocks / kTotalThreads;
+static_assert(kTotalPairs * kTotalThreads == kNmseMaxBlocks, "every lane adds the same number of pairs");
+__global__ __launch_bounds__(kTotalThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums,
+                                                                   uint32_t* flag, uint32_t seq) {
+    double2 p[kTotalPairs];
+#pragma unroll
+    for (int k = 0; k < kTotalPairs; ++k) {
+        const int i = (int)threadIdx.x + k * kTotalThreads;
+        p[k] = i < n_partial ? partial[i] : make_double2(0.0, 0.0);
     }
-    block_sum_pair(err, ref);
+    double err = 0.0, ref = 0.0;
+#pragma unroll
+    for (int k = 0; k < kTotalPairs; ++k) { err += p[k].x; ref += p[k].y; }
+    block_sum_pair<kTotalThreads>(err, ref);
     if (threadIdx.x == 0) {
         sums[0] = err;
         sums[1] = ref;
+        __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
     }
-    publish(flag, seq);
 }
 
 static inline unsigned tiles_for(int64_t n) { return (unsigned)((n + kCodecTile - 1) / kCodecTile); }
@@ -1662,7 +1671,7 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
     dispatch_codec(variance, linear, 2, x, nullptr, nullptr, nullptr, n, partial, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kThreads), 0, s, partial, (int)nmse_blocks(n), sums, flag,
+    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kTotalThreads), 0, s, partial, (int)nmse_blocks(n), sums, flag,
                        seq);
     return hipGetLastError();
 }
