@@ -51,9 +51,8 @@ inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 
 // ----------------------------------------------------- cached device tables --
 //
-// A "plan" is what a multi-tensor launch needs on the device: the tensor table and the index
-// table (for steps and conversions a coarse workgroup -> tensor table, for copies one entry
-// per workgroup).  It belongs to the list's identity (device, operation, every state pointer and
+// A "plan" is what a multi-tensor launch needs on the device: the table of tensors (for copies, of
+// segments) and a coarse index table into it by workgroup.  It belongs to the list's identity (device, operation, every state pointer and
 // numel; NOT the gradient pointers or lr/wd, which legitimately change from step to step).
 // The tensor table is re-uploaded (104 B per tensor, through pinned staging, in stream
 // order) only when its content differs from what the device already holds; a learning rate that all
@@ -98,8 +97,9 @@ struct Plan {
     std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
     void* d_mem = nullptr;         // one allocation: the table, then the index
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
-    void* d_index = nullptr;       // uint32 coarse table (steps, conversions) or uint2 piece table (copies)
+    void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
+    uint32_t n_segs = 0, coarse_shift = 0;      // copies only
     // Pinned memory, one allocation: the slots' flags, the source of the first upload of both tables (kept until the
     // plan is freed), and kRingSlots slots of slot_bytes through which later tables and headers reach the device.  The kernel that
     // reads slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
@@ -610,6 +610,7 @@ void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* bl
             if (pack) { s.src = static_cast<const uint8_t*>(tensor_buf); s.dst = blob + off; s.pad_bytes = align64(bytes); }
             else { s.src = blob + off; s.dst = static_cast<uint8_t*>(const_cast<void*>(tensor_buf)); s.pad_bytes = bytes; }
             s.bytes = bytes;
+            s.first_piece = s.n_pieces = 0;
             segs.push_back(s);
         }
         off += align64(bytes);
@@ -640,21 +641,34 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
     int64_t total = 0;
     for (const TensorDev& d : list) total += tensor_payload(d.numel, kind);
     if (total == 0 && !pack) return FLASHOPTIM_OK;
-    const int piece = total < fo::kCopySmallBytes ? fo::kCopyPieceSmall : fo::kCopyPieceLarge;
+    // (one workgroup per piece, and one for the header: the launch grid is a 31-bit count, sections included that end
+    // in a short piece)
+    if (total / fo::kCopyPiece + 6 * n + 1 > (int64_t)0x7fffffff) return FLASHOPTIM_ERR_NUMEL_RANGE;
     std::lock_guard<std::mutex> lock(g_mu);
     Plan* plan = find_plan(tag, hash, list);
     if (!plan) {
         std::vector<CopySegment> segs;
         build_segments(kind, t, n, blob, pack, segs);
-        std::vector<uint2> pieces;
-        pieces.reserve((size_t)(total / piece) + segs.size());
-        for (size_t si = 0; si < segs.size(); ++si) {
-            const int64_t nc = (segs[si].pad_bytes + piece - 1) / piece;
-            for (int64_t ci = 0; ci < nc; ++ci) pieces.push_back(make_uint2((unsigned)si, (unsigned)ci));
+        int64_t n_pieces = 0;
+        for (CopySegment& sg : segs) {
+            sg.first_piece = (uint32_t)n_pieces;
+            sg.n_pieces = (uint32_t)((sg.pad_bytes + fo::kCopyPiece - 1) / fo::kCopyPiece);
+            n_pieces += sg.n_pieces;
         }
-        const int rc = make_plan(tag, hash, list, segs.data(), segs.size() * sizeof(CopySegment), pieces.data(),
-                                 pieces.size() * sizeof(uint2), header_bytes, (int64_t)pieces.size(), stream, &plan);
+        uint32_t shift = 0;
+        while ((n_pieces >> shift) > (int64_t)fo::kCoarseMaxEntries) ++shift;
+        std::vector<uint32_t> coarse(n_pieces ? (size_t)(((n_pieces - 1) >> shift) + 1) : 0);
+        size_t si = 0;
+        for (size_t j = 0; j < coarse.size(); ++j) {
+            const int64_t b = (int64_t)j << shift;
+            while ((int64_t)segs[si].first_piece + segs[si].n_pieces <= b) ++si;
+            coarse[j] = (uint32_t)si;
+        }
+        const int rc = make_plan(tag, hash, list, segs.data(), segs.size() * sizeof(CopySegment), coarse.data(),
+                                 coarse.size() * sizeof(uint32_t), header_bytes, n_pieces, stream, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
+        plan->n_segs = (uint32_t)segs.size();
+        plan->coarse_shift = shift;
     }
     void* slot = nullptr;
     uint32_t *flag = nullptr, seq = 0;
@@ -662,8 +676,19 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         const int rc = stage(*plan, header, header_bytes, &slot, &flag, &seq);
         if (rc != FLASHOPTIM_OK) return rc;
     }
-    FO_HIP(fo::launch_copy(piece, static_cast<const CopySegment*>(plan->d_table), static_cast<const uint2*>(plan->d_index),
-                           plan->n_chunks, slot, blob, (int64_t)header_bytes, flag, seq, stream));
+    fo::CopyArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.segs = static_cast<const CopySegment*>(plan->d_table);
+    a.coarse = static_cast<const uint32_t*>(plan->d_index);
+    a.coarse_shift = plan->coarse_shift;
+    a.n_segs = plan->n_segs;
+    a.n_pieces = (uint32_t)plan->n_chunks;
+    a.header_n16 = (uint32_t)(header_bytes / 16);
+    a.header = static_cast<const uint4*>(slot);
+    a.header_dst = reinterpret_cast<uint4*>(blob);
+    a.flag = flag;
+    a.seq = seq;
+    FO_HIP(fo::launch_copy(a, stream));
     if (slot) mark_in_flight(*plan);
     return FLASHOPTIM_OK;
 }

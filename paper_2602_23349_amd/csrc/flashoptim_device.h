@@ -47,9 +47,7 @@ constexpr int step_threads(int kind, bool split, bool quant, bool small) {
 constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
     return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);
 }
-constexpr int kCopyPieceLarge = 128 * 1024;        // checkpoint copy: bytes per workgroup ...
-constexpr int kCopyPieceSmall = 32 * 1024;         // ... when fewer than kCopySmallBytes are copied in all
-constexpr int64_t kCopySmallBytes = (int64_t)2048 * kCopyPieceLarge;
+constexpr int kCopyPiece = 16 * 1024;        // checkpoint copy: bytes per workgroup
 
 // One tensor as the kernels see it (device pointers), 104 bytes.
 struct TensorDev {
@@ -124,6 +122,23 @@ struct CopySegment {
     uint8_t* dst;
     int64_t bytes;       // bytes to copy
     int64_t pad_bytes;   // >= bytes; [bytes, pad_bytes) of dst is zero-filled
+    uint32_t first_piece;   // index of the workgroup that copies the segment's first piece
+    uint32_t n_pieces;
+};
+
+struct CopyArgs {
+    const CopySegment* segs;
+    const uint32_t* coarse;     // segment index per 2^coarse_shift pieces, as in StepArgs
+    uint32_t coarse_shift;
+    uint32_t n_segs;
+    uint32_t n_pieces;
+    // the blob's header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst; it sets *flag
+    // (pinned) to seq when it has read the slot
+    uint32_t header_n16;
+    const uint4* header;
+    uint4* header_dst;
+    uint32_t* flag;
+    uint32_t seq;
 };
 
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,
@@ -146,10 +161,7 @@ constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per comp
 // they are there
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
                        uint32_t* flag, uint32_t seq, hipStream_t s);
-// header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst, header_bytes a multiple of 16;
-// it sets *flag (pinned) to seq when it has read the slot
-hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pieces, int64_t n_pieces, const void* header,
-                       void* header_dst, int64_t header_bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
+hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
 // The same from a pinned slot, by one workgroup that sets *flag (pinned) to seq when it has read the slot.

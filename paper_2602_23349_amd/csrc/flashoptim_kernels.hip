@@ -1950,72 +1950,44 @@ __device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
     if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Gather / scatter of byte segments: each workgroup copies one piece of one segment with 128-bit accesses
-// (segment starts are 16-byte aligned on both sides), the ragged end byte by byte, and - when packing -
-// zero-fills the padding up to pad_bytes.  Bound: HBM.
+// Gather / scatter of byte segments: each workgroup copies one piece of one segment, 16 bytes per lane (segment starts
+// are 16-byte aligned on both sides), the ragged end byte by byte, and - when packing - zero-fills the padding up to
+// pad_bytes.  Bound: HBM.
 //
-// A full piece is BATCH loads per lane, all issued before the first store.  Long copies take 16 (pieces of 128 KB:
-// GPT-2's 638 MB blob 228 us, 5.6 TB/s, against 233 with 32 KB; two Llama layers with embedding and head 2.75 ms
-// against 2.97).  Below kCopySmallBytes there are fewer than two generations of such pieces - 1024 workgroups are
-// resident at a time - and the last one is mostly empty; four loads per lane then do better (ResNet-50, 131 MB:
-// 59.6 -> 51.8 us; a tensor of 3 M elements: 19.2 -> 15.1 us).  The last piece of every segment was a serial chain of
-// up to 16 load-store pairs; with its loads together as well the two take 46.7 and 7 us.
+// One access per lane and 1024 lanes: pieces of 16 KB that are read and written at once and make room for the next.
+// More per lane is slower, less so in fewer lanes (pack of GPT-2's 638 MB / of a Llama layer / of two layers with
+// embedding and head, in us: 512 lanes x 16 accesses 225 / 387 / 2749; 1024 x 8 217 / 378 / 2659; 1024 x 1 201 / 355 /
+// 2520, 6.1 TB/s).  Pieces are found as the step kernels find their tiles, through a coarse table and the segments
+// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
 //
 // header: the blob's header and table when packing, in a pinned slot; the workgroup behind the last piece writes it to
 // header_dst.
-constexpr int kCopyThreads = 512;
-template <int BATCH>
-__global__ __launch_bounds__(kCopyThreads) void copy_kernel(const CopySegment* segs, const uint2* pieces, uint32_t n_pieces,
-                                                            const uint4* header, uint4* header_dst, uint32_t header_n16,
-                                                            uint32_t* flag, uint32_t seq) {
-    constexpr int64_t kStride = (int64_t)kCopyThreads * 16;
-    constexpr int64_t kPiece = kStride * BATCH;
-    if (blockIdx.x == n_pieces) {
-        for (uint32_t i = threadIdx.x; i < header_n16; i += kCopyThreads) header_dst[i] = header[i];
-        release_slot(flag, seq);
+constexpr int kCopyThreads = kCopyPiece / 16;
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
+    if (blockIdx.x == a.n_pieces) {
+        for (uint32_t i = threadIdx.x; i < a.header_n16; i += kCopyThreads) a.header_dst[i] = a.header[i];
+        release_slot(a.flag, a.seq);
         return;
     }
-    const uint2 ck = pieces[blockIdx.x];
-    const CopySegment sg = segs[ck.x];
-    const int64_t begin = (int64_t)ck.y * kPiece;
-    const int64_t total = sg.pad_bytes;                  // >= sg.bytes
-    const int64_t end = (total - begin < kPiece) ? total : begin + kPiece;
-    const uint8_t* src = sg.src;
-    uint8_t* dst = sg.dst;
-    const int64_t o = begin + (int64_t)threadIdx.x * 16;
-    uint4 v[BATCH];
-    if (begin + kPiece <= sg.bytes) {
-#pragma unroll
-        for (int k = 0; k < BATCH; ++k) v[k] = ld128(src + o + k * kStride);
-#pragma unroll
-        for (int k = 0; k < BATCH; ++k) st128(dst + o + k * kStride, v[k].x, v[k].y, v[k].z, v[k].w);
-        return;
+    uint32_t t = a.coarse[blockIdx.x >> a.coarse_shift];
+    CopySegment sg = a.segs[t];
+    while (blockIdx.x - sg.first_piece >= sg.n_pieces && t + 1 < a.n_segs) {
+        ++t;
+        sg = a.segs[t];
     }
-    // a segment's last piece: the same batch with the accesses past its end left out, then its ragged end
-#pragma unroll
-    for (int k = 0; k < BATCH; ++k) if (o + k * kStride + 16 <= sg.bytes) v[k] = ld128(src + o + k * kStride);
-#pragma unroll
-    for (int k = 0; k < BATCH; ++k)
-        if (o + k * kStride + 16 <= sg.bytes) st128(dst + o + k * kStride, v[k].x, v[k].y, v[k].z, v[k].w);
-    for (int64_t e = o; e < end; e += kStride) {
-        if (e + 16 <= sg.bytes) continue;
-        for (int k = 0; k < 16 && e + k < end; ++k) dst[e + k] = (e + k < sg.bytes) ? src[e + k] : (uint8_t)0;
+    const int64_t o = (int64_t)(blockIdx.x - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
+    if (o + 16 <= sg.bytes) {
+        const uint4 v = ld128(sg.src + o);
+        st128(sg.dst + o, v.x, v.y, v.z, v.w);
+    } else {
+        for (int k = 0; k < 16 && o + k < sg.pad_bytes; ++k) sg.dst[o + k] = (o + k < sg.bytes) ? sg.src[o + k] : (uint8_t)0;
     }
 }
-static_assert(kCopyPieceLarge == kCopyThreads * 16 * 16 && kCopyPieceSmall == kCopyThreads * 16 * 4,
-              "the host cuts the segments into pieces of these sizes");
 
 // (Issuing the copy as several shorter launches, which helps the step kernels, changed its rate by
 // less than 2 %: it stays one launch.)
-hipError_t launch_copy(int piece_bytes, const CopySegment* segs, const uint2* pieces, int64_t n_pieces, const void* header,
-                       void* header_dst, int64_t header_bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
-    const dim3 grid((unsigned)(n_pieces + (header ? 1 : 0))), block(kCopyThreads);
-    if (piece_bytes == kCopyPieceLarge)
-        hipLaunchKernelGGL(copy_kernel<16>, grid, block, 0, s, segs, pieces, (uint32_t)n_pieces, (const uint4*)header,
-                           (uint4*)header_dst, (uint32_t)(header_bytes / 16), flag, seq);
-    else
-        hipLaunchKernelGGL(copy_kernel<4>, grid, block, 0, s, segs, pieces, (uint32_t)n_pieces, (const uint4*)header,
-                           (uint4*)header_dst, (uint32_t)(header_bytes / 16), flag, seq);
+hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(copy_kernel, dim3(a.n_pieces + (a.header ? 1u : 0u)), dim3(kCopyThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -399,9 +399,9 @@ def test_checkpoint_pack_unpack_small_lists():
 
 
 @pytest.mark.parametrize("kind,sizes", [
-    # sections of 1 or 2 bytes per element around the ends of a 32 KB piece, and of its 8 KB rows
+    # sections of 1 or 2 bytes per element around the ends of a 16 KB piece and of two
     ("adamw", [4095, 4096, 8191, 8192, 8200, 16383, 16384, 16385, 32767, 32768, 32769, 32784, 65536, 65551]),
-    # the same for the 128 KB pieces of a long copy (above 256 MB in all)
+    # a copy of more pieces than the coarse table has entries, with short sections between long ones
     ("adamw", [65535, 65536, 65537, 131071, 131072, 131073, 131088, 53_000_000]),
     ("sgd", [3]),
 ])
