@@ -27,7 +27,8 @@
  *    streams must be ordered by the caller, as for any other kernel; calls on disjoint
  *    lists may run concurrently (the library is thread-safe).
  *  - One call covers at most 2^31 - 1 workgroups (2048 elements each for AdamW, 4096 for
- *    SGD / Lion): more returns FLASHOPTIM_ERR_NUMEL_RANGE.
+ *    SGD / Lion, 256 to 2048 for the ablation variants and conversions): more returns
+ *    FLASHOPTIM_ERR_NUMEL_RANGE.
  *  - Return value: FLASHOPTIM_OK (0) or a negative flashoptim_status.  Arguments are
  *    validated before anything is enqueued: when an error is returned no buffer has
  *    been modified.  Nothing throws or aborts.
@@ -122,7 +123,7 @@ typedef struct flashoptim_lion_hp { float beta1, beta2; } flashoptim_lion_hp;
  *                                2^-60 <= eps <= 1 and the operands do not exceed 2^60; otherwise this entry point
  *                                takes the IEEE division (slower, same results as the exact entry point).
  *   flashoptim_adamw_step_exact  the quotient is correctly rounded for every input: the whole step is
- *                                bit-identical to the arithmetic stated above.  About 3 % slower on MI355X.
+ *                                bit-identical to the arithmetic stated above.  About 2 % slower on MI355X.
  * Everything else is identical between the two. */
 int flashoptim_adamw_step(const flashoptim_tensor* tensors, int64_t n_tensors,
                           const flashoptim_adamw_hp* hp, void* stream);

@@ -40,7 +40,7 @@
 //     result for operands inside a stated range (the square root: verified for every value of
 //     the range by the device self-test; the division: the classical refinement); a
 //     wave-uniform range test selects the general sequence otherwise.  With EXACT = false the
-//     division takes one residual correction instead of a refined reciprocal and two (div_faithful).
+//     division takes one residual correction of the unrefined quotient (div_faithful).
 //
 // Work decomposition.  A lane owns 8 consecutive elements per tile: BF16 streams move as
 // 128-bit and byte streams as 64-bit accesses, and a quantisation group (32 elements) is a
@@ -48,7 +48,9 @@
 // lanes for AdamW, 512 for SGD and Lion) handles one tile of consecutive elements of one
 // tensor; a small two-level table maps the workgroup index to (tensor, tile) so that one call covers a
 // whole parameter list, issued as a few consecutive launches.  Stream addresses are a scalar 64-bit
-// tile base plus a 32-bit lane offset.
+// tile base plus a 32-bit lane offset.  A lane owns 4 elements, and a group is 8 lanes, where FP32 streams are
+// moved (ablation variants, codecs, conversions: a 128-bit FP32 access per lane then covers whole cache lines)
+// and where a launch is small (fewer than 2^20 elements: more wavefronts, each with half the work).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -144,18 +146,7 @@ __device__ __forceinline__ uint32_t bf16_pack(float a, float b) {
     return __builtin_bit_cast(uint32_t, r);
 }
 
-// FP16 scale of a group from its FP32 absmax: saturate at 65504, round to nearest even.
-// Returns the FP16 bits; *r is the correctly rounded reciprocal of the scale as the decoder
-// will read it (0 when the scale is 0, so that every code of the group becomes 0).
-__device__ __forceinline__ uint32_t group_scale(float absmax, float* r) {
-    const float a = fminf(absmax, 65504.0f);
-    const _Float16 h = (_Float16)a;
-    const float s = (float)h;
-    *r = (s == 0.0f) ? 0.0f : 1.0f / s;
-    return (uint32_t)__builtin_bit_cast(uint16_t, h);
-}
-
-// Same, with the reciprocal formed as hardware estimate + one Newton step.  The argument takes
+// Reciprocal of an FP16 scale, formed as hardware estimate + one Newton step.  The argument takes
 // only the 31,743 positive finite FP16 values; for every one of them this sequence returns the
 // correctly rounded 1/s (checked exhaustively on the device by flashoptim_selftest).
 __device__ __forceinline__ float recip_of_fp16(float s) {
@@ -163,7 +154,10 @@ __device__ __forceinline__ float recip_of_fp16(float s) {
     const float e = fmaf(-s, r0, 1.0f);
     return fmaf(e, r0, r0);
 }
-__device__ __forceinline__ uint32_t group_scale_fast(float absmax, float* r) {
+// FP16 scale of a group from its FP32 absmax: saturate at 65504, round to nearest even.
+// Returns the FP16 bits; *r is the correctly rounded reciprocal of the scale as the decoder
+// will read it (0 when the scale is 0, so that every code of the group becomes 0).
+__device__ __forceinline__ uint32_t group_scale(float absmax, float* r) {
     const float a = fminf(absmax, 65504.0f);
     const _Float16 h = (_Float16)a;
     const float s = (float)h;
@@ -392,10 +386,9 @@ __device__ __forceinline__ uint32_t rho_bits_lds(const DecodeTables& t, float th
 
 // -------------------------------------------------------------- lane vectors --
 //
-// VEC consecutive elements per lane (8 or 16).  With 16, every stream moves as 128-bit
-// accesses and a group of 32 is a lane pair; with 8, the byte streams move as 64-bit
-// accesses and a group is a lane quad, but the kernel needs half the registers and more
-// wavefronts fit on a SIMD.
+// VEC consecutive elements per lane: 8 (the byte streams move as 64-bit accesses, a group is a lane quad) or 4 (32-bit
+// accesses, a group is eight lanes).  With 16 every stream would move as 128-bit accesses, but a lane's BF16 data would
+// be two of them that each cover half of every line, and fewer wavefronts fit on a SIMD.
 
 template <int VEC>
 struct LaneIO {
@@ -685,7 +678,7 @@ __device__ __forceinline__ void split_block(LaneIO<VEC>& y, const DecodeTables& 
 
 // KIND: 0 AdamW (Algorithm 4), 1 SGD (Algorithm 5), 2 Lion (Algorithm 6).
 // Operates on the VEC elements of one lane; the lanes holding the rest of the same 32-element
-// group (lane ^ 1, and lane ^ 2, lane ^ 3 when VEC == 8) must execute this function with it.
+// group (the lane's quad when VEC == 8, its run of eight lanes when VEC == 4) must execute this function with it.
 // SPLIT / QUANT: the paper's ablations (Section 4.3).  SPLIT = false keeps the master weight in
 // FP32 (x.th32 -> y.th32); QUANT = false keeps the states in FP32 (x.m32, x.v32 -> y.m32, y.v32).
 // EXACT (AdamW only): the quotient m_hat / (sqrt(v_hat) + eps) is the correctly rounded one for every
@@ -822,16 +815,16 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
         return;
     }
 
-    // epilogue, part 2: group scales (one DPP swap joins the two lanes of a group).  The square root
+    // epilogue, part 2: group scales (DPP steps join the lanes of a group).  The square root
     // is monotone, so the group maximum of sqrt(v) is the square root of the maximum of v.
     amax_m = group_max<VEC>(amax_m);
     float r_m, r_v = 0.0f, kr255 = 0.0f;
-    y.ms = group_scale_fast(amax_m, &r_m);
+    y.ms = group_scale(amax_m, &r_m);
     if (HAS_V) {
         // the group's maximum lies between the extremes of the wavefront's lanes: in the short root's range if they are
         amax_v = group_max<VEC>(amax_v);
         const float root_max = fast ? sqrt_rn_midrange(amax_v) : sqrtf(amax_v);
-        y.vs = group_scale_fast(root_max, &r_v);
+        y.vs = group_scale(root_max, &r_v);
         // 255 * sqrt(1 / rbc2) * r_v to within one rounding: the constant comes from the host as the two halves of
         // its double-precision value
         kr255 = fmaf(c.k255_hi, r_v, c.k255_lo * r_v);
@@ -1417,7 +1410,7 @@ __device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], u
     a = group_max<kCodecVec>(a);
     if (VARIANCE && !LINEAR) a = sqrtf(a);
     float r;
-    const uint32_t sbits = group_scale_fast(a, &r);
+    const uint32_t sbits = group_scale(a, &r);
     uint32_t c[kCodecVec];
     if (!LINEAR) {
         uint32_t lo_w = 0, hi_w = 0;
