@@ -100,9 +100,10 @@ struct Plan {
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
-    // Pinned memory, one allocation: the slots' flags, the source of the first upload of both tables (kept until the
-    // plan is freed), and kRingSlots slots of slot_bytes through which later tables and headers reach the device.  The kernel that
-    // reads slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
+    // Pinned memory (coherent whatever the environment's default is: the flags are watched while kernels run), one
+    // allocation: the slots' flags, the source of the first upload of both tables (kept until the plan is freed), and
+    // kRingSlots slots of slot_bytes through which later tables and headers reach the device.  The kernel that reads
+    // slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
     uint8_t* h_mem = nullptr;
     uint8_t* h_slots = nullptr;
     size_t slot_bytes = 0;
@@ -138,12 +139,13 @@ int stage(Plan& p, const void* src, size_t bytes, void** slot, uint32_t** flag, 
     if (p.in_slot[i]) {
         const volatile uint32_t* f = p.flag(i);
         // (bounded: a kernel that was captured into a graph and has not been replayed, or that a failed stream dropped,
-        // never sets the flag; once the device has drained nothing reads the slot)
+        // never sets the flag, and a replay sets it back to the number it was captured with; once the device has drained
+        // nothing reads the slot)
         const auto t0 = std::chrono::steady_clock::now();
         for (uint32_t k = 0; *f != p.in_slot[i]; ++k) {
             if (k < 1000) continue;
             std::this_thread::yield();
-            if (std::chrono::steady_clock::now() - t0 < std::chrono::seconds(5)) continue;
+            if (std::chrono::steady_clock::now() - t0 < std::chrono::seconds(1)) continue;
             FO_HIP(hipDeviceSynchronize());
             break;
         }
@@ -193,7 +195,7 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     const size_t index_at = (size_t)align64((int64_t)table_bytes), both = index_at + round16(index_bytes);
     const size_t source_at = kRingSlots * kFlagStride, slots_at = source_at + (size_t)align64((int64_t)both);
     hipError_t e = hipMalloc(&p.d_mem, both > 0 ? both : 16);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, slots_at + kRingSlots * p.slot_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, slots_at + kRingSlots * p.slot_bytes, hipHostMallocCoherent);
     if (e == hipSuccess) {
         p.d_table = p.d_mem;
         p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
@@ -711,7 +713,7 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
 struct CallSpace {
     int device = 0;
     double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs
-    void* host = nullptr;           // pinned, host_bytes and the flag behind them
+    void* host = nullptr;           // pinned and coherent, host_bytes and the flag behind them
     size_t host_bytes = 0;
     uint32_t seq = 0;               // the value that marks the end of the workspace's current use
 
@@ -743,7 +745,7 @@ int take_space(CallSpace& w, size_t host_bytes) {
     }
     w.host_bytes = host_bytes > kMinSpaceHost ? (size_t)align64((int64_t)host_bytes) : kMinSpaceHost;
     hipError_t e = hipMalloc((void**)&w.partial, fo::kNmseMaxBlocks * sizeof(double2));
-    if (e == hipSuccess) e = hipHostMalloc(&w.host, w.host_bytes + kFlagStride, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&w.host, w.host_bytes + kFlagStride, hipHostMallocCoherent);
     if (e != hipSuccess) {
         destroy_space(w);
         g_last_hip_error = (int)e;
