@@ -9,7 +9,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflashoptim.so")
 SOURCES = [os.path.join(CSRC, "flashoptim_kernels.hip"), os.path.join(CSRC, "flashoptim_api.hip")]
-HEADERS = [os.path.join(CSRC, "flashoptim_device.h"), os.path.join(ROOT, "include", "flashoptim.h")]
+HEADERS = [os.path.join(CSRC, "flashoptim_device.h"), os.path.join(CSRC, "flashoptim_launch.h"),
+           os.path.join(ROOT, "include", "flashoptim.h")]
 
 # Exact arithmetic is part of the contract: no FMA contraction, IEEE division and square root,
 # subnormals kept.  Packed FP32 instructions are disabled.

@@ -383,8 +383,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     PlanTag tag = {0, (int32_t)op, kind, (int32_t)(split ? 1 : 0) | (int32_t)(quant ? 2 : 0), nullptr};
     FO_HIP(hipGetDevice(&tag.device));
     const uint64_t hash = identity_hash(tag, live);
-    uint32_t shift = 0;
-    while ((total_chunks >> shift) > (int64_t)fo::kCoarseMaxEntries) ++shift;
+    const uint32_t shift = fo::coarse_shift(total_chunks);
     std::lock_guard<std::mutex> lock(g_mu);
     Plan* plan = find_plan(tag, hash, live);
     int rc;
@@ -392,7 +391,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
         rc = refresh_table(*plan, live, shared_lr, stream);
     } else {
         // the coarse workgroup -> tensor table
-        std::vector<uint32_t> coarse((size_t)(((total_chunks - 1) >> shift) + 1));
+        std::vector<uint32_t> coarse((size_t)fo::coarse_entries(total_chunks, shift));
         size_t ti = 0;
         for (size_t j = 0; j < coarse.size(); ++j) {
             const int64_t b = (int64_t)j << shift;
@@ -657,9 +656,8 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
             sg.n_pieces = (uint32_t)((sg.pad_bytes + fo::kCopyPiece - 1) / fo::kCopyPiece);
             n_pieces += sg.n_pieces;
         }
-        uint32_t shift = 0;
-        while ((n_pieces >> shift) > (int64_t)fo::kCoarseMaxEntries) ++shift;
-        std::vector<uint32_t> coarse(n_pieces ? (size_t)(((n_pieces - 1) >> shift) + 1) : 0);
+        const uint32_t shift = fo::coarse_shift(n_pieces);
+        std::vector<uint32_t> coarse((size_t)fo::coarse_entries(n_pieces, shift));
         size_t si = 0;
         for (size_t j = 0; j < coarse.size(); ++j) {
             const int64_t b = (int64_t)j << shift;
@@ -1328,9 +1326,8 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
         hipLaunchKernelGGL(noalloc_fill_table, dim3(1), dim3(64), 0, stream, batch, table);
         FO_HIP(hipGetLastError());
     }
-    uint32_t shift = 0;
-    while ((total_tiles >> shift) > (int64_t)fo::kCoarseMaxEntries) ++shift;
-    const uint32_t n_coarse = (uint32_t)(((total_tiles - 1) >> shift) + 1);
+    const uint32_t shift = fo::coarse_shift(total_tiles);
+    const uint32_t n_coarse = (uint32_t)fo::coarse_entries(total_tiles, shift);
     hipLaunchKernelGGL(noalloc_fill_coarse, dim3((n_coarse + 255) / 256), dim3(256), 0, stream, table,
                        (uint32_t)n_live, coarse, n_coarse, shift);
     FO_HIP(hipGetLastError());

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "flashoptim_launch.h"
+
 namespace fo {
 
 constexpr int kGroup = 32;                         // quantisation group (Algorithms 2, 3)
@@ -85,12 +87,6 @@ struct StepConsts {
                           // check on this device; the step kernels fill it in from StepArgs::sqrt_min_word
 };
 
-// A multi-tensor launch maps workgroup b to (tensor, tile) in two steps: coarse[b >> coarse_shift] is
-// the tensor that holds tile (b >> coarse_shift) << coarse_shift, and the tensors' first_tile /
-// n_tiles fields carry the search on from there (usually zero further steps).  Both tables are
-// small (at most 16 K coarse entries) and stay cache-resident, unlike a table with one entry per
-// workgroup, whose entries every workgroup would fetch from HBM.
-constexpr int kCoarseMaxEntries = 16384;
 // One logical launch is issued as consecutive launches that cover at most this many elements each.
 // Measured on the Llama list (8.03 G parameters): the memory-bound SGD and Lion steps run 3-9 % faster
 // in ~30-60 launches than in one launch of 1.96 M workgroups (12.9-13.0 vs 13.4-14.0 ms); AdamW gains
@@ -102,7 +98,7 @@ constexpr int kCoarseMaxEntries = 16384;
 constexpr int64_t kSegmentElems = FO_SEGMENT_ELEMS;
 struct StepArgs {
     const TensorDev* tensors;   // device table (multi-tensor launch)
-    const uint32_t* coarse;     // device table: tensor index per 2^coarse_shift workgroups
+    const uint32_t* coarse;     // device table: tensor index per 2^coarse_shift workgroups (flashoptim_launch.h)
     uint32_t coarse_shift;
     uint32_t n_tensors;
     uint32_t block_offset;      // tile index of this launch's workgroup 0 (a list or tensor is covered by several launches)

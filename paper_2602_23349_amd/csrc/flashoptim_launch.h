@@ -1,0 +1,26 @@
+// Internal: the arithmetic by which the host cuts a call into workgroups and launches and sizes the tables that the
+// kernels look things up in.  Plain C++ without HIP, so that its limits can be tested without a GPU.
+#ifndef FLASHOPTIM_LAUNCH_H
+#define FLASHOPTIM_LAUNCH_H
+
+#include <stdint.h>
+
+namespace fo {
+
+// A launch over a list maps workgroup b to (tensor, tile), or in a copy to (segment, piece), in two steps:
+// coarse[b >> shift] is the table entry that holds workgroup (b >> shift) << shift, and the entries' own ranges carry
+// the search on from there (usually zero further steps).  Both tables are small (at most kCoarseMaxEntries coarse
+// entries) and stay cache-resident, unlike a table with one entry per workgroup, whose entries every workgroup would
+// fetch from HBM.
+constexpr int64_t kCoarseMaxEntries = 16384;
+// Coarse entries for `total` (>= 0) workgroups.
+constexpr int64_t coarse_entries(int64_t total, uint32_t shift) { return total > 0 ? ((total - 1) >> shift) + 1 : 0; }
+// The smallest shift with which they fit.
+constexpr uint32_t coarse_shift(int64_t total) {
+    uint32_t shift = 0;
+    while (coarse_entries(total, shift) > kCoarseMaxEntries) ++shift;
+    return shift;
+}
+
+}  // namespace fo
+#endif

@@ -1,0 +1,34 @@
+"""The host arithmetic of the launches (csrc/flashoptim_launch.h), compiled into a small program: table sizes at their
+limits, without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def _run(tmp_path, body):
+    """Compiles `body` as main()'s statements behind the header and returns the lines that it prints."""
+    src, exe = tmp_path / "launch.cpp", tmp_path / "launch"
+    src.write_text('#include <cstdio>\n#include "flashoptim_launch.h"\nint main() {\n' + body + "\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-O1", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+
+
+def test_coarse_tables_never_exceed_their_entries(tmp_path):
+    # the step without allocation writes the table into a fixed array of 16384 entries: totals just above
+    # 16384 * 2^k, where total >> k is 16384 but the last, partial entry makes one more
+    totals = sorted({t for k in range(18) for d in range(-3, 5) if 0 < (t := (16384 << k) + d) <= 0x7fffffff} | {1, 2, 3, 0x7fffffff})
+    out = _run(tmp_path, "const long long totals[] = {" + ", ".join(f"{t}LL" for t in totals) + "};\n"
+               "for (long long t : totals) std::printf(\"%lld %u %lld\\n\", t, fo::coarse_shift(t), "
+               "(long long)fo::coarse_entries(t, fo::coarse_shift(t)));")
+    assert len(out) == len(totals)
+    for line, total in zip(out, totals):
+        t, shift, entries = (int(x) for x in line.split())
+        assert t == total and entries <= 16384, line
+        assert (entries - 1) << shift < total <= entries << shift, line          # every workgroup has its entry
+        assert shift == 0 or -(-total // (1 << (shift - 1))) > 16384, line        # no coarser than needed

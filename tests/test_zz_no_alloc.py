@@ -74,3 +74,13 @@ def test_noalloc_step_single_tensor_and_limits():
     fo.adamw_step_noalloc(got[:1024], HP["beta1"], HP["beta2"], HP["eps"], 1)
     fo.adamw_step_exact(ref[:1024], HP["beta1"], HP["beta2"], HP["eps"], 1)
     _assert_equal(ref[:1024], got[:1024], many[:1024], "1024 tensors")
+
+
+def test_noalloc_step_where_the_coarse_table_is_full():
+    # 32769 tiles of 2048 elements: one tile more than the table's 16384 entries hold at two tiles per entry
+    specs = [W.ParamSpec("a", (16384 * 2048,), "matrix"), W.ParamSpec("b", (16384 * 2048 + 1,), "matrix")]
+    ref, got = _twin_lists(specs, seed=7)
+    for t in (3, 4):
+        fo.adamw_step_noalloc(got, HP["beta1"], HP["beta2"], HP["eps"], t)
+        fo.adamw_step_exact(ref, HP["beta1"], HP["beta2"], HP["eps"], t)
+        _assert_equal(ref, got, specs, f"32769 tiles, step {t}")
