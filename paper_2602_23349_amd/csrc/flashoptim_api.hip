@@ -642,8 +642,7 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
     int64_t total = 0;
     for (const TensorDev& d : list) total += tensor_payload(d.numel, kind);
     if (total == 0 && !pack) return FLASHOPTIM_OK;
-    // (one workgroup per piece, and one for the header: the launch grid is a 31-bit count, sections included that end
-    // in a short piece)
+    // (one workgroup per piece, sections included that end in a short piece, and one for the header: a 32-bit index)
     if (total / fo::kCopyPiece + 6 * n + 1 > (int64_t)0x7fffffff) return FLASHOPTIM_ERR_NUMEL_RANGE;
     std::lock_guard<std::mutex> lock(g_mu);
     Plan* plan = find_plan(tag, hash, list);

@@ -128,6 +128,7 @@ struct CopyArgs {
     uint32_t coarse_shift;
     uint32_t n_segs;
     uint32_t n_pieces;
+    uint32_t piece_offset;      // index of this launch's workgroup 0
     // the blob's header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst; it sets *flag
     // (pinned) to seq when it has read the slot
     uint32_t header_n16;
@@ -157,7 +158,7 @@ constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per comp
 // they are there
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
                        uint32_t* flag, uint32_t seq, hipStream_t s);
-hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
+hipError_t launch_copy(CopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
 // The same from a pinned slot, by one workgroup that sets *flag (pinned) to seq when it has read the slot.

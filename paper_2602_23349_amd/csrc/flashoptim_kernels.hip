@@ -1957,18 +1957,19 @@ __device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
 // header_dst.
 constexpr int kCopyThreads = kCopyPiece / 16;
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
-    if (blockIdx.x == a.n_pieces) {
+    const uint32_t b = blockIdx.x + a.piece_offset;
+    if (b == a.n_pieces) {
         for (uint32_t i = threadIdx.x; i < a.header_n16; i += kCopyThreads) a.header_dst[i] = a.header[i];
         release_slot(a.flag, a.seq);
         return;
     }
-    uint32_t t = a.coarse[blockIdx.x >> a.coarse_shift];
+    uint32_t t = a.coarse[b >> a.coarse_shift];
     CopySegment sg = a.segs[t];
-    while (blockIdx.x - sg.first_piece >= sg.n_pieces && t + 1 < a.n_segs) {
+    while (b - sg.first_piece >= sg.n_pieces && t + 1 < a.n_segs) {
         ++t;
         sg = a.segs[t];
     }
-    const int64_t o = (int64_t)(blockIdx.x - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
+    const int64_t o = (int64_t)(b - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
     if (o + 16 <= sg.bytes) {
         const uint4 v = ld128(sg.src + o);
         st128(sg.dst + o, v.x, v.y, v.z, v.w);
@@ -1977,11 +1978,17 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     }
 }
 
-// (Issuing the copy as several shorter launches, which helps the step kernels, changed its rate by
-// less than 2 %: it stays one launch.)
-hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(copy_kernel, dim3(a.n_pieces + (a.header ? 1u : 0u)), dim3(kCopyThreads), 0, s, a);
-    return hipGetLastError();
+// Consecutive launches of as many pieces as one may have: 2^22 - 1, or 64 GiB.
+hipError_t launch_copy(CopyArgs a, hipStream_t s) {
+    const int64_t total = (int64_t)a.n_pieces + (a.header ? 1 : 0);
+    for (int64_t first = 0, n; first < total; first += n) {
+        n = launch_span(total, first, kCopyThreads);
+        a.piece_offset = (uint32_t)first;
+        hipLaunchKernelGGL(copy_kernel, dim3((unsigned)n), dim3(kCopyThreads), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Small transfers between pinned host memory and device memory by a kernel instead of a copy command (16-byte

@@ -22,5 +22,13 @@ constexpr uint32_t coarse_shift(int64_t total) {
     return shift;
 }
 
+// A HIP launch must stay below 2^32 work-items (gridDim.x * blockDim.x), so work of more workgroups goes out as
+// consecutive launches: of `total` workgroups of `threads` lanes each, those from `first` on that go with one launch.
+constexpr int64_t kMaxWorkItems = ((int64_t)1 << 32) - 1;
+constexpr int64_t launch_span(int64_t total, int64_t first, int threads) {
+    const int64_t most = kMaxWorkItems / threads;
+    return total - first < most ? total - first : most;
+}
+
 }  // namespace fo
 #endif

@@ -431,6 +431,45 @@ def test_checkpoint_at_the_edges_of_a_piece(kind, sizes):
                                             y.view(torch.int16 if y.element_size() == 2 else y.dtype)), (f.numel, k)
 
 
+def test_checkpoint_of_more_than_one_launch():
+    # above 64 GiB a copy no longer fits into one launch; sections of both launches, and the one that is cut, are compared
+    sizes = [1000, 17_000_000_000 // 64 * 64, 70_001]          # 4.0625 bytes each: 69 GB, and as much for the blob
+    if torch.cuda.mem_get_info()[0] < 160e9:
+        pytest.skip("needs 160 GB of free device memory")
+    bufs = [fo.ParamBuffers(n, "sgd", with_grad=False) for n in sizes]
+    arrays = [[b.param, b.rho, b.m_q, b.m_scale] for b in bufs]
+    as_bytes = [[x.view(torch.uint8) for x in row] for row in arrays]
+    for row in as_bytes:
+        for x in row:
+            for part in x.split(1 << 30):
+                (part.view(torch.int64) if part.numel() % 8 == 0 else part).random_()
+    blob = torch.empty(fo.checkpoint_size("sgd", sizes), dtype=torch.uint8, device="cuda")
+    assert blob.numel() > 64 << 30
+
+    def sections_equal():
+        off = 64 + 64
+        for row in as_bytes:
+            for x in row:
+                for at in range(0, x.numel(), 1 << 30):
+                    part = x[at:at + (1 << 30)]
+                    assert torch.equal(part, blob[off + at:off + at + part.numel()]), (x.numel(), at)
+                pad = -x.numel() % 64
+                assert not blob[off + x.numel():off + x.numel() + pad].any()
+                off += x.numel() + pad
+        assert off == blob.numel()
+
+    fo.checkpoint_pack("sgd", bufs, 12, blob)
+    sections_equal()
+    for row in as_bytes:
+        for x in row:
+            x.zero_()
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 12
+    sections_equal()
+    del bufs, arrays, as_bytes, blob, row, x
+    fo.release_cache()
+    torch.cuda.empty_cache()
+
+
 def test_hyperparameters_and_gradient_buffers_may_change_between_steps():
     # lr follows a schedule, weight decay toggles, and gradients arrive in different buffers: the cached
     # device table of the list must follow (it is re-uploaded in stream order when its content changes)

@@ -1,5 +1,5 @@
 """The host arithmetic of the launches (csrc/flashoptim_launch.h), compiled into a small program: table sizes at their
-limits, without a GPU."""
+limits and the cutting of work into launches, without a GPU."""
 import os
 import shutil
 import subprocess
@@ -32,3 +32,21 @@ def test_coarse_tables_never_exceed_their_entries(tmp_path):
         assert t == total and entries <= 16384, line
         assert (entries - 1) << shift < total <= entries << shift, line          # every workgroup has its entry
         assert shift == 0 or -(-total // (1 << (shift - 1))) > 16384, line        # no coarser than needed
+
+
+@pytest.mark.parametrize("threads", [64, 256, 512, 1024])
+def test_launches_stay_below_the_work_item_limit_and_cover_every_workgroup(tmp_path, threads):
+    # the checkpoint copy (1024 lanes per 16 KB piece, the header's workgroup behind the last one) reaches the limit of
+    # one launch, 2^32 - 1 work-items, at 64 GiB: 2^22 - 1 pieces fit, with the header's workgroup 2^22 - 2
+    most = (2**32 - 1) // threads
+    totals = [0, 1, most - 1, most, most + 1, most + 2, 2 * most, 2 * most + 1, 5 * most + 7]
+    out = _run(tmp_path, "const long long totals[] = {" + ", ".join(f"{t}LL" for t in totals) + "};\n"
+               "for (long long t : totals) {\n"
+               f"    for (long long first = 0, n; first < t; first += n) {{ n = fo::launch_span(t, first, {threads}); "
+               "std::printf(\"%lld %lld \", first, n); }\n    std::printf(\"\\n\");\n}")
+    assert len(out) == len(totals)
+    for line, total in zip(out, totals):
+        spans = [int(x) for x in line.split()]
+        first, n = spans[::2], spans[1::2]
+        assert all(0 < k and k * threads < 2**32 for k in n), line
+        assert len(n) == -(-total // most) and sum(n) == total and first == [sum(n[:i]) for i in range(len(n))], line
