@@ -947,24 +947,21 @@ int flashoptim_decompress_state(int kind, const flashoptim_tensor_ex* tensors, i
 int flashoptim_split_weights(const float* theta, void* param_bf16, int8_t* rho, int64_t n, void* stream) {
     int rc = check_elementwise(theta, param_bf16, rho, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_split(8, theta, param_bf16, rho, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_split(8, theta, param_bf16, rho, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
 int flashoptim_reconstruct_weights(const void* param_bf16, const int8_t* rho, float* theta, int64_t n, void* stream) {
     int rc = check_elementwise(param_bf16, rho, theta, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_reconstruct(8, param_bf16, rho, theta, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_reconstruct(8, param_bf16, rho, theta, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
 int flashoptim_split_weights_i16(const float* theta, void* param_bf16, int16_t* rho, int64_t n, void* stream) {
     int rc = check_elementwise(theta, param_bf16, rho, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_split(16, theta, param_bf16, rho, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_split(16, theta, param_bf16, rho, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
@@ -972,8 +969,7 @@ int flashoptim_reconstruct_weights_i16(const void* param_bf16, const int16_t* rh
                                        void* stream) {
     int rc = check_elementwise(param_bf16, rho, theta, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_reconstruct(16, param_bf16, rho, theta, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_reconstruct(16, param_bf16, rho, theta, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
@@ -1016,32 +1012,28 @@ int flashoptim_reconstruction_sweep_ex(int correction_bits, int ulp_reading, uin
 int flashoptim_quantize_momentum(const float* m, int8_t* q, uint16_t* scale, int64_t n, void* stream) {
     int rc = check_elementwise(m, q, scale, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_quantize(false, false, m, q, scale, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_quantize(false, false, m, q, scale, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
 int flashoptim_dequantize_momentum(const int8_t* q, const uint16_t* scale, float* m, int64_t n, void* stream) {
     int rc = check_elementwise(q, scale, m, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_dequantize(false, false, q, scale, m, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_dequantize(false, false, q, scale, m, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
 int flashoptim_quantize_variance(const float* v, uint8_t* q, uint16_t* scale, int64_t n, void* stream) {
     int rc = check_elementwise(v, q, scale, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_quantize(true, false, v, q, scale, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_quantize(true, false, v, q, scale, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
 int flashoptim_dequantize_variance(const uint8_t* q, const uint16_t* scale, float* v, int64_t n, void* stream) {
     int rc = check_elementwise(q, scale, v, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_dequantize(true, false, q, scale, v, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_dequantize(true, false, q, scale, v, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
@@ -1050,8 +1042,7 @@ int flashoptim_quantize_state(int state, int linear, const float* x, void* q, ui
     if (state < 0 || state > 1 || linear < 0 || linear > 1) return FLASHOPTIM_ERR_INVALID_ARG;
     int rc = check_elementwise(x, q, scale, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_quantize(state == 1, linear == 1, x, q, scale, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_quantize(state == 1, linear == 1, x, q, scale, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 
@@ -1060,8 +1051,7 @@ int flashoptim_dequantize_state(int state, int linear, const void* q, const uint
     if (state < 0 || state > 1 || linear < 0 || linear > 1) return FLASHOPTIM_ERR_INVALID_ARG;
     int rc = check_elementwise(q, scale, x, n);
     if (rc != FLASHOPTIM_OK || n == 0) return rc;
-    fo::launch_dequantize(state == 1, linear == 1, q, scale, x, n, static_cast<hipStream_t>(stream));
-    FO_HIP(hipGetLastError());
+    FO_HIP(fo::launch_dequantize(state == 1, linear == 1, q, scale, x, n, static_cast<hipStream_t>(stream)));
     return FLASHOPTIM_OK;
 }
 

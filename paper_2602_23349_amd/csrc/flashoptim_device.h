@@ -143,16 +143,16 @@ hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small
 constexpr int kConvChunkElems = 1024;   // elements per workgroup of the layout-conversion kernel: one pass of its lanes
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);
 hipError_t launch_probe(int kind, bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s);
-void launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s);
-void launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s);
+hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s);
+hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s);
 constexpr int kSweepStats = 8 + 3 * 256;
 hipError_t launch_clock_monitor(unsigned long long* samples, int n_samples, unsigned long long ticks_per_sample,
                                 hipStream_t s);
 hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t stride, uint64_t count, double* stats,
                         hipStream_t s);
-void launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s);
-void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
-                       hipStream_t s);
+hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s);
+hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
+                             hipStream_t s);
 constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per compute unit
 // partial: device memory for kNmseMaxBlocks pairs; sums: two doubles of pinned memory; *flag (pinned) becomes seq once
 // they are there

@@ -55,6 +55,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "flashoptim_device.h"
 
 namespace fo {
@@ -1604,23 +1606,45 @@ __global__ __launch_bounds__(kTotalThreads) void nmse_total_kernel(const double2
     }
 }
 
-static inline unsigned tiles_for(int64_t n) { return (unsigned)((n + kCodecTile - 1) / kCodecTile); }
+// launch(blocks, first, n) for every launch that the tiles of n elements take: the n elements from `first` on.  (One
+// launch holds 2^24 - 1 tiles, 2^35 elements less a tile.)
+template <typename F>
+static hipError_t for_each_launch(int64_t n, F launch) {
+    const int64_t tiles = (n + kCodecTile - 1) / kCodecTile;
+    for (int64_t t = 0, k; t < tiles; t += k) {
+        k = launch_span(tiles, t, kThreads);
+        const int64_t first = t * kCodecTile, left = n - first;
+        launch(dim3((unsigned)k), first, left < k * kCodecTile ? left : k * kCodecTile);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 static inline unsigned nmse_blocks(int64_t n) {
     const int64_t tiles = (n + kCodecTile - 1) / kCodecTile;
     return (unsigned)(tiles < kNmseMaxBlocks ? tiles : kNmseMaxBlocks);
 }
 
-void launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
-    if (bits == 8) hipLaunchKernelGGL((split_kernel<127, int8_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s, theta,
-                                      (uint16_t*)param, (int8_t*)rho, n);
-    else hipLaunchKernelGGL((split_kernel<32767, int16_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s, theta,
-                            (uint16_t*)param, (int16_t*)rho, n);
+template <int N, typename RHO>
+static hipError_t launch_split_n(const float* theta, uint16_t* param, RHO* rho, int64_t n, hipStream_t s) {
+    return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+        hipLaunchKernelGGL((split_kernel<N, RHO>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
+    });
 }
-void launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s) {
-    if (bits == 8) hipLaunchKernelGGL((reconstruct_kernel<127, int8_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
-                                      (const uint16_t*)param, (const int8_t*)rho, theta, n);
-    else hipLaunchKernelGGL((reconstruct_kernel<32767, int16_t>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
-                            (const uint16_t*)param, (const int16_t*)rho, theta, n);
+hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
+    return bits == 8 ? launch_split_n<127>(theta, (uint16_t*)param, (int8_t*)rho, n, s)
+                     : launch_split_n<32767>(theta, (uint16_t*)param, (int16_t*)rho, n, s);
+}
+template <int N, typename RHO>
+static hipError_t launch_reconstruct_n(const uint16_t* param, const RHO* rho, float* theta, int64_t n, hipStream_t s) {
+    return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+        hipLaunchKernelGGL((reconstruct_kernel<N, RHO>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at,
+                           count);
+    });
+}
+hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s) {
+    return bits == 8 ? launch_reconstruct_n<127>((const uint16_t*)param, (const int8_t*)rho, theta, n, s)
+                     : launch_reconstruct_n<32767>((const uint16_t*)param, (const int16_t*)rho, theta, n, s);
 }
 hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t stride, uint64_t count, double* stats,
                         hipStream_t s) {
@@ -1632,37 +1656,38 @@ hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t str
 #undef FO_SWEEP
     return hipGetLastError();
 }
-template <bool VARIANCE, bool LINEAR>
-static void launch_codec(int op, const void* in, const uint16_t* scale_in, void* out, uint16_t* scale_out, int64_t n,
-                         double2* partial, hipStream_t s) {
-    if (op == 0) hipLaunchKernelGGL((quantize_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
-                                    (const float*)in, (uint8_t*)out, scale_out, n);
-    else if (op == 1) hipLaunchKernelGGL((dequantize_kernel<VARIANCE, LINEAR>), dim3(tiles_for(n)), dim3(kThreads), 0, s,
-                                         (const uint8_t*)in, scale_in, (float*)out, n);
-    else hipLaunchKernelGGL((nmse_kernel<VARIANCE, LINEAR>), dim3(nmse_blocks(n)), dim3(kThreads), 0, s, (const float*)in,
-                            n, partial);
+// Calls f(VARIANCE, LINEAR) with the two choices as compile-time constants (std::integral_constant).
+template <typename F>
+static hipError_t dispatch_codec(bool variance, bool linear, F f) {
+    typedef std::true_type yes;
+    typedef std::false_type no;
+    if (variance) return linear ? f(yes(), yes()) : f(yes(), no());
+    return linear ? f(no(), yes()) : f(no(), no());
 }
-static void dispatch_codec(bool variance, bool linear, int op, const void* in, const uint16_t* scale_in, void* out,
-                           uint16_t* scale_out, int64_t n, double2* partial, hipStream_t s) {
-    if (variance) {
-        if (linear) launch_codec<true, true>(op, in, scale_in, out, scale_out, n, partial, s);
-        else launch_codec<true, false>(op, in, scale_in, out, scale_out, n, partial, s);
-    } else {
-        if (linear) launch_codec<false, true>(op, in, scale_in, out, scale_out, n, partial, s);
-        else launch_codec<false, false>(op, in, scale_in, out, scale_out, n, partial, s);
-    }
+hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
+    return dispatch_codec(variance, linear, [=](auto V, auto L) {
+        return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+            hipLaunchKernelGGL((quantize_kernel<decltype(V)::value, decltype(L)::value>), blocks, dim3(kThreads), 0, s, x + at,
+                               (uint8_t*)q + at, scale + at / kGroup, count);
+        });
+    });
 }
-void launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
-    dispatch_codec(variance, linear, 0, x, nullptr, q, scale, n, nullptr, s);
-}
-void launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
-                       hipStream_t s) {
-    dispatch_codec(variance, linear, 1, q, scale, x, nullptr, n, nullptr, s);
+hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
+                             hipStream_t s) {
+    return dispatch_codec(variance, linear, [=](auto V, auto L) {
+        return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+            hipLaunchKernelGGL((dequantize_kernel<decltype(V)::value, decltype(L)::value>), blocks, dim3(kThreads), 0, s,
+                               (const uint8_t*)q + at, scale + at / kGroup, x + at, count);
+        });
+    });
 }
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
                        uint32_t* flag, uint32_t seq, hipStream_t s) {
-    dispatch_codec(variance, linear, 2, x, nullptr, nullptr, nullptr, n, partial, s);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = dispatch_codec(variance, linear, [=](auto V, auto L) {
+        hipLaunchKernelGGL((nmse_kernel<decltype(V)::value, decltype(L)::value>), dim3(nmse_blocks(n)), dim3(kThreads), 0, s,
+                           x, n, partial);
+        return hipGetLastError();
+    });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kTotalThreads), 0, s, partial, (int)nmse_blocks(n), sums, flag,
                        seq);

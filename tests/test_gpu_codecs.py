@@ -213,3 +213,38 @@ def test_empty_inputs_are_noops():
     fo.split_weights(e32, torch.empty(0, dtype=torch.bfloat16, device="cuda"), torch.empty(0, dtype=torch.int8, device="cuda"))
     fo.quantize_momentum(e32, torch.empty(0, dtype=torch.int8, device="cuda"), torch.empty(0, dtype=torch.float16, device="cuda"))
     torch.cuda.synchronize()
+
+
+def test_codec_of_more_than_one_launch():
+    # 2^35 - 2048 elements fill one launch (2^24 - 1 workgroups of 256 lanes): the momentum codes and scales on both sides
+    # of that element, at the ragged end and at the start against the same call on a copy of the part
+    n = (1 << 35) + 3 * 2048 + 33
+    if torch.cuda.mem_get_info()[0] < 200e9:
+        pytest.skip("needs 200 GB of free device memory")
+    limit, part = (1 << 35) - 2048, 1 << 20
+    x = torch.zeros(n, device="cuda")
+    q = torch.full((n,), 99, dtype=torch.int8, device="cuda")
+    scale = torch.full(((n + 31) // 32,), 3.0, dtype=torch.float16, device="cuda")
+    places = [(0, part), (limit - part, part), (limit, n - limit)]
+    for at, count in places:
+        x[at:at + count].normal_()
+    fo.quantize_momentum(x, q, scale)
+    for at, count in places:
+        want_q = torch.empty(count, dtype=torch.int8, device="cuda")
+        want_s = torch.empty((count + 31) // 32, dtype=torch.float16, device="cuda")
+        fo.quantize_momentum(x[at:at + count].clone(), want_q, want_s)
+        assert want_q.any() and torch.equal(q[at:at + count], want_q), at
+        assert torch.equal(scale[at // 32:at // 32 + want_s.numel()].view(torch.int16), want_s.view(torch.int16)), at
+    for at in range(part, limit - part, 1 << 30):
+        end = min(at + (1 << 30), limit - part)
+        assert not q[at:end].any() and not scale[at // 32:end // 32].any(), at
+    y = torch.zeros(n - (limit - part), device="cuda")       # and back, the last part through a call of its own
+    del x
+    back = torch.full((n,), 5.0, device="cuda")
+    fo.dequantize_momentum(q, scale, back)
+    fo.dequantize_momentum(q[limit - part:].clone(), scale[(limit - part) // 32:].clone(), y)
+    assert torch.equal(back[limit - part:], y)
+    for at in range(part, limit - part, 1 << 30):
+        assert not back[at:min(at + (1 << 30), limit - part)].any(), at
+    del q, scale, back, y
+    torch.cuda.empty_cache()
