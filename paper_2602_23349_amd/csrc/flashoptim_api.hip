@@ -46,7 +46,6 @@ thread_local int g_last_hip_error = 0;
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int64_t n_groups(int64_t n) { return (n + fo::kGroup - 1) / fo::kGroup; }
-inline size_t round16(size_t x) { return (x + 15) & ~(size_t)15; }
 inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 
 // ----------------------------------------------------- cached device tables --
@@ -95,14 +94,15 @@ struct Plan {
     PlanTag tag = {};
     uint64_t hash = 0;
     std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
-    void* d_mem = nullptr;         // one allocation: the table, then the index
+    void* d_mem = nullptr;         // one allocation: the table, the index, the header
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
+    void* d_header = nullptr;      // packing only: the blob's header and table, all but the step
     // Pinned memory (coherent whatever the environment's default is: the flags are watched while kernels run), one
-    // allocation: the slots' flags, the source of the first upload of both tables (kept until the plan is freed), and
-    // kRingSlots slots of slot_bytes through which later tables and headers reach the device.  The kernel that reads
+    // allocation: the slots' flags, the source of the first upload of d_mem (kept until the plan is freed), and
+    // kRingSlots slots of slot_bytes through which later tables reach the device.  The kernel that reads
     // slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
     uint8_t* h_mem = nullptr;
     uint8_t* h_slots = nullptr;
@@ -179,31 +179,43 @@ Plan* find_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>&
     return nullptr;
 }
 
-// Makes the plan of a list that has none.  Both tables are copied to pinned memory of the plan and uploaded in stream
+// What a plan puts on the device.
+struct PlanSource {
+    const void* table;
+    size_t table_bytes;
+    const std::vector<uint32_t>& index;
+    const std::vector<uint8_t>& header;
+};
+
+// Makes the plan of a list that has none.  The tables are copied to pinned memory of the plan and uploaded in stream
 // order on `stream`, ahead of the launch that the creating call enqueues there (later calls with the same list touch
 // the same tensors, so the caller orders them after this one like any other work on those tensors).  Nothing here
 // waits for the stream.  slot_bytes: the most that stage() is asked to hold.
-int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors, const void* table,
-              size_t table_bytes, const void* index, size_t index_bytes, size_t slot_bytes, int64_t n_chunks,
-              hipStream_t stream, Plan** out) {
+int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors, const PlanSource& src,
+              size_t slot_bytes, int64_t n_chunks, hipStream_t stream, Plan** out) {
     Plan p;
     p.tag = tag;
     p.hash = hash;
     p.tensors = tensors;
     p.n_chunks = n_chunks;
     p.slot_bytes = (size_t)align64((int64_t)slot_bytes);
-    const size_t index_at = (size_t)align64((int64_t)table_bytes), both = index_at + round16(index_bytes);
-    const size_t source_at = kRingSlots * kFlagStride, slots_at = source_at + (size_t)align64((int64_t)both);
-    hipError_t e = hipMalloc(&p.d_mem, both > 0 ? both : 16);
+    const size_t index_bytes = src.index.size() * sizeof(uint32_t);
+    const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
+    const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
+    const size_t all = header_at + (size_t)align64((int64_t)src.header.size());
+    const size_t source_at = kRingSlots * kFlagStride, slots_at = source_at + all;
+    hipError_t e = hipMalloc(&p.d_mem, all > 0 ? all : 16);
     if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, slots_at + kRingSlots * p.slot_bytes, hipHostMallocCoherent);
     if (e == hipSuccess) {
         p.d_table = p.d_mem;
         p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
+        p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
         p.h_slots = p.h_mem + slots_at;
-        std::memset(p.h_mem, 0, source_at);
-        if (table_bytes) std::memcpy(p.h_mem + source_at, table, table_bytes);
-        if (index_bytes) std::memcpy(p.h_mem + source_at + index_at, index, index_bytes);
-        if (both) e = fo::launch_move(p.h_mem + source_at, p.d_mem, both, stream);
+        std::memset(p.h_mem, 0, slots_at);
+        if (src.table_bytes) std::memcpy(p.h_mem + source_at, src.table, src.table_bytes);
+        if (index_bytes) std::memcpy(p.h_mem + source_at + index_at, src.index.data(), index_bytes);
+        if (!src.header.empty()) std::memcpy(p.h_mem + source_at + header_at, src.header.data(), src.header.size());
+        if (all) e = fo::launch_move(p.h_mem + source_at, p.d_mem, all, stream);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -399,8 +411,8 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
             coarse[j] = (uint32_t)ti;
         }
         const size_t bytes = live.size() * sizeof(TensorDev);
-        rc = make_plan(tag, hash, live, live.data(), bytes, coarse.data(), coarse.size() * sizeof(uint32_t), bytes,
-                       total_chunks, stream, &plan);
+        const std::vector<uint8_t> no_header;
+        rc = make_plan(tag, hash, live, {live.data(), bytes, coarse, no_header}, bytes, total_chunks, stream, &plan);
     }
     if (rc != FLASHOPTIM_OK) return rc;
     a.tensors = static_cast<const TensorDev*>(plan->d_table);
@@ -584,12 +596,14 @@ void put_i64(uint8_t* p, int64_t v) { for (int i = 0; i < 8; ++i) p[i] = (uint8_
 void put_u32(uint8_t* p, uint32_t v) { for (int i = 0; i < 4; ++i) p[i] = (uint8_t)(v >> (8 * i)); }
 int64_t get_i64(const uint8_t* p) { uint64_t v = 0; for (int i = 0; i < 8; ++i) v |= (uint64_t)p[i] << (8 * i); return (int64_t)v; }
 
+int64_t header_size(int64_t n) { return 64 + align64(16 * n); }
+
 std::vector<uint8_t> build_header(int kind, const flashoptim_tensor* t, int64_t n, int64_t step, int64_t total) {
-    std::vector<uint8_t> h((size_t)(64 + align64(16 * n)), 0);
+    std::vector<uint8_t> h((size_t)header_size(n), 0);
     std::memcpy(h.data(), kMagic, 8);
     put_u32(h.data() + 8, 1u);
     put_u32(h.data() + 12, (uint32_t)kind);
-    put_i64(h.data() + 16, step);
+    put_i64(h.data() + fo::kHeaderStepAt, step);
     put_i64(h.data() + 24, n);
     put_i64(h.data() + 32, total);
     int64_t off = (int64_t)h.size();
@@ -604,7 +618,7 @@ std::vector<uint8_t> build_header(int kind, const flashoptim_tensor* t, int64_t 
 // Segments (one per section per tensor) between the tensors' buffers and the blob.
 void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack,
                     std::vector<CopySegment>& segs) {
-    int64_t off = 64 + align64(16 * n);
+    int64_t off = header_size(n);
     auto add = [&](const void* tensor_buf, int64_t bytes) {
         if (bytes > 0) {
             CopySegment s;
@@ -623,10 +637,11 @@ void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* bl
     }
 }
 
-// Copies between the list's buffers and the blob.  header (pack only): `header_bytes` of host memory that go to the
-// blob's start in stream order, with the copy.
-int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, const void* header,
-             size_t header_bytes, hipStream_t stream) {
+// Copies between the list's buffers and the blob.  When packing, the blob's header and table go with the copy: they
+// follow from the list but for the step, so the plan holds them on the device and the step is an argument of the kernel.
+// Nothing is staged per call: calls behind any amount of earlier work never wait, and a captured one can be replayed.
+int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, int64_t total_bytes, int64_t step,
+             hipStream_t stream) {
     // the identity: every tensor, those without elements included (they lengthen the header and move the sections)
     std::vector<TensorDev> list;
     list.reserve((size_t)n);
@@ -663,17 +678,13 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
             while ((int64_t)segs[si].first_piece + segs[si].n_pieces <= b) ++si;
             coarse[j] = (uint32_t)si;
         }
-        const int rc = make_plan(tag, hash, list, segs.data(), segs.size() * sizeof(CopySegment), coarse.data(),
-                                 coarse.size() * sizeof(uint32_t), header_bytes, n_pieces, stream, &plan);
+        std::vector<uint8_t> header;
+        if (pack) header = build_header(kind, t, n, 0, total_bytes);
+        const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header}, 0,
+                                 n_pieces, stream, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
         plan->n_segs = (uint32_t)segs.size();
         plan->coarse_shift = shift;
-    }
-    void* slot = nullptr;
-    uint32_t *flag = nullptr, seq = 0;
-    if (header) {
-        const int rc = stage(*plan, header, header_bytes, &slot, &flag, &seq);
-        if (rc != FLASHOPTIM_OK) return rc;
     }
     fo::CopyArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -682,13 +693,13 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
     a.coarse_shift = plan->coarse_shift;
     a.n_segs = plan->n_segs;
     a.n_pieces = (uint32_t)plan->n_chunks;
-    a.header_n16 = (uint32_t)(header_bytes / 16);
-    a.header = static_cast<const uint4*>(slot);
-    a.header_dst = reinterpret_cast<uint4*>(blob);
-    a.flag = flag;
-    a.seq = seq;
+    if (pack) {
+        a.header = static_cast<const uint4*>(plan->d_header);
+        a.header_n16 = (uint32_t)(header_size(n) / 16);
+        a.header_dst = reinterpret_cast<uint4*>(blob);
+        a.step = step;
+    }
     FO_HIP(fo::launch_copy(a, stream));
-    if (slot) mark_in_flight(*plan);
     return FLASHOPTIM_OK;
 }
 
@@ -1076,7 +1087,7 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
 
 int64_t flashoptim_checkpoint_size(int kind, const int64_t* numels, int64_t n_tensors) {
     if (kind < 0 || kind > 2 || n_tensors < 0 || (n_tensors > 0 && !numels)) return FLASHOPTIM_ERR_INVALID_ARG;
-    int64_t total = 64 + align64(16 * n_tensors);
+    int64_t total = header_size(n_tensors);
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (numels[i] < 0 || numels[i] >= kMaxNumel) return FLASHOPTIM_ERR_NUMEL_RANGE;
         total += tensor_payload(numels[i], kind);
@@ -1099,11 +1110,9 @@ int flashoptim_checkpoint_pack(int kind, const flashoptim_tensor* tensors, int64
     const int64_t total = list_size(kind, tensors, n_tensors);
     if (total < 0) return (int)total;
     if (blob_bytes < total) return FLASHOPTIM_ERR_BAD_BLOB;
-    hipStream_t stream = static_cast<hipStream_t>(stream_);
-    // header and table: staged in pinned memory and copied in stream order, like the sections themselves
-    // (the blob may still be in use by earlier work on the stream); the call does not wait
-    const std::vector<uint8_t> header = build_header(kind, tensors, n_tensors, step, total);
-    return run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(blob), true, header.data(), header.size(), stream);
+    // (header and table reach the blob in stream order, like the sections: earlier work may still be using it)
+    return run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(blob), true, total, step,
+                    static_cast<hipStream_t>(stream_));
 }
 
 int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes, const flashoptim_tensor* tensors,
@@ -1126,10 +1135,10 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     const uint8_t* got = static_cast<const uint8_t*>(w.host);
     const bool match = std::memcmp(got, want.data(), 16) == 0 &&
                        std::memcmp(got + 24, want.data() + 24, want.size() - 24) == 0;
-    const int64_t step = get_i64(got + 16);
+    const int64_t step = get_i64(got + fo::kHeaderStepAt);
     give_space(w);
     if (!match) return FLASHOPTIM_ERR_BAD_BLOB;
-    rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, nullptr, 0, stream);
+    rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, total, 0, stream);
     if (rc != FLASHOPTIM_OK) return rc;
     *step_out = step;
     return FLASHOPTIM_OK;

@@ -50,6 +50,7 @@ constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
     return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);
 }
 constexpr int kCopyPiece = 16 * 1024;        // checkpoint copy: bytes per workgroup
+constexpr int kHeaderStepAt = 16;            // byte offset of the step (little-endian int64) in a blob's header
 
 // One tensor as the kernels see it (device pointers), 104 bytes.
 struct TensorDev {
@@ -129,13 +130,12 @@ struct CopyArgs {
     uint32_t n_segs;
     uint32_t n_pieces;
     uint32_t piece_offset;      // index of this launch's workgroup 0
-    // the blob's header: a pinned slot (nullptr: none) that one further workgroup writes to header_dst; it sets *flag
-    // (pinned) to seq when it has read the slot
-    uint32_t header_n16;
+    // packing: the blob's header and table (nullptr: none), which one further workgroup writes to header_dst with `step`
+    // in its place
     const uint4* header;
     uint4* header_dst;
-    uint32_t* flag;
-    uint32_t seq;
+    uint32_t header_n16;
+    int64_t step;
 };
 
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,

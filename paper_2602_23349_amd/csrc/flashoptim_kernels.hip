@@ -1961,13 +1961,6 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 
 // ----------------------------------------------------------- checkpoint copy --
 //
-// Tells the host that a workgroup has read all of a slot of pinned memory.  Called by every lane of the workgroup after
-// its last use of the values it read (its loads have returned by then); the word itself carries no other data.
-__device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Gather / scatter of byte segments: each workgroup copies one piece of one segment, 16 bytes per lane (segment starts
 // are 16-byte aligned on both sides), the ragged end byte by byte, and - when packing - zero-fills the padding up to
 // pad_bytes.  Bound: HBM.
@@ -1978,14 +1971,20 @@ __device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
 // 2520, 6.1 TB/s).  Pieces are found as the step kernels find their tiles, through a coarse table and the segments
 // themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
 //
-// header: the blob's header and table when packing, in a pinned slot; the workgroup behind the last piece writes it to
-// header_dst.
+// header: the blob's header and table when packing; the workgroup behind the last piece writes them to header_dst.
 constexpr int kCopyThreads = kCopyPiece / 16;
+static_assert(kHeaderStepAt % 16 == 0, "the step is the low half of one 16-byte access");
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     const uint32_t b = blockIdx.x + a.piece_offset;
     if (b == a.n_pieces) {
-        for (uint32_t i = threadIdx.x; i < a.header_n16; i += kCopyThreads) a.header_dst[i] = a.header[i];
-        release_slot(a.flag, a.seq);
+        for (uint32_t i = threadIdx.x; i < a.header_n16; i += kCopyThreads) {
+            uint4 v = a.header[i];
+            if (i == kHeaderStepAt / 16) {
+                v.x = (uint32_t)a.step;
+                v.y = (uint32_t)(a.step >> 32);
+            }
+            a.header_dst[i] = v;
+        }
         return;
     }
     uint32_t t = a.coarse[b >> a.coarse_shift];
@@ -2029,6 +2028,12 @@ hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s) 
     return hipGetLastError();
 }
 
+// Tells the host that a workgroup has read all of a slot of pinned memory.  Called by every lane of the workgroup after
+// its last use of the values it read (its loads have returned by then); the word itself carries no other data.
+__device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // One workgroup takes a descriptor table (104 bytes per tensor) from a pinned slot: four loads per lane in flight.
 constexpr int kUploadThreads = 1024;
 __global__ __launch_bounds__(kUploadThreads) void upload_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,

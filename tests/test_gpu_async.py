@@ -67,6 +67,30 @@ def test_checkpoint_pack_does_not_wait_for_the_stream():
         assert torch.equal(a.param.view(torch.int16), b.param.view(torch.int16)) and torch.equal(a.v_q, b.v_q)
 
 
+def test_checkpoint_packs_in_any_number_do_not_wait_for_the_stream():
+    # twelve packs behind one busy stream, each with its own step in the header; each blob is copied behind its pack
+    specs = W.odd_sizes()[:12]
+    bufs, states = _state(specs, seed=27)
+    size = fo.checkpoint_size("adamw", [s.numel for s in specs])
+    blob = torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda")
+    kept = torch.zeros((12, size), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("adamw", bufs, 1, blob)
+    kept[0].copy_(blob)
+    torch.cuda.synchronize()
+    mon = _busy_stream(0.4)
+    t0 = time.perf_counter()
+    with torch.cuda.stream(mon.stream):
+        for i in range(12):
+            fo.checkpoint_pack("adamw", bufs, 100 + i, blob, stream=mon.stream)
+            kept[i].copy_(blob)
+    dt = time.perf_counter() - t0
+    still_busy = not mon.stream.query()
+    mon.stream.synchronize()
+    assert still_busy and dt < 0.3, f"twelve packs took {dt:.3f} s on the host; stream busy afterwards: {still_busy}"
+    for i in range(12):
+        assert np.array_equal(kept[i].cpu().numpy(), oracle.checkpoint_pack("adamw", states, 100 + i)), i
+
+
 def test_descriptor_uploads_behind_a_busy_stream_keep_their_order():
     # every step uploads other learning rates through one of four pinned slots: four steps are enqueued without waiting,
     # further ones wait for a slot and never overwrite one that a kernel has still to read

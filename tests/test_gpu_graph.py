@@ -104,3 +104,28 @@ def test_captured_learning_rates_are_kept_and_later_calls_do_not_reach_them():
             rates(tl_ref, captured)
             fo.adamw_step_exact(tl_ref, B1, B2, EPS, 2)
             _assert_equal(ref, got, f"common={common} replay {replay}")
+
+
+def test_captured_pack_keeps_its_own_header():
+    specs = W.odd_sizes()[:9]
+    bufs, other = _twins(specs, seed=45)
+    size = fo.checkpoint_size("adamw", [sp.numel for sp in specs])
+    blob, want = (torch.zeros(size, dtype=torch.uint8, device="cuda") for _ in range(2))
+    steps = [7, -1, 1 << 40]
+    fo.checkpoint_pack("adamw", bufs, 1, blob)                 # the list's tables
+    torch.cuda.synchronize()
+    graphs = []
+    for step in steps:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            fo.checkpoint_pack("adamw", bufs, step, blob)
+    for replay in range(3):
+        for step, graph in zip(steps, graphs):
+            for i in range(5):                                 # eager packs of the same list into the same blob
+                fo.checkpoint_pack("adamw", bufs, 1000 + i, blob)
+            torch.cuda.synchronize()
+            graph.replay()
+            fo.checkpoint_pack("adamw", other, step, want)
+            torch.cuda.synchronize()
+            assert torch.equal(blob, want), (replay, step)
+            assert fo.checkpoint_unpack("adamw", blob, bufs) == step
