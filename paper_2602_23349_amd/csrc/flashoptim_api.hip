@@ -15,7 +15,6 @@
 #include <cstring>
 #include <list>
 #include <mutex>
-#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -53,9 +52,9 @@ inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 // A "plan" is what a multi-tensor launch needs on the device: the table of tensors (for copies, of
 // segments) and a coarse index table into it by workgroup.  It belongs to the list's identity (device, operation, every state pointer and
 // numel; NOT the gradient pointers or lr/wd, which legitimately change from step to step).
-// The tensor table is re-uploaded (104 B per tensor, through pinned staging, in stream
-// order) only when its content differs from what the device already holds; a learning rate that all
-// tensors share is not part of it.
+// What a later call on the same list may change (gradient pointer, rates, weight decay) is written into the
+// tensor table in stream order, from kernel arguments, only when it differs from what the device already holds; a
+// learning rate that all tensors share is not part of it.
 //
 // A call finds its plan through a 64-bit hash of the identity and then compares the descriptors themselves, so a
 // collision costs time and nothing else.  (With the identity as a string key, built and hashed byte by byte on
@@ -87,30 +86,18 @@ uint64_t identity_hash(const PlanTag& tag, const std::vector<TensorDev>& t) {
     return h ^ (h >> 32);
 }
 
-constexpr uint32_t kRingSlots = 4;
-constexpr size_t kFlagStride = 64;      // bytes: each slot's flag has a cache line of its own
-
 struct Plan {
     PlanTag tag = {};
     uint64_t hash = 0;
     std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
+    bool table_known = true;           // false: an update failed part of the way, so the table is written as a whole next
     void* d_mem = nullptr;         // one allocation: the table, the index, the header
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
     void* d_header = nullptr;      // packing only: the blob's header and table, all but the step
-    // Pinned memory (coherent whatever the environment's default is: the flags are watched while kernels run), one
-    // allocation: the slots' flags, the source of the first upload of d_mem (kept until the plan is freed), and
-    // kRingSlots slots of slot_bytes through which later tables reach the device.  The kernel that reads
-    // slot i sets flag i to the number of the upload (1, 2, ...) when it is done with it.
-    uint8_t* h_mem = nullptr;
-    uint8_t* h_slots = nullptr;
-    size_t slot_bytes = 0;
-    uint32_t n_uploads = 0;
-    uint32_t in_slot[kRingSlots] = {};     // number of the upload last put into each slot (0: none)
-
-    uint32_t* flag(uint32_t slot) const { return reinterpret_cast<uint32_t*>(h_mem + slot * kFlagStride); }
+    void* h_mem = nullptr;         // pinned source of d_mem's one upload, kept until the plan is freed
 };
 
 std::mutex g_mu;
@@ -129,39 +116,6 @@ void destroy_plan(Plan& p) {
     if (p.h_mem) (void)hipHostFree(p.h_mem);
     p.d_mem = nullptr; p.h_mem = nullptr;
     (void)hipSetDevice(cur);
-}
-
-// Puts `bytes` of `src` (host memory that the caller may reuse at once; at most slot_bytes) into one of the plan's
-// pinned slots, for a kernel that the caller then launches with *flag and *seq.  Never waits for the stream: a slot is
-// waited for only when the kernel that reads it, of kRingSlots uploads ago, has not run yet.
-int stage(Plan& p, const void* src, size_t bytes, void** slot, uint32_t** flag, uint32_t* seq) {
-    const uint32_t i = p.n_uploads % kRingSlots;
-    if (p.in_slot[i]) {
-        const volatile uint32_t* f = p.flag(i);
-        // (bounded: a kernel that was captured into a graph and has not been replayed, or that a failed stream dropped,
-        // never sets the flag, and a replay sets it back to the number it was captured with; once the device has drained
-        // nothing reads the slot)
-        const auto t0 = std::chrono::steady_clock::now();
-        for (uint32_t k = 0; *f != p.in_slot[i]; ++k) {
-            if (k < 1000) continue;
-            std::this_thread::yield();
-            if (std::chrono::steady_clock::now() - t0 < std::chrono::seconds(1)) continue;
-            FO_HIP(hipDeviceSynchronize());
-            break;
-        }
-        std::atomic_thread_fence(std::memory_order_acquire);
-        p.in_slot[i] = 0;
-    }
-    *slot = p.h_slots + i * p.slot_bytes;
-    std::memcpy(*slot, src, bytes);
-    *flag = p.flag(i);
-    *seq = p.n_uploads + 1;
-    return FLASHOPTIM_OK;
-}
-// The kernel that reads the slot of the last stage() call has been launched.
-void mark_in_flight(Plan& p) {
-    const uint32_t i = p.n_uploads % kRingSlots;
-    p.in_slot[i] = ++p.n_uploads;
 }
 
 // Finds the plan of a list and makes it the most recently used one; nullptr if there is none.
@@ -190,32 +144,31 @@ struct PlanSource {
 // Makes the plan of a list that has none.  The tables are copied to pinned memory of the plan and uploaded in stream
 // order on `stream`, ahead of the launch that the creating call enqueues there (later calls with the same list touch
 // the same tensors, so the caller orders them after this one like any other work on those tensors).  Nothing here
-// waits for the stream.  slot_bytes: the most that stage() is asked to hold.
+// waits for the stream.
 int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors, const PlanSource& src,
-              size_t slot_bytes, int64_t n_chunks, hipStream_t stream, Plan** out) {
+              int64_t n_chunks, hipStream_t stream, Plan** out) {
     Plan p;
     p.tag = tag;
     p.hash = hash;
     p.tensors = tensors;
     p.n_chunks = n_chunks;
-    p.slot_bytes = (size_t)align64((int64_t)slot_bytes);
     const size_t index_bytes = src.index.size() * sizeof(uint32_t);
     const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
     const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
     const size_t all = header_at + (size_t)align64((int64_t)src.header.size());
-    const size_t source_at = kRingSlots * kFlagStride, slots_at = source_at + all;
-    hipError_t e = hipMalloc(&p.d_mem, all > 0 ? all : 16);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p.h_mem, slots_at + kRingSlots * p.slot_bytes, hipHostMallocCoherent);
+    const size_t bytes = all > 0 ? all : 64;
+    hipError_t e = hipMalloc(&p.d_mem, bytes);
+    if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, bytes, hipHostMallocCoherent);
     if (e == hipSuccess) {
         p.d_table = p.d_mem;
         p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
         p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
-        p.h_slots = p.h_mem + slots_at;
-        std::memset(p.h_mem, 0, slots_at);
-        if (src.table_bytes) std::memcpy(p.h_mem + source_at, src.table, src.table_bytes);
-        if (index_bytes) std::memcpy(p.h_mem + source_at + index_at, src.index.data(), index_bytes);
-        if (!src.header.empty()) std::memcpy(p.h_mem + source_at + header_at, src.header.data(), src.header.size());
-        if (all) e = fo::launch_move(p.h_mem + source_at, p.d_mem, all, stream);
+        uint8_t* h = static_cast<uint8_t*>(p.h_mem);
+        std::memset(h, 0, bytes);
+        if (src.table_bytes) std::memcpy(h, src.table, src.table_bytes);
+        if (index_bytes) std::memcpy(h + index_at, src.index.data(), index_bytes);
+        if (!src.header.empty()) std::memcpy(h + header_at, src.header.data(), src.header.size());
+        if (all) e = fo::launch_move(p.h_mem, p.d_mem, all, stream);
     }
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -237,25 +190,46 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     return FLASHOPTIM_OK;
 }
 
-// Brings a step's table up to date in stream order if any descriptor has changed since its last upload.  Where the
-// launch carries the learning rate, the table keeps the rates it was last uploaded with: an earlier launch that was
-// captured into a graph may still read them.
+// Brings a step's table up to date in stream order if any descriptor has changed since its last update.  Where the
+// launch carries the learning rate, the table keeps the rates it was last given: an earlier launch that was captured
+// into a graph may still read them.  The new values travel as kernel arguments: no staging memory is involved, so
+// nothing is waited for however far the stream is behind, and a captured update writes the same values at every replay.
 int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr, hipStream_t stream) {
-    const size_t bytes = tensors.size() * sizeof(TensorDev);
-    if (std::memcmp(p.tensors.data(), tensors.data(), bytes) == 0) return FLASHOPTIM_OK;
-    if (ignore_lr) {
-        bool same = true;       // (the same list: what a call can change beside lr is the gradient and the weight decay)
-        for (size_t i = 0; i < tensors.size() && same; ++i)
-            same = p.tensors[i].grad == tensors[i].grad && std::memcmp(&p.tensors[i].wd, &tensors[i].wd, sizeof(float)) == 0;
-        if (same) return FLASHOPTIM_OK;
+    auto bits = [](float x) { uint32_t u; std::memcpy(&u, &x, sizeof(u)); return u; };
+    uint64_t grad = 0;          // bits that differ (the same list: what a call can change are these three)
+    uint32_t lr = 0, wd = 0;
+    const size_t n = tensors.size();
+    for (size_t i = 0; i < n; ++i) {
+        const TensorDev &x = p.tensors[i], &y = tensors[i];
+        grad |= (uint64_t)reinterpret_cast<uintptr_t>(x.grad) ^ (uint64_t)reinterpret_cast<uintptr_t>(y.grad);
+        lr |= bits(x.lr) ^ bits(y.lr);
+        wd |= bits(x.wd) ^ bits(y.wd);
     }
-    void* slot = nullptr;
-    uint32_t *flag = nullptr, seq = 0;
-    const int rc = stage(p, tensors.data(), bytes, &slot, &flag, &seq);
-    if (rc != FLASHOPTIM_OK) return rc;
-    FO_HIP(fo::launch_upload(slot, p.d_table, bytes, flag, seq, stream));
-    mark_in_flight(p);
-    p.tensors = tensors;
+    fo::TableUpdate u;
+    u.fields = (grad || !p.table_known ? fo::kUpdateGrad : 0) | ((lr && !ignore_lr) || !p.table_known ? fo::kUpdateLr : 0) |
+               (wd || !p.table_known ? fo::kUpdateWd : 0);
+    if (!u.fields) return FLASHOPTIM_OK;
+    const uint32_t most = fo::update_batch(u.fields);
+    p.table_known = false;      // until every launch has been accepted
+    for (size_t first = 0; first < n; first += u.count) {
+        u.first = (uint32_t)first;
+        u.count = n - first < most ? (uint32_t)(n - first) : most;
+        uint32_t* w = u.words;
+        for (size_t i = first; i < first + u.count; ++i) {
+            TensorDev& x = p.tensors[i];
+            const TensorDev& y = tensors[i];
+            if (u.fields & fo::kUpdateGrad) {
+                x.grad = y.grad;
+                const uint64_t g = (uint64_t)reinterpret_cast<uintptr_t>(y.grad);
+                *w++ = (uint32_t)g;
+                *w++ = (uint32_t)(g >> 32);
+            }
+            if (u.fields & fo::kUpdateLr) *w++ = bits(x.lr = y.lr);
+            if (u.fields & fo::kUpdateWd) *w++ = bits(x.wd = y.wd);
+        }
+        FO_HIP(fo::launch_table_update(u, static_cast<TensorDev*>(p.d_table), stream));
+    }
+    p.table_known = true;
     return FLASHOPTIM_OK;
 }
 
@@ -410,9 +384,9 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
             while ((int64_t)live[ti].first_tile + live[ti].n_tiles <= b) ++ti;
             coarse[j] = (uint32_t)ti;
         }
-        const size_t bytes = live.size() * sizeof(TensorDev);
         const std::vector<uint8_t> no_header;
-        rc = make_plan(tag, hash, live, {live.data(), bytes, coarse, no_header}, bytes, total_chunks, stream, &plan);
+        rc = make_plan(tag, hash, live, {live.data(), live.size() * sizeof(TensorDev), coarse, no_header},
+                       total_chunks, stream, &plan);
     }
     if (rc != FLASHOPTIM_OK) return rc;
     a.tensors = static_cast<const TensorDev*>(plan->d_table);
@@ -680,7 +654,7 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         }
         std::vector<uint8_t> header;
         if (pack) header = build_header(kind, t, n, 0, total_bytes);
-        const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header}, 0,
+        const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header},
                                  n_pieces, stream, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
         plan->n_segs = (uint32_t)segs.size();
@@ -727,6 +701,7 @@ struct CallSpace {
 
     uint32_t* flag() const { return reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(host) + host_bytes); }
 };
+constexpr size_t kFlagStride = 64;              // bytes: the flag has a cache line of its own
 std::mutex g_space_mu;
 constexpr int kMaxIdleSpaces = 16;              // 32 KB of device and at least 64 KB of pinned memory each; beyond that
 constexpr size_t kMinSpaceHost = 64 * 1024;     // a workspace is freed after its call, like one that had to be larger

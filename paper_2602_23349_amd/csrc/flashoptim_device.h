@@ -161,10 +161,21 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
 hipError_t launch_copy(CopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
-// The same from a pinned slot, by one workgroup that sets *flag (pinned) to seq when it has read the slot.
 // Device to pinned memory; *flag (pinned) becomes seq once all of it is there.
 hipError_t launch_fetch(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
-hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s);
+// New values for `count` entries of a step's table, from entry `first` on.  Only the fields of the entries that change
+// travel, in the order of the masks below, so that as many entries as possible go with one launch.
+enum : uint32_t { kUpdateGrad = 1, kUpdateLr = 2, kUpdateWd = 4 };
+constexpr uint32_t update_words(uint32_t fields) {
+    return ((fields & kUpdateGrad) ? 2 : 0) + ((fields & kUpdateLr) ? 1 : 0) + ((fields & kUpdateWd) ? 1 : 0);
+}
+struct TableUpdate {
+    uint32_t first, count, fields;
+    uint32_t words[960];        // update_words(fields) of them per entry
+};
+constexpr uint32_t update_batch(uint32_t fields) { return (uint32_t)(sizeof(TableUpdate::words) / 4) / update_words(fields); }
+static_assert(sizeof(TableUpdate) + 2 * sizeof(void*) <= 4096, "kernel arguments");
+hipError_t launch_table_update(const TableUpdate& u, TensorDev* table, hipStream_t s);
 constexpr int kSelftestSectionCount = 7;
 constexpr unsigned long long kSelftestSqrtValues = 0x7f800000ull - 0x0f800000ull;   // section 2: every FP32 value in [2^-96, FLT_MAX]
 constexpr int kSelftestCounters = 15;   // two per section, then the inexact count of section 6

@@ -2016,9 +2016,7 @@ hipError_t launch_copy(CopyArgs a, hipStream_t s) {
 }
 
 // Small transfers between pinned host memory and device memory by a kernel instead of a copy command (16-byte
-// multiples; bound by the link to the host).  A copy command and the event that marks its end cost the host 17 us and
-// the stream 6 us in front of a step whose descriptors changed; these kernels cost 8 and 3 (ResNet-50 list under a
-// learning-rate schedule: 75 us a step -> 60).
+// multiples; bound by the link to the host), which costs the host several times a launch.
 __global__ __launch_bounds__(256) void move_kernel(const uint4* src, uint4* dst, uint32_t n16) {
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n16; i += gridDim.x * 256u) dst[i] = src[i];
 }
@@ -2028,38 +2026,35 @@ hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s) 
     return hipGetLastError();
 }
 
-// Tells the host that a workgroup has read all of a slot of pinned memory.  Called by every lane of the workgroup after
-// its last use of the values it read (its loads have returned by then); the word itself carries no other data.
-__device__ __forceinline__ void release_slot(uint32_t* flag, uint32_t seq) {
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-// One workgroup takes a descriptor table (104 bytes per tensor) from a pinned slot: four loads per lane in flight.
-constexpr int kUploadThreads = 1024;
-__global__ __launch_bounds__(kUploadThreads) void upload_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,
-                                                                uint32_t seq) {
-    for (uint32_t i = threadIdx.x; i < n16; i += 4 * kUploadThreads) {
-        uint4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) if (i + k * kUploadThreads < n16) v[k] = src[i + k * kUploadThreads];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) if (i + k * kUploadThreads < n16) dst[i + k * kUploadThreads] = v[k];
+// Table entries from kernel arguments.  Against a pinned buffer that a kernel reads and reports as read, which the host
+// then has to wait for: ResNet-50 list with other rates in every step 58.3 -> 54.9 us a step, 9 us of them on the host.
+__global__ __launch_bounds__(256) void table_update_kernel(TableUpdate u, TensorDev* table) {
+    const uint32_t per = update_words(u.fields);
+    for (uint32_t i = threadIdx.x; i < u.count; i += 256) {
+        TensorDev& t = table[u.first + i];
+        uint32_t at = i * per;
+        if (u.fields & kUpdateGrad) {
+            t.grad = reinterpret_cast<const void*>(u.words[at] | (uint64_t)u.words[at + 1] << 32);
+            at += 2;
+        }
+        if (u.fields & kUpdateLr) t.lr = u2f(u.words[at++]);
+        if (u.fields & kUpdateWd) t.wd = u2f(u.words[at]);
     }
-    release_slot(flag, seq);
 }
-// The other way, for a host that waits for the flag.
-__global__ __launch_bounds__(kUploadThreads) void fetch_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,
-                                                               uint32_t seq) {
-    for (uint32_t i = threadIdx.x; i < n16; i += kUploadThreads) dst[i] = src[i];
+hipError_t launch_table_update(const TableUpdate& u, TensorDev* table, hipStream_t s) {
+    hipLaunchKernelGGL(table_update_kernel, dim3(1), dim3(256), 0, s, u, table);
+    return hipGetLastError();
+}
+
+// From device to pinned memory, for a host that waits for the flag.
+constexpr int kFetchThreads = 1024;
+__global__ __launch_bounds__(kFetchThreads) void fetch_kernel(const uint4* src, uint4* dst, uint32_t n16, uint32_t* flag,
+                                                              uint32_t seq) {
+    for (uint32_t i = threadIdx.x; i < n16; i += kFetchThreads) dst[i] = src[i];
     publish(flag, seq);
 }
 hipError_t launch_fetch(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
-    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kUploadThreads), 0, s, (const uint4*)src, (uint4*)dst,
-                       (uint32_t)((bytes + 15) / 16), flag, seq);
-    return hipGetLastError();
-}
-hipError_t launch_upload(const void* src, void* dst, size_t bytes, uint32_t* flag, uint32_t seq, hipStream_t s) {
-    hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(kUploadThreads), 0, s, (const uint4*)src, (uint4*)dst,
+    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(kFetchThreads), 0, s, (const uint4*)src, (uint4*)dst,
                        (uint32_t)((bytes + 15) / 16), flag, seq);
     return hipGetLastError();
 }

@@ -5,6 +5,7 @@ is still running."""
 import os
 import subprocess
 import sys
+import threading
 import time
 
 import numpy as np
@@ -92,8 +93,7 @@ def test_checkpoint_packs_in_any_number_do_not_wait_for_the_stream():
 
 
 def test_descriptor_uploads_behind_a_busy_stream_keep_their_order():
-    # every step uploads other learning rates through one of four pinned slots: four steps are enqueued without waiting,
-    # further ones wait for a slot and never overwrite one that a kernel has still to read
+    # every step has other learning rates: none of them may reach an earlier step that has still to run
     specs = W.odd_sizes()
     bufs, _ = _state(specs, seed=25)
     ref, _ = _state(specs, seed=25)
@@ -118,6 +118,55 @@ def test_descriptor_uploads_behind_a_busy_stream_keep_their_order():
         torch.cuda.synchronize()
     for a, b in zip(ref, bufs):
         assert torch.equal(a.rho, b.rho) and torch.equal(a.param.view(torch.int16), b.param.view(torch.int16))
+
+
+@pytest.mark.parametrize("n_tensors", [2, 240, 241, 321, 961])
+def test_changed_descriptors_in_any_number_do_not_wait_for_the_stream(n_tensors):
+    # steps with other gradient buffers, differing rates and other weight decays, in every combination, behind one busy
+    # stream (960 words per table update: two for the gradient, one for each of the others);
+    # a second thread's multi-tensor call on an idle stream is not held up either
+    specs = [W.ParamSpec(f"t{i}", (33 + i % 70,), "matrix") for i in range(n_tensors)]
+    bufs, _ = _state(specs, seed=28)
+    ref, _ = _state(specs, seed=28)
+    idle, _ = _state(specs, seed=29)
+    grads = [[torch.randn_like(b.grad, dtype=torch.float32).to(torch.bfloat16) for b in bufs] for _ in range(3)]
+    tl, tl_ref, tl_idle = fo.TensorList(bufs), fo.TensorList(ref), fo.TensorList(idle)
+
+    def prepare(t_list, step):
+        for i in range(t_list.n):
+            if step & 1:
+                t_list.set_hyper(i, lr=1e-3 * (step + i % 5))
+            if step & 2:
+                t_list.set_hyper(i, weight_decay=1e-3 * (step % 7))
+            if step & 4:
+                t_list.set_grad(i, grads[step % 3][i])
+
+    for t_list in (tl, tl_ref, tl_idle):
+        fo.adamw_step_exact(t_list, 0.9, 0.999, 1e-8, 1)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    other = threading.Thread(target=lambda: [fo.adamw_step_exact(tl_idle, 0.9, 0.999, 1e-8, 2 + k, stream=side) for k in range(5)])
+    mon = _busy_stream(0.4)
+    spent = 0.0
+    for step in range(1, 16):
+        prepare(tl, step)
+        t0 = time.perf_counter()
+        fo.adamw_step_exact(tl, 0.9, 0.999, 1e-8, step, stream=mon.stream)
+        spent += time.perf_counter() - t0
+    other.start()
+    other.join()
+    side.synchronize()
+    still_busy = not mon.stream.query()
+    mon.stream.synchronize()
+    assert still_busy and spent < 0.2, f"15 steps took {spent:.3f} s on the host; stream busy afterwards: {still_busy}"
+    for step in range(1, 16):
+        prepare(tl_ref, step)
+        fo.adamw_step_exact(tl_ref, 0.9, 0.999, 1e-8, step)
+        torch.cuda.synchronize()
+    for a, b in zip(ref, bufs):
+        for k in ("param", "rho", "m_q", "m_scale", "v_q", "v_scale"):
+            x, y = getattr(a, k), getattr(b, k)
+            assert torch.equal(x.view(torch.int16) if x.element_size() == 2 else x, y.view(torch.int16) if y.element_size() == 2 else y), k
 
 
 def test_calls_that_return_values_wait_for_a_stream_that_stays_busy():

@@ -129,3 +129,35 @@ def test_captured_pack_keeps_its_own_header():
             torch.cuda.synchronize()
             assert torch.equal(blob, want), (replay, step)
             assert fo.checkpoint_unpack("adamw", blob, bufs) == step
+
+
+def _list_with(bufs, grads, lrs):
+    """A descriptor list over `bufs` with other gradient buffers and rates (the same list to the library)."""
+    tl = fo.TensorList(bufs)
+    for i in range(tl.n):
+        tl.set_grad(i, grads[i])
+        tl.set_hyper(i, lr=lrs[i % len(lrs)])
+    return tl
+
+
+def test_captured_change_of_descriptors_replays_its_own():
+    # gradients of a captured step usually lie in buffers of their own, and the captured call is the first to name them
+    specs = W.odd_sizes()[4:16]
+    ref, got = _twins(specs, seed=46)
+    sets = [[torch.randn(b.numel, device="cuda").mul_(1e-3 * (k + 1)).to(torch.bfloat16) for b in got] for k in range(8)]
+    lists = {id(bufs): [_list_with(bufs, sets[k], [1e-3 * (k + 1), 2e-3]) for k in range(8)] for bufs in (ref, got)}
+    tl_ref, tl_got = lists[id(ref)], lists[id(got)]
+    for tl in (tl_ref[0], tl_got[0]):
+        fo.adamw_step_exact(tl, B1, B2, EPS, 1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fo.adamw_step_exact(tl_got[1], B1, B2, EPS, 2)
+    for replay in range(3):
+        for k in (2, 3, 4, 5, 6, 7):                           # eager steps, each with gradients and rates of its own
+            fo.adamw_step_exact(tl_got[k], B1, B2, EPS, 3)
+            fo.adamw_step_exact(tl_ref[k], B1, B2, EPS, 3)
+        torch.cuda.synchronize()
+        graph.replay()
+        fo.adamw_step_exact(tl_ref[1], B1, B2, EPS, 2)
+        _assert_equal(ref, got, f"replay {replay}")
