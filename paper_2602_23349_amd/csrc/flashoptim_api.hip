@@ -47,6 +47,17 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline int64_t n_groups(int64_t n) { return (n + fo::kGroup - 1) / fo::kGroup; }
 inline int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 
+// Whether what is enqueued on `stream` is being captured into a graph.  (An error means that another stream's capture
+// forbids the question for the default stream: that stream itself is not capturing.)
+bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // ----------------------------------------------------- cached device tables --
 //
 // A "plan" is what a multi-tensor launch needs on the device: the table of tensors (for copies, of
@@ -91,6 +102,7 @@ struct Plan {
     uint64_t hash = 0;
     std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
     bool table_known = true;           // false: an update failed part of the way, so the table is written as a whole next
+    bool in_graphs = false;            // an update was captured: replays write the table, so every call writes it as a whole
     void* d_mem = nullptr;         // one allocation: the table, the index, the header
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
@@ -193,7 +205,8 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
 // Brings a step's table up to date in stream order if any descriptor has changed since its last update.  Where the
 // launch carries the learning rate, the table keeps the rates it was last given: an earlier launch that was captured
 // into a graph may still read them.  The new values travel as kernel arguments: no staging memory is involved, so
-// nothing is waited for however far the stream is behind, and a captured update writes the same values at every replay.
+// nothing is waited for however far the stream is behind, and a captured update writes the same values at every replay
+// (from the first one on, what the table holds when a later call runs is not known here).
 int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr, hipStream_t stream) {
     auto bits = [](float x) { uint32_t u; std::memcpy(&u, &x, sizeof(u)); return u; };
     uint64_t grad = 0;          // bits that differ (the same list: what a call can change are these three)
@@ -205,10 +218,12 @@ int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr
         lr |= bits(x.lr) ^ bits(y.lr);
         wd |= bits(x.wd) ^ bits(y.wd);
     }
+    if (p.in_graphs) p.table_known = false;
     fo::TableUpdate u;
     u.fields = (grad || !p.table_known ? fo::kUpdateGrad : 0) | ((lr && !ignore_lr) || !p.table_known ? fo::kUpdateLr : 0) |
                (wd || !p.table_known ? fo::kUpdateWd : 0);
     if (!u.fields) return FLASHOPTIM_OK;
+    if (is_capturing(stream)) p.in_graphs = true;
     const uint32_t most = fo::update_batch(u.fields);
     p.table_known = false;      // until every launch has been accepted
     for (size_t first = 0; first < n; first += u.count) {

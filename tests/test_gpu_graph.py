@@ -161,3 +161,26 @@ def test_captured_change_of_descriptors_replays_its_own():
         graph.replay()
         fo.adamw_step_exact(tl_ref[1], B1, B2, EPS, 2)
         _assert_equal(ref, got, f"replay {replay}")
+
+
+def test_eager_calls_around_a_captured_change_of_descriptors_use_their_own():
+    # a captured call changes nothing until it is replayed, and every replay changes the list's table: an eager call with
+    # the captured call's descriptors, or with those of the last eager call, finds other ones there
+    specs = W.odd_sizes()[6:15]
+    ref, got = _twins(specs, seed=47)
+    sets = [[torch.randn(b.numel, device="cuda").mul_(1e-3 * (k + 1)).to(torch.bfloat16) for b in got] for k in range(2)]
+    lists = {id(bufs): [_list_with(bufs, sets[k], [1e-3 * (k + 1), 2e-3]) for k in range(2)] for bufs in (ref, got)}
+    for bufs in (ref, got):
+        fo.adamw_step_exact(lists[id(bufs)][0], B1, B2, EPS, 1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fo.adamw_step_exact(lists[id(got)][1], B1, B2, EPS, 2)
+    for step, k in enumerate((1, 0, None, 0, None, None, 1, 0, 0, None, 1)):         # None: a replay
+        if k is None:
+            graph.replay()
+            fo.adamw_step_exact(lists[id(ref)][1], B1, B2, EPS, 2)
+        else:
+            for bufs in (ref, got):
+                fo.adamw_step_exact(lists[id(bufs)][k], B1, B2, EPS, 3)
+        _assert_equal(ref, got, f"step {step}")
