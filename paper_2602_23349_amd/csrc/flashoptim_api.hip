@@ -109,7 +109,9 @@ struct Plan {
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
     void* d_header = nullptr;      // packing only: the blob's header and table, all but the step
-    void* h_mem = nullptr;         // pinned source of d_mem's one upload, kept until the plan is freed
+    void* h_mem = nullptr;         // pinned source of d_mem's upload, kept until the plan is freed
+    size_t bytes = 0;              // of each
+    bool uploaded = false;         // an upload has been enqueued (one that was captured runs with the graph, if at all)
 };
 
 std::mutex g_mu;
@@ -153,12 +155,20 @@ struct PlanSource {
     const std::vector<uint8_t>& header;
 };
 
-// Makes the plan of a list that has none.  The tables are copied to pinned memory of the plan and uploaded in stream
-// order on `stream`, ahead of the launch that the creating call enqueues there (later calls with the same list touch
-// the same tensors, so the caller orders them after this one like any other work on those tensors).  Nothing here
-// waits for the stream.
+// Uploads a plan's tables in stream order on `stream`, ahead of the launch that the calling call enqueues there, unless
+// an earlier call has (calls with the same list touch the same tensors, so the caller orders them like any other work on
+// those tensors).
+int upload_tables(Plan& p, hipStream_t stream) {
+    if (p.uploaded) return FLASHOPTIM_OK;
+    FO_HIP(fo::launch_move(p.h_mem, p.d_mem, p.bytes, stream));
+    if (is_capturing(stream)) p.in_graphs = true;       // (a replay brings back the entries that the list began with)
+    else p.uploaded = true;
+    return FLASHOPTIM_OK;
+}
+
+// Makes the plan of a list that has none, its tables in pinned memory of the plan.  Nothing here waits for the stream.
 int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& tensors, const PlanSource& src,
-              int64_t n_chunks, hipStream_t stream, Plan** out) {
+              int64_t n_chunks, Plan** out) {
     Plan p;
     p.tag = tag;
     p.hash = hash;
@@ -168,26 +178,23 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
     const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
     const size_t all = header_at + (size_t)align64((int64_t)src.header.size());
-    const size_t bytes = all > 0 ? all : 64;
-    hipError_t e = hipMalloc(&p.d_mem, bytes);
-    if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, bytes, hipHostMallocCoherent);
-    if (e == hipSuccess) {
-        p.d_table = p.d_mem;
-        p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
-        p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
-        uint8_t* h = static_cast<uint8_t*>(p.h_mem);
-        std::memset(h, 0, bytes);
-        if (src.table_bytes) std::memcpy(h, src.table, src.table_bytes);
-        if (index_bytes) std::memcpy(h + index_at, src.index.data(), index_bytes);
-        if (!src.header.empty()) std::memcpy(h + header_at, src.header.data(), src.header.size());
-        if (all) e = fo::launch_move(p.h_mem, p.d_mem, all, stream);
-    }
+    p.bytes = all > 0 ? all : 64;
+    hipError_t e = hipMalloc(&p.d_mem, p.bytes);
+    if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, p.bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
         (void)hipGetLastError();
         destroy_plan(p);
         return FLASHOPTIM_ERR_HIP;
     }
+    p.d_table = p.d_mem;
+    p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
+    p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
+    uint8_t* h = static_cast<uint8_t*>(p.h_mem);
+    std::memset(h, 0, p.bytes);
+    if (src.table_bytes) std::memcpy(h, src.table, src.table_bytes);
+    if (index_bytes) std::memcpy(h + index_at, src.index.data(), index_bytes);
+    if (!src.header.empty()) std::memcpy(h + header_at, src.header.data(), src.header.size());
     g_plans.push_front(std::move(p));
     g_index.emplace(hash, g_plans.begin());
     while (g_plans.size() > kMaxPlans) {
@@ -387,10 +394,8 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     const uint32_t shift = fo::coarse_shift(total_chunks);
     std::lock_guard<std::mutex> lock(g_mu);
     Plan* plan = find_plan(tag, hash, live);
-    int rc;
-    if (plan) {
-        rc = refresh_table(*plan, live, shared_lr, stream);
-    } else {
+    int rc = FLASHOPTIM_OK;
+    if (!plan) {
         // the coarse workgroup -> tensor table
         std::vector<uint32_t> coarse((size_t)fo::coarse_entries(total_chunks, shift));
         size_t ti = 0;
@@ -401,8 +406,10 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
         }
         const std::vector<uint8_t> no_header;
         rc = make_plan(tag, hash, live, {live.data(), live.size() * sizeof(TensorDev), coarse, no_header},
-                       total_chunks, stream, &plan);
+                       total_chunks, &plan);
     }
+    if (rc == FLASHOPTIM_OK) rc = upload_tables(*plan, stream);
+    if (rc == FLASHOPTIM_OK) rc = refresh_table(*plan, live, shared_lr, stream);
     if (rc != FLASHOPTIM_OK) return rc;
     a.tensors = static_cast<const TensorDev*>(plan->d_table);
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
@@ -670,11 +677,13 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         std::vector<uint8_t> header;
         if (pack) header = build_header(kind, t, n, 0, total_bytes);
         const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header},
-                                 n_pieces, stream, &plan);
+                                 n_pieces, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
         plan->n_segs = (uint32_t)segs.size();
         plan->coarse_shift = shift;
     }
+    const int rc = upload_tables(*plan, stream);
+    if (rc != FLASHOPTIM_OK) return rc;
     fo::CopyArgs a;
     std::memset(&a, 0, sizeof(a));
     a.segs = static_cast<const CopySegment*>(plan->d_table);

@@ -184,3 +184,33 @@ def test_eager_calls_around_a_captured_change_of_descriptors_use_their_own():
             for bufs in (ref, got):
                 fo.adamw_step_exact(lists[id(bufs)][k], B1, B2, EPS, 3)
         _assert_equal(ref, got, f"step {step}")
+
+
+@pytest.mark.parametrize("first_eager", [1, 0])
+def test_list_whose_first_call_is_captured(first_eager):
+    # a capture in relaxed mode may allocate, so a list's tables can be made by a captured call: they reach the device
+    # with the replays, and an eager call in between may be the first of all to need them
+    specs = W.odd_sizes()[5:13]
+    ref, got = _twins(specs, seed=48)
+    sets = [[torch.randn(b.numel, device="cuda").mul_(1e-3 * (k + 1)).to(torch.bfloat16) for b in got] for k in range(2)]
+    lists = {id(bufs): [_list_with(bufs, sets[k], [1e-3 * (k + 1), 2e-3]) for k in range(2)] for bufs in (ref, got)}
+    warm, _ = _twins(specs, seed=49)
+    fo.adamw_step_exact(warm, B1, B2, EPS, 1)                  # the library's per-device set-up
+    size = fo.checkpoint_size("adamw", [sp.numel for sp in specs])
+    blob, want = (torch.zeros(size, dtype=torch.uint8, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        fo.adamw_step_exact(lists[id(got)][1], B1, B2, EPS, 2)
+        fo.checkpoint_pack("adamw", got, 5, blob)
+    for step, k in enumerate((0, None, 0, None, None, 1, None, 0)[1 - first_eager:]):         # None: a replay
+        if k is None:
+            graph.replay()
+            fo.adamw_step_exact(lists[id(ref)][1], B1, B2, EPS, 2)
+            fo.checkpoint_pack("adamw", ref, 5, want)
+        else:
+            for bufs, b in ((ref, want), (got, blob)):
+                fo.adamw_step_exact(lists[id(bufs)][k], B1, B2, EPS, 3)
+                fo.checkpoint_pack("adamw", bufs, 6, b)
+        _assert_equal(ref, got, f"step {step}")
+        assert torch.equal(blob, want), step
