@@ -100,9 +100,14 @@ typedef struct flashoptim_lion_hp { float beta1, beta2; } flashoptim_lion_hp;
  * with a further distinct list frees the least recently used one after synchronising the device.  The grad pointers are not part of the
  * cached identity of a list, so gradients may live in different buffers each step.  A call whose descriptors
  * (pointers, grad pointers, numel, lr, weight_decay) equal those of the previous call on the same list enqueues
- * kernels only and may be captured into a HIP graph; changed descriptors are uploaded in stream order first.  A change
- * of lr alone, to a value that all tensors share, needs no upload: it is an argument of the kernels (a captured call
- * keeps the value it was captured with).
+ * kernels only; changed ones are first written into the list's table by a small kernel, or, where all that has changed
+ * is a rate that all tensors share, by the step itself.
+ *
+ * Under capture into a HIP graph: the list's tables should have been made by an earlier call (making them allocates), and
+ * must be kept while the graph is in use (see the 256 lists above and release_cache).  A captured call with unchanged
+ * descriptors reads gradients, rates and weight decays from the table at every replay, as the latest call on the list has
+ * left them: an eager call with another rate reaches the replays.  A captured call with changed descriptors writes them
+ * into the table at every replay.  A list of length one has no table: its call keeps what it was captured with.
  *
  * flashoptim_adamw_step: Algorithm 4, the body of the loop after the gradient (reconstruct m, v, theta; AdamW
  *   update with bias correction and decoupled weight decay; quantize m, v; split theta).

@@ -65,7 +65,7 @@ bool is_capturing(hipStream_t stream) {
 // numel; NOT the gradient pointers or lr/wd, which legitimately change from step to step).
 // What a later call on the same list may change (gradient pointer, rates, weight decay) is written into the
 // tensor table in stream order, from kernel arguments, only when it differs from what the device already holds; a
-// learning rate that all tensors share is not part of it.
+// new learning rate that all tensors share goes with the step's own launch.
 //
 // A call finds its plan through a 64-bit hash of the identity and then compares the descriptors themselves, so a
 // collision costs time and nothing else.  (With the identity as a string key, built and hashed byte by byte on
@@ -101,7 +101,7 @@ struct Plan {
     PlanTag tag = {};
     uint64_t hash = 0;
     std::vector<TensorDev> tensors;    // the list; for steps and conversions also what the device table holds
-    bool table_known = true;           // false: an update failed part of the way, so the table is written as a whole next
+    bool table_known = true;           // false: a call failed part of the way, so the table is written as a whole next
     bool in_graphs = false;            // an update was captured: replays write the table, so every call writes it as a whole
     void* d_mem = nullptr;         // one allocation: the table, the index, the header
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
@@ -209,12 +209,13 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     return FLASHOPTIM_OK;
 }
 
-// Brings a step's table up to date in stream order if any descriptor has changed since its last update.  Where the
-// launch carries the learning rate, the table keeps the rates it was last given: an earlier launch that was captured
-// into a graph may still read them.  The new values travel as kernel arguments: no staging memory is involved, so
-// nothing is waited for however far the stream is behind, and a captured update writes the same values at every replay
-// (from the first one on, what the table holds when a later call runs is not known here).
-int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr, hipStream_t stream) {
+// Brings a step's table up to date in stream order if any descriptor has changed since its last update.  A rate that all
+// tensors share, if it is all that has changed of the rates, is left to the launch (*lr_by_launch): its kernels take the
+// rate from their arguments and write it into the table.  Not in a captured call, whose kernels read the table at every
+// replay, as the latest call on the list has left it.  The new values travel as kernel arguments: no staging memory is
+// involved, so nothing is waited for however far the stream is behind, and a captured update writes the same values at
+// every replay (from the first one on, what the table holds when a later call runs is not known here).
+int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool shared_lr, hipStream_t stream, bool* lr_by_launch) {
     auto bits = [](float x) { uint32_t u; std::memcpy(&u, &x, sizeof(u)); return u; };
     uint64_t grad = 0;          // bits that differ (the same list: what a call can change are these three)
     uint32_t lr = 0, wd = 0;
@@ -225,12 +226,20 @@ int refresh_table(Plan& p, const std::vector<TensorDev>& tensors, bool ignore_lr
         lr |= bits(x.lr) ^ bits(y.lr);
         wd |= bits(x.wd) ^ bits(y.wd);
     }
+    *lr_by_launch = false;
     if (p.in_graphs) p.table_known = false;
+    if (p.table_known && !grad && !lr && !wd) return FLASHOPTIM_OK;
+    const bool capturing = is_capturing(stream);
     fo::TableUpdate u;
-    u.fields = (grad || !p.table_known ? fo::kUpdateGrad : 0) | ((lr && !ignore_lr) || !p.table_known ? fo::kUpdateLr : 0) |
-               (wd || !p.table_known ? fo::kUpdateWd : 0);
+    u.fields = fo::kUpdateGrad | fo::kUpdateLr | fo::kUpdateWd;
+    if (p.table_known) {
+        *lr_by_launch = lr && shared_lr && !capturing;
+        u.fields = (grad ? fo::kUpdateGrad : 0) | (lr && !*lr_by_launch ? fo::kUpdateLr : 0) | (wd ? fo::kUpdateWd : 0);
+    }
+    if (*lr_by_launch)
+        for (size_t i = 0; i < n; ++i) p.tensors[i].lr = tensors[i].lr;
     if (!u.fields) return FLASHOPTIM_OK;
-    if (is_capturing(stream)) p.in_graphs = true;
+    if (capturing) p.in_graphs = true;
     const uint32_t most = fo::update_batch(u.fields);
     p.table_known = false;      // until every launch has been accepted
     for (size_t first = 0; first < n; first += u.count) {
@@ -382,11 +391,12 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
         return FLASHOPTIM_OK;
     }
 
-    // a learning rate that all tensors share goes with the launch, not through the table
+    const bool step = op == kOpStep || op == kOpStepExact;
     bool shared_lr = true;
-    for (const TensorDev& d : live) shared_lr = shared_lr && std::memcmp(&d.lr, &live[0].lr, sizeof(float)) == 0;
-    a.table_lr_mask = shared_lr ? 0u : ~0u;
-    if (shared_lr) std::memcpy(&a.shared_lr_bits, &live[0].lr, sizeof(float));
+    for (TensorDev& d : live) {
+        if (!step) d.lr = d.wd = 0.0f;         // not used
+        shared_lr = shared_lr && std::memcmp(&d.lr, &live[0].lr, sizeof(float)) == 0;
+    }
 
     PlanTag tag = {0, (int32_t)op, kind, (int32_t)(split ? 1 : 0) | (int32_t)(quant ? 2 : 0), nullptr};
     FO_HIP(hipGetDevice(&tag.device));
@@ -409,13 +419,18 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
                        total_chunks, &plan);
     }
     if (rc == FLASHOPTIM_OK) rc = upload_tables(*plan, stream);
-    if (rc == FLASHOPTIM_OK) rc = refresh_table(*plan, live, shared_lr, stream);
+    bool lr_by_launch = false;
+    if (rc == FLASHOPTIM_OK) rc = refresh_table(*plan, live, shared_lr, stream, &lr_by_launch);
     if (rc != FLASHOPTIM_OK) return rc;
-    a.tensors = static_cast<const TensorDev*>(plan->d_table);
+    a.table_lr_mask = lr_by_launch ? 0u : ~0u;
+    if (lr_by_launch) std::memcpy(&a.shared_lr_bits, &live[0].lr, sizeof(float));
+    a.tensors = static_cast<TensorDev*>(plan->d_table);
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)live.size();
-    FO_HIP(launch_op(op, kind, false, split, quant, small, a, plan->n_chunks, ce, stream));
+    const hipError_t e = launch_op(op, kind, false, split, quant, small, a, plan->n_chunks, ce, stream);
+    if (e != hipSuccess) plan->table_known = false;        // the launches that were accepted may have written a rate
+    FO_HIP(e);
     return FLASHOPTIM_OK;
 }
 

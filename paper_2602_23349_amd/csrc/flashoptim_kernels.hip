@@ -883,8 +883,9 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
 // ------------------------------------------------------------ step kernels --
 // The tensor and the tile within it that workgroup blockIdx.x handles.  Every load is wave-uniform
 // (scalar).  The search loop ends at the last tensor at the latest.
+// *index (multi-tensor launches): the tensor's index in the table.
 template <bool DIRECT>
-__device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T) {
+__device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, uint32_t* index = nullptr) {
     const uint32_t b = blockIdx.x + a.block_offset;
     if (DIRECT) {
         T = a.single;
@@ -896,9 +897,9 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T) 
         ++t;
         T = a.tensors[t];
     }
+    if (index) *index = t;
     return (int64_t)(b - T.first_tile);
 }
-
 
 // One tile of one tensor.  FULL: every lane of the workgroup holds VEC elements (all tiles of a
 // tensor but possibly its last); the code then has no per-lane case distinction at all.
@@ -939,12 +940,19 @@ __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
     TableEntries entries;
     if constexpr (SPLIT || QUANT) load_table_entries<THREADS>(entries, tid);
     TensorDev T;
-    const int64_t chunk = locate_tile<DIRECT>(a, T);
+    uint32_t index = 0;
+    const int64_t chunk = locate_tile<DIRECT>(a, T, &index);
     const int64_t tile0 = chunk * (int64_t)kTile;              // first element of the tile (wave-uniform)
     const int64_t rem = T.numel - tile0;                       // elements from there to the tensor's end
-    if (!DIRECT) T.lr = u2f((f2u(T.lr) & a.table_lr_mask) | a.shared_lr_bits);     // (integers: stays on the scalar unit)
     StepConsts c = a.c;
-    if (KIND == 0) c.sqrt_min = *a.sqrt_min_word;              // one scalar load, needed only after the streaming loads
+    if (KIND == 0) c.sqrt_min = *a.sqrt_min_word;              // one scalar load, needed only after the streaming loads; ahead
+                                                               // of the store below, or it would be a vector load
+    if (!DIRECT) {
+        const uint32_t lr = (f2u(T.lr) & a.table_lr_mask) | a.shared_lr_bits;      // (integers: stays on the scalar unit)
+        // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
+        if (chunk == 0 && lr != f2u(T.lr) && tid == 0) a.tensors[index].lr = u2f(lr);
+        T.lr = u2f(lr);
+    }
     if (rem >= kTile) {
         step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, true>(T, c, tab, entries, tile0, kTile, tid);
     } else {

@@ -76,34 +76,36 @@ def test_captured_steps_replay_like_eager_calls():
         torch.cuda.synchronize()
 
 
-def test_captured_learning_rates_are_kept_and_later_calls_do_not_reach_them():
-    # a rate that all tensors share is an argument of the captured kernels; rates that differ are read from the list's
-    # table, which an eager call with one common rate leaves alone
-    specs = W.odd_sizes()[4:14]
+@pytest.mark.parametrize("n_tensors", [10, 2])
+def test_replays_take_the_rates_of_the_latest_call(n_tensors):
+    # the captured kernels read the list's table, and every eager call leaves its rates there, also a common one that its
+    # own kernels take from their arguments
+    specs = W.odd_sizes()[4:4 + n_tensors] + [W.ParamSpec("big", (70_000 // n_tensors, 33), "matrix")]
     ref, got = _twins(specs, seed=43)
     tl_ref, tl_got = fo.TensorList(ref), fo.TensorList(got)
 
-    def rates(tl, lrs):
-        for i in range(tl.n):
-            tl.set_hyper(i, lr=lrs[i % len(lrs)])
+    def eager(lists, lrs, t):
+        for tl in lists:
+            for i in range(tl.n):
+                tl.set_hyper(i, lr=lrs[i % len(lrs)])
+            fo.adamw_step_exact(tl, B1, B2, EPS, t)
 
-    for common in (True, False):
-        captured = [2e-3] if common else [1e-3, 3e-3]
-        for tl in (tl_ref, tl_got):
-            rates(tl, captured)
-            fo.adamw_step_exact(tl, B1, B2, EPS, 1)            # tables and descriptors as the capture will find them
+    common, differing = [2e-3], [1e-3, 3e-3]
+    for before, captured in (([common], common), ([common, [7e-4]], [7e-4]), ([differing], differing),
+                             ([differing, common], common), ([common, differing], differing)):
+        for lrs in before:                                     # the last of them leaves the captured call's rates
+            eager((tl_ref, tl_got), lrs, 1)
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
-            fo.adamw_step_exact(tl_got, B1, B2, EPS, 2)
-        for replay in range(3):
-            for tl in (tl_ref, tl_got):                        # an eager step at another common rate in between
-                rates(tl, [5e-4 * (replay + 1)])
-                fo.adamw_step_exact(tl, B1, B2, EPS, 3)
-            graph.replay()
-            rates(tl_ref, captured)
-            fo.adamw_step_exact(tl_ref, B1, B2, EPS, 2)
-            _assert_equal(ref, got, f"common={common} replay {replay}")
+            eager((tl_got,), captured, 2)
+        for replay, lrs in enumerate((captured, [5e-4], [6e-4], [4e-3, 5e-4, 6e-4], [6e-4], differing, common)):
+            if replay:
+                eager((tl_ref, tl_got), lrs, 3)
+            for _ in range(1 + replay % 2):
+                graph.replay()
+                eager((tl_ref,), lrs, 2)
+            _assert_equal(ref, got, f"captured at {captured}, replay {replay}")
 
 
 def test_captured_pack_keeps_its_own_header():
