@@ -107,7 +107,9 @@ typedef struct flashoptim_lion_hp { float beta1, beta2; } flashoptim_lion_hp;
  * must be kept while the graph is in use (see the 256 lists above and release_cache).  A captured call with unchanged
  * descriptors reads gradients, rates and weight decays from the table at every replay, as the latest call on the list has
  * left them: an eager call with another rate reaches the replays.  A captured call with changed descriptors writes them
- * into the table at every replay.  A list of length one has no table: its call keeps what it was captured with.
+ * into the table at every replay.  A list of length one has no table: its call keeps what it was captured with.  The calls
+ * that wait for completion (each says so) return FLASHOPTIM_ERR_HIP on a capturing stream, with nothing enqueued and the
+ * capture intact.
  *
  * flashoptim_adamw_step: Algorithm 4, the body of the loop after the gradient (reconstruct m, v, theta; AdamW
  *   update with bias correction and decoupled weight decay; quantize m, v; split theta).

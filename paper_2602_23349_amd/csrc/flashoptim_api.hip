@@ -58,6 +58,14 @@ bool is_capturing(hipStream_t stream) {
     return status != hipStreamCaptureStatusNone;
 }
 
+// The calls that wait for values from the device refuse a capturing stream before anything is enqueued: their kernels
+// would run with the graph only, on memory that this call gives back.
+int refuse_capture(hipStream_t stream) {
+    if (!is_capturing(stream)) return FLASHOPTIM_OK;
+    g_last_hip_error = (int)hipErrorStreamCaptureUnsupported;
+    return FLASHOPTIM_ERR_HIP;
+}
+
 // ----------------------------------------------------- cached device tables --
 //
 // A "plan" is what a multi-tensor launch needs on the device: the table of tensors (for copies, of
@@ -788,7 +796,7 @@ void give_space(CallSpace& w) {
 
 // Waits for the work that uses `w` (launched with result `e`).  For up to 2 ms the host watches the flag, which it sees
 // some microseconds before the runtime reports the stream idle (2^24 momentum values: 31.5 -> 27.9 us a call); longer work,
-// and work that never sets the flag (a failed or capturing stream), is waited for through the stream.  If anything
+// and work that never sets the flag (on a failed stream), is waited for through the stream.  If anything
 // failed the workspace is freed, which waits for whatever may still use it.
 int wait_space(CallSpace& w, hipError_t e, hipStream_t stream) {
     if (e == hipSuccess) {
@@ -802,6 +810,8 @@ int wait_space(CallSpace& w, hipError_t e, hipStream_t stream) {
             if (k % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
         }
         e = hipStreamSynchronize(stream);
+        std::atomic_thread_fence(std::memory_order_acquire);
+        if (e == hipSuccess && *f != w.seq) e = hipErrorUnknown;        // (never: the kernel that sets it has run)
     }
     if (e == hipSuccess) return FLASHOPTIM_OK;
     g_last_hip_error = (int)e;
@@ -1009,6 +1019,8 @@ static int run_sweep(int correction_bits, int ulp_reading, uint64_t first, uint6
     const uint64_t count = first < limit ? (limit - first + stride - 1) / stride : 0;
     for (int i = 0; i < n_stats; ++i) stats[i] = 0.0;
     if (count == 0) return FLASHOPTIM_OK;
+    const int rc = refuse_capture(stream);
+    if (rc != FLASHOPTIM_OK) return rc;
     double* d = nullptr;
     FO_HIP(hipMalloc((void**)&d, fo::kSweepStats * sizeof(double)));
     hipError_t e = hipMemsetAsync(d, 0, fo::kSweepStats * sizeof(double), stream);
@@ -1088,8 +1100,10 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     if (!x) return FLASHOPTIM_ERR_INVALID_ARG;
     if (!aligned16(x)) return FLASHOPTIM_ERR_MISALIGNED;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
+    int rc = refuse_capture(stream);
+    if (rc != FLASHOPTIM_OK) return rc;
     CallSpace w;
-    int rc = take_space(w, 2 * sizeof(double));
+    rc = take_space(w, 2 * sizeof(double));
     if (rc != FLASHOPTIM_OK) return rc;
     rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, static_cast<double*>(w.host), w.flag(), w.seq,
                                        stream), stream);
@@ -1139,6 +1153,8 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     if (total < 0) return (int)total;
     if (blob_bytes < total) return FLASHOPTIM_ERR_BAD_BLOB;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
+    rc = refuse_capture(stream);
+    if (rc != FLASHOPTIM_OK) return rc;
     const std::vector<uint8_t> want = build_header(kind, tensors, n_tensors, 0, total);
     CallSpace w;
     rc = take_space(w, want.size());
@@ -1161,6 +1177,8 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
 // Runs the self-test sections and copies the raw device counters to h.
 static int run_selftest(unsigned long long (&h)[fo::kSelftestCounters], bool only_faithful, void* stream_) {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
+    const int rc = refuse_capture(stream);
+    if (rc != FLASHOPTIM_OK) return rc;
     unsigned long long* d = nullptr;
     FO_HIP(hipMalloc((void**)&d, fo::kSelftestCounters * sizeof(unsigned long long)));
     hipError_t e = hipMemsetAsync(d, 0, fo::kSelftestCounters * sizeof(unsigned long long), stream);

@@ -216,3 +216,36 @@ def test_list_whose_first_call_is_captured(first_eager):
                 fo.checkpoint_pack("adamw", bufs, 6, b)
         _assert_equal(ref, got, f"step {step}")
         assert torch.equal(blob, want), step
+
+
+@pytest.mark.parametrize("mode", ["global", "relaxed"])
+def test_calls_that_wait_for_values_refuse_a_capturing_stream_and_leave_the_capture_intact(mode):
+    specs = W.odd_sizes()[5:9]
+    bufs, ref = _twins(specs, seed=50)
+    blob = torch.zeros(fo.checkpoint_size("adamw", [sp.numel for sp in specs]), dtype=torch.uint8, device="cuda")
+    x = torch.full((4096,), 2.0, device="cuda")
+
+    def calls():
+        yield lambda: fo.quantization_nmse("momentum", False, x)
+        yield lambda: fo.checkpoint_unpack("adamw", blob, bufs)
+        yield lambda: fo.reconstruction_sweep(8, 0, 1 << 20)
+        yield lambda: fo.selftest()
+
+    fo.adamw_step_exact(bufs, B1, B2, EPS, 1)
+    fo.adamw_step_exact(ref, B1, B2, EPS, 1)
+    fo.checkpoint_pack("adamw", bufs, 3, blob)
+    assert fo.quantization_nmse("momentum", False, x) == (0.0, 16384.0)        # (leaves a workspace for the next call)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode=mode):
+        for call in calls():
+            with pytest.raises(fo.FlashOptimError) as err:
+                call()
+            assert err.value.status == -4
+        fo.adamw_step_exact(bufs, B1, B2, EPS, 2)
+    for replay in range(2):
+        graph.replay()
+        fo.adamw_step_exact(ref, B1, B2, EPS, 2)
+        _assert_equal(ref, bufs, f"replay {replay}")
+    assert fo.quantization_nmse("momentum", False, x) == (0.0, 16384.0)
+    assert fo.checkpoint_unpack("adamw", blob, bufs) == 3
