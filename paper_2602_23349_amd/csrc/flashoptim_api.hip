@@ -736,23 +736,24 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
 //
 // The calls that return values to the host (quantisation error, unpack's header check) let a kernel write them to
 // pinned memory and wait for a flag that it sets last; the quantisation error also needs device memory for the
-// workgroups' partial sums.  Both are kept from call to call (allocating and freeing them cost ~20 us a call); a call takes a workspace
-// out of the pool for as long as it runs, so calls of several threads and streams never share one, and a workspace
-// goes back only once its kernels have set the flag or their stream has been waited for.
+// workgroups' partial sums.  Both are kept from call to call (allocating and freeing them cost ~20 us a call, and freeing
+// waits for every stream of the device); a call takes a workspace out of the pool for as long as it runs, so calls of
+// several threads and streams never share one, and a workspace goes back only once its kernels have set the flag or
+// their stream has been waited for.
 struct CallSpace {
     int device = 0;
     double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs
-    void* host = nullptr;           // pinned and coherent, host_bytes and the flag behind them
-    size_t host_bytes = 0;
+    uint8_t* host = nullptr;        // pinned and coherent: kSpaceHost bytes and the flag behind them
     uint32_t seq = 0;               // the value that marks the end of the workspace's current use
 
-    uint32_t* flag() const { return reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(host) + host_bytes); }
+    uint32_t* flag() const;
 };
+constexpr size_t kSpaceHost = 64 * 1024;        // a header of up to 4092 tensors; longer ones come in parts
 constexpr size_t kFlagStride = 64;              // bytes: the flag has a cache line of its own
+uint32_t* CallSpace::flag() const { return reinterpret_cast<uint32_t*>(host + kSpaceHost); }
 std::mutex g_space_mu;
-constexpr int kMaxIdleSpaces = 16;              // 32 KB of device and at least 64 KB of pinned memory each; beyond that
-constexpr size_t kMinSpaceHost = 64 * 1024;     // a workspace is freed after its call, like one that had to be larger
-CallSpace g_space_idle[kMaxIdleSpaces];
+constexpr int kMaxIdleSpaces = 16;              // 32 KB of device and 64 KB of pinned memory each; what more calls than that
+CallSpace g_space_idle[kMaxIdleSpaces];         // give back at once is freed
 int g_space_n_idle = 0;
 
 void destroy_space(CallSpace& w) {
@@ -761,9 +762,9 @@ void destroy_space(CallSpace& w) {
     w = CallSpace();
 }
 
-int take_space(CallSpace& w, size_t host_bytes) {
+int take_space(CallSpace& w) {
     FO_HIP(hipGetDevice(&w.device));
-    if (host_bytes <= kMinSpaceHost) {
+    {
         std::lock_guard<std::mutex> lock(g_space_mu);
         for (int i = 0; i < g_space_n_idle; ++i) {
             if (g_space_idle[i].device != w.device) continue;
@@ -773,9 +774,8 @@ int take_space(CallSpace& w, size_t host_bytes) {
             return FLASHOPTIM_OK;
         }
     }
-    w.host_bytes = host_bytes > kMinSpaceHost ? (size_t)align64((int64_t)host_bytes) : kMinSpaceHost;
     hipError_t e = hipMalloc((void**)&w.partial, fo::kNmseMaxBlocks * sizeof(double2));
-    if (e == hipSuccess) e = hipHostMalloc(&w.host, w.host_bytes + kFlagStride, hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&w.host, kSpaceHost + kFlagStride, hipHostMallocCoherent);
     if (e != hipSuccess) {
         destroy_space(w);
         g_last_hip_error = (int)e;
@@ -790,7 +790,7 @@ int take_space(CallSpace& w, size_t host_bytes) {
 // Takes a workspace back whose work is known to have finished.
 void give_space(CallSpace& w) {
     std::lock_guard<std::mutex> lock(g_space_mu);
-    if (g_space_n_idle < kMaxIdleSpaces && w.host_bytes == kMinSpaceHost) g_space_idle[g_space_n_idle++] = w;
+    if (g_space_n_idle < kMaxIdleSpaces) g_space_idle[g_space_n_idle++] = w;
     else destroy_space(w);
 }
 
@@ -1103,9 +1103,9 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     int rc = refuse_capture(stream);
     if (rc != FLASHOPTIM_OK) return rc;
     CallSpace w;
-    rc = take_space(w, 2 * sizeof(double));
+    rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
-    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, static_cast<double*>(w.host), w.flag(), w.seq,
+    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, reinterpret_cast<double*>(w.host), w.flag(), w.seq,
                                        stream), stream);
     if (rc != FLASHOPTIM_OK) return rc;
     std::memcpy(sums, w.host, 2 * sizeof(double));
@@ -1157,15 +1157,23 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     if (rc != FLASHOPTIM_OK) return rc;
     const std::vector<uint8_t> want = build_header(kind, tensors, n_tensors, 0, total);
     CallSpace w;
-    rc = take_space(w, want.size());
-    if (rc != FLASHOPTIM_OK) return rc;
-    rc = wait_space(w, fo::launch_fetch(blob, w.host, want.size(), w.flag(), w.seq, stream), stream);
+    rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
     // everything but the step field must match what this (kind, list) would have written
-    const uint8_t* got = static_cast<const uint8_t*>(w.host);
-    const bool match = std::memcmp(got, want.data(), 16) == 0 &&
-                       std::memcmp(got + 24, want.data() + 24, want.size() - 24) == 0;
-    const int64_t step = get_i64(got + fo::kHeaderStepAt);
+    bool match = true;
+    int64_t step = 0;
+    for (size_t at = 0; at < want.size() && match; at += kSpaceHost) {
+        const size_t bytes = want.size() - at < kSpaceHost ? want.size() - at : kSpaceHost;
+        if (at) ++w.seq;
+        rc = wait_space(w, fo::launch_fetch(static_cast<const uint8_t*>(blob) + at, w.host, bytes, w.flag(), w.seq, stream),
+                        stream);
+        if (rc != FLASHOPTIM_OK) return rc;
+        if (at == 0) {
+            step = get_i64(w.host + fo::kHeaderStepAt);
+            put_i64(w.host + fo::kHeaderStepAt, 0);
+        }
+        match = std::memcmp(w.host, want.data() + at, bytes) == 0;
+    }
     give_space(w);
     if (!match) return FLASHOPTIM_ERR_BAD_BLOB;
     rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, total, 0, stream);

@@ -187,6 +187,38 @@ def test_calls_that_return_values_wait_for_a_stream_that_stays_busy():
             assert torch.equal(a.rho, b.rho) and torch.equal(a.v_q, b.v_q)
 
 
+@pytest.mark.parametrize("n_tensors", [4092, 4093, 9000])
+def test_unpacking_a_long_list_waits_for_its_own_stream_only(n_tensors):
+    # a header of more than 64 KB (4092 tensors) is read in parts, through the same workspace as a shorter one
+    bufs = [fo.ParamBuffers(33 + i % 40, "sgd", with_grad=False) for i in range(n_tensors)]
+    for i, b in enumerate(bufs):
+        b.rho.fill_(i % 100)
+    numels = [b.numel for b in bufs]
+    blob = torch.zeros(fo.checkpoint_size("sgd", numels), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("sgd", bufs, 77, blob)
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 77       # the list's tables
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    mon = _busy_stream(0.4)
+    t0 = time.perf_counter()
+    assert fo.checkpoint_unpack("sgd", blob, bufs, stream=side) == 77
+    dt = time.perf_counter() - t0
+    still_busy = not mon.stream.query()
+    mon.stream.synchronize()
+    assert still_busy and dt < 0.3, f"unpack took {dt:.3f} s on the host; other stream busy afterwards: {still_busy}"
+    for b in bufs[::501]:
+        b.rho.zero_()
+    for at in (8, 64 + 16 * (n_tensors - 1), 64 + 16 * (n_tensors - 1) + 8):       # version, last tensor's size and offset
+        bad = blob.clone()
+        bad[at] ^= 1
+        with pytest.raises(fo.FlashOptimError) as err:
+            fo.checkpoint_unpack("sgd", bad, bufs)
+        assert err.value.status == -5
+    assert not any(b.rho.any() for b in bufs[::501])
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 77
+    assert all((b.rho == i * 501 % 100).all() for i, b in enumerate(bufs[::501]))
+
+
 def test_packing_lists_that_differ_in_empty_tensors_only():
     # the header grows with every tensor of the list, also with those that have no element
     one = fo.ParamBuffers(64, "sgd")
