@@ -28,6 +28,23 @@ def _busy_stream(seconds):
     return mon
 
 
+def _stream_beside(mon):
+    """A stream whose work runs while mon's stream is busy (the runtime maps streams to a few hardware queues, and two on
+    the same one run in turn)."""
+    for _ in range(16):
+        side = torch.cuda.Stream()
+        done = torch.cuda.Event()
+        with torch.cuda.stream(side):
+            torch.zeros(1, device="cuda")
+            done.record()
+        until = time.perf_counter() + 0.01
+        while time.perf_counter() < until:
+            if done.query():
+                assert not mon.stream.query()
+                return side
+    raise AssertionError("no stream runs beside the busy one")
+
+
 def _state(specs, seed):
     bufs, states = [], []
     for i, sp in enumerate(specs):
@@ -144,9 +161,9 @@ def test_changed_descriptors_in_any_number_do_not_wait_for_the_stream(n_tensors)
     for t_list in (tl, tl_ref, tl_idle):
         fo.adamw_step_exact(t_list, 0.9, 0.999, 1e-8, 1)
     torch.cuda.synchronize()
-    side = torch.cuda.Stream()
+    mon = _busy_stream(0.6)
+    side = _stream_beside(mon)
     other = threading.Thread(target=lambda: [fo.adamw_step_exact(tl_idle, 0.9, 0.999, 1e-8, 2 + k, stream=side) for k in range(5)])
-    mon = _busy_stream(0.4)
     spent = 0.0
     for step in range(1, 16):
         prepare(tl, step)
@@ -198,8 +215,8 @@ def test_unpacking_a_long_list_waits_for_its_own_stream_only(n_tensors):
     fo.checkpoint_pack("sgd", bufs, 77, blob)
     assert fo.checkpoint_unpack("sgd", blob, bufs) == 77       # the list's tables
     torch.cuda.synchronize()
-    side = torch.cuda.Stream()
-    mon = _busy_stream(0.4)
+    mon = _busy_stream(0.6)
+    side = _stream_beside(mon)
     t0 = time.perf_counter()
     assert fo.checkpoint_unpack("sgd", blob, bufs, stream=side) == 77
     dt = time.perf_counter() - t0
