@@ -311,11 +311,12 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
 const char* flashoptim_strerror(int status);
 
 /* ---- device self-test ------------------------------------------------------------------
- * The step kernels obtain some correctly rounded results (1/s of an FP16 scale, sqrt, the
+ * The kernels obtain some correctly rounded results (1/s of an FP16 scale, sqrt, the
  * decision of an 8-bit code) from shorter instruction sequences that are exact provided the
  * hardware reciprocal and square root are within 1 ulp.  This call checks those provisions on
  * the current device against plain IEEE operations, exhaustively where the domain is small:
- *   [0] Newton reciprocal of every positive finite FP16 value      [1] v_rcp_f32 within 1 ulp, refined exact on [1, 4)
+ *   [0] Newton reciprocal of every positive finite FP16 value
+ *   [1] v_rcp_f32 within 1 ulp, its refinement exact, and v_sqrt_f32 within 1 ulp, for every value of [1, 4)
  *   [2] short square root (reciprocal-square-root estimate + one correction) == sqrtf for EVERY FP32 value
  *       of its range [2^-96, FLT_MAX] (1,879,048,192 values)
  *   [3] momentum codes (Algorithm 2) and [4] variance codes (Algorithm 3): the estimate equals the

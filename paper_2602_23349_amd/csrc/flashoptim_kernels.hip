@@ -1403,7 +1403,7 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(uint64_t first, uint64_
 // The companded codes are decided from an estimate, as in the step kernels: with their exact form (an IEEE division
 // or square root per element) throughout, 150 M elements of m / v took 120 / 125 us, with the estimate 117 / 118
 // (6.5 TB/s).  Momentum: m_code_bracket.  Variance: y* = v_sqrt_f32(v) * RN(255 r), where the hardware root is
-// within one ulp.  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and the exact argument of Round()
+// within one ulp (flashoptim_selftest, section 1).  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and the exact argument of Round()
 // by 3 (root, * r, * 255): 6 * 2^-24 * 255.5 < 9.2e-5, and the fused multiply-add that forms y* -+ w rounds by at
 // most 2^-17 = 7.7e-6, so w = 1.1e-4 decides.  A subnormal v has y below 1e-9 for every FP16 scale, far from a tie.
 constexpr float kTieWindowCodecV = 1.1e-4f;
@@ -1821,7 +1821,9 @@ hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs
 // for the square root built on v_rsq_f32, as verified here value by value.  This kernel checks
 // those provisions on the device it runs on, against the plain IEEE operations:
 //   section 0: recip_of_fp16(s) == 1.0f / s for every positive finite FP16 value s;
-//   section 1: v_rcp_f32(d) within 1 ulp of 1.0f / d, and its Newton refinement equal to 1.0f / d, for every d in [1, 4);
+//   section 1: v_rcp_f32(d) within 1 ulp of 1.0f / d, its Newton refinement equal to 1.0f / d, and v_sqrt_f32(d) (the
+//              codecs' variance codes) within 1 ulp of sqrtf(d), for every d in [1, 4): every mantissa, and for the
+//              root either parity of the exponent;
 //   section 2: sqrt_rn_midrange(x) == sqrtf(x) for EVERY FP32 value x of its range [2^-96, FLT_MAX];
 //   section 3: momentum codes: wherever the two conversions of m_code_bracket agree, they agree with
 //              m_code_exact, for every m' in [2^-13, 2) of either sign;
@@ -1859,8 +1861,10 @@ __device__ __forceinline__ void selftest_one(int section, uint64_t gid, const St
             const float d = u2f(0x3f800000u + (uint32_t)gid);            // [1, 4)
             const float r0 = __builtin_amdgcn_rcpf(d);
             const int32_t diff = (int32_t)f2u(r0) - (int32_t)f2u(1.0f / d);
+            const int32_t root_diff = (int32_t)f2u(__builtin_amdgcn_sqrtf(d)) - (int32_t)f2u(sqrtf(d));
             checked = true;
-            failed = diff > 1 || diff < -1 || f2u(fmaf(fmaf(-d, r0, 1.0f), r0, r0)) != f2u(1.0f / d);
+            failed = diff > 1 || diff < -1 || f2u(fmaf(fmaf(-d, r0, 1.0f), r0, r0)) != f2u(1.0f / d) ||
+                     root_diff > 1 || root_diff < -1;
         }
     } else if (section == 2) {
         if (gid < kSelftestSqrtCount) {

@@ -11,7 +11,7 @@ def test_device_selftest_passes():
     print("self-test sections (checked / failed):", list(zip(checked, failed)))
     assert status == 0 and sum(failed) == 0
     assert checked[0] == 0x7BFF                      # every positive finite FP16 scale
-    assert checked[1] == 1 << 24                     # every d in [1, 4)
+    assert checked[1] == 1 << 24                     # every d in [1, 4): reciprocal, its refinement, root
     assert checked[2] == 0x7f800000 - 0x0f800000      # every FP32 value in [2^-96, FLT_MAX]
     # code sections: all candidates minus the few inside the tie window
     assert checked[3] > 0.99 * 2 * 14 * (1 << 23)
