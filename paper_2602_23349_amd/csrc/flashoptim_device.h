@@ -11,7 +11,7 @@
 namespace fo {
 
 constexpr int kGroup = 32;                         // quantisation group (Algorithms 2, 3)
-constexpr int kThreads = 256;                      // lanes per workgroup (codec and copy kernels)
+constexpr int kThreads = 256;                      // lanes per workgroup (codecs, conversions, sweep, self-test)
 // Launch shape of the step kernels, per optimizer kind (0 AdamW, 1 SGD, 2 Lion): consecutive
 // elements per lane and lanes per workgroup.  One workgroup handles one tile of chunk_elems(kind)
 // consecutive elements.

@@ -38,9 +38,10 @@
 //   * sqrt(v_hat) and m_hat / (sqrt(v_hat) + eps) use the 1-ulp hardware reciprocal square
 //     root / reciprocal followed by FMA residual corrections that yield the correctly rounded
 //     result for operands inside a stated range (the square root: verified for every value of
-//     the range by the device self-test; the division: the classical refinement); a
-//     wave-uniform range test selects the general sequence otherwise.  With EXACT = false the
-//     division takes one residual correction of the unrefined quotient (div_faithful).
+//     the range by the device self-test; the division: by the argument beside div_rn_midrange, from
+//     a property of the reciprocal that the self-test checks); a wave-uniform range test selects the
+//     general sequence otherwise.  With EXACT = false the division takes one residual correction of
+//     the unrefined quotient (div_faithful).
 //
 // Work decomposition.  A lane owns 8 consecutive elements per tile: BF16 streams move as
 // 128-bit and byte streams as 64-bit accesses, and a quantisation group (32 elements) is a
@@ -97,8 +98,7 @@ __device__ __forceinline__ void st128(void* p, uint32_t a, uint32_t b, uint32_t 
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 
-// Maximum over the lanes that share a 32-element group: a lane pair (16 elements per lane),
-// a lane quad (8 per lane) or two quads (4 per lane).  Each step is ONE instruction, v_max_f32 with its first operand taken
+// Maximum over the lanes that share a 32-element group: a lane quad (8 elements per lane) or two quads (4 per lane).  Each step is ONE instruction, v_max_f32 with its first operand taken
 // from the neighbouring lane through a DPP quad permute (written as inline assembly: from the
 // builtin the compiler makes a DPP move, two canonicalising maxima and the maximum itself).  The
 // s_nop covers the two wait states a DPP read needs after the instruction that wrote its source.
@@ -122,9 +122,8 @@ __device__ __forceinline__ float max_across_two_quads(float x) {
 }
 template <int VEC>
 __device__ __forceinline__ float group_max(float x) {
-    static_assert(VEC == 4 || VEC == 8 || VEC == 16, "lanes per group: 8, 4 or 2");
-    x = max_across_lane_pair(x);
-    if (VEC <= 8) x = max_across_pair_of_pairs(x);
+    static_assert(VEC == 4 || VEC == 8, "lanes per group: 8 or 4");
+    x = max_across_pair_of_pairs(max_across_lane_pair(x));
     if (VEC == 4) x = max_across_two_quads(x);
     return x;
 }
@@ -547,7 +546,7 @@ __device__ __forceinline__ void load_full(LaneIO<VEC>& x, const TensorDev& T, in
 // element yields zero moments and therefore never raises its group's absmax).  Every load is issued, those of missing
 // elements from the last existing one, so that all of a lane's loads are in flight together: written as "load it if it
 // exists", each became a branch with a wait behind its load, and the list of 25 small odd sizes spent most of its
-// kernel time in this chain of about 40 loads.  For cnt == 0 nothing is read.
+// kernel time in this chain of about 40 loads.  cnt >= 1: a lane without elements has no last one, its caller reads nothing.
 template <int N, typename T>
 __device__ __forceinline__ void load_elements(T (&e)[N], const T* p, int cnt) {
 #pragma unroll
@@ -1168,7 +1167,7 @@ __device__ __forceinline__ uint32_t byte_of(const uint32_t (&w)[kCodecVec / 4], 
 __device__ __forceinline__ uint32_t half_of(const uint32_t (&w)[kCodecVec / 2], int i) {
     return (w[i >> 1] >> (16 * (i & 1))) & 0xffffu;
 }
-// Eight small integers -> packed bytes / packed 16-bit fields (two's complement).
+// A lane's small integers -> packed bytes / packed 16-bit fields (two's complement).
 __device__ __forceinline__ void pack_u8(uint32_t (&w)[kCodecVec / 4], const uint32_t (&c)[kCodecVec]) {
 #pragma unroll
     for (int j = 0; j < kCodecVec / 4; ++j) w[j] = pack_low_bytes(c[4 * j], c[4 * j + 1], c[4 * j + 2], c[4 * j + 3]);
@@ -1403,9 +1402,10 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(uint64_t first, uint64_
 // The companded codes are decided from an estimate, as in the step kernels: with their exact form (an IEEE division
 // or square root per element) throughout, 150 M elements of m / v took 120 / 125 us, with the estimate 117 / 118
 // (6.5 TB/s).  Momentum: m_code_bracket.  Variance: y* = v_sqrt_f32(v) * RN(255 r), where the hardware root is
-// within one ulp (flashoptim_selftest, section 1).  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and the exact argument of Round()
-// by 3 (root, * r, * 255): 6 * 2^-24 * 255.5 < 9.2e-5, and the fused multiply-add that forms y* -+ w rounds by at
-// most 2^-17 = 7.7e-6, so w = 1.1e-4 decides.  A subnormal v has y below 1e-9 for every FP16 scale, far from a tie.
+// within one ulp (flashoptim_selftest, section 1).  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and
+// the exact argument of Round() by 3 (root, * r, * 255): 6 * 2^-24 * 255.5 < 9.2e-5, and the fused multiply-add that
+// forms y* -+ w rounds by at most 2^-17 = 7.7e-6, so w = 1.1e-4 decides.  A subnormal v has y below 1e-9 for every FP16
+// scale, far from a tie.
 constexpr float kTieWindowCodecV = 1.1e-4f;
 
 // quantize_lane: the codes of a lane, one byte each, and the FP16 scale bits of its group.  All eight lanes of
