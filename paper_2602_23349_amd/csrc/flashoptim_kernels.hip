@@ -1981,7 +1981,9 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 // More per lane is slower, less so in fewer lanes (pack of GPT-2's 638 MB / of a Llama layer / of two layers with
 // embedding and head, in us: 512 lanes x 16 accesses 225 / 387 / 2749; 1024 x 8 217 / 378 / 2659; 1024 x 1 201 / 355 /
 // 2520, 6.1 TB/s).  Pieces are found as the step kernels find their tiles, through a coarse table and the segments
-// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
+// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.  Within a coarse entry by
+// bisection: beside a large tensor an entry spans hundreds of pieces, and as many segments where a list has thousands of
+// small tensors (8000 of them beside 16 GB: one after the other 6025 us a pack, so 5589).
 //
 // header: the blob's header and table when packing; the workgroup behind the last piece writes them to header_dst.
 constexpr int kCopyThreads = kCopyPiece / 16;
@@ -1999,12 +2001,17 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
         }
         return;
     }
-    uint32_t t = a.coarse[b >> a.coarse_shift];
-    CopySegment sg = a.segs[t];
-    while (b - sg.first_piece >= sg.n_pieces && t + 1 < a.n_segs) {
-        ++t;
-        sg = a.segs[t];
+    // the last segment that begins at piece b or before, among those of this coarse entry
+    const uint32_t j = b >> a.coarse_shift;
+    uint32_t t = a.coarse[j];
+    if (a.coarse_shift) {
+        uint32_t last = j < (a.n_pieces - 1) >> a.coarse_shift ? a.coarse[j + 1] : a.n_segs - 1;
+        while (t < last) {
+            const uint32_t mid = (t + last + 1) >> 1;
+            if (a.segs[mid].first_piece <= b) t = mid; else last = mid - 1;
+        }
     }
+    const CopySegment sg = a.segs[t];
     const int64_t o = (int64_t)(b - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
     if (o + 16 <= sg.bytes) {
         const uint4 v = ld128(sg.src + o);

@@ -431,6 +431,30 @@ def test_checkpoint_at_the_edges_of_a_piece(kind, sizes):
                                             y.view(torch.int16 if y.element_size() == 2 else y.dtype)), (f.numel, k)
 
 
+def test_checkpoint_of_thousands_of_small_tensors_beside_a_large_one():
+    # about 40,000 pieces, so a coarse entry spans four of them: up to four one-piece segments, or parts of the large one
+    sizes = [33 + i % 60 for i in range(3001)] + [100_000_001] + [1 + i % 5000 for i in range(501)]
+    rng = np.random.default_rng(3)
+    states, bufs = [], []
+    for n in sizes:
+        st, ng = oracle.TensorState(np.zeros(1, np.float32), "sgd"), (n + 31) // 32
+        st.n = n
+        st.thp, st.ms = rng.integers(0, 1 << 16, n, dtype=np.uint16), rng.integers(0, 1 << 16, ng, dtype=np.uint16)
+        st.rho, st.mq = (rng.integers(-128, 128, n, dtype=np.int8) for _ in range(2))
+        states.append(st)
+        bufs.append(upload_state(st, with_grad=False))
+    blob = torch.zeros(fo.checkpoint_size("sgd", sizes), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("sgd", bufs, 21, blob)
+    assert np.array_equal(blob.cpu().numpy(), oracle.checkpoint_pack("sgd", states, 21))
+    again = torch.zeros_like(blob)
+    for b in bufs:
+        for x in (b.param, b.rho, b.m_q, b.m_scale):
+            x.zero_()
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 21
+    fo.checkpoint_pack("sgd", bufs, 21, again)
+    assert torch.equal(again, blob)
+
+
 def test_checkpoint_of_more_than_one_launch():
     # above 64 GiB a copy no longer fits into one launch; sections of both launches, and the one that is cut, are compared
     sizes = [1000, 17_000_000_000 // 64 * 64, 70_001]          # 4.0625 bytes each: 69 GB, and as much for the blob
