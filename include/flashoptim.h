@@ -292,7 +292,8 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
  *   AdamW only: v codes (n) | v scales (2 ceil(n/32))
  * checkpoint_size: total blob bytes for a list (numels: host array), or a negative status.
  * checkpoint_pack:   gathers the tensors' state into `blob` (DEVICE memory, 16-byte aligned,
- *                    blob_bytes >= checkpoint_size).  grad fields are ignored.
+ *                    blob_bytes >= checkpoint_size).  grad fields are ignored.  Does not wait; under capture
+ *                    as a step call (see above), and every replay writes the step it was captured with.
  * checkpoint_unpack: scatters `blob` (DEVICE memory) back into the tensors' buffers and
  *                    returns the stored step in *step_out (host).  The header and table
  *                    are validated against (kind, list) first; this reads the header back to
