@@ -412,6 +412,14 @@ struct LaneIO {
 typedef const __attribute__((address_space(1))) uint8_t* gcptr_t;
 typedef __attribute__((address_space(1))) uint8_t* gptr_t;
 
+// A pointer marked as global memory, for the accesses that are not of that form (ragged ends, a group's scale): of a
+// pointer that comes from the tensor table the compiler does not know what it points to, and a single FLAT access in a
+// kernel makes it wait for every outstanding load wherever the paths join, the one without the access included.
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* as_global(T* p) {
+    return (__attribute__((address_space(1))) T*)p;
+}
+
 // The base is passed through readfirstlane (a register copy for a value that is already uniform)
 // so that the compiler keeps it apart from the lane offset instead of folding both into one
 // 64-bit vector address.
@@ -548,7 +556,8 @@ __device__ __forceinline__ void load_full(LaneIO<VEC>& x, const TensorDev& T, in
 // exists", each became a branch with a wait behind its load, and the list of 25 small odd sizes spent most of its
 // kernel time in this chain of about 40 loads.  cnt >= 1: a lane without elements has no last one, its caller reads nothing.
 template <int N, typename T>
-__device__ __forceinline__ void load_elements(T (&e)[N], const T* p, int cnt) {
+__device__ __forceinline__ void load_elements(T (&e)[N], const T* elements, int cnt) {
+    const auto p = as_global(elements);
 #pragma unroll
     for (int i = 0; i < N; ++i) e[i] = p[i < cnt ? i : cnt - 1];
 #pragma unroll
@@ -582,10 +591,10 @@ __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, in
     }
     if constexpr (QUANT) {
         load_elements(mq, reinterpret_cast<const uint8_t*>(T.m_q) + off, cnt);
-        x.ms = T.m_scale[off >> 5];
+        x.ms = as_global(T.m_scale)[off >> 5];
         if constexpr (HAS_V) {
             load_elements(vq, T.v_q + off, cnt);
-            x.vs = T.v_scale[off >> 5];
+            x.vs = as_global(T.v_scale)[off >> 5];
         }
     } else {
         load_elements(x.m32, T.m32 + off, cnt);
@@ -629,10 +638,10 @@ __device__ __forceinline__ void store_full(const LaneIO<VEC>& y, const TensorDev
 template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void store_tail(const LaneIO<VEC>& y, const TensorDev& T, int64_t off, int cnt,
                                            bool group_leader) {
-    uint16_t* p = reinterpret_cast<uint16_t*>(T.param) + off;
-    uint8_t* r = reinterpret_cast<uint8_t*>(T.rho) + off;
-    uint8_t* mq = reinterpret_cast<uint8_t*>(T.m_q) + off;
-    uint8_t* vq = T.v_q + off;
+    const auto p = as_global(reinterpret_cast<uint16_t*>(T.param)) + off;
+    const auto r = as_global(reinterpret_cast<uint8_t*>(T.rho)) + off;
+    const auto mq = as_global(reinterpret_cast<uint8_t*>(T.m_q)) + off;
+    const auto vq = as_global(T.v_q) + off;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
         if (i < cnt) {
@@ -640,20 +649,20 @@ __device__ __forceinline__ void store_tail(const LaneIO<VEC>& y, const TensorDev
                 p[i] = (uint16_t)(y.p[i >> 1] >> (16 * (i & 1)));
                 r[i] = (uint8_t)(y.r[i >> 2] >> (8 * (i & 3)));
             } else {
-                T.theta32[off + i] = y.th32[i];
+                as_global(T.theta32)[off + i] = y.th32[i];
             }
             if (QUANT) {
                 mq[i] = (uint8_t)(y.mq[i >> 2] >> (8 * (i & 3)));
                 if (HAS_V) vq[i] = (uint8_t)(y.vq[i >> 2] >> (8 * (i & 3)));
             } else {
-                T.m32[off + i] = y.m32[i];
-                if (HAS_V) T.v32[off + i] = y.v32[i];
+                as_global(T.m32)[off + i] = y.m32[i];
+                if (HAS_V) as_global(T.v32)[off + i] = y.v32[i];
             }
         }
     }
     if (QUANT && group_leader && cnt > 0) {
-        T.m_scale[off >> 5] = (uint16_t)y.ms;
-        if (HAS_V) T.v_scale[off >> 5] = (uint16_t)y.vs;
+        as_global(T.m_scale)[off >> 5] = (uint16_t)y.ms;
+        if (HAS_V) as_global(T.v_scale)[off >> 5] = (uint16_t)y.vs;
     }
 }
 
@@ -1114,7 +1123,7 @@ __device__ __forceinline__ void store_f32(float* p, const LanePos& L, const floa
     if (L.cnt == kCodecVec) {
         gst_floats(gbase(p, 4 * L.tile0), 4u * block_local(L.lane_el), f);
     } else {
-        float* q = p + L.tile0 + L.lane_el;
+        const auto q = as_global(p) + L.tile0 + L.lane_el;
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) if (i < L.cnt) q[i] = f[i];
     }
@@ -1135,7 +1144,7 @@ __device__ __forceinline__ void store_u16(void* p, const LanePos& L, const uint3
     if (L.cnt == kCodecVec) {
         gst_words(gbase(p, 2 * L.tile0), 2u * block_local(L.lane_el), w);
     } else {
-        uint16_t* q = reinterpret_cast<uint16_t*>(p) + L.tile0 + L.lane_el;
+        const auto q = as_global(reinterpret_cast<uint16_t*>(p)) + L.tile0 + L.lane_el;
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) if (i < L.cnt) q[i] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
     }
@@ -1156,7 +1165,7 @@ __device__ __forceinline__ void store_u8(void* p, const LanePos& L, const uint32
     if (L.cnt == kCodecVec) {
         gst_words(gbase(p, L.tile0), block_local(L.lane_el), w);
     } else {
-        uint8_t* q = reinterpret_cast<uint8_t*>(p) + L.tile0 + L.lane_el;
+        const auto q = as_global(reinterpret_cast<uint8_t*>(p)) + L.tile0 + L.lane_el;
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) if (i < L.cnt) q[i] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
     }
@@ -1483,7 +1492,7 @@ __device__ __forceinline__ void quantize_tile(const float* x, uint8_t* q, uint16
         uint32_t w[kCodecVec / 4];
         const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v[r], w);
         if (L.cnt > 0) store_u8(q, L, w);
-        if (group_leader(L)) scale[(L.tile0 + L.lane_el) >> 5] = (uint16_t)sbits;
+        if (group_leader(L)) as_global(scale)[(L.tile0 + L.lane_el) >> 5] = (uint16_t)sbits;
     }
 }
 template <bool VARIANCE, bool LINEAR>
@@ -1495,7 +1504,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* x, uint
 }
 
 __device__ __forceinline__ float load_scale(const uint16_t* scale, const LanePos& L) {
-    return L.cnt > 0 ? (float)__builtin_bit_cast(_Float16, scale[(L.tile0 + L.lane_el) >> 5]) : 0.0f;
+    return L.cnt > 0 ? (float)__builtin_bit_cast(_Float16, (uint16_t)as_global(scale)[(L.tile0 + L.lane_el) >> 5]) : 0.0f;
 }
 
 template <bool VARIANCE, bool LINEAR, bool FULL>
@@ -1738,11 +1747,11 @@ __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0)
         }
         const uint32_t ms = quantize_lane<false, false>(m[r], w);
         if (L.cnt > 0) store_u8(T.m_q, L, w);
-        if (group_leader(L)) T.m_scale[group] = (uint16_t)ms;
+        if (group_leader(L)) as_global(T.m_scale)[group] = (uint16_t)ms;
         if (HAS_V) {
             const uint32_t vs = quantize_lane<true, false>(v[r], w);
             if (L.cnt > 0) store_u8(T.v_q, L, w);
-            if (group_leader(L)) T.v_scale[group] = (uint16_t)vs;
+            if (group_leader(L)) as_global(T.v_scale)[group] = (uint16_t)vs;
         }
     }
 }
