@@ -288,21 +288,11 @@ struct DecodeTables {
     float rho[256];    // (float)(int8)i / 127
     float m[256];      // phi_m^-1((float)(int8)i / 127)
     float v[256];      // (float)i / 255
-    float half_ulp[256];   // 2^l, l = max(E,1) - 135: half the BF16 ULP of a value with exponent field E
-    float2 split[256];     // {2^h, 127 * 2^(-l-h)}, h = floor(-l/2): the two scalings of Algorithm 1's encoder
 };
-
-constexpr float pow2_const(int k) {     // 2^k, exact for -149 <= k <= 127
-    float x = 1.0f;
-    for (int i = 0; i < k; ++i) x *= 2.0f;
-    for (int i = 0; i > k; --i) x *= 0.5f;
-    return x;
-}
 
 // All tables are compile-time constants.  The compiler evaluates constant expressions in
 // IEEE binary32 with round-to-nearest-even, so every entry is the result of the same single
-// divisions the definitions prescribe (the decoders of Algorithms 1, 2 and 3); the powers of two
-// are exact.
+// divisions the definitions prescribe (the decoders of Algorithms 1, 2 and 3).
 constexpr DecodeTables make_decode_tables() {
     DecodeTables t{};
     for (int i = 0; i < 256; ++i) {
@@ -312,78 +302,85 @@ constexpr DecodeTables make_decode_tables() {
         t.rho[i] = z;
         t.m[i] = z / (2.0f - az);
         t.v[i] = (float)i / 255.0f;
-        const int l = (i < 1 ? 1 : i) - 135;
-        const int h = (-l >= 0) ? (-l) / 2 : -((l + 1) / 2);    // floor(-l / 2)
-        t.half_ulp[i] = pow2_const(l);
-        t.split[i].x = pow2_const(h);
-        t.split[i].y = 127.0f * pow2_const(-l - h);
     }
     return t;
 }
 __device__ const DecodeTables g_decode_tables = make_decode_tables();
 
-// Each workgroup stages the tables (6 KB, L2-resident) into LDS: one entry per lane per table.
-// With 512 lanes the two halves of the workgroup share the work.  The staging is split into its
-// load half and its store half so that a kernel can issue the loads first of all (they depend on
-// nothing) and store to LDS only after it has issued its streaming loads.
-struct TableEntries {
-    float rho, m, v, half_ulp;
-    float2 split;
+// A step's workgroup stages the tables that its variant reads (up to 3 KB, L2-resident) into LDS: rho (SPLIT), m
+// (QUANT), v (QUANT with a variance).  256 lanes load an entry of each; of 512, the lower half loads rho and v, the upper
+// m.  The staging is split into its load half and its store half so that a kernel can issue the loads first of all (they
+// depend on nothing) and store to LDS only after it has issued its streaming loads.
+struct StepTables {
+    float rho_scaled[256];    // rho / 127 * 2^-8 (exact), see reconstruct_fast
+    float m[256];
+    float v[256];
 };
-template <int THREADS>
+struct TableEntries {
+    float rho, m, v;
+};
+template <int THREADS, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_table_entries(TableEntries& e, int tid) {
     static_assert(THREADS == 256 || THREADS == 512, "");
     // scalar base + 32-bit lane offset, so that no 64-bit address arithmetic lands on the vector ALU
     typedef const __attribute__((address_space(1))) uint8_t* base_t;
     typedef const __attribute__((address_space(1))) float* fptr_t;
-    typedef float f2_t __attribute__((ext_vector_type(2)));
-    typedef const __attribute__((address_space(1))) f2_t* f2ptr_t;
     const base_t base = (base_t)&g_decode_tables;
     const uint32_t o4 = (uint32_t)(tid & 255) * 4u;
     if (THREADS == 256 || tid < 256) {
-        e.rho = *(fptr_t)(base + offsetof(DecodeTables, rho) + o4);
-        e.m = *(fptr_t)(base + offsetof(DecodeTables, m) + o4);
-        e.v = *(fptr_t)(base + offsetof(DecodeTables, v) + o4);
+        if (SPLIT) e.rho = *(fptr_t)(base + offsetof(DecodeTables, rho) + o4);
+        if (QUANT && HAS_V) e.v = *(fptr_t)(base + offsetof(DecodeTables, v) + o4);
     }
     if (THREADS == 256 || tid >= 256) {
-        e.half_ulp = *(fptr_t)(base + offsetof(DecodeTables, half_ulp) + o4);
-        const f2_t sp = *(f2ptr_t)(base + offsetof(DecodeTables, split) + (o4 + o4));
-        e.split = make_float2(sp[0], sp[1]);
+        if (QUANT) e.m = *(fptr_t)(base + offsetof(DecodeTables, m) + o4);
     }
 }
-template <int THREADS>
-__device__ __forceinline__ void store_table_entries(DecodeTables& t, const TableEntries& e, int tid) {
+template <int THREADS, bool HAS_V, bool SPLIT, bool QUANT>
+__device__ __forceinline__ void store_table_entries(StepTables& t, const TableEntries& e, int tid) {
     const int i = tid & 255;
     if (THREADS == 256 || tid < 256) {
-        t.rho[i] = e.rho;
-        t.m[i] = e.m;
-        t.v[i] = e.v;
+        if (SPLIT) t.rho_scaled[i] = e.rho * 0.00390625f;
+        if (QUANT && HAS_V) t.v[i] = e.v;
     }
     if (THREADS == 256 || tid >= 256) {
-        t.half_ulp[i] = e.half_ulp;
-        t.split[i] = e.split;
+        if (QUANT) t.m[i] = e.m;
     }
 }
 
-// In-kernel forms of C^-1 and of the rho half of C through the LDS tables.  E is the exponent
-// field of theta' (bits 7..14 of its BF16 pattern).
-//   C^-1: theta_hat = theta' + q * 2^l.  The product is exact, or rounds once when it is
-//         subnormal - exactly what the two-factor form in Algorithm 1's decoder does.
-//   C:    rho = Round(((e * 2^h) * (127 * 2^(-l-h)))): both products are exact (e has at most
-//         16 significant bits below theta'), so this is Round(e_norm * 127).  For a finite
-//         theta' the clamp of Algorithm 1 is the identity (|e| <= 2^l under round-to-nearest);
-//         for theta' = +-inf the products are +-inf or NaN and the low mantissa byte of
-//         (+-inf or NaN) + 1.5 * 2^23 is 0.
-__device__ __forceinline__ float reconstruct_lds(const DecodeTables& t, uint32_t E, float base, float q) {
-    return base + (q * t.half_ulp[E]);
+// In-kernel forms of C^-1 and of the rho half of C (Algorithm 1).  E is the exponent field of theta', 2^l half the BF16
+// ULP of theta' (l = E - 135 for E >= 1), q = rho / 127; `base` and `t` are theta' as FP32.
+//   C^-1: theta_hat = theta' + q * 2^l, the product rounded if it is subnormal (what the two-factor form in Algorithm 1's
+//         decoder does).  With the exponent field of theta' as a float of its own, 2^(E-127), and q * 2^-8 from the table,
+//         the product is the same one; it is exact, and one fused multiply-add gives the sum, if E >= 16.
+//   C:    rho = Round(e_norm * 127) with e_norm = e * 2^-l.  127 * 2^-l is a float for 15 <= E: its bits follow from those
+//         of theta' by one subtraction.  e has at most 16 significant bits below theta', so e * (127 * 2^-l) is exact, and
+//         adding the rounding constant inside the fused multiply-add rounds the value that Round() would.  For a finite
+//         theta' the clamp of Algorithm 1 is the identity (|e| <= 2^l under round-to-nearest); for theta' = +-inf the
+//         product is +-inf or NaN and the low byte of (+-inf or NaN) + 1.5 * 2^23 is 0.
+// Callers take these forms where every weight of the wavefront has a magnitude of at least kSplitFastLo = 2^-110, hence
+// E >= 16, before and after the update; otherwise (zero weights, above all) the general forms below, with the same bits
+// where both apply.  A theta' of +-inf passes only with a rho that leaves it infinite: 0 * inf and inf - inf are NaN, which
+// the test refuses.
+// (These took tables of 2^l and of the encoder's two factors, indexed by E: two look-ups and two instructions more per element.)
+constexpr float kSplitFastLo = 7.703719777548943e-34f;    // 2^-110
+__device__ __forceinline__ float reconstruct_fast(float base, float q_scaled) {
+    return fmaf(q_scaled, u2f(f2u(base) & 0x7f800000u), base);
 }
-__device__ __forceinline__ uint32_t rho_bits_lds(const DecodeTables& t, float theta, uint32_t b16, uint32_t E) {
-    const float e = theta - u2f(b16 << 16);
-    const float2 sc = t.split[E];
-    // (e * sc.x) * sc.y is exact, so adding the rounding constant inside one fused multiply-add rounds the same
-    // value as Round() of the product would
-    return f2u(fmaf(e * sc.x, sc.y, 12582912.0f));
+__device__ __forceinline__ float reconstruct_general(float base, float q_scaled) {
+    const int E = (int)((f2u(base) >> 23) & 0xffu);
+    return base + ldexpf(q_scaled, (E < 1 ? 1 : E) - 127);
 }
+__device__ __forceinline__ uint32_t rho_bits_fast(float theta, float t) {
+    const float scale = u2f(0x867e0000u - (f2u(t) & 0x7f800000u));     // 127 * 2^(135 - E)
+    return f2u(fmaf(theta - t, scale, 12582912.0f));
+}
+__device__ __forceinline__ uint32_t rho_bits_general(float theta, float t) {
+    const int E = (int)((f2u(t) >> 23) & 0xffu);
+    const float y = ldexpf(theta - t, 135 - (E < 1 ? 1 : E)) * 127.0f;
+    return E == 255 ? 0u : round_to_int_bits(y);
+}
+// Minimum that is NaN if either operand is (one v_minimum3_f32 for two of them).
+__device__ __forceinline__ float min_or_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 
 // -------------------------------------------------------------- lane vectors --
 //
@@ -441,6 +438,12 @@ __device__ __forceinline__ gptr_t gbase(void* p, int64_t byte_off) {
 __device__ __forceinline__ uint32_t block_local(uint32_t v) {
     asm volatile("" : "+v"(v));
     return v;
+}
+
+// Element i of packed BF16 values, as FP32.
+template <int N>
+__device__ __forceinline__ float bf16_of(const uint32_t (&w)[N], int i) {
+    return (i & 1) ? u2f(w[i >> 1] & 0xffff0000u) : u2f(w[i >> 1] << 16);
 }
 
 // 4 * N bytes from / to base + byte_off (4N-byte aligned, N <= 4)
@@ -579,6 +582,10 @@ __device__ __forceinline__ void pack_elements(uint32_t (&w)[N / 2], const uint16
 template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, int64_t off, int cnt) {
     x = LaneIO<VEC>{};
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int j = 0; j < VEC / 2; ++j) x.p[j] = 0x3f803f80u;
+    }
     if (cnt == 0) return;
     uint16_t g[VEC], p[VEC];
     uint8_t r[VEC], mq[VEC], vq[VEC];
@@ -602,6 +609,8 @@ __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, in
     }
     pack_elements(x.g, g);
     if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) if (i >= cnt) p[i] = 0x3f80u;
         pack_elements(x.p, p);
         pack_elements(x.r, r);
     }
@@ -668,21 +677,49 @@ __device__ __forceinline__ void store_tail(const LaneIO<VEC>& y, const TensorDev
 
 // ------------------------------------------------------- the per-lane update --
 //
-// Splits (or stores as FP32) the four new master weights of block j of a lane.
+// Splits (or stores as FP32) the new master weights of a lane.
 template <int VEC, bool SPLIT>
-__device__ __forceinline__ void split_block(LaneIO<VEC>& y, const DecodeTables& tab, const float (&tht)[4], int j) {
-    if (SPLIT) {
-        const uint32_t w0 = bf16_pack(tht[0], tht[1]), w1 = bf16_pack(tht[2], tht[3]);
-        y.p[2 * j] = w0;
-        y.p[2 * j + 1] = w1;
-        const uint32_t e0 = w0 << 1, e1 = w1 << 1;     // exponent fields on byte boundaries
-        y.r[j] = pack_low_bytes(rho_bits_lds(tab, tht[0], w0 & 0xffffu, (e0 >> 8) & 0xffu),
-                                rho_bits_lds(tab, tht[1], w0 >> 16, e0 >> 24),
-                                rho_bits_lds(tab, tht[2], w1 & 0xffffu, (e1 >> 8) & 0xffu),
-                                rho_bits_lds(tab, tht[3], w1 >> 16, e1 >> 24));
+__device__ __forceinline__ void split_lane(LaneIO<VEC>& y, const float (&tht)[VEC]) {
+    if constexpr (SPLIT) {
+        float lowest = 3.0e38f;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) lowest = min_or_nan(lowest, fabsf(tht[i]));
+#pragma unroll
+        for (int j = 0; j < VEC / 2; ++j) y.p[j] = bf16_pack(tht[2 * j], tht[2 * j + 1]);
+        uint32_t c[VEC];
+        if (!any_lane(!(lowest >= kSplitFastLo))) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) c[i] = rho_bits_fast(tht[i], bf16_of(y.p, i));
+        } else {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) c[i] = rho_bits_general(tht[i], bf16_of(y.p, i));
+        }
+#pragma unroll
+        for (int j = 0; j < VEC / 4; ++j) y.r[j] = pack_low_bytes(c[4 * j], c[4 * j + 1], c[4 * j + 2], c[4 * j + 3]);
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) y.th32[4 * j + k] = tht[k];
+        for (int i = 0; i < VEC; ++i) y.th32[i] = tht[i];
+    }
+}
+
+// The master weights of a lane.
+template <int VEC, bool SPLIT>
+__device__ __forceinline__ void master_weights(const LaneIO<VEC>& x, const StepTables& tab, float (&th)[VEC]) {
+    if constexpr (SPLIT) {
+        float q[VEC], lowest = 3.0e38f;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            q[i] = tab.rho_scaled[(x.r[i >> 2] >> (8 * (i & 3))) & 0xffu];
+            th[i] = reconstruct_fast(bf16_of(x.p, i), q[i]);
+            lowest = min_or_nan(lowest, fabsf(th[i]));
+        }
+        if (any_lane(!(lowest >= kSplitFastLo))) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) th[i] = reconstruct_general(bf16_of(x.p, i), q[i]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) th[i] = x.th32[i];
     }
 }
 
@@ -694,9 +731,10 @@ __device__ __forceinline__ void split_block(LaneIO<VEC>& y, const DecodeTables& 
 // EXACT (AdamW only): the quotient m_hat / (sqrt(v_hat) + eps) is the correctly rounded one for every
 // input; otherwise it is the faithful form above.  Everything else, the square root, the state codes and
 // the scales included, is exact in both modes.
-template <int KIND, int VEC, bool SPLIT, bool QUANT, bool EXACT>
-__device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y, const DecodeTables& tab,
-                                            const StepConsts& c, float lr, float wd) {
+// cnt: the elements of the lane that exist (VEC where FULL).
+template <int KIND, int VEC, bool SPLIT, bool QUANT, bool EXACT, bool FULL>
+__device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y, const StepTables& tab,
+                                            const StepConsts& c, float lr, float wd, int cnt) {
     constexpr bool HAS_V = (KIND == 0);
     const float s_m = QUANT ? (float)__builtin_bit_cast(_Float16, (uint16_t)x.ms) : 0.0f;
     const float s_v = (QUANT && HAS_V) ? (float)__builtin_bit_cast(_Float16, (uint16_t)x.vs) : 0.0f;
@@ -704,70 +742,48 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
     float mt[VEC];    // new momentum
     float vt[VEC];    // new variance (AdamW)
     float rh[VEC];    // sqrt of the bias-corrected new variance (AdamW)
-    float tha[VEC];   // AdamW: master weights, held until the range tests below are known
+    float th[VEC];    // master weights, replaced by the new ones
     float amax_m = 0.0f, amax_v = 0.0f;
     float amin_m = 3.0e38f, amin_v = 3.0e38f;     // AdamW: smallest |m_t| and v_t of the lane
     bool fast = false;                            // AdamW: the wavefront takes the short square root and division
 
+    // prologue: reconstruct master weights and optimizer state
+    master_weights<VEC, SPLIT>(x, tab, th);
 #pragma unroll
-    for (int j = 0; j < VEC / 4; ++j) {
-        // four elements at a time (one word of each byte stream)
-        float tht[4];     // new master weights of this block (SGD, Lion)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = 4 * j + k;
-            const uint32_t gw = x.g[i >> 1];
-            const float g = (i & 1) ? u2f(gw & 0xffff0000u) : u2f(gw << 16);
-            // prologue: reconstruct optimizer state and master weight
-            float m, th;
+    for (int i = 0; i < VEC; ++i) {
+        const float g = bf16_of(x.g, i);
+        float m;
+        if (QUANT) m = tab.m[(x.mq[i >> 2] >> (8 * (i & 3))) & 0xffu] * s_m;       // Q_m^-1
+        else m = x.m32[i];
+        float m_new;
+        if (KIND == 0) {
+            float v;
             if (QUANT) {
-                const uint32_t mb = (x.mq[j] >> (8 * k)) & 0xffu;
-                m = tab.m[mb] * s_m;                                 // Q_m^-1
+                const float v1 = tab.v[(x.vq[i >> 2] >> (8 * (i & 3))) & 0xffu] * s_v;     // Q_v^-1
+                v = v1 * v1;
             } else {
-                m = x.m32[i];
+                v = x.v32[i];
             }
-            if (SPLIT) {
-                const uint32_t pw = x.p[i >> 1];
-                // (pair << 1) puts the two exponent fields on byte boundaries (bytes 1 and 3)
-                const uint32_t pE = (i & 1) ? ((pw << 1) >> 24) : (((pw << 1) >> 8) & 0xffu);
-                const float base = (i & 1) ? u2f(pw & 0xffff0000u) : u2f(pw << 16);
-                const uint32_t rb = (x.r[j] >> (8 * k)) & 0xffu;
-                th = reconstruct_lds(tab, pE, base, tab.rho[rb]);    // C^-1
-            } else {
-                th = x.th32[i];
-            }
-            float m_new;
-            if (KIND == 0) {
-                float v;
-                if (QUANT) {
-                    const uint32_t vb = (x.vq[j] >> (8 * k)) & 0xffu;
-                    const float v1 = tab.v[vb] * s_v;                // Q_v^-1
-                    v = v1 * v1;
-                } else {
-                    v = x.v32[i];
-                }
-                m_new = (c.beta1 * m) + (c.omb1 * g);
-                const float gg = g * g;
-                const float v_new = (c.beta2 * v) + (c.omb2 * gg);
-                tha[i] = th;
-                vt[i] = v_new;
-                amax_v = fmaxf(amax_v, v_new);
+            m_new = (c.beta1 * m) + (c.omb1 * g);
+            const float gg = g * g;
+            const float v_new = (c.beta2 * v) + (c.omb2 * gg);
+            vt[i] = v_new;
+            amax_v = fmaxf(amax_v, v_new);
+            if (FULL || i < cnt) {          // (an element that does not exist has zero moments)
                 amin_v = fminf(amin_v, v_new);
                 amin_m = fminf(amin_m, fabsf(m_new));
-            } else if (KIND == 1) {
-                m_new = (c.beta1 * m) + g;                           // beta1 carries the momentum mu
-                tht[k] = th - (lr * (m_new + (wd * th)));
-            } else {
-                const float cc = (c.beta1 * m) + (c.omb1 * g);
-                const float u = (cc > 0.0f) ? 1.0f : ((cc < 0.0f) ? -1.0f : 0.0f);
-                m_new = (c.beta2 * m) + (c.omb2 * g);
-                tht[k] = th - (lr * (u + (wd * th)));
             }
-            mt[i] = m_new;
-            amax_m = fmaxf(amax_m, fabsf(m_new));
+        } else if (KIND == 1) {
+            m_new = (c.beta1 * m) + g;                           // beta1 carries the momentum mu
+            th[i] = th[i] - (lr * (m_new + (wd * th[i])));
+        } else {
+            const float cc = (c.beta1 * m) + (c.omb1 * g);
+            const float u = (cc > 0.0f) ? 1.0f : ((cc < 0.0f) ? -1.0f : 0.0f);
+            m_new = (c.beta2 * m) + (c.omb2 * g);
+            th[i] = th[i] - (lr * (u + (wd * th[i])));
         }
-        // epilogue, part 1 (SGD, Lion): split the new master weights of this block
-        if (KIND != 0) split_block<VEC, SPLIT>(y, tab, tht, j);
+        mt[i] = m_new;
+        amax_m = fmaxf(amax_m, fabsf(m_new));
     }
     if (KIND == 0) {
         // One wave-uniform range test, on the raw extremes of every lane, selects the short square root
@@ -784,7 +800,7 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
                  any_lane(!(amax_m <= c.m_max)) | (EXACT ? any_lane(!(amin_m >= kDivFastLo)) : false));
 #pragma unroll
         for (int j = 0; j < VEC / 4; ++j) {
-            float mh4[4], vh4[4], quo[4], tht[4];
+            float mh4[4], vh4[4], quo[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 mh4[k] = mt[4 * j + k] * c.rbc1;
@@ -809,13 +825,13 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float upd = quo[k] + (wd * tha[4 * j + k]);
-                tht[k] = tha[4 * j + k] - (lr * upd);
+                const float upd = quo[k] + (wd * th[4 * j + k]);
+                th[4 * j + k] = th[4 * j + k] - (lr * upd);
             }
-            // epilogue, part 1 (AdamW): split the new master weights of this block
-            split_block<VEC, SPLIT>(y, tab, tht, j);
         }
     }
+    // epilogue, part 1: split the new master weights
+    split_lane<VEC, SPLIT>(y, th);
     if (!QUANT) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
@@ -914,7 +930,7 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
 // (Variants in which a workgroup loads two or four such tiles up front and then updates them in
 // turn - fewer look-ups, more bytes in flight per workgroup - ran at the same rate.)
 template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool FULL>
-__device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& c, DecodeTables& tab,
+__device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& c, StepTables& tab,
                                           const TableEntries& entries, int64_t tile0, int tile_cnt, int tid) {
     constexpr bool HAS_V = (KIND == 0);
     const bool leader = (tid & (kGroup / VEC - 1)) == 0;
@@ -926,12 +942,12 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& 
     if (FULL || cnt == VEC) load_full<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0, lane_el);
     else load_tail<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0 + lane_el, cnt);
     if constexpr (SPLIT || QUANT) {        // the plain FP32 step decodes nothing
-        store_table_entries<THREADS>(tab, entries, tid);
+        store_table_entries<THREADS, HAS_V, SPLIT, QUANT>(tab, entries, tid);
         __syncthreads();
     }
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
-    update_lane<KIND, VEC, SPLIT, QUANT, EXACT>(x, y, tab, c, T.lr, T.wd);
+    update_lane<KIND, VEC, SPLIT, QUANT, EXACT, FULL>(x, y, tab, c, T.lr, T.wd, cnt);
     if (FULL || cnt == VEC) store_full<VEC, HAS_V, SPLIT, QUANT>(y, T, tile0, lane_el, leader);
     else store_tail<VEC, HAS_V, SPLIT, QUANT>(y, T, tile0 + lane_el, cnt, leader);
 }
@@ -943,10 +959,10 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& 
 template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT>
 __global__ __launch_bounds__(THREADS) void step_kernel(StepArgs a) {
     constexpr int kTile = THREADS * VEC;       // elements per workgroup
-    __shared__ DecodeTables tab;
+    __shared__ StepTables tab;
     const int tid = (int)threadIdx.x;
     TableEntries entries;
-    if constexpr (SPLIT || QUANT) load_table_entries<THREADS>(entries, tid);
+    if constexpr (SPLIT || QUANT) load_table_entries<THREADS, KIND == 0, SPLIT, QUANT>(entries, tid);
     TensorDev T;
     uint32_t index = 0;
     const int64_t chunk = locate_tile<DIRECT>(a, T, &index);
