@@ -238,9 +238,9 @@ __device__ __forceinline__ void m_code_bracket(float m, float r, float* lo, floa
     const float m1 = m * r;
     const float den = 1.0f + fabsf(m1);
     const float rc = __builtin_amdgcn_rcpf(den);
-    const float p = fmaxf(m1 * rc, -0.5f);
-    *lo = fmaf(p, 254.0f, 128.0f - kTieWindowM);
-    *hi = fmaf(p, 254.0f, 128.0f + kTieWindowM);
+    const float p = __builtin_amdgcn_fmed3f(fmaf(m1, rc, 0.5f), 0.0f, 1.0f);
+    *lo = fmaf(p, 254.0f, 1.0f - kTieWindowM);
+    *hi = fmaf(p, 254.0f, 1.0f + kTieWindowM);
 }
 
 // Exact Q_v code of one element from v and the reciprocal group scale (Algorithm 3, encoder).
