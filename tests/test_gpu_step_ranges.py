@@ -98,3 +98,24 @@ def test_weights_around_the_range_of_the_short_split(kind, n, weights):
         b.grad.copy_(to_dev_u16(g, torch.bfloat16))
         _step(kind, [b], [st], [g], t, HP)
         _same(b, st, f"{kind} {weights} step {t}")
+
+
+@pytest.mark.parametrize("beta1,steps", [(0.9, (163, 164, 165, 166)), (0.5, (24, 25, 26)), (0.0, (1, 2))])
+def test_steps_around_the_one_from_which_the_momentum_needs_no_correction(beta1, steps):
+    # 1 - beta1^t rounds to 1 in FP32 from t = 165 on for 0.9, from 25 on for 0.5 and always for 0
+    rng = np.random.default_rng(7)
+    states, bufs = [], []
+    for n in (33, 5000, (1 << 20) + 100):
+        thp = rng.normal(0, 0.02, n).astype(np.float32).view(np.uint32) >> 16
+        states.append(_state(rng, n, "adamw", thp))
+        bufs.append(upload_state(states[-1]))
+        bufs[-1].lr, bufs[-1].weight_decay = 1e-3, 0.01
+    for t in steps:
+        grads = []
+        for b in bufs:
+            g = (rng.normal(0, 1e-4, b.numel).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+            b.grad.copy_(to_dev_u16(g, torch.bfloat16))
+            grads.append(g)
+        _step("adamw", bufs, states, grads, t, dict(HP, beta1=beta1))
+        for b, st in zip(bufs, states):
+            _same(b, st, f"beta1 {beta1} step {t} numel {st.n}")
