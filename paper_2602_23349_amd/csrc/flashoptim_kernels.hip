@@ -918,6 +918,10 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
     }
     uint32_t t = a.coarse[b >> a.coarse_shift];
     T = a.tensors[t];
+    // (an empty asm statement that takes every field: the descriptor is loaded as a whole, instead of its range first and,
+    // after the test, the rest)
+    asm("" : "+s"(T.n_tiles) : "s"(T.param), "s"(T.rho), "s"(T.grad), "s"(T.m_q), "s"(T.m_scale), "s"(T.v_q), "s"(T.v_scale),
+        "s"(T.theta32), "s"(T.m32), "s"(T.v32), "s"(T.numel), "s"(T.lr), "s"(T.wd));
     while (b - T.first_tile >= T.n_tiles && t + 1 < a.n_tensors) {
         ++t;
         T = a.tensors[t];
@@ -931,7 +935,7 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
 // (Variants in which a workgroup loads two or four such tiles up front and then updates them in
 // turn - fewer look-ups, more bytes in flight per workgroup - ran at the same rate.)
 template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool FULL>
-__device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& c, StepTables& tab,
+__device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a, StepTables& tab,
                                           const TableEntries& entries, int64_t tile0, int tile_cnt, int tid) {
     constexpr bool HAS_V = (KIND == 0);
     const bool leader = (tid & (kGroup / VEC - 1)) == 0;
@@ -946,6 +950,9 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepConsts& 
         store_table_entries<THREADS, HAS_V, SPLIT, QUANT>(tab, entries, tid);
         __syncthreads();
     }
+    StepConsts c = a.c;
+    // One scalar load, behind the streaming loads: nothing writes the word while a step runs, so it counts as constant.
+    if (KIND == 0) c.sqrt_min = *(const __attribute__((address_space(4))) float*)a.sqrt_min_word;
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
     update_lane<KIND, VEC, SPLIT, QUANT, EXACT, M_HAT, FULL>(x, y, tab, c, T.lr, T.wd, cnt);
@@ -969,21 +976,16 @@ __device__ __forceinline__ void step_workgroup(const StepArgs& a) {
     const int64_t chunk = locate_tile<DIRECT>(a, T, &index);
     const int64_t tile0 = chunk * (int64_t)kTile;              // first element of the tile (wave-uniform)
     const int64_t rem = T.numel - tile0;                       // elements from there to the tensor's end
-    StepConsts c = a.c;
-    if (KIND == 0) c.sqrt_min = *a.sqrt_min_word;              // one scalar load, needed only after the streaming loads; ahead
-                                                               // of the store below, or it would be a vector load
-    if (!DIRECT) {
-        const uint32_t lr = (f2u(T.lr) & a.table_lr_mask) | a.shared_lr_bits;      // (integers: stays on the scalar unit)
-        // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
-        if (chunk == 0 && lr != f2u(T.lr) && tid == 0) a.tensors[index].lr = u2f(lr);
-        T.lr = u2f(lr);
-    }
+    const float table_lr = T.lr;
+    if (!DIRECT) T.lr = u2f((f2u(table_lr) & a.table_lr_mask) | a.shared_lr_bits);      // (integers: stays on the scalar unit)
     if (rem >= kTile) {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, true>(T, c, tab, entries, tile0, kTile, tid);
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, true>(T, a, tab, entries, tile0, kTile, tid);
     } else {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, false>(T, c, tab, entries, tile0,
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, false>(T, a, tab, entries, tile0,
                                                                          rem > 0 ? (int)rem : 0, tid);
     }
+    // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
+    if (!DIRECT && chunk == 0 && f2u(T.lr) != f2u(table_lr) && tid == 0) a.tensors[index].lr = T.lr;
 }
 
 // The kernel is overloaded by the type of its arguments, one overload for each way of doing the same step: AdamW with and
