@@ -361,6 +361,8 @@ hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, b
     for (int64_t first = 0; first < blocks; first += seg) {
         a.block_offset = (uint32_t)first;
         const int64_t n = blocks - first < seg ? blocks - first : seg;
+        a.through = op == kOpCompress || op == kOpDecompress ? fo::convert_through(n * tile_elems)
+                                                             : fo::step_through(kind, split, quant, n * tile_elems);
         const hipError_t e = launch_segment(op, kind, direct, split, quant, small, a, n, stream);
         if (e != hipSuccess) return e;
     }

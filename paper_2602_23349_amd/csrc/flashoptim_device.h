@@ -49,6 +49,27 @@ constexpr int step_threads(int kind, bool split, bool quant, bool small) {
 constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
     return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);
 }
+// Whether the stores of a launch go through to memory at device scope, or stay non-temporal only.  Lines that are passed on
+// as they are written leave the DRAM fewer, larger turns from reading to writing and the end of the kernel nothing to write
+// back.  But lists whose arrays fit the 256 MB memory-side cache with room to spare are faster where their lines may wait.
+// In us, non-temporal -> through:
+//   steps, in place, by the size of their arrays: plain FP32 AdamW over a Llama layer (3 GB) 851 -> 839, four
+//       Llama layers AdamW (14 GB) 3942 -> 3890, one by gradient release 453 -> 450, GPT-2 Lion (0.8 GB) 195.3 -> 194.1, AdamW
+//       over 60 M elements (430 MB) 123.5 -> 122.0, ResNet-50's 25.6 M (182 MB) 54.8 -> 54.3; 24 M (171 MB) 50.5 -> 50.3,
+//       FP32 AdamW over 12 M (168 MB) 51.1 -> 52.1, SGD over 24 M (145 MB) 39.5 -> 40.1, AdamW over 6 M (43 MB) 16.9 -> 17.2;
+//   conversions: GPT-2 compress 339.7 -> 336.2, decompress 342.8 -> 341.8; 25 M elements 70.6 -> 70.4 and 70.6 -> 71.4, 12 M
+//       33.7 -> 34.2 and 35.2 -> 35.7;
+//   codecs, the six of them: 38.6 M elements 215.7 -> 212.1, 12 M 78.4 -> 76.8, 5 M 40.7 -> 40.9.
+constexpr int64_t kThroughBytes = (int64_t)168 << 20;
+constexpr int step_array_bytes(int kind, bool split, bool quant) {      // per element, without the scales
+    return 2 + (split ? 3 : 4) + (kind == 0 ? 2 : 1) * (quant ? 1 : 4);
+}
+constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
+    return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
+}
+constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25); }
+constexpr bool codec_through(int64_t elems) { return elems >= ((int64_t)1 << 23); }
+
 constexpr int kCopyPiece = 16 * 1024;        // checkpoint copy: bytes per workgroup
 constexpr int kHeaderStepAt = 16;            // byte offset of the step (little-endian int64) in a blob's header
 
@@ -111,6 +132,7 @@ struct StepArgs {
     uint32_t table_lr_mask;
     uint32_t shared_lr_bits;
     TensorDev single;           // the one tensor of a direct launch
+    bool through;               // stores go through to memory (step_through, convert_through): per launch
     StepConsts c;
     const float* sqrt_min_word; // AdamW steps: device word that holds StepConsts::sqrt_min for this device
 };

@@ -70,29 +70,14 @@ typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-#ifndef FO_NT_LOAD
-#define FO_NT_LOAD 1
-#endif
-#ifndef FO_NT_STORE
-#define FO_NT_STORE 1
-#endif
-
 // 128-bit global accesses of the streaming data (each byte is touched once per step).
 __device__ __forceinline__ uint4 ld128(const void* p) {
-#if FO_NT_LOAD
     const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-#else
-    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(p);
-#endif
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void st128(void* p, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     const u32x4_t v = {a, b, c, d};
-#if FO_NT_STORE
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p));
-#else
-    *reinterpret_cast<u32x4_t*>(p) = v;
-#endif
 }
 
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
@@ -446,21 +431,26 @@ __device__ __forceinline__ float bf16_of(const uint32_t (&w)[N], int i) {
     return (i & 1) ? u2f(w[i >> 1] & 0xffff0000u) : u2f(w[i >> 1] << 16);
 }
 
+// Stores of the streaming data are non-temporal, and where THROUGH at device scope (sc1) on top of that: a line then goes on
+// to memory as it is written, instead of when the L2 needs its place or the kernel ends.  The launches say which (see
+// step_through).  Only the buffer instructions let a program choose (aux: bit 1 nt, bit 4 sc1); the descriptor holds the
+// base, no upper bound (the callers' lanes are known to exist) and 32-bit raw data.
+constexpr int kNonTemporalThrough = 2 | 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t store_rsrc(gptr_t base) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000);
+}
+
 // 4 * N bytes from / to base + byte_off (4N-byte aligned, N <= 4)
 template <int N>
 __device__ __forceinline__ void gld(uint32_t (&w)[N], gcptr_t base, uint32_t byte_off) {
     static_assert(N == 1 || N == 2 || N == 4, "");
     typedef uint32_t vec_t __attribute__((ext_vector_type(N)));
     typedef const __attribute__((address_space(1))) vec_t* vptr_t;
-#if FO_NT_LOAD
     const vec_t v = __builtin_nontemporal_load((vptr_t)(base + byte_off));
-#else
-    const vec_t v = *(vptr_t)(base + byte_off);
-#endif
 #pragma unroll
     for (int k = 0; k < N; ++k) w[k] = v[k];
 }
-template <int N>
+template <bool THROUGH, int N>
 __device__ __forceinline__ void gst(gptr_t base, uint32_t byte_off, const uint32_t (&w)[N]) {
     static_assert(N == 1 || N == 2 || N == 4, "");
     typedef uint32_t vec_t __attribute__((ext_vector_type(N)));
@@ -468,11 +458,10 @@ __device__ __forceinline__ void gst(gptr_t base, uint32_t byte_off, const uint32
     vec_t v;
 #pragma unroll
     for (int k = 0; k < N; ++k) v[k] = w[k];
-#if FO_NT_STORE
-    __builtin_nontemporal_store(v, (vptr_t)(base + byte_off));
-#else
-    *(vptr_t)(base + byte_off) = v;
-#endif
+    if constexpr (!THROUGH) __builtin_nontemporal_store(v, (vptr_t)(base + byte_off));
+    else if constexpr (N == 1) __builtin_amdgcn_raw_buffer_store_b32(w[0], store_rsrc(base), byte_off, 0, kNonTemporalThrough);
+    else if constexpr (N == 2) __builtin_amdgcn_raw_buffer_store_b64(v, store_rsrc(base), byte_off, 0, kNonTemporalThrough);
+    else __builtin_amdgcn_raw_buffer_store_b128(v, store_rsrc(base), byte_off, 0, kNonTemporalThrough);
 }
 // 4 * N bytes as consecutive 16-byte (or one 8-byte) accesses
 template <int N>
@@ -489,36 +478,29 @@ __device__ __forceinline__ void gld_words(uint32_t (&w)[N], gcptr_t base, uint32
         }
     }
 }
-template <int N>
+template <bool THROUGH, int N>
 __device__ __forceinline__ void gst_words(gptr_t base, uint32_t byte_off, const uint32_t (&w)[N]) {
     if constexpr (N <= 4) {
-        gst(base, byte_off, w);
+        gst<THROUGH>(base, byte_off, w);
     } else {
         static_assert(N % 4 == 0, "");
 #pragma unroll
         for (int k = 0; k < N / 4; ++k) {
             const uint32_t t[4] = {w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
-            gst(base, byte_off + 16u * k, t);
+            gst<THROUGH>(base, byte_off + 16u * k, t);
         }
     }
 }
 // FP32 streams: four floats per lane, so that one access of a wavefront covers 1 KB of consecutive bytes.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void gld_floats(float (&f)[4], gcptr_t base, uint32_t byte_off) {
-#if FO_NT_LOAD
     const f32x4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) f32x4_t*)(base + byte_off));
-#else
-    const f32x4_t v = *(const __attribute__((address_space(1))) f32x4_t*)(base + byte_off);
-#endif
     f[0] = v[0]; f[1] = v[1]; f[2] = v[2]; f[3] = v[3];
 }
+template <bool THROUGH>
 __device__ __forceinline__ void gst_floats(gptr_t base, uint32_t byte_off, const float (&f)[4]) {
-    const f32x4_t v = {f[0], f[1], f[2], f[3]};
-#if FO_NT_STORE
-    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) f32x4_t*)(base + byte_off));
-#else
-    *(__attribute__((address_space(1))) f32x4_t*)(base + byte_off) = v;
-#endif
+    const uint32_t w[4] = {f2u(f[0]), f2u(f[1]), f2u(f[2]), f2u(f[3])};
+    gst<THROUGH>(base, byte_off, w);
 }
 __device__ __forceinline__ uint32_t gld_u16(gcptr_t base, uint32_t byte_off) {
     return *(const __attribute__((address_space(1))) uint16_t*)(base + byte_off);
@@ -620,27 +602,27 @@ __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, in
     }
 }
 
-template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
+template <int VEC, bool HAS_V, bool SPLIT, bool QUANT, bool THROUGH>
 __device__ __forceinline__ void store_full(const LaneIO<VEC>& y, const TensorDev& T, int64_t tile0, uint32_t lane_el,
                                            bool group_leader) {
     lane_el = block_local(lane_el);
     if constexpr (SPLIT) {
-        gst_words(gbase(T.param, 2 * tile0), 2u * lane_el, y.p);
-        gst_words(gbase(T.rho, tile0), lane_el, y.r);
+        gst_words<THROUGH>(gbase(T.param, 2 * tile0), 2u * lane_el, y.p);
+        gst_words<THROUGH>(gbase(T.rho, tile0), lane_el, y.r);
     } else {
-        gst_floats(gbase(T.theta32, 4 * tile0), 4u * lane_el, y.th32);
+        gst_floats<THROUGH>(gbase(T.theta32, 4 * tile0), 4u * lane_el, y.th32);
     }
     if constexpr (QUANT) {
-        gst_words(gbase(T.m_q, tile0), lane_el, y.mq);
-        if (HAS_V) gst_words(gbase(T.v_q, tile0), lane_el, y.vq);
+        gst_words<THROUGH>(gbase(T.m_q, tile0), lane_el, y.mq);
+        if (HAS_V) gst_words<THROUGH>(gbase(T.v_q, tile0), lane_el, y.vq);
         if (group_leader) {
             const uint32_t scale_off = (lane_el >> 5) * 2u;
             gst_u16(gbase(T.m_scale, (tile0 >> 5) * 2), scale_off, y.ms);
             if (HAS_V) gst_u16(gbase(T.v_scale, (tile0 >> 5) * 2), scale_off, y.vs);
         }
     } else {
-        gst_floats(gbase(T.m32, 4 * tile0), 4u * lane_el, y.m32);
-        if constexpr (HAS_V) gst_floats(gbase(T.v32, 4 * tile0), 4u * lane_el, y.v32);
+        gst_floats<THROUGH>(gbase(T.m32, 4 * tile0), 4u * lane_el, y.m32);
+        if constexpr (HAS_V) gst_floats<THROUGH>(gbase(T.v32, 4 * tile0), 4u * lane_el, y.v32);
     }
 }
 
@@ -934,7 +916,7 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
 // tensor but possibly its last); the code then has no per-lane case distinction at all.
 // (Variants in which a workgroup loads two or four such tiles up front and then updates them in
 // turn - fewer look-ups, more bytes in flight per workgroup - ran at the same rate.)
-template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool FULL>
+template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool THROUGH, bool FULL>
 __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a, StepTables& tab,
                                           const TableEntries& entries, int64_t tile0, int tile_cnt, int tid) {
     constexpr bool HAS_V = (KIND == 0);
@@ -956,7 +938,7 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a,
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
     update_lane<KIND, VEC, SPLIT, QUANT, EXACT, M_HAT, FULL>(x, y, tab, c, T.lr, T.wd, cnt);
-    if (FULL || cnt == VEC) store_full<VEC, HAS_V, SPLIT, QUANT>(y, T, tile0, lane_el, leader);
+    if (FULL || cnt == VEC) store_full<VEC, HAS_V, SPLIT, QUANT, THROUGH>(y, T, tile0, lane_el, leader);
     else store_tail<VEC, HAS_V, SPLIT, QUANT>(y, T, tile0 + lane_el, cnt, leader);
 }
 
@@ -964,7 +946,7 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a,
 // over many tiles were measured 10 % slower: an iteration's loads then wait behind the previous
 // iteration's stores).  Order of issue: decode-table loads, the (tensor, tile) look-up, the
 // streaming loads; then the tables go to LDS.
-template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT>
+template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool THROUGH>
 __device__ __forceinline__ void step_workgroup(const StepArgs& a) {
     constexpr int kTile = THREADS * VEC;       // elements per workgroup
     __shared__ StepTables tab;
@@ -979,39 +961,49 @@ __device__ __forceinline__ void step_workgroup(const StepArgs& a) {
     const float table_lr = T.lr;
     if (!DIRECT) T.lr = u2f((f2u(table_lr) & a.table_lr_mask) | a.shared_lr_bits);      // (integers: stays on the scalar unit)
     if (rem >= kTile) {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, true>(T, a, tab, entries, tile0, kTile, tid);
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, true>(T, a, tab, entries, tile0, kTile, tid);
     } else {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, false>(T, a, tab, entries, tile0,
-                                                                         rem > 0 ? (int)rem : 0, tid);
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, false>(T, a, tab, entries, tile0,
+                                                                                  rem > 0 ? (int)rem : 0, tid);
     }
     // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
     if (!DIRECT && chunk == 0 && f2u(T.lr) != f2u(table_lr) && tid == 0) a.tensors[index].lr = T.lr;
 }
 
 // The kernel is overloaded by the type of its arguments, one overload for each way of doing the same step: AdamW with and
-// without a bias correction of the momentum that is not 1.  An instruction per element less is 0.3-0.9 % of a step's time
-// (GPT-2 253.0 -> 251.9 us, Llama layer 445.6 -> 441.9).
-template <bool M_HAT>
+// without a bias correction of the momentum that is not 1 (an instruction per element less is 0.3-0.9 % of a step's time:
+// GPT-2 253.0 -> 251.9 us, Llama layer 445.6 -> 441.9), and either kind of stores (a branch in the kernel instead costs plain
+// FP32 steps over a few million elements 1 %).
+template <bool M_HAT, bool THROUGH>
 struct VariantArgs : StepArgs {
     explicit VariantArgs(const StepArgs& a) : StepArgs(a) {}
 };
-#define FO_STEP_KERNEL(M_HAT)                                                                              \
+#define FO_STEP_KERNEL(M_HAT, THROUGH)                                                                     \
     template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT>             \
-    __global__ __launch_bounds__(THREADS) void step_kernel(VariantArgs<M_HAT> a) {                         \
-        step_workgroup<KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT, M_HAT>(a);                         \
+    __global__ __launch_bounds__(THREADS) void step_kernel(VariantArgs<M_HAT, THROUGH> a) {                \
+        step_workgroup<KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT, M_HAT, THROUGH>(a);                \
     }
-FO_STEP_KERNEL(true)
-FO_STEP_KERNEL(false)
+FO_STEP_KERNEL(true, true)
+FO_STEP_KERNEL(true, false)
+FO_STEP_KERNEL(false, true)
+FO_STEP_KERNEL(false, false)
 #undef FO_STEP_KERNEL
 
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL, bool M_HAT>
-static hipError_t launch_m_hat(bool direct, const StepArgs& args, int64_t n_blocks, hipStream_t s) {
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL, bool M_HAT, bool THROUGH>
+static hipError_t launch_through(bool direct, const StepArgs& args, int64_t n_blocks, hipStream_t s) {
     constexpr int VEC = step_vec(KIND, SPLIT, QUANT, SMALL), THREADS = step_threads(KIND, SPLIT, QUANT, SMALL);
     const dim3 grid((unsigned)n_blocks), block(THREADS);
-    const VariantArgs<M_HAT> a(args);
+    const VariantArgs<M_HAT, THROUGH> a(args);
     if (direct) step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT><<<grid, block, 0, s>>>(a);
     else step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT><<<grid, block, 0, s>>>(a);
     return hipGetLastError();
+}
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL, bool M_HAT>
+static hipError_t launch_m_hat(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    if constexpr (!SMALL) {
+        if (a.through) return launch_through<KIND, SPLIT, QUANT, EXACT, SMALL, M_HAT, true>(direct, a, n_blocks, s);
+    }
+    return launch_through<KIND, SPLIT, QUANT, EXACT, SMALL, M_HAT, false>(direct, a, n_blocks, s);
 }
 template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL>
 static hipError_t launch_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
@@ -1074,8 +1066,10 @@ __global__ __launch_bounds__(THREADS) void probe_kernel(StepArgs a) {
     // keeps the load from being removed.
 #pragma unroll
     for (int j = 0; j < VEC / 2; ++j) asm volatile("" : : "v"(x.g[j]));
-    if (cnt == VEC) store_full<VEC, HAS_V, true, true>(x, T, tile0, lane_el, leader);
-    else store_tail<VEC, HAS_V, true, true>(x, T, tile0 + lane_el, cnt, leader);
+    if (cnt == VEC) {
+        if (a.through) store_full<VEC, HAS_V, true, true, true>(x, T, tile0, lane_el, leader);
+        else store_full<VEC, HAS_V, true, true, false>(x, T, tile0, lane_el, leader);
+    } else store_tail<VEC, HAS_V, true, true>(x, T, tile0 + lane_el, cnt, leader);
 }
 
 template <int KIND, bool SMALL>
@@ -1162,9 +1156,10 @@ __device__ __forceinline__ void load_f32(float (&f)[kCodecVec], const float* p, 
         for (int i = 0; i < kCodecVec; ++i) f[i] = 0.0f;
     }
 }
+template <bool THROUGH>
 __device__ __forceinline__ void store_f32(float* p, const LanePos& L, const float (&f)[kCodecVec]) {
     if (L.cnt == kCodecVec) {
-        gst_floats(gbase(p, 4 * L.tile0), 4u * block_local(L.lane_el), f);
+        gst_floats<THROUGH>(gbase(p, 4 * L.tile0), 4u * block_local(L.lane_el), f);
     } else {
         const auto q = as_global(p) + L.tile0 + L.lane_el;
 #pragma unroll
@@ -1183,9 +1178,10 @@ __device__ __forceinline__ void load_u16(uint32_t (&w)[kCodecVec / 2], const voi
         for (int j = 0; j < kCodecVec / 2; ++j) w[j] = 0;
     }
 }
+template <bool THROUGH>
 __device__ __forceinline__ void store_u16(void* p, const LanePos& L, const uint32_t (&w)[kCodecVec / 2]) {
     if (L.cnt == kCodecVec) {
-        gst_words(gbase(p, 2 * L.tile0), 2u * block_local(L.lane_el), w);
+        gst_words<THROUGH>(gbase(p, 2 * L.tile0), 2u * block_local(L.lane_el), w);
     } else {
         const auto q = as_global(reinterpret_cast<uint16_t*>(p)) + L.tile0 + L.lane_el;
 #pragma unroll
@@ -1204,9 +1200,10 @@ __device__ __forceinline__ void load_u8(uint32_t (&w)[kCodecVec / 4], const void
         for (int j = 0; j < kCodecVec / 4; ++j) w[j] = 0;
     }
 }
+template <bool THROUGH>
 __device__ __forceinline__ void store_u8(void* p, const LanePos& L, const uint32_t (&w)[kCodecVec / 4]) {
     if (L.cnt == kCodecVec) {
-        gst_words(gbase(p, L.tile0), block_local(L.lane_el), w);
+        gst_words<THROUGH>(gbase(p, L.tile0), block_local(L.lane_el), w);
     } else {
         const auto q = as_global(reinterpret_cast<uint8_t*>(p)) + L.tile0 + L.lane_el;
 #pragma unroll
@@ -1300,7 +1297,7 @@ __device__ __forceinline__ uint32_t split_rho_bits(float theta, uint32_t b) {
     return E == 255 ? 0u : round_to_int_bits(y);
 }
 
-template <int N, typename RHO, bool FULL>
+template <int N, typename RHO, bool THROUGH, bool FULL>
 __device__ __forceinline__ void split_tile(const float* theta, uint16_t* param, RHO* rho, int64_t n, int64_t tile0) {
     float th[kCodecPasses][kCodecVec];
 #pragma unroll
@@ -1313,26 +1310,26 @@ __device__ __forceinline__ void split_tile(const float* theta, uint16_t* param, 
         for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[r][2 * j], th[r][2 * j + 1]);
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<N>(th[r][i], half_of(pw, i));
-        store_u16(param, L, pw);
+        store_u16<THROUGH>(param, L, pw);
         if constexpr (sizeof(RHO) == 1) {
             uint32_t rw[kCodecVec / 4];
             pack_u8(rw, c);
-            store_u8(rho, L, rw);
+            store_u8<THROUGH>(rho, L, rw);
         } else {
             uint32_t rw[kCodecVec / 2];
             pack_u16(rw, c);
-            store_u16(rho, L, rw);
+            store_u16<THROUGH>(rho, L, rw);
         }
     }
 }
-template <int N, typename RHO>
+template <int N, typename RHO, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void split_kernel(const float* theta, uint16_t* param, RHO* rho, int64_t n) {
     const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) split_tile<N, RHO, true>(theta, param, rho, n, tile0);
-    else split_tile<N, RHO, false>(theta, param, rho, n, tile0);
+    if (n - tile0 >= kCodecTile) split_tile<N, RHO, THROUGH, true>(theta, param, rho, n, tile0);
+    else split_tile<N, RHO, THROUGH, false>(theta, param, rho, n, tile0);
 }
 
-template <int N, typename RHO, bool FULL>
+template <int N, typename RHO, bool THROUGH, bool FULL>
 __device__ __forceinline__ void reconstruct_tile(const uint16_t* param, const RHO* rho, float* theta, int64_t n,
                                                  int64_t tile0, float* rho_over_n) {
     constexpr int kRhoWords = sizeof(RHO) == 1 ? kCodecVec / 4 : kCodecVec / 2;
@@ -1354,17 +1351,17 @@ __device__ __forceinline__ void reconstruct_tile(const uint16_t* param, const RH
             if constexpr (sizeof(RHO) == 1) th[i] = reconstruct_tab(rho_over_n, half_of(pw[r], i), byte_of(rw[r], i));
             else th[i] = reconstruct_n<N>(half_of(pw[r], i), (int)(int16_t)half_of(rw[r], i));
         }
-        store_f32(theta, L, th);
+        store_f32<THROUGH>(theta, L, th);
     }
 }
-template <int N, typename RHO>
+template <int N, typename RHO, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const uint16_t* param, const RHO* rho, float* theta,
                                                                int64_t n) {
     static_assert(sizeof(RHO) != 1 || N == 127, "the table holds rho / 127");
     __shared__ float rho_over_n[sizeof(RHO) == 1 ? 256 : 1];
     const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) reconstruct_tile<N, RHO, true>(param, rho, theta, n, tile0, rho_over_n);
-    else reconstruct_tile<N, RHO, false>(param, rho, theta, n, tile0, rho_over_n);
+    if (n - tile0 >= kCodecTile) reconstruct_tile<N, RHO, THROUGH, true>(param, rho, theta, n, tile0, rho_over_n);
+    else reconstruct_tile<N, RHO, THROUGH, false>(param, rho, theta, n, tile0, rho_over_n);
 }
 
 // The data-independent experiment of Section 4.4: FP32 bit patterns first, first + stride, ...
@@ -1524,7 +1521,7 @@ __device__ __forceinline__ bool group_leader(const LanePos& L) {
     return (threadIdx.x & (kGroup / kCodecVec - 1)) == 0 && L.cnt > 0;
 }
 
-template <bool VARIANCE, bool LINEAR, bool FULL>
+template <bool VARIANCE, bool LINEAR, bool THROUGH, bool FULL>
 __device__ __forceinline__ void quantize_tile(const float* x, uint8_t* q, uint16_t* scale, int64_t n, int64_t tile0) {
     float v[kCodecPasses][kCodecVec];
 #pragma unroll
@@ -1534,23 +1531,23 @@ __device__ __forceinline__ void quantize_tile(const float* x, uint8_t* q, uint16
         const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
         uint32_t w[kCodecVec / 4];
         const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v[r], w);
-        if (L.cnt > 0) store_u8(q, L, w);
+        if (L.cnt > 0) store_u8<THROUGH>(q, L, w);
         if (group_leader(L)) as_global(scale)[(L.tile0 + L.lane_el) >> 5] = (uint16_t)sbits;
     }
 }
-template <bool VARIANCE, bool LINEAR>
+template <bool VARIANCE, bool LINEAR, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* x, uint8_t* q, uint16_t* scale,
                                                             int64_t n) {
     const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) quantize_tile<VARIANCE, LINEAR, true>(x, q, scale, n, tile0);
-    else quantize_tile<VARIANCE, LINEAR, false>(x, q, scale, n, tile0);
+    if (n - tile0 >= kCodecTile) quantize_tile<VARIANCE, LINEAR, THROUGH, true>(x, q, scale, n, tile0);
+    else quantize_tile<VARIANCE, LINEAR, THROUGH, false>(x, q, scale, n, tile0);
 }
 
 __device__ __forceinline__ float load_scale(const uint16_t* scale, const LanePos& L) {
     return L.cnt > 0 ? (float)__builtin_bit_cast(_Float16, (uint16_t)as_global(scale)[(L.tile0 + L.lane_el) >> 5]) : 0.0f;
 }
 
-template <bool VARIANCE, bool LINEAR, bool FULL>
+template <bool VARIANCE, bool LINEAR, bool THROUGH, bool FULL>
 __device__ __forceinline__ void dequantize_tile(const uint8_t* q, const uint16_t* scale, float* x, int64_t n,
                                                 int64_t tile0, float* tab) {
     uint32_t w[kCodecPasses][kCodecVec / 4];
@@ -1568,16 +1565,16 @@ __device__ __forceinline__ void dequantize_tile(const uint8_t* q, const uint16_t
         float v[kCodecVec];
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) v[i] = dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w[r], i), s[r]);
-        store_f32(x, L, v);
+        store_f32<THROUGH>(x, L, v);
     }
 }
-template <bool VARIANCE, bool LINEAR>
+template <bool VARIANCE, bool LINEAR, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, const uint16_t* scale, float* x,
                                                               int64_t n) {
     __shared__ float tab[256];
     const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) dequantize_tile<VARIANCE, LINEAR, true>(q, scale, x, n, tile0, tab);
-    else dequantize_tile<VARIANCE, LINEAR, false>(q, scale, x, n, tile0, tab);
+    if (n - tile0 >= kCodecTile) dequantize_tile<VARIANCE, LINEAR, THROUGH, true>(q, scale, x, n, tile0, tab);
+    else dequantize_tile<VARIANCE, LINEAR, THROUGH, false>(q, scale, x, n, tile0, tab);
 }
 
 // Quantisation error of a buffer (Section 4.5): sum (Q^-1(Q(x)) - x)^2 and sum x^2, in double.  A workgroup walks
@@ -1688,7 +1685,8 @@ static inline unsigned nmse_blocks(int64_t n) {
 template <int N, typename RHO>
 static hipError_t launch_split_n(const float* theta, uint16_t* param, RHO* rho, int64_t n, hipStream_t s) {
     return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-        hipLaunchKernelGGL((split_kernel<N, RHO>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
+        if (codec_through(n)) hipLaunchKernelGGL((split_kernel<N, RHO, true>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
+        else hipLaunchKernelGGL((split_kernel<N, RHO, false>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
     });
 }
 hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
@@ -1698,8 +1696,8 @@ hipError_t launch_split(int bits, const float* theta, void* param, void* rho, in
 template <int N, typename RHO>
 static hipError_t launch_reconstruct_n(const uint16_t* param, const RHO* rho, float* theta, int64_t n, hipStream_t s) {
     return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-        hipLaunchKernelGGL((reconstruct_kernel<N, RHO>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at,
-                           count);
+        if (codec_through(n)) hipLaunchKernelGGL((reconstruct_kernel<N, RHO, true>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at, count);
+        else hipLaunchKernelGGL((reconstruct_kernel<N, RHO, false>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at, count);
     });
 }
 hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s) {
@@ -1716,34 +1714,37 @@ hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t str
 #undef FO_SWEEP
     return hipGetLastError();
 }
-// Calls f(VARIANCE, LINEAR) with the two choices as compile-time constants (std::integral_constant).
+// Calls f(VARIANCE, LINEAR, THROUGH) with the choices as compile-time constants (std::integral_constant).
 template <typename F>
-static hipError_t dispatch_codec(bool variance, bool linear, F f) {
+static hipError_t dispatch_codec(bool variance, bool linear, bool through, F f) {
     typedef std::true_type yes;
     typedef std::false_type no;
-    if (variance) return linear ? f(yes(), yes()) : f(yes(), no());
-    return linear ? f(no(), yes()) : f(no(), no());
+    const auto with = [=](auto T) {
+        if (variance) return linear ? f(yes(), yes(), T) : f(yes(), no(), T);
+        return linear ? f(no(), yes(), T) : f(no(), no(), T);
+    };
+    return through ? with(yes()) : with(no());
 }
 hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
-    return dispatch_codec(variance, linear, [=](auto V, auto L) {
+    return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
         return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-            hipLaunchKernelGGL((quantize_kernel<decltype(V)::value, decltype(L)::value>), blocks, dim3(kThreads), 0, s, x + at,
+            hipLaunchKernelGGL((quantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s, x + at,
                                (uint8_t*)q + at, scale + at / kGroup, count);
         });
     });
 }
 hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                              hipStream_t s) {
-    return dispatch_codec(variance, linear, [=](auto V, auto L) {
+    return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
         return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-            hipLaunchKernelGGL((dequantize_kernel<decltype(V)::value, decltype(L)::value>), blocks, dim3(kThreads), 0, s,
+            hipLaunchKernelGGL((dequantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s,
                                (const uint8_t*)q + at, scale + at / kGroup, x + at, count);
         });
     });
 }
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
                        uint32_t* flag, uint32_t seq, hipStream_t s) {
-    const hipError_t e = dispatch_codec(variance, linear, [=](auto V, auto L) {
+    const hipError_t e = dispatch_codec(variance, linear, false, [=](auto V, auto L, auto) {
         hipLaunchKernelGGL((nmse_kernel<decltype(V)::value, decltype(L)::value>), dim3(nmse_blocks(n)), dim3(kThreads), 0, s,
                            x, n, partial);
         return hipGetLastError();
@@ -1763,7 +1764,7 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
 constexpr int kConvPasses = kConvChunkElems / kCodecPass;
 static_assert(kConvPasses * kCodecPass == kConvChunkElems, "the host builds the conversion's tables for tiles of this size");
 
-template <bool HAS_V, bool FULL>
+template <bool HAS_V, bool THROUGH, bool FULL>
 __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0) {
     float th[kConvPasses][kCodecVec], m[kConvPasses][kCodecVec], v[kConvPasses][kCodecVec];
 #pragma unroll
@@ -1785,21 +1786,21 @@ __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0)
         for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<127>(th[r][i], half_of(pw, i));
         pack_u8(w, c);
         if (L.cnt > 0) {
-            store_u16(T.param, L, pw);
-            store_u8(T.rho, L, w);
+            store_u16<THROUGH>(T.param, L, pw);
+            store_u8<THROUGH>(T.rho, L, w);
         }
         const uint32_t ms = quantize_lane<false, false>(m[r], w);
-        if (L.cnt > 0) store_u8(T.m_q, L, w);
+        if (L.cnt > 0) store_u8<THROUGH>(T.m_q, L, w);
         if (group_leader(L)) as_global(T.m_scale)[group] = (uint16_t)ms;
         if (HAS_V) {
             const uint32_t vs = quantize_lane<true, false>(v[r], w);
-            if (L.cnt > 0) store_u8(T.v_q, L, w);
+            if (L.cnt > 0) store_u8<THROUGH>(T.v_q, L, w);
             if (group_leader(L)) as_global(T.v_scale)[group] = (uint16_t)vs;
         }
     }
 }
 
-template <bool HAS_V, bool FULL>
+template <bool HAS_V, bool THROUGH, bool FULL>
 __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0, float (&tab)[3][256]) {
     uint32_t pw[kConvPasses][kCodecVec / 2], rw[kConvPasses][kCodecVec / 4], mw[kConvPasses][kCodecVec / 4],
         vw[kConvPasses][kCodecVec / 4];
@@ -1825,36 +1826,40 @@ __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile
         float f[kCodecVec];
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_tab(tab[0], half_of(pw[r], i), byte_of(rw[r], i));
-        store_f32(T.theta32, L, f);
+        store_f32<THROUGH>(T.theta32, L, f);
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw[r], i), sm[r]);
-        store_f32(T.m32, L, f);
+        store_f32<THROUGH>(T.m32, L, f);
         if (HAS_V) {
 #pragma unroll
             for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(vw[r], i), sv[r]);
-            store_f32(T.v32, L, f);
+            store_f32<THROUGH>(T.v32, L, f);
         }
     }
 }
 
-template <bool HAS_V, bool COMPRESS, bool DIRECT>
+template <bool HAS_V, bool COMPRESS, bool DIRECT, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void convert_kernel(StepArgs a) {
     TensorDev T;
     const int64_t tile0 = locate_tile<DIRECT>(a, T) * (int64_t)kConvChunkElems;
     const bool full = T.numel - tile0 >= kConvChunkElems;
     if constexpr (COMPRESS) {
-        if (full) compress_tile<HAS_V, true>(T, tile0);
-        else compress_tile<HAS_V, false>(T, tile0);
+        if (full) compress_tile<HAS_V, THROUGH, true>(T, tile0);
+        else compress_tile<HAS_V, THROUGH, false>(T, tile0);
     } else {
         __shared__ float tab[3][256];        // rho / 127, phi_m^-1(q / 127), q / 255
-        if (full) decompress_tile<HAS_V, true>(T, tile0, tab);
-        else decompress_tile<HAS_V, false>(T, tile0, tab);
+        if (full) decompress_tile<HAS_V, THROUGH, true>(T, tile0, tab);
+        else decompress_tile<HAS_V, THROUGH, false>(T, tile0, tab);
     }
 }
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     const dim3 grid((unsigned)n_blocks), block(kThreads);
-#define FO_CONV(HV, CP, DR) hipLaunchKernelGGL((convert_kernel<HV, CP, DR>), grid, block, 0, s, a)
+#define FO_CONV(HV, CP, DR)                                                                                   \
+    do {                                                                                                      \
+        if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, 0, s, a);          \
+        else hipLaunchKernelGGL((convert_kernel<HV, CP, DR, false>), grid, block, 0, s, a);                   \
+    } while (0)
     if (has_v) {
         if (compress) { if (direct) FO_CONV(true, true, true); else FO_CONV(true, true, false); }
         else { if (direct) FO_CONV(true, false, true); else FO_CONV(true, false, false); }

@@ -119,3 +119,107 @@ def test_steps_around_the_one_from_which_the_momentum_needs_no_correction(beta1,
         _step("adamw", bufs, states, grads, t, dict(HP, beta1=beta1))
         for b, st in zip(bufs, states):
             _same(b, st, f"beta1 {beta1} step {t} numel {st.n}")
+
+
+# The first sizes whose stores go through to memory (176160768 bytes of arrays at 7, 6 and 14 bytes an element), and the
+# limits below which a launch's workgroups are not held back.
+@pytest.mark.parametrize("kind,n", [("adamw", 25165824), ("adamw", 25165823), ("sgd", 29360128), ("lion", 29360127),
+                                    ("adamw", 1 << 22), ("sgd", (1 << 22) - 1), ("lion", 1 << 22)])
+def test_launch_rules_on_both_sides_of_their_limits(kind, n):
+    rng = np.random.default_rng(n)
+    small = 1000
+    thp = rng.normal(0, 0.02, n).astype(np.float32).view(np.uint32) >> 16
+    g = (rng.normal(0, 1e-4, n).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    for sizes in ((n,), (small, n - small)):             # one tensor (no table), and a list
+        cut = np.cumsum((0,) + sizes)
+        states = [_state(rng, k, kind, thp[a:a + k]) for a, k in zip(cut, sizes)]
+        grads = [g[a:a + k] for a, k in zip(cut, sizes)]
+        bufs = [upload_state(st) for st in states]
+        for b, x in zip(bufs, grads):
+            b.lr, b.weight_decay = 1e-3, 0.01
+            b.grad.copy_(to_dev_u16(x, torch.bfloat16))
+        _step(kind, bufs, states, grads, 1, HP)
+        for b, st in zip(bufs, states):
+            _same(b, st, f"{kind} {sizes}")
+
+
+@pytest.mark.parametrize("kind,split,quant,n", [("adamw", False, False, 12582912), ("sgd", False, False, 17616077),
+                                                ("adamw", True, False, 13550829), ("lion", True, False, 19573419),
+                                                ("adamw", False, True, 22020096), ("sgd", False, True, 25165824)])
+def test_ablation_launch_rules_on_both_sides_of_their_limits(kind, split, quant, n):
+    # (the first sizes whose stores go through: 14, 10, 13, 9, 8 and 7 bytes an element)
+    f32 = lambda t: t.cpu().numpy().view(np.uint32)
+    for k in (n, n - 1):
+        rng = np.random.default_rng(k)
+        st = oracle.TensorState(rng.normal(0, 0.02, k).astype(np.float32), kind, split_weights=split, quantize_states=quant)
+        b = fo.ParamBuffers(k, kind, split_weights=split, quantize_states=quant)
+        if split:
+            b.param.copy_(to_dev_u16(st.thp, torch.bfloat16)); b.rho.copy_(torch.from_numpy(st.rho))
+        else:
+            b.theta.copy_(torch.from_numpy(st.theta32))
+        g = (rng.normal(0, 1e-4, k).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+        b.grad.copy_(to_dev_u16(g, torch.bfloat16))
+        b.lr, b.weight_decay = 1e-3, 0.01
+        lr, wd = np.float32(b.lr), np.float32(b.weight_decay)
+        if kind == "adamw":
+            fo.adamw_step_ex([b], HP["beta1"], HP["beta2"], HP["eps"], 1)
+            oracle.adamw_step(st, g, lr, wd, HP["beta1"], HP["beta2"], HP["eps"], 1, 16)
+        elif kind == "sgd":
+            fo.sgd_step_ex([b], HP["momentum"])
+            oracle.sgd_step(st, g, lr, wd, HP["momentum"], 16)
+        else:
+            fo.lion_step_ex([b], HP["beta1"], HP["beta2"])
+            oracle.lion_step(st, g, lr, wd, HP["beta1"], HP["beta2"], 16)
+        if split:
+            assert np.array_equal(bits16(b.param), st.thp) and np.array_equal(b.rho.cpu().numpy(), st.rho)
+        else:
+            assert np.array_equal(f32(b.theta), st.theta32.view(np.uint32))
+        if quant:
+            assert np.array_equal(b.m_q.cpu().numpy(), st.mq) and np.array_equal(bits16(b.m_scale), st.ms)
+        else:
+            assert np.array_equal(f32(b.m), st.m32.view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [(1 << 23) - 1, (1 << 23) + 1])
+def test_codecs_on_both_sides_of_the_limit_of_their_stores(n):
+    rng = np.random.default_rng(n)
+    x = rng.normal(0, 1e-3, n).astype(np.float32)
+    d, ng = torch.from_numpy(x).cuda(), (n + 31) // 32
+    e = lambda k, dt: torch.zeros(k, dtype=dt, device="cuda")
+    p, r, mq, ms, back = e(n, torch.bfloat16), e(n, torch.int8), e(n, torch.int8), e(ng, torch.float16), e(n, torch.float32)
+    fo.split_weights(d, p, r)
+    thp, rho = oracle.split(x)
+    assert np.array_equal(bits16(p), thp) and np.array_equal(r.cpu().numpy(), rho)
+    fo.reconstruct_weights(p, r, back)
+    assert np.array_equal(back.cpu().numpy().view(np.uint32), oracle.reconstruct(thp, rho).view(np.uint32))
+    fo.quantize_momentum(d, mq, ms)
+    q, s = oracle.quantize_momentum(x)
+    assert np.array_equal(mq.cpu().numpy(), q) and np.array_equal(bits16(ms), s)
+    fo.dequantize_momentum(mq, ms, back)
+    assert np.array_equal(back.cpu().numpy().view(np.uint32), oracle.dequantize_momentum(q, s).view(np.uint32))
+    v, vq, vs = d * d, e(n, torch.uint8), e(ng, torch.float16)
+    fo.quantize_variance(v, vq, vs)
+    q, s = oracle.quantize_variance(v.cpu().numpy())
+    assert np.array_equal(vq.cpu().numpy(), q) and np.array_equal(bits16(vs), s)
+    fo.dequantize_variance(vq, vs, back)
+    assert np.array_equal(back.cpu().numpy().view(np.uint32), oracle.dequantize_variance(q, s).view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [(1 << 25) + 1, (1 << 25) - 1, 1 << 22, (1 << 22) - 1])
+def test_conversions_on_both_sides_of_their_limits(n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    f = fo.ParamBuffers(n, "sgd", with_grad=False, split_weights=False, quantize_states=False)
+    f.theta.normal_(0, 0.02, generator=g)
+    f.m.normal_(0, 1e-4, generator=g)
+    c = fo.ParamBuffers(n, "sgd", with_grad=False)
+    c.theta, c.m = f.theta, f.m
+    theta, m = f.theta.cpu().numpy(), f.m.cpu().numpy()
+    fo.compress_state("sgd", [c])
+    thp, rho = oracle.split(theta)
+    q, s = oracle.quantize_momentum(m)
+    got = download(c)
+    assert np.array_equal(got["thp"], thp) and np.array_equal(got["rho"], rho)
+    assert np.array_equal(got["mq"], q) and np.array_equal(got["ms"], s)
+    fo.decompress_state("sgd", [c])
+    assert np.array_equal(f.theta.cpu().numpy().view(np.uint32), oracle.reconstruct(thp, rho).view(np.uint32))
+    assert np.array_equal(f.m.cpu().numpy().view(np.uint32), oracle.dequantize_momentum(q, s).view(np.uint32))
