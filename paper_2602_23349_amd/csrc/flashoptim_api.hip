@@ -345,17 +345,17 @@ int to_dev_ex(const flashoptim_tensor_ex* t, int64_t n, bool has_v, bool split, 
 enum LiveOp { kOpStep = 0, kOpCompress = 1, kOpDecompress = 2, kOpProbe = 3, kOpStepExact = 4 };
 constexpr int32_t kOpPack = 5, kOpUnpack = 6;
 
-hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool quant, bool small, const StepArgs& a, int64_t blocks,
-                          hipStream_t stream) {
+hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool quant, fo::StepShape shape, const StepArgs& a,
+                          int64_t blocks, hipStream_t stream) {
     if (op == kOpStep || op == kOpStepExact)
-        return fo::launch_step(kind, direct, split, quant, small, op == kOpStepExact, a, blocks, stream);
-    if (op == kOpProbe) return fo::launch_probe(kind, direct, small, a, blocks, stream);
+        return fo::launch_step(kind, direct, split, quant, shape, op == kOpStepExact, a, blocks, stream);
+    if (op == kOpProbe) return fo::launch_probe(kind, direct, shape, a, blocks, stream);
     return fo::launch_convert(kind == FLASHOPTIM_ADAMW, op == kOpCompress, direct, a, blocks, stream);
 }
 
 // The workgroups 0 .. blocks-1 of one logical launch (each handles `tile_elems` elements), issued as
 // back-to-back launches on the same stream, each covering at most kSegmentElems elements.
-hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, bool small, StepArgs a, int64_t blocks,
+hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, fo::StepShape shape, StepArgs a, int64_t blocks,
                      int64_t tile_elems, hipStream_t stream) {
     const int64_t seg = fo::kSegmentElems / tile_elems > 0 ? fo::kSegmentElems / tile_elems : 1;
     for (int64_t first = 0; first < blocks; first += seg) {
@@ -363,7 +363,7 @@ hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, b
         const int64_t n = blocks - first < seg ? blocks - first : seg;
         a.through = op == kOpCompress || op == kOpDecompress ? fo::convert_through(n * tile_elems)
                                                              : fo::step_through(kind, split, quant, n * tile_elems);
-        const hipError_t e = launch_segment(op, kind, direct, split, quant, small, a, n, stream);
+        const hipError_t e = launch_segment(op, kind, direct, split, quant, shape, a, n, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -379,9 +379,9 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     a.sqrt_min_word = sqrt_min_word;
     int64_t elems = 0;
     for (const TensorDev& d : live) elems += d.numel;
-    const bool small = fo::step_small(split, quant, elems);
+    const fo::StepShape shape = fo::step_shape(kind, split, quant, elems);
     const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems
-                                                                  : fo::chunk_elems(kind, split, quant, small);
+                                                                  : fo::chunk_elems(split, quant, shape);
     // one workgroup per chunk: the launch grid is a 31-bit count
     uint32_t log2_ce = 0;
     while (((int64_t)1 << log2_ce) < ce) ++log2_ce;        // every tile size is a power of two
@@ -397,7 +397,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     if (live.size() == 1) {
         // gradient-release call: no table, no allocation, no lock
         a.single = live[0];
-        FO_HIP(launch_op(op, kind, true, split, quant, small, a, total_chunks, ce, stream));
+        FO_HIP(launch_op(op, kind, true, split, quant, shape, a, total_chunks, ce, stream));
         return FLASHOPTIM_OK;
     }
 
@@ -438,7 +438,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)live.size();
-    const hipError_t e = launch_op(op, kind, false, split, quant, small, a, plan->n_chunks, ce, stream);
+    const hipError_t e = launch_op(op, kind, false, split, quant, shape, a, plan->n_chunks, ce, stream);
     if (e != hipSuccess) plan->table_known = false;        // the launches that were accepted may have written a rate
     FO_HIP(e);
     return FLASHOPTIM_OK;
@@ -1308,8 +1308,8 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     if (rc != FLASHOPTIM_OK) return rc;
     int64_t elems = 0;
     for (int64_t i = 0; i < n_tensors; ++i) elems += tensors[i].numel;
-    const bool small = fo::step_small(true, true, elems);
-    const int64_t ce = fo::chunk_elems(FLASHOPTIM_ADAMW, true, true, small);
+    const fo::StepShape shape = fo::step_shape(FLASHOPTIM_ADAMW, true, true, elems);
+    const int64_t ce = fo::chunk_elems(true, true, shape);
     int64_t n_live = 0, total_tiles = 0, only = -1;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (tensors[i].numel == 0) continue;
@@ -1337,7 +1337,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     a.sqrt_min_word = word;
     if (n_live == 1) {          // one tensor: no table at all
         a.single = to_dev(tensors[only], true);
-        FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, true, true, true, small, a, total_tiles, ce, stream));
+        FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, true, true, true, shape, a, total_tiles, ce, stream));
         return FLASHOPTIM_OK;
     }
     unsigned char* base = nullptr;
@@ -1376,7 +1376,7 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
     a.coarse_shift = shift;
     a.n_tensors = (uint32_t)n_live;
     a.table_lr_mask = ~0u;
-    FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, small, a, total_tiles, ce, stream));
+    FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, shape, a, total_tiles, ce, stream));
     return FLASHOPTIM_OK;
 }
 
@@ -1403,7 +1403,7 @@ int64_t flashoptim_step_launch_count(int kind, const int64_t* numels, int64_t n_
         if (numels[i] < 0 || numels[i] >= kMaxNumel) return FLASHOPTIM_ERR_NUMEL_RANGE;
         elems += numels[i];
     }
-    const int64_t ce = fo::chunk_elems(kind, true, true, fo::step_small(true, true, elems));
+    const int64_t ce = fo::chunk_elems(true, true, fo::step_shape(kind, true, true, elems));
     for (int64_t i = 0; i < n_tensors; ++i) {
         tiles += (numels[i] + ce - 1) / ce;
     }

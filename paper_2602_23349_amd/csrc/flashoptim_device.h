@@ -12,48 +12,75 @@ namespace fo {
 
 constexpr int kGroup = 32;                         // quantisation group (Algorithms 2, 3)
 constexpr int kThreads = 256;                      // lanes per workgroup (codecs, conversions, sweep, self-test)
-// Launch shape of the step kernels, per optimizer kind (0 AdamW, 1 SGD, 2 Lion): consecutive
-// elements per lane and lanes per workgroup.  One workgroup handles one tile of chunk_elems(kind)
-// consecutive elements.
-#ifndef FO_VEC_ADAMW
-#define FO_VEC_ADAMW 8
-#endif
-#ifndef FO_VEC_SGD_LION
-#define FO_VEC_SGD_LION 8
-#endif
-#ifndef FO_THREADS_ADAMW
-#define FO_THREADS_ADAMW 256
-#endif
-#ifndef FO_THREADS_SGD_LION
-#define FO_THREADS_SGD_LION 512
-#endif
+// Launch shapes of the step kernels: consecutive elements per lane and lanes per workgroup.  One workgroup handles one
+// tile of chunk_elems() consecutive elements.
+//   kUsual: eight elements per lane and 256 lanes.
+//   kSmall: calls over fewer than kSmallElems elements fill less than half the chip with tiles of 2048: they take four
+//       elements per lane, twice the workgroups with half the work per lane (kernel time, eight -> four elements per lane: a
+//       flat tensor of 2^18 elements AdamW 3.9 -> 3.5 us, SGD 3.5 -> 2.8; 25 tensors of odd sizes below 2^16, SGD 4.9 -> 3.8;
+//       at 2^20 elements the two are equal, from 2^22 on the larger tile wins by 2-8 %).
+//   kWide: SGD and Lion over kWideElems elements or more, eight elements per lane and 512 lanes, three workgroups to a compute
+//       unit (below); against kUsual, six to a unit: four Llama layers with embedding and head SGD 3067 -> 3026 us, one layer
+//       343.3 -> 340.7, Lion 338.7 -> 340.9; GPT-2 SGD 197.3 with kUsual, 199.4 with kWide, 24 M elements 39.4, 40.0.
 // The ablation variants (weights not split, states not quantized, or both) move FP32 arrays: four elements per lane,
 // so that a wavefront's 128-bit FP32 access covers whole cache lines (with eight, each of two accesses covered half
 // of every line: the plain FP32 AdamW step over a decoder layer of Llama-3.1-8B, 218 M parameters, took 1034 us
-// against 963 with four).  The lanes per workgroup follow from the decode tables that it has to stage: none in the plain
-// FP32 step, whose workgroups are single wavefronts that start and retire on their own (same layer, with 256 / 128 /
-// 64 lanes: AdamW 974 / 955 / 928 us, SGD 639 / 629 / 599); 256 lanes where the weights are split (512: +3 %,
-// 128: +2 % on the GPT-2 list); 512 where the states are quantized (AdamW, same layer: 509 us against 519 with 256).
-// Launches over fewer than kSmallElems elements fill less than half the chip with tiles of 2048: they take four elements
-// per lane and 256 lanes as well, twice to four times the workgroups with half the work per lane (kernel time, eight
-// -> four elements per lane: a flat tensor of 2^18 elements AdamW 3.9 -> 3.5 us, SGD 3.5 -> 2.8; 25 tensors of odd sizes
-// below 2^16, SGD 4.9 -> 3.8; at 2^20 elements the two are equal, from 2^22 on the larger tile wins by 2-8 %).
-constexpr int64_t kSmallElems = (int64_t)1 << 20;
-constexpr bool step_small(bool split, bool quant, int64_t elems) { return split && quant && elems < kSmallElems; }
-constexpr int step_vec(int kind, bool split, bool quant, bool small) {
-    return !(split && quant) || small ? 4 : kind == 0 ? FO_VEC_ADAMW : FO_VEC_SGD_LION;
+// against 963 with four).  The plain FP32 step has no decode tables to stage, so its workgroups are single wavefronts
+// that start and retire on their own (same layer, with 256 / 128 / 64 lanes: AdamW 974 / 955 / 928 us, SGD 639 / 629 / 599).
+enum class StepShape { kSmall, kUsual, kWide };
+constexpr int64_t kSmallElems = (int64_t)1 << 20, kWideElems = (int64_t)1 << 27;
+constexpr StepShape step_shape(int kind, bool split, bool quant, int64_t elems) {
+    if (!(split && quant)) return StepShape::kUsual;
+    return elems < kSmallElems ? StepShape::kSmall : kind != 0 && elems >= kWideElems ? StepShape::kWide : StepShape::kUsual;
 }
-constexpr int step_threads(int kind, bool split, bool quant, bool small) {
-    return small ? 256 : !(split && quant) ? (quant ? 512 : split ? 256 : 64) : kind == 0 ? FO_THREADS_ADAMW : FO_THREADS_SGD_LION;
+constexpr int step_vec(bool split, bool quant, StepShape shape) {
+    return split && quant && shape != StepShape::kSmall ? 8 : 4;
 }
-constexpr int chunk_elems(int kind, bool split, bool quant, bool small) {
-    return step_threads(kind, split, quant, small) * step_vec(kind, split, quant, small);
+constexpr int step_threads(bool split, bool quant, StepShape shape) {
+    return shape == StepShape::kWide ? 512 : split || quant ? 256 : 64;
 }
+constexpr int chunk_elems(bool split, bool quant, StepShape shape) {
+    return step_threads(split, quant, shape) * step_vec(split, quant, shape);
+}
+
+// How many workgroups of a launch share a compute unit.  The memory system is fastest with about 10 MB of loads on their
+// way, which is what latency times bandwidth asks for; all that the registers admit (eight wavefronts per SIMD) have up to
+// 25 MB on their way, queue up in front of the DRAM and make it change rows more often.  (Wavefronts that also compute for a
+// while have fewer on average: the compressed steps want more of them than the FP32 ones.)  A launch is held to fewer by the
+// LDS it asks for beyond what it uses.  The lines are where the best counts lie, in us with no limit -> with it:
+//   AdamW, 6 of 256 lanes: Llama layer 442 -> 428, four layers with embedding and head 3994 -> 3867, flat 16 M 34.8 -> 34.5;
+//       7 for lists of fewer than 2^27 elements, whose workgroups spend a larger part of their time on looking up their
+//       tile (GPT-2 245.5 -> 244.2, and 244.7 with 6; ResNet-50 53.9 -> 53.8, and 54.1; 60 tensors of 60 M 118.9 -> 118.6,
+//       and 119.2).  With 5: 4 layers 3856, GPT-2 248.1, ResNet-50 54.7.
+//   SGD and Lion, 6 of 256 lanes or 3 of 512; before, four of 512 (all that fit): Llama layer 346 -> 341 / 345 -> 341, flat
+//       400 M SGD 659 -> 637, GPT-2 200.8 -> 197.3 / 194.5 -> 194.1, ResNet-50 SGD 42.7 -> 42.2.
+//   Plain FP32 steps, single wavefronts: AdamW 11 (Llama layer 896 -> 845, flat 25 M 104.2 -> 97.7, 300 M 1247 -> 1155; 32
+//       fit), SGD and Lion 14 (603 -> 581, 69.3 -> 67.0, 829 -> 798).
+//   Weight split only, 256 lanes: AdamW 4 (897 -> 832, 96.6 -> 93.8), SGD and Lion 5 (25 M 62.6 -> 62.1, 124 M 313.9 -> 303.6).
+//   State quantisation only: AdamW 6 of 256 lanes (before, all of 512: 488 -> 484, 58.5 -> 56.9), SGD and Lion 7 (25 M 47.8
+//       -> 47.6, 300 M 568 -> 546).
+// Not held back: compressed steps under 2^22 elements (AdamW over 3 M 8.75 us, with the limit 8.92; SGD over 4 M 8.40, 8.56),
+// and the ablation variants where stores do not go through (plain FP32 SGD over 5 M elements 15.3 us, with 18 wavefronts 16.4).
+constexpr int kNoLimit = 0;
+constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, bool direct, int64_t elems, bool through) {
+    if (split && quant && elems < ((int64_t)1 << 22)) return kNoLimit;
+    if (split && quant) return shape == StepShape::kWide ? 3 : kind == 0 && !direct && elems < ((int64_t)1 << 27) ? 7 : 6;
+    if (!through) return kNoLimit;
+    return split ? (kind == 0 ? 4 : 5) : quant ? (kind == 0 ? 6 : 7) : kind == 0 ? 11 : 14;
+}
+// Layout conversion to FP32: 5 M elements 16.5 -> 16.1 us, GPT-2 348.9 -> 344.5, 300 M 861 -> 842; 2 M 5.9 with no limit, 7.4.
+constexpr int decompress_resident(int64_t elems) { return elems < ((int64_t)1 << 22) ? kNoLimit : 7; }
+// The dynamic LDS, in bytes, with which exactly `resident` workgroups that use `used` bytes fit into a compute unit's
+// 160 KB (given out in units of 1280 bytes).
+constexpr unsigned lds_to_hold(int resident, unsigned used) {
+    return resident == kNoLimit ? 0u : (128u / (unsigned)resident) * 1280u - used;
+}
+
 // Whether the stores of a launch go through to memory at device scope, or stay non-temporal only.  Lines that are passed on
 // as they are written leave the DRAM fewer, larger turns from reading to writing and the end of the kernel nothing to write
 // back.  But lists whose arrays fit the 256 MB memory-side cache with room to spare are faster where their lines may wait.
 // In us, non-temporal -> through:
-//   steps, in place, by the size of their arrays: plain FP32 AdamW over a Llama layer (3 GB) 851 -> 839, four
+//   steps, in place, by the size of their arrays: plain FP32 AdamW over a Llama layer (3 GB) 851 -> 839, SGD 619 -> 584, four
 //       Llama layers AdamW (14 GB) 3942 -> 3890, one by gradient release 453 -> 450, GPT-2 Lion (0.8 GB) 195.3 -> 194.1, AdamW
 //       over 60 M elements (430 MB) 123.5 -> 122.0, ResNet-50's 25.6 M (182 MB) 54.8 -> 54.3; 24 M (171 MB) 50.5 -> 50.3,
 //       FP32 AdamW over 12 M (168 MB) 51.1 -> 52.1, SGD over 24 M (145 MB) 39.5 -> 40.1, AdamW over 6 M (43 MB) 16.9 -> 17.2;
@@ -161,11 +188,11 @@ struct CopyArgs {
     int64_t step;
 };
 
-hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,
+hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
                        int64_t n_blocks, hipStream_t s);
 constexpr int kConvChunkElems = 1024;   // elements per workgroup of the layout-conversion kernel: one pass of its lanes
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);
-hipError_t launch_probe(int kind, bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s);
+hipError_t launch_probe(int kind, bool direct, StepShape shape, const StepArgs& a, int64_t n_blocks, hipStream_t s);
 hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s);
 hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s);
 constexpr int kSweepStats = 8 + 3 * 256;

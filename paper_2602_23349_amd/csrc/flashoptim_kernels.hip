@@ -46,7 +46,7 @@
 // Work decomposition.  A lane owns 8 consecutive elements per tile: BF16 streams move as
 // 128-bit and byte streams as 64-bit accesses, and a quantisation group (32 elements) is a
 // lane quad, so the group absmax needs two DPP quad permutes and no LDS.  A workgroup (256
-// lanes for AdamW, 512 for SGD and Lion) handles one tile of consecutive elements of one
+// lanes, or 512) handles one tile of consecutive elements of one
 // tensor; a small two-level table maps the workgroup index to (tensor, tile) so that one call covers a
 // whole parameter list, issued as a few consecutive launches.  Stream addresses are a scalar 64-bit
 // tile base plus a 32-bit lane offset.  A lane owns 4 elements, and a group is 8 lanes, where FP32 streams are
@@ -989,54 +989,59 @@ FO_STEP_KERNEL(false, true)
 FO_STEP_KERNEL(false, false)
 #undef FO_STEP_KERNEL
 
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL, bool M_HAT, bool THROUGH>
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT, bool THROUGH>
 static hipError_t launch_through(bool direct, const StepArgs& args, int64_t n_blocks, hipStream_t s) {
-    constexpr int VEC = step_vec(KIND, SPLIT, QUANT, SMALL), THREADS = step_threads(KIND, SPLIT, QUANT, SMALL);
+    constexpr int VEC = step_vec(SPLIT, QUANT, SHAPE), THREADS = step_threads(SPLIT, QUANT, SHAPE);
     const dim3 grid((unsigned)n_blocks), block(THREADS);
+    const int resident = step_resident(KIND, SPLIT, QUANT, SHAPE, direct, n_blocks * (THREADS * VEC), THROUGH);
+    const unsigned lds = lds_to_hold(resident, SPLIT || QUANT ? sizeof(StepTables) : 0);
     const VariantArgs<M_HAT, THROUGH> a(args);
-    if (direct) step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT><<<grid, block, 0, s>>>(a);
-    else step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT><<<grid, block, 0, s>>>(a);
+    if (direct) step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT><<<grid, block, lds, s>>>(a);
+    else step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT><<<grid, block, lds, s>>>(a);
     return hipGetLastError();
 }
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL, bool M_HAT>
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT>
 static hipError_t launch_m_hat(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    if constexpr (!SMALL) {
-        if (a.through) return launch_through<KIND, SPLIT, QUANT, EXACT, SMALL, M_HAT, true>(direct, a, n_blocks, s);
+    if constexpr (SHAPE != StepShape::kSmall) {
+        if (a.through) return launch_through<KIND, SPLIT, QUANT, EXACT, SHAPE, M_HAT, true>(direct, a, n_blocks, s);
     }
-    return launch_through<KIND, SPLIT, QUANT, EXACT, SMALL, M_HAT, false>(direct, a, n_blocks, s);
+    return launch_through<KIND, SPLIT, QUANT, EXACT, SHAPE, M_HAT, false>(direct, a, n_blocks, s);
 }
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT, bool SMALL>
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE>
 static hipError_t launch_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     if constexpr (KIND == 0) {
-        if (a.c.rbc1 != 1.0f) return launch_m_hat<KIND, SPLIT, QUANT, EXACT, SMALL, true>(direct, a, n_blocks, s);
+        if (a.c.rbc1 != 1.0f) return launch_m_hat<KIND, SPLIT, QUANT, EXACT, SHAPE, true>(direct, a, n_blocks, s);
     }
-    return launch_m_hat<KIND, SPLIT, QUANT, EXACT, SMALL, false>(direct, a, n_blocks, s);
+    return launch_m_hat<KIND, SPLIT, QUANT, EXACT, SHAPE, false>(direct, a, n_blocks, s);
 }
 
 template <int KIND, bool EXACT>
-static hipError_t launch_packed(bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    return small ? launch_variant<KIND, true, true, EXACT, true>(direct, a, n_blocks, s)
-                 : launch_variant<KIND, true, true, EXACT, false>(direct, a, n_blocks, s);
+static hipError_t launch_packed(bool direct, StepShape shape, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    if (shape == StepShape::kSmall) return launch_variant<KIND, true, true, EXACT, StepShape::kSmall>(direct, a, n_blocks, s);
+    if constexpr (KIND != 0) {
+        if (shape == StepShape::kWide) return launch_variant<KIND, true, true, EXACT, StepShape::kWide>(direct, a, n_blocks, s);
+    }
+    return launch_variant<KIND, true, true, EXACT, StepShape::kUsual>(direct, a, n_blocks, s);
 }
 
 template <int KIND>
-static hipError_t launch_kind(bool direct, bool split, bool quant, bool small, const StepArgs& a, int64_t n_blocks,
+static hipError_t launch_kind(bool direct, bool split, bool quant, StepShape shape, const StepArgs& a, int64_t n_blocks,
                               hipStream_t s) {
-    if (split && quant) return launch_packed<KIND, true>(direct, small, a, n_blocks, s);
-    if (split) return launch_variant<KIND, true, false, true, false>(direct, a, n_blocks, s);
-    if (quant) return launch_variant<KIND, false, true, true, false>(direct, a, n_blocks, s);
-    return launch_variant<KIND, false, false, true, false>(direct, a, n_blocks, s);
+    if (split && quant) return launch_packed<KIND, true>(direct, shape, a, n_blocks, s);
+    if (split) return launch_variant<KIND, true, false, true, StepShape::kUsual>(direct, a, n_blocks, s);
+    if (quant) return launch_variant<KIND, false, true, true, StepShape::kUsual>(direct, a, n_blocks, s);
+    return launch_variant<KIND, false, false, true, StepShape::kUsual>(direct, a, n_blocks, s);
 }
 
 // exact = false selects the faithful division; it exists for AdamW in the compressed
 // layout only (SGD and Lion have neither operation; the ablation variants are always exact).
-hipError_t launch_step(int kind, bool direct, bool split, bool quant, bool small, bool exact, const StepArgs& a,
+hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
                        int64_t n_blocks, hipStream_t s) {
     if (kind == 0 && !a.sqrt_min_word) return hipErrorInvalidValue;     // the AdamW kernels dereference it
-    if (kind == 0 && split && quant && !exact) return launch_packed<0, false>(direct, small, a, n_blocks, s);
-    if (kind == 0) return launch_kind<0>(direct, split, quant, small, a, n_blocks, s);
-    if (kind == 1) return launch_kind<1>(direct, split, quant, small, a, n_blocks, s);
-    return launch_kind<2>(direct, split, quant, small, a, n_blocks, s);
+    if (kind == 0 && split && quant && !exact) return launch_packed<0, false>(direct, shape, a, n_blocks, s);
+    if (kind == 0) return launch_kind<0>(direct, split, quant, shape, a, n_blocks, s);
+    if (kind == 1) return launch_kind<1>(direct, split, quant, shape, a, n_blocks, s);
+    return launch_kind<2>(direct, split, quant, shape, a, n_blocks, s);
 }
 
 // ------------------------------------------------------------- stream probe --
@@ -1072,18 +1077,26 @@ __global__ __launch_bounds__(THREADS) void probe_kernel(StepArgs a) {
     } else store_tail<VEC, HAS_V, true, true>(x, T, tile0 + lane_el, cnt, leader);
 }
 
-template <int KIND, bool SMALL>
-static void launch_probe_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    constexpr int VEC = step_vec(KIND, true, true, SMALL), THREADS = step_threads(KIND, true, true, SMALL);
+template <int KIND, StepShape SHAPE>
+static hipError_t launch_probe_variant(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    constexpr int VEC = step_vec(true, true, SHAPE), THREADS = step_threads(true, true, SHAPE);
     const dim3 grid((unsigned)n_blocks), block(THREADS);
-    if (direct) hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, false>), grid, block, 0, s, a);
-}
-hipError_t launch_probe(int kind, bool direct, bool small, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    if (kind == 0) { if (small) launch_probe_variant<0, true>(direct, a, n_blocks, s); else launch_probe_variant<0, false>(direct, a, n_blocks, s); }
-    else if (kind == 1) { if (small) launch_probe_variant<1, true>(direct, a, n_blocks, s); else launch_probe_variant<1, false>(direct, a, n_blocks, s); }
-    else { if (small) launch_probe_variant<2, true>(direct, a, n_blocks, s); else launch_probe_variant<2, false>(direct, a, n_blocks, s); }
+    const unsigned lds = lds_to_hold(step_resident(KIND, true, true, SHAPE, direct, n_blocks * (THREADS * VEC), a.through), 0);
+    if (direct) hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((probe_kernel<KIND, VEC, THREADS, false>), grid, block, lds, s, a);
     return hipGetLastError();
+}
+template <int KIND>
+static hipError_t launch_probe_kind(bool direct, StepShape shape, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    if (shape == StepShape::kSmall) return launch_probe_variant<KIND, StepShape::kSmall>(direct, a, n_blocks, s);
+    if constexpr (KIND != 0) {
+        if (shape == StepShape::kWide) return launch_probe_variant<KIND, StepShape::kWide>(direct, a, n_blocks, s);
+    }
+    return launch_probe_variant<KIND, StepShape::kUsual>(direct, a, n_blocks, s);
+}
+hipError_t launch_probe(int kind, bool direct, StepShape shape, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    if (kind == 0) return launch_probe_kind<0>(direct, shape, a, n_blocks, s);
+    return kind == 1 ? launch_probe_kind<1>(direct, shape, a, n_blocks, s) : launch_probe_kind<2>(direct, shape, a, n_blocks, s);
 }
 
 // ------------------------------------------------------------ clock monitor --
@@ -1855,10 +1868,11 @@ __global__ __launch_bounds__(kThreads) void convert_kernel(StepArgs a) {
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     const dim3 grid((unsigned)n_blocks), block(kThreads);
+    const unsigned lds = compress ? 0u : lds_to_hold(decompress_resident(n_blocks * kConvChunkElems), 3 * 256 * sizeof(float));
 #define FO_CONV(HV, CP, DR)                                                                                   \
     do {                                                                                                      \
-        if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, 0, s, a);          \
-        else hipLaunchKernelGGL((convert_kernel<HV, CP, DR, false>), grid, block, 0, s, a);                   \
+        if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, lds, s, a);        \
+        else hipLaunchKernelGGL((convert_kernel<HV, CP, DR, false>), grid, block, lds, s, a);                 \
     } while (0)
     if (has_v) {
         if (compress) { if (direct) FO_CONV(true, true, true); else FO_CONV(true, true, false); }
