@@ -116,7 +116,9 @@ struct Plan {
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
-    void* d_header = nullptr;      // packing only: the blob's header and table, all but the step
+    void* d_header = nullptr;      // copies only: the blob's header and table, all but the step
+    uint32_t* d_verdict = nullptr; // unpacking only: whether the blob's header was found to be this one (calls with the same
+                                   // plan write the same tensors, so the caller orders them)
     void* h_mem = nullptr;         // pinned source of d_mem's upload, kept until the plan is freed
     size_t bytes = 0;              // of each
     bool uploaded = false;         // an upload has been enqueued (one that was captured runs with the graph, if at all)
@@ -185,8 +187,8 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     const size_t index_bytes = src.index.size() * sizeof(uint32_t);
     const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
     const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
-    const size_t all = header_at + (size_t)align64((int64_t)src.header.size());
-    p.bytes = all > 0 ? all : 64;
+    const size_t verdict_at = header_at + (size_t)align64((int64_t)src.header.size());
+    p.bytes = verdict_at + 64;
     hipError_t e = hipMalloc(&p.d_mem, p.bytes);
     if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, p.bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
@@ -198,6 +200,7 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     p.d_table = p.d_mem;
     p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
     p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
+    p.d_verdict = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.d_mem) + verdict_at);
     uint8_t* h = static_cast<uint8_t*>(p.h_mem);
     std::memset(h, 0, p.bytes);
     if (src.table_bytes) std::memcpy(h, src.table, src.table_bytes);
@@ -615,7 +618,6 @@ int64_t tensor_payload(int64_t n, int kind) {
 
 void put_i64(uint8_t* p, int64_t v) { for (int i = 0; i < 8; ++i) p[i] = (uint8_t)((uint64_t)v >> (8 * i)); }
 void put_u32(uint8_t* p, uint32_t v) { for (int i = 0; i < 4; ++i) p[i] = (uint8_t)(v >> (8 * i)); }
-int64_t get_i64(const uint8_t* p) { uint64_t v = 0; for (int i = 0; i < 8; ++i) v |= (uint64_t)p[i] << (8 * i); return (int64_t)v; }
 
 int64_t header_size(int64_t n) { return 64 + align64(16 * n); }
 
@@ -658,74 +660,6 @@ void build_segments(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* bl
     }
 }
 
-// Copies between the list's buffers and the blob.  When packing, the blob's header and table go with the copy: they
-// follow from the list but for the step, so the plan holds them on the device and the step is an argument of the kernel.
-// Nothing is staged per call: calls behind any amount of earlier work never wait, and a captured one can be replayed.
-int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, int64_t total_bytes, int64_t step,
-             hipStream_t stream) {
-    // the identity: every tensor, those without elements included (they lengthen the header and move the sections)
-    std::vector<TensorDev> list;
-    list.reserve((size_t)n);
-    for (int64_t i = 0; i < n; ++i) {
-        TensorDev d = to_dev(t[i], kind == FLASHOPTIM_ADAMW);
-        d.grad = nullptr;
-        d.lr = d.wd = 0.0f;
-        list.push_back(d);
-    }
-    PlanTag tag = {0, pack ? kOpPack : kOpUnpack, kind, 0, blob};
-    FO_HIP(hipGetDevice(&tag.device));
-    const uint64_t hash = identity_hash(tag, list);
-    int64_t total = 0;
-    for (const TensorDev& d : list) total += tensor_payload(d.numel, kind);
-    if (total == 0 && !pack) return FLASHOPTIM_OK;
-    // (one workgroup per piece, sections included that end in a short piece, and one for the header: a 32-bit index)
-    if (total / fo::kCopyPiece + 6 * n + 1 > (int64_t)0x7fffffff) return FLASHOPTIM_ERR_NUMEL_RANGE;
-    std::lock_guard<std::mutex> lock(g_mu);
-    Plan* plan = find_plan(tag, hash, list);
-    if (!plan) {
-        std::vector<CopySegment> segs;
-        build_segments(kind, t, n, blob, pack, segs);
-        int64_t n_pieces = 0;
-        for (CopySegment& sg : segs) {
-            sg.first_piece = (uint32_t)n_pieces;
-            sg.n_pieces = (uint32_t)((sg.pad_bytes + fo::kCopyPiece - 1) / fo::kCopyPiece);
-            n_pieces += sg.n_pieces;
-        }
-        const uint32_t shift = fo::coarse_shift(n_pieces);
-        std::vector<uint32_t> coarse((size_t)fo::coarse_entries(n_pieces, shift));
-        size_t si = 0;
-        for (size_t j = 0; j < coarse.size(); ++j) {
-            const int64_t b = (int64_t)j << shift;
-            while ((int64_t)segs[si].first_piece + segs[si].n_pieces <= b) ++si;
-            coarse[j] = (uint32_t)si;
-        }
-        std::vector<uint8_t> header;
-        if (pack) header = build_header(kind, t, n, 0, total_bytes);
-        const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header},
-                                 n_pieces, &plan);
-        if (rc != FLASHOPTIM_OK) return rc;
-        plan->n_segs = (uint32_t)segs.size();
-        plan->coarse_shift = shift;
-    }
-    const int rc = upload_tables(*plan, stream);
-    if (rc != FLASHOPTIM_OK) return rc;
-    fo::CopyArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.segs = static_cast<const CopySegment*>(plan->d_table);
-    a.coarse = static_cast<const uint32_t*>(plan->d_index);
-    a.coarse_shift = plan->coarse_shift;
-    a.n_segs = plan->n_segs;
-    a.n_pieces = (uint32_t)plan->n_chunks;
-    if (pack) {
-        a.header = static_cast<const uint4*>(plan->d_header);
-        a.header_n16 = (uint32_t)(header_size(n) / 16);
-        a.header_dst = reinterpret_cast<uint4*>(blob);
-        a.step = step;
-    }
-    FO_HIP(fo::launch_copy(a, stream));
-    return FLASHOPTIM_OK;
-}
-
 int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
     if (n < 0 || n >= kMaxNumel) return FLASHOPTIM_ERR_NUMEL_RANGE;
     if (n == 0) return FLASHOPTIM_OK;
@@ -750,12 +684,12 @@ struct CallSpace {
 
     uint32_t* flag() const;
 };
-constexpr size_t kSpaceHost = 64 * 1024;        // a header of up to 4092 tensors; longer ones come in parts
+constexpr size_t kSpaceHost = 64;               // two values of eight bytes
 constexpr size_t kFlagStride = 64;              // bytes: the flag has a cache line of its own
 uint32_t* CallSpace::flag() const { return reinterpret_cast<uint32_t*>(host + kSpaceHost); }
 std::mutex g_space_mu;
-constexpr int kMaxIdleSpaces = 16;              // 32 KB of device and 64 KB of pinned memory each; what more calls than that
-CallSpace g_space_idle[kMaxIdleSpaces];         // give back at once is freed
+constexpr int kMaxIdleSpaces = 16;              // 32 KB of device memory and 128 bytes of pinned memory each; what more calls
+CallSpace g_space_idle[kMaxIdleSpaces];         // than that give back at once is freed
 int g_space_n_idle = 0;
 
 void destroy_space(CallSpace& w) {
@@ -820,6 +754,80 @@ int wait_space(CallSpace& w, hipError_t e, hipStream_t stream) {
     (void)hipGetLastError();
     destroy_space(w);
     return FLASHOPTIM_ERR_HIP;
+}
+
+// ------------------------------------------------------------------- copies --
+
+// Copies between the list's buffers and the blob.  The blob's header and table follow from the list but for the step, so the
+// plan holds them on the device.  When packing they go with the copy, and the step is an argument of the kernel: nothing is
+// staged per call, calls behind any amount of earlier work never wait, and a captured one can be replayed.  When unpacking
+// (check: the workspace that the host will wait for) a kernel compares them with the blob's ahead of the copy, which does
+// nothing unless they agree.
+int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, int64_t total_bytes, int64_t step,
+             hipStream_t stream, CallSpace* check = nullptr) {
+    // the identity: every tensor, those without elements included (they lengthen the header and move the sections)
+    std::vector<TensorDev> list;
+    list.reserve((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+        TensorDev d = to_dev(t[i], kind == FLASHOPTIM_ADAMW);
+        d.grad = nullptr;
+        d.lr = d.wd = 0.0f;
+        list.push_back(d);
+    }
+    PlanTag tag = {0, pack ? kOpPack : kOpUnpack, kind, 0, blob};
+    FO_HIP(hipGetDevice(&tag.device));
+    const uint64_t hash = identity_hash(tag, list);
+    int64_t total = 0;
+    for (const TensorDev& d : list) total += tensor_payload(d.numel, kind);
+    // (one workgroup per piece, sections included that end in a short piece, and one for the header: a 32-bit index)
+    if (total / fo::kCopyPiece + 6 * n + 1 > (int64_t)0x7fffffff) return FLASHOPTIM_ERR_NUMEL_RANGE;
+    std::lock_guard<std::mutex> lock(g_mu);
+    Plan* plan = find_plan(tag, hash, list);
+    if (!plan) {
+        std::vector<CopySegment> segs;
+        build_segments(kind, t, n, blob, pack, segs);
+        int64_t n_pieces = 0;
+        for (CopySegment& sg : segs) {
+            sg.first_piece = (uint32_t)n_pieces;
+            sg.n_pieces = (uint32_t)((sg.pad_bytes + fo::kCopyPiece - 1) / fo::kCopyPiece);
+            n_pieces += sg.n_pieces;
+        }
+        const uint32_t shift = fo::coarse_shift(n_pieces);
+        std::vector<uint32_t> coarse((size_t)fo::coarse_entries(n_pieces, shift));
+        size_t si = 0;
+        for (size_t j = 0; j < coarse.size(); ++j) {
+            const int64_t b = (int64_t)j << shift;
+            while ((int64_t)segs[si].first_piece + segs[si].n_pieces <= b) ++si;
+            coarse[j] = (uint32_t)si;
+        }
+        const std::vector<uint8_t> header = build_header(kind, t, n, 0, total_bytes);
+        const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header},
+                                 n_pieces, &plan);
+        if (rc != FLASHOPTIM_OK) return rc;
+        plan->n_segs = (uint32_t)segs.size();
+        plan->coarse_shift = shift;
+    }
+    const int rc = upload_tables(*plan, stream);
+    if (rc != FLASHOPTIM_OK) return rc;
+    fo::CopyArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.segs = static_cast<const CopySegment*>(plan->d_table);
+    a.coarse = static_cast<const uint32_t*>(plan->d_index);
+    a.coarse_shift = plan->coarse_shift;
+    a.n_segs = plan->n_segs;
+    a.n_pieces = (uint32_t)plan->n_chunks;
+    if (pack) {
+        a.header = static_cast<const uint4*>(plan->d_header);
+        a.header_n16 = (uint32_t)(header_size(n) / 16);
+        a.header_dst = reinterpret_cast<uint4*>(blob);
+        a.step = step;
+    } else {
+        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), plan->d_verdict,
+                                       reinterpret_cast<int64_t*>(check->host), check->flag(), check->seq, stream));
+        a.verdict = plan->d_verdict;
+    }
+    FO_HIP(fo::launch_copy(a, stream));
+    return FLASHOPTIM_OK;
 }
 
 // ------------------------------------------ the step entry point that allocates nothing --
@@ -1157,30 +1165,21 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     rc = refuse_capture(stream);
     if (rc != FLASHOPTIM_OK) return rc;
-    const std::vector<uint8_t> want = build_header(kind, tensors, n_tensors, 0, total);
     CallSpace w;
     rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
-    // everything but the step field must match what this (kind, list) would have written
-    bool match = true;
-    int64_t step = 0;
-    for (size_t at = 0; at < want.size() && match; at += kSpaceHost) {
-        const size_t bytes = want.size() - at < kSpaceHost ? want.size() - at : kSpaceHost;
-        if (at) ++w.seq;
-        rc = wait_space(w, fo::launch_fetch(static_cast<const uint8_t*>(blob) + at, w.host, bytes, w.flag(), w.seq, stream),
-                        stream);
-        if (rc != FLASHOPTIM_OK) return rc;
-        if (at == 0) {
-            step = get_i64(w.host + fo::kHeaderStepAt);
-            put_i64(w.host + fo::kHeaderStepAt, 0);
-        }
-        match = std::memcmp(w.host, want.data() + at, bytes) == 0;
+    rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, total, 0, stream, &w);
+    if (rc != FLASHOPTIM_OK) {
+        destroy_space(w);       // (the check may be on its way: freeing waits for it)
+        return rc;
     }
-    give_space(w);
-    if (!match) return FLASHOPTIM_ERR_BAD_BLOB;
-    rc = run_copy(kind, tensors, n_tensors, static_cast<uint8_t*>(const_cast<void*>(blob)), false, total, 0, stream);
+    rc = wait_space(w, hipSuccess, stream);
     if (rc != FLASHOPTIM_OK) return rc;
-    *step_out = step;
+    int64_t found[2];
+    std::memcpy(found, w.host, sizeof(found));
+    give_space(w);
+    if (!found[0]) return FLASHOPTIM_ERR_BAD_BLOB;
+    *step_out = found[1];
     return FLASHOPTIM_OK;
 }
 
