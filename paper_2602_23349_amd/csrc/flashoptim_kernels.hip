@@ -1130,16 +1130,18 @@ hipError_t launch_clock_monitor(unsigned long long* samples, int n_samples, unsi
 // array on one side, and that array is most of the traffic, so the lane layout follows it: a lane owns four
 // consecutive elements per pass, one 128-bit FP32 access, 64 bits of BF16 or 32 bits of codes, and a wavefront's
 // access covers whole cache lines of every stream.  A quantisation group is eight lanes.  A workgroup of 256 lanes
-// covers kCodecTile consecutive elements in passes of 1024, all of whose loads are issued before the first use.
-// Bound: HBM.  150 M elements, before (eight consecutive elements per lane: two FP32 accesses that each cover half
-// of every line, so no non-temporal hint) and now: split 174 -> 163 us (6.4 TB/s), reconstruct 191 -> 163, quantize
-// 123 -> 117, dequantize 146 -> 119.  Two passes: with one, dequantize stays at 147 us (the table is staged twice as
-// often), with four at 136.
+// covers kCodecTile consecutive elements in passes of 1024, all of whose loads are issued before the first use; split and
+// reconstruct take single wavefronts (below).
+// Bound: HBM.  (Eight consecutive elements per lane, so two FP32 accesses that each cover half of every line and no
+// non-temporal hint: 150 M elements split 174 us and, with the kernels of that time, 163 with four; reconstruct 191 and 163,
+// quantize 123 and 117, dequantize 146 and 119.)
 
 constexpr int kCodecVec = 4;
 constexpr int kCodecPass = kThreads * kCodecVec;          // elements per pass
 constexpr int kCodecPasses = 2;
 constexpr int kCodecTile = kCodecPass * kCodecPasses;     // elements per workgroup
+constexpr int kWaveThreads = 64;                          // split and reconstruct
+constexpr int kWaveTile = kWaveThreads * kCodecVec;
 
 struct LanePos {
     int64_t tile0;       // first element of the pass (wave-uniform)
@@ -1257,11 +1259,21 @@ __device__ __forceinline__ float reconstruct_n(uint32_t b, int rho) {
     const float q = (float)rho / (float)N;
     return base + ldexpf(q, half_ulp_log2(b));
 }
-// The 8-bit case with rho / 127 read from a staged copy of the table of these divisions.
-__device__ __forceinline__ float reconstruct_tab(const float* rho_over_127, uint32_t b, uint32_t rho_byte) {
+// i / 127 of a signed and i / 255 of an unsigned byte, correctly rounded: the reciprocal as the sum of two floats, of which
+// the product with i needs one rounding each.  That this is the IEEE quotient for all 256 bytes is a matter of trying them.
+__device__ __forceinline__ float code_over_127(uint32_t byte) {
+    const float i = (float)(int8_t)byte;
+    return fmaf(i, 0x1.020408p-7f, i * 0x1.020408p-35f);
+}
+__device__ __forceinline__ float code_over_255(uint32_t byte) {
+    const float i = (float)byte;
+    return fmaf(i, 0x1.010102p-8f, i * -0x1.fdfdfep-33f);
+}
+// The 8-bit case given q = rho / 127.
+__device__ __forceinline__ float reconstruct_q(uint32_t b, float q) {
     const float base = u2f(b << 16);
     if (((b >> 7) & 0xffu) == 255u) return base;
-    return base + ldexpf(rho_over_127[rho_byte], half_ulp_log2(b));
+    return base + ldexpf(q, half_ulp_log2(b));
 }
 
 // The "directional" reading of ULP(theta'), for the experiment of Section 4.4 only.  The BF16 grid is twice
@@ -1310,71 +1322,62 @@ __device__ __forceinline__ uint32_t split_rho_bits(float theta, uint32_t b) {
     return E == 255 ? 0u : round_to_int_bits(y);
 }
 
+// C and C^-1 as workgroups of one wavefront with one access to each stream: nothing is staged and nothing is shared, so a
+// wavefront starts, moves its 256 elements and makes room for the next.  us, 256 lanes in two passes (the decoder with rho / 127
+// from a staged table) -> this: split of 12 M / 38 M / 100 M elements 14.9 / 42.0 / 109.9 -> 14.2 / 40.1 / 102.3 (6.8 TB/s),
+// reconstruct 15.6 / 43.0 / 108.1 -> 14.3 / 40.2 / 103.0.  Two passes per wavefront: 14.9 / 41.6 / 106.6.  The quantisers, which
+// compute more, are better off as they are (momentum, 38 M: 31.2, as single wavefronts 34.5 with one pass and 31.4 with two).
 template <int N, typename RHO, bool THROUGH, bool FULL>
 __device__ __forceinline__ void split_tile(const float* theta, uint16_t* param, RHO* rho, int64_t n, int64_t tile0) {
-    float th[kCodecPasses][kCodecVec];
+    float th[kCodecVec];
+    const LanePos L = lane_pos_at<FULL>(tile0, n);
+    load_f32(th, theta, L);
+    uint32_t pw[kCodecVec / 2], c[kCodecVec];
 #pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) load_f32(th[r], theta, lane_pos_at<FULL>(tile0 + r * kCodecPass, n));
+    for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[2 * j], th[2 * j + 1]);
 #pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
-        uint32_t pw[kCodecVec / 2], c[kCodecVec];
-#pragma unroll
-        for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[r][2 * j], th[r][2 * j + 1]);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<N>(th[r][i], half_of(pw, i));
-        store_u16<THROUGH>(param, L, pw);
-        if constexpr (sizeof(RHO) == 1) {
-            uint32_t rw[kCodecVec / 4];
-            pack_u8(rw, c);
-            store_u8<THROUGH>(rho, L, rw);
-        } else {
-            uint32_t rw[kCodecVec / 2];
-            pack_u16(rw, c);
-            store_u16<THROUGH>(rho, L, rw);
-        }
+    for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<N>(th[i], half_of(pw, i));
+    store_u16<THROUGH>(param, L, pw);
+    if constexpr (sizeof(RHO) == 1) {
+        uint32_t rw[kCodecVec / 4];
+        pack_u8(rw, c);
+        store_u8<THROUGH>(rho, L, rw);
+    } else {
+        uint32_t rw[kCodecVec / 2];
+        pack_u16(rw, c);
+        store_u16<THROUGH>(rho, L, rw);
     }
 }
 template <int N, typename RHO, bool THROUGH>
-__global__ __launch_bounds__(kThreads) void split_kernel(const float* theta, uint16_t* param, RHO* rho, int64_t n) {
-    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) split_tile<N, RHO, THROUGH, true>(theta, param, rho, n, tile0);
+__global__ __launch_bounds__(kWaveThreads) void split_kernel(const float* theta, uint16_t* param, RHO* rho, int64_t n) {
+    const int64_t tile0 = (int64_t)blockIdx.x * kWaveTile;
+    if (n - tile0 >= kWaveTile) split_tile<N, RHO, THROUGH, true>(theta, param, rho, n, tile0);
     else split_tile<N, RHO, THROUGH, false>(theta, param, rho, n, tile0);
 }
 
 template <int N, typename RHO, bool THROUGH, bool FULL>
 __device__ __forceinline__ void reconstruct_tile(const uint16_t* param, const RHO* rho, float* theta, int64_t n,
-                                                 int64_t tile0, float* rho_over_n) {
-    constexpr int kRhoWords = sizeof(RHO) == 1 ? kCodecVec / 4 : kCodecVec / 2;
-    uint32_t pw[kCodecPasses][kCodecVec / 2], rw[kCodecPasses][kRhoWords];
+                                                 int64_t tile0) {
+    static_assert(sizeof(RHO) != 1 || N == 127, "rho_over_127");
+    uint32_t pw[kCodecVec / 2], rw[sizeof(RHO) == 1 ? kCodecVec / 4 : kCodecVec / 2];
+    const LanePos L = lane_pos_at<FULL>(tile0, n);
+    load_u16(pw, param, L);
+    if constexpr (sizeof(RHO) == 1) load_u8(rw, rho, L);
+    else load_u16(rw, rho, L);
+    float th[kCodecVec];
 #pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
-        load_u16(pw[r], param, L);
-        if constexpr (sizeof(RHO) == 1) load_u8(rw[r], rho, L);
-        else load_u16(rw[r], rho, L);
+    for (int i = 0; i < kCodecVec; ++i) {
+        if constexpr (sizeof(RHO) == 1) th[i] = reconstruct_q(half_of(pw, i), code_over_127(byte_of(rw, i)));
+        else th[i] = reconstruct_n<N>(half_of(pw, i), (int)(int16_t)half_of(rw, i));
     }
-    if constexpr (sizeof(RHO) == 1) stage_table(rho_over_n, g_decode_tables.rho);
-#pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
-        float th[kCodecVec];
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) {
-            if constexpr (sizeof(RHO) == 1) th[i] = reconstruct_tab(rho_over_n, half_of(pw[r], i), byte_of(rw[r], i));
-            else th[i] = reconstruct_n<N>(half_of(pw[r], i), (int)(int16_t)half_of(rw[r], i));
-        }
-        store_f32<THROUGH>(theta, L, th);
-    }
+    store_f32<THROUGH>(theta, L, th);
 }
 template <int N, typename RHO, bool THROUGH>
-__global__ __launch_bounds__(kThreads) void reconstruct_kernel(const uint16_t* param, const RHO* rho, float* theta,
-                                                               int64_t n) {
-    static_assert(sizeof(RHO) != 1 || N == 127, "the table holds rho / 127");
-    __shared__ float rho_over_n[sizeof(RHO) == 1 ? 256 : 1];
-    const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) reconstruct_tile<N, RHO, THROUGH, true>(param, rho, theta, n, tile0, rho_over_n);
-    else reconstruct_tile<N, RHO, THROUGH, false>(param, rho, theta, n, tile0, rho_over_n);
+__global__ __launch_bounds__(kWaveThreads) void reconstruct_kernel(const uint16_t* param, const RHO* rho, float* theta,
+                                                                   int64_t n) {
+    const int64_t tile0 = (int64_t)blockIdx.x * kWaveTile;
+    if (n - tile0 >= kWaveTile) reconstruct_tile<N, RHO, THROUGH, true>(param, rho, theta, n, tile0);
+    else reconstruct_tile<N, RHO, THROUGH, false>(param, rho, theta, n, tile0);
 }
 
 // The data-independent experiment of Section 4.4: FP32 bit patterns first, first + stride, ...
@@ -1518,8 +1521,23 @@ __device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], u
 }
 
 // Decoders of Algorithms 2 and 3 (and of the linear baseline).  What is multiplied by the group scale
-// is a function of the code byte alone - q / 255, q / 127, phi_m^-1(q / 127) - and comes from a staged
-// copy of the table of those defining divisions instead of one or two IEEE divisions per element.
+// is a function of the code byte alone: q / 255, q / 127, phi_m^-1(q / 127).  dequantize_byte forms it (the second division has
+// a denominator in [0.99, 2] and a numerator that is 0 or at least 1 / 127); where a workgroup decodes enough to stage a
+// copy of the table of these divisions (the quantisation error, the conversions) dequantize_one reads it there.  The dequantiser
+// with the table took 6.2 us for 5 M momentum codes (5.0 without), 30.9 (31.0) for 38 M and 77.5 (77.0) for 100 M; variance
+// codes, 38 M, 31.3 (30.5).
+template <bool VARIANCE, bool LINEAR>
+__device__ __forceinline__ float dequantize_byte(uint32_t q, float s) {
+    float c;
+    if (VARIANCE) {
+        c = code_over_255(q);
+    } else {
+        const float z = code_over_127(q);
+        c = LINEAR ? z : div_rn_midrange(z, 2.0f - fabsf(z));
+    }
+    const float f = c * s;
+    return (VARIANCE && !LINEAR) ? f * f : f;
+}
 template <bool VARIANCE, bool LINEAR>
 __device__ __forceinline__ const float* decode_table() {
     return VARIANCE ? g_decode_tables.v : (LINEAR ? g_decode_tables.rho : g_decode_tables.m);
@@ -1562,7 +1580,7 @@ __device__ __forceinline__ float load_scale(const uint16_t* scale, const LanePos
 
 template <bool VARIANCE, bool LINEAR, bool THROUGH, bool FULL>
 __device__ __forceinline__ void dequantize_tile(const uint8_t* q, const uint16_t* scale, float* x, int64_t n,
-                                                int64_t tile0, float* tab) {
+                                                int64_t tile0) {
     uint32_t w[kCodecPasses][kCodecVec / 4];
     float s[kCodecPasses];
 #pragma unroll
@@ -1571,23 +1589,21 @@ __device__ __forceinline__ void dequantize_tile(const uint8_t* q, const uint16_t
         load_u8(w[r], q, L);
         s[r] = load_scale(scale, L);
     }
-    stage_table(tab, decode_table<VARIANCE, LINEAR>());
 #pragma unroll
     for (int r = 0; r < kCodecPasses; ++r) {
         const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, n);
         float v[kCodecVec];
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) v[i] = dequantize_one<VARIANCE, LINEAR>(tab, byte_of(w[r], i), s[r]);
+        for (int i = 0; i < kCodecVec; ++i) v[i] = dequantize_byte<VARIANCE, LINEAR>(byte_of(w[r], i), s[r]);
         store_f32<THROUGH>(x, L, v);
     }
 }
 template <bool VARIANCE, bool LINEAR, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, const uint16_t* scale, float* x,
                                                               int64_t n) {
-    __shared__ float tab[256];
     const int64_t tile0 = (int64_t)blockIdx.x * kCodecTile;
-    if (n - tile0 >= kCodecTile) dequantize_tile<VARIANCE, LINEAR, THROUGH, true>(q, scale, x, n, tile0, tab);
-    else dequantize_tile<VARIANCE, LINEAR, THROUGH, false>(q, scale, x, n, tile0, tab);
+    if (n - tile0 >= kCodecTile) dequantize_tile<VARIANCE, LINEAR, THROUGH, true>(q, scale, x, n, tile0);
+    else dequantize_tile<VARIANCE, LINEAR, THROUGH, false>(q, scale, x, n, tile0);
 }
 
 // Quantisation error of a buffer (Section 4.5): sum (Q^-1(Q(x)) - x)^2 and sum x^2, in double.  A workgroup walks
@@ -1669,15 +1685,15 @@ __global__ __launch_bounds__(kTotalThreads) void nmse_total_kernel(const double2
     }
 }
 
-// launch(blocks, first, n) for every launch that the tiles of n elements take: the n elements from `first` on.  (One
-// launch holds 2^24 - 1 tiles, 2^35 elements less a tile.)
+// launch(blocks, first, n) for every launch that the tiles of n elements take, `tile` of them to a workgroup of `threads` lanes:
+// the n elements from `first` on.  (One launch holds fewer than 2^32 work-items.)
 template <typename F>
-static hipError_t for_each_launch(int64_t n, F launch) {
-    const int64_t tiles = (n + kCodecTile - 1) / kCodecTile;
+static hipError_t for_each_launch(int64_t n, int tile, int threads, F launch) {
+    const int64_t tiles = (n + tile - 1) / tile;
     for (int64_t t = 0, k; t < tiles; t += k) {
-        k = launch_span(tiles, t, kThreads);
-        const int64_t first = t * kCodecTile, left = n - first;
-        launch(dim3((unsigned)k), first, left < k * kCodecTile ? left : k * kCodecTile);
+        k = launch_span(tiles, t, threads);
+        const int64_t first = t * tile, left = n - first;
+        launch(dim3((unsigned)k), first, left < k * tile ? left : k * tile);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1690,9 +1706,9 @@ static inline unsigned nmse_blocks(int64_t n) {
 
 template <int N, typename RHO>
 static hipError_t launch_split_n(const float* theta, uint16_t* param, RHO* rho, int64_t n, hipStream_t s) {
-    return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-        if (codec_through(n)) hipLaunchKernelGGL((split_kernel<N, RHO, true>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
-        else hipLaunchKernelGGL((split_kernel<N, RHO, false>), blocks, dim3(kThreads), 0, s, theta + at, param + at, rho + at, count);
+    return for_each_launch(n, kWaveTile, kWaveThreads, [=](dim3 blocks, int64_t at, int64_t count) {
+        if (codec_through(n)) hipLaunchKernelGGL((split_kernel<N, RHO, true>), blocks, dim3(kWaveThreads), 0, s, theta + at, param + at, rho + at, count);
+        else hipLaunchKernelGGL((split_kernel<N, RHO, false>), blocks, dim3(kWaveThreads), 0, s, theta + at, param + at, rho + at, count);
     });
 }
 hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
@@ -1701,9 +1717,9 @@ hipError_t launch_split(int bits, const float* theta, void* param, void* rho, in
 }
 template <int N, typename RHO>
 static hipError_t launch_reconstruct_n(const uint16_t* param, const RHO* rho, float* theta, int64_t n, hipStream_t s) {
-    return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
-        if (codec_through(n)) hipLaunchKernelGGL((reconstruct_kernel<N, RHO, true>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at, count);
-        else hipLaunchKernelGGL((reconstruct_kernel<N, RHO, false>), blocks, dim3(kThreads), 0, s, param + at, rho + at, theta + at, count);
+    return for_each_launch(n, kWaveTile, kWaveThreads, [=](dim3 blocks, int64_t at, int64_t count) {
+        if (codec_through(n)) hipLaunchKernelGGL((reconstruct_kernel<N, RHO, true>), blocks, dim3(kWaveThreads), 0, s, param + at, rho + at, theta + at, count);
+        else hipLaunchKernelGGL((reconstruct_kernel<N, RHO, false>), blocks, dim3(kWaveThreads), 0, s, param + at, rho + at, theta + at, count);
     });
 }
 hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s) {
@@ -1733,7 +1749,7 @@ static hipError_t dispatch_codec(bool variance, bool linear, bool through, F f) 
 }
 hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
     return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
-        return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+        return for_each_launch(n, kCodecTile, kThreads, [=](dim3 blocks, int64_t at, int64_t count) {
             hipLaunchKernelGGL((quantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s, x + at,
                                (uint8_t*)q + at, scale + at / kGroup, count);
         });
@@ -1742,7 +1758,7 @@ hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, 
 hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                              hipStream_t s) {
     return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
-        return for_each_launch(n, [=](dim3 blocks, int64_t at, int64_t count) {
+        return for_each_launch(n, kCodecTile, kThreads, [=](dim3 blocks, int64_t at, int64_t count) {
             hipLaunchKernelGGL((dequantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s,
                                (const uint8_t*)q + at, scale + at / kGroup, x + at, count);
         });
@@ -1831,7 +1847,7 @@ __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile
         const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
         float f[kCodecVec];
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_tab(tab[0], half_of(pw[r], i), byte_of(rw[r], i));
+        for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_q(half_of(pw[r], i), tab[0][byte_of(rw[r], i)]);
         store_f32<THROUGH>(T.theta32, L, f);
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw[r], i), sm[r]);
