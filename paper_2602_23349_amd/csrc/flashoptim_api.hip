@@ -364,8 +364,7 @@ hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, f
     for (int64_t first = 0; first < blocks; first += seg) {
         a.block_offset = (uint32_t)first;
         const int64_t n = blocks - first < seg ? blocks - first : seg;
-        a.through = op == kOpCompress || op == kOpDecompress ? fo::convert_through(n * tile_elems)
-                                                             : fo::step_through(kind, split, quant, n * tile_elems);
+        if (op != kOpCompress && op != kOpDecompress) a.through = fo::step_through(kind, split, quant, n * tile_elems);
         const hipError_t e = launch_segment(op, kind, direct, split, quant, shape, a, n, stream);
         if (e != hipSuccess) return e;
     }
@@ -383,8 +382,9 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     int64_t elems = 0;
     for (const TensorDev& d : live) elems += d.numel;
     const fo::StepShape shape = fo::step_shape(kind, split, quant, elems);
-    const int64_t ce = (op == kOpCompress || op == kOpDecompress) ? fo::kConvChunkElems
-                                                                  : fo::chunk_elems(split, quant, shape);
+    const bool convert = op == kOpCompress || op == kOpDecompress;
+    if (convert) a.through = fo::convert_through(elems);
+    const int64_t ce = convert ? fo::convert_chunk(op == kOpCompress, a.through) : fo::chunk_elems(split, quant, shape);
     // one workgroup per chunk: the launch grid is a 31-bit count
     uint32_t log2_ce = 0;
     while (((int64_t)1 << log2_ce) < ce) ++log2_ce;        // every tile size is a power of two

@@ -68,8 +68,12 @@ constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, b
     if (!through) return kNoLimit;
     return split ? (kind == 0 ? 4 : 5) : quant ? (kind == 0 ? 6 : 7) : kind == 0 ? 11 : 14;
 }
-// Layout conversion to FP32: 5 M elements 16.5 -> 16.1 us, GPT-2 348.9 -> 344.5, 300 M 861 -> 842; 2 M 5.9 with no limit, 7.4.
-constexpr int decompress_resident(int64_t elems) { return elems < ((int64_t)1 << 22) ? kNoLimit : 7; }
+// Layout conversions, in us with no limit -> with it.  To FP32: 5 M elements 16.5 -> 16.1, GPT-2 348.9 -> 344.5, 300 M 861 -> 842;
+// 2 M 5.9 with no limit, 7.4.  From FP32, in the shape of single wavefronts: GPT-2 337 -> 323, 300 M 825 -> 777 (21 of them 321
+// and 793, 16 330 and 790).
+constexpr int convert_resident(bool compress, bool through, int64_t elems) {
+    return compress ? (through ? 18 : kNoLimit) : elems < ((int64_t)1 << 22) ? kNoLimit : 7;
+}
 // The dynamic LDS, in bytes, with which exactly `resident` workgroups that use `used` bytes fit into a compute unit's
 // 160 KB (given out in units of 1280 bytes).
 constexpr unsigned lds_to_hold(int resident, unsigned used) {
@@ -94,7 +98,7 @@ constexpr int step_array_bytes(int kind, bool split, bool quant) {      // per e
 constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
     return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
 }
-constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25); }
+constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25); }      // (of the whole call)
 constexpr bool codec_through(int64_t elems) { return elems >= ((int64_t)1 << 23); }
 
 constexpr int kCopyPiece = 16 * 1024;        // checkpoint copy: bytes per workgroup
@@ -159,7 +163,7 @@ struct StepArgs {
     uint32_t table_lr_mask;
     uint32_t shared_lr_bits;
     TensorDev single;           // the one tensor of a direct launch
-    bool through;               // stores go through to memory (step_through, convert_through): per launch
+    bool through;               // stores go through to memory (step_through per launch, convert_through per call)
     StepConsts c;
     const float* sqrt_min_word; // AdamW steps: device word that holds StepConsts::sqrt_min for this device
 };
@@ -191,7 +195,12 @@ struct CopyArgs {
 
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
                        int64_t n_blocks, hipStream_t s);
-constexpr int kConvChunkElems = 1024;   // elements per workgroup of the layout-conversion kernel: one pass of its lanes
+// Lanes per workgroup and elements per tile of the layout conversions.  Compressing stages nothing: calls whose stores go
+// through take single wavefronts, 18 to a compute unit (GPT-2 344.8 -> 322.6 us, 300 M elements 816 -> 777, 25 M 70.0 -> 69.8);
+// smaller ones 256 lanes (5 M 15.0 us, as single wavefronts 15.5).  Decompressing stages three tables (without them, as single
+// wavefronts, GPT-2 342 -> 360 us with no limit and 346 with 14 to a unit).
+constexpr int convert_threads(bool compress, bool through) { return compress && through ? 64 : 256; }
+constexpr int convert_chunk(bool compress, bool through) { return convert_threads(compress, through) * 4; }
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);
 hipError_t launch_probe(int kind, bool direct, StepShape shape, const StepArgs& a, int64_t n_blocks, hipStream_t s);
 hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s);

@@ -1783,88 +1783,74 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
 // the compressed layout: COMPRESS applies C, Q_m, Q_v (Algorithms 1-3) in one pass over a list;
 // the other direction applies the inverses (its per-code factors from staged tables of the defining
 // divisions).  Tile look-up of the step kernels, lane layout and arithmetic of the standalone codecs.
-constexpr int kConvPasses = kConvChunkElems / kCodecPass;
-static_assert(kConvPasses * kCodecPass == kConvChunkElems, "the host builds the conversion's tables for tiles of this size");
+// One access of a lane to each stream: tiles of convert_chunk() elements.
 
 template <bool HAS_V, bool THROUGH, bool FULL>
 __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0) {
-    float th[kConvPasses][kCodecVec], m[kConvPasses][kCodecVec], v[kConvPasses][kCodecVec];
-#pragma unroll
-    for (int r = 0; r < kConvPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
-        load_f32(th[r], T.theta32, L);
-        load_f32(m[r], T.m32, L);
-        if (HAS_V) load_f32(v[r], T.v32, L);
-    }
+    float th[kCodecVec], m[kCodecVec], v[kCodecVec];
+    const LanePos L = lane_pos_at<FULL>(tile0, T.numel);
+    load_f32(th, T.theta32, L);
+    load_f32(m, T.m32, L);
+    if (HAS_V) load_f32(v, T.v32, L);
     // every lane of a group takes part in the group maxima, also those past the end
+    const int64_t group = (L.tile0 + L.lane_el) >> 5;
+    uint32_t pw[kCodecVec / 2], c[kCodecVec], w[kCodecVec / 4];
 #pragma unroll
-    for (int r = 0; r < kConvPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
-        const int64_t group = (L.tile0 + L.lane_el) >> 5;
-        uint32_t pw[kCodecVec / 2], c[kCodecVec], w[kCodecVec / 4];
+    for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[2 * j], th[2 * j + 1]);
 #pragma unroll
-        for (int j = 0; j < kCodecVec / 2; ++j) pw[j] = bf16_pack(th[r][2 * j], th[r][2 * j + 1]);
-#pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<127>(th[r][i], half_of(pw, i));
-        pack_u8(w, c);
-        if (L.cnt > 0) {
-            store_u16<THROUGH>(T.param, L, pw);
-            store_u8<THROUGH>(T.rho, L, w);
-        }
-        const uint32_t ms = quantize_lane<false, false>(m[r], w);
-        if (L.cnt > 0) store_u8<THROUGH>(T.m_q, L, w);
-        if (group_leader(L)) as_global(T.m_scale)[group] = (uint16_t)ms;
-        if (HAS_V) {
-            const uint32_t vs = quantize_lane<true, false>(v[r], w);
-            if (L.cnt > 0) store_u8<THROUGH>(T.v_q, L, w);
-            if (group_leader(L)) as_global(T.v_scale)[group] = (uint16_t)vs;
-        }
+    for (int i = 0; i < kCodecVec; ++i) c[i] = split_rho_bits<127>(th[i], half_of(pw, i));
+    pack_u8(w, c);
+    if (L.cnt > 0) {
+        store_u16<THROUGH>(T.param, L, pw);
+        store_u8<THROUGH>(T.rho, L, w);
+    }
+    const uint32_t ms = quantize_lane<false, false>(m, w);
+    if (L.cnt > 0) store_u8<THROUGH>(T.m_q, L, w);
+    if (group_leader(L)) as_global(T.m_scale)[group] = (uint16_t)ms;
+    if (HAS_V) {
+        const uint32_t vs = quantize_lane<true, false>(v, w);
+        if (L.cnt > 0) store_u8<THROUGH>(T.v_q, L, w);
+        if (group_leader(L)) as_global(T.v_scale)[group] = (uint16_t)vs;
     }
 }
 
 template <bool HAS_V, bool THROUGH, bool FULL>
 __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0, float (&tab)[3][256]) {
-    uint32_t pw[kConvPasses][kCodecVec / 2], rw[kConvPasses][kCodecVec / 4], mw[kConvPasses][kCodecVec / 4],
-        vw[kConvPasses][kCodecVec / 4];
-    float sm[kConvPasses], sv[kConvPasses];
-#pragma unroll
-    for (int r = 0; r < kConvPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
-        load_u16(pw[r], T.param, L);
-        load_u8(rw[r], T.rho, L);
-        load_u8(mw[r], T.m_q, L);
-        sm[r] = load_scale(T.m_scale, L);
-        if (HAS_V) {
-            load_u8(vw[r], T.v_q, L);
-            sv[r] = load_scale(T.v_scale, L);
-        }
+    uint32_t pw[kCodecVec / 2], rw[kCodecVec / 4], mw[kCodecVec / 4], vw[kCodecVec / 4];
+    const LanePos L = lane_pos_at<FULL>(tile0, T.numel);
+    load_u16(pw, T.param, L);
+    load_u8(rw, T.rho, L);
+    load_u8(mw, T.m_q, L);
+    const float sm = load_scale(T.m_scale, L);
+    float sv = 0.0f;
+    if (HAS_V) {
+        load_u8(vw, T.v_q, L);
+        sv = load_scale(T.v_scale, L);
     }
     tab[0][threadIdx.x] = g_decode_tables.rho[threadIdx.x];
     tab[1][threadIdx.x] = g_decode_tables.m[threadIdx.x];
     stage_table(tab[2], g_decode_tables.v);
+    float f[kCodecVec];
 #pragma unroll
-    for (int r = 0; r < kConvPasses; ++r) {
-        const LanePos L = lane_pos_at<FULL>(tile0 + r * kCodecPass, T.numel);
-        float f[kCodecVec];
+    for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_q(half_of(pw, i), tab[0][byte_of(rw, i)]);
+    store_f32<THROUGH>(T.theta32, L, f);
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_q(half_of(pw[r], i), tab[0][byte_of(rw[r], i)]);
-        store_f32<THROUGH>(T.theta32, L, f);
+    for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw, i), sm);
+    store_f32<THROUGH>(T.m32, L, f);
+    if (HAS_V) {
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw[r], i), sm[r]);
-        store_f32<THROUGH>(T.m32, L, f);
-        if (HAS_V) {
-#pragma unroll
-            for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(vw[r], i), sv[r]);
-            store_f32<THROUGH>(T.v32, L, f);
-        }
+        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(vw, i), sv);
+        store_f32<THROUGH>(T.v32, L, f);
     }
 }
 
 template <bool HAS_V, bool COMPRESS, bool DIRECT, bool THROUGH>
-__global__ __launch_bounds__(kThreads) void convert_kernel(StepArgs a) {
+__global__ __launch_bounds__(convert_threads(COMPRESS, THROUGH)) void convert_kernel(StepArgs a) {
+    constexpr int kTile = convert_chunk(COMPRESS, THROUGH);
+    static_assert(kTile == convert_threads(COMPRESS, THROUGH) * kCodecVec, "one access of a lane to each stream");
     TensorDev T;
-    const int64_t tile0 = locate_tile<DIRECT>(a, T) * (int64_t)kConvChunkElems;
-    const bool full = T.numel - tile0 >= kConvChunkElems;
+    const int64_t tile0 = locate_tile<DIRECT>(a, T) * (int64_t)kTile;
+    const bool full = T.numel - tile0 >= kTile;
     if constexpr (COMPRESS) {
         if (full) compress_tile<HAS_V, THROUGH, true>(T, tile0);
         else compress_tile<HAS_V, THROUGH, false>(T, tile0);
@@ -1876,8 +1862,9 @@ __global__ __launch_bounds__(kThreads) void convert_kernel(StepArgs a) {
 }
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    const dim3 grid((unsigned)n_blocks), block(kThreads);
-    const unsigned lds = compress ? 0u : lds_to_hold(decompress_resident(n_blocks * kConvChunkElems), 3 * 256 * sizeof(float));
+    const dim3 grid((unsigned)n_blocks), block(convert_threads(compress, a.through));
+    const unsigned lds = lds_to_hold(convert_resident(compress, a.through, n_blocks * convert_chunk(compress, a.through)),
+                                     compress ? 0 : 3 * 256 * sizeof(float));
 #define FO_CONV(HV, CP, DR)                                                                                   \
     do {                                                                                                      \
         if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, lds, s, a);        \

@@ -223,3 +223,26 @@ def test_conversions_on_both_sides_of_their_limits(n):
     fo.decompress_state("sgd", [c])
     assert np.array_equal(f.theta.cpu().numpy().view(np.uint32), oracle.reconstruct(thp, rho).view(np.uint32))
     assert np.array_equal(f.m.cpu().numpy().view(np.uint32), oracle.dequantize_momentum(q, s).view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [1 << 25, (1 << 25) - 1])       # single wavefronts, and 256 lanes
+def test_compressing_a_list_on_both_sides_of_its_limit(n):
+    sizes = [1, 31, 255, 256, 257, 1023, 1025, 4097]
+    sizes.append(n - sum(sizes))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    bufs = []
+    for k in sizes:
+        f = fo.ParamBuffers(k, "adamw", with_grad=False, split_weights=False, quantize_states=False)
+        f.theta.normal_(0, 0.02, generator=g)
+        f.m.normal_(0, 1e-4, generator=g)
+        f.v.normal_(0, 1e-4, generator=g).square_()
+        c = fo.ParamBuffers(k, "adamw", with_grad=False)
+        c.theta, c.m, c.v = f.theta, f.m, f.v
+        bufs.append(c)
+    fo.compress_state("adamw", bufs)
+    for c in bufs:
+        thp, rho = oracle.split(c.theta.cpu().numpy())
+        mq, ms = oracle.quantize_momentum(c.m.cpu().numpy())
+        vq, vs = oracle.quantize_variance(c.v.cpu().numpy())
+        for k, want in dict(thp=thp, rho=rho, mq=mq, ms=ms, vq=vq, vs=vs).items():
+            assert np.array_equal(download(c)[k], want), (c.numel, k)
