@@ -117,8 +117,8 @@ struct Plan {
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
     void* d_header = nullptr;      // copies only: the blob's header and table, all but the step
-    uint32_t* d_verdict = nullptr; // unpacking only: whether the blob's header was found to be this one (calls with the same
-                                   // plan write the same tensors, so the caller orders them)
+    uint32_t* d_verdict = nullptr; // unpacking only: whether the blob's header was found to be this one, a word per call in
+    uint32_t verdicts = 0;         // turn: a refused call's copy may be still to run when a later call's check does
     void* h_mem = nullptr;         // pinned source of d_mem's upload, kept until the plan is freed
     size_t bytes = 0;              // of each
     bool uploaded = false;         // an upload has been enqueued (one that was captured runs with the graph, if at all)
@@ -157,6 +157,8 @@ Plan* find_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>&
     return nullptr;
 }
 
+constexpr uint32_t kVerdictWords = 64;      // (a power of two)
+
 // What a plan puts on the device.
 struct PlanSource {
     const void* table;
@@ -188,7 +190,7 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
     const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
     const size_t verdict_at = header_at + (size_t)align64((int64_t)src.header.size());
-    p.bytes = verdict_at + 64;
+    p.bytes = verdict_at + kVerdictWords * sizeof(uint32_t);
     hipError_t e = hipMalloc(&p.d_mem, p.bytes);
     if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, p.bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
@@ -822,9 +824,10 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         a.header_dst = reinterpret_cast<uint4*>(blob);
         a.step = step;
     } else {
-        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), plan->d_verdict,
+        uint32_t* verdict = plan->d_verdict + plan->verdicts++ % kVerdictWords;
+        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), verdict,
                                        reinterpret_cast<int64_t*>(check->host), check->flag(), check->seq, stream));
-        a.verdict = plan->d_verdict;
+        a.verdict = verdict;
     }
     FO_HIP(fo::launch_copy(a, stream));
     return FLASHOPTIM_OK;

@@ -246,3 +246,28 @@ def test_compressing_a_list_on_both_sides_of_its_limit(n):
         vq, vs = oracle.quantize_variance(c.v.cpu().numpy())
         for k, want in dict(thp=thp, rho=rho, mq=mq, ms=ms, vq=vq, vs=vs).items():
             assert np.array_equal(download(c)[k], want), (c.numel, k)
+
+
+# Whatever differs, unpacking has to leave every buffer as it was: any word of the header and of the table, in a table that
+# ends inside a workgroup's first pass and in longer ones.
+@pytest.mark.parametrize("n_tensors", [1, 5, 600, 5000])
+def test_unpacking_checks_every_word_of_the_table(n_tensors):
+    bufs = [fo.ParamBuffers(1 + i % 67, "sgd", with_grad=False) for i in range(n_tensors)]
+    for i, b in enumerate(bufs):
+        b.rho.fill_(i % 50 + 1)
+    blob = torch.zeros(fo.checkpoint_size("sgd", [b.numel for b in bufs]), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("sgd", bufs, 5, blob)
+    table = 64 + 16 * n_tensors
+    for b in bufs:
+        b.rho.zero_()
+    for at in sorted({0, 4, 8, 12, 24, 32, 40, 48, 56, 63, 64, table // 2 // 4 * 4, table - 16, table - 5, table - 1}):
+        blob[at] ^= 0x10
+        with pytest.raises(fo.FlashOptimError) as err:
+            fo.checkpoint_unpack("sgd", blob, bufs)
+        assert err.value.status == -5, at
+        blob[at] ^= 0x10
+    assert not any(b.rho.any() for b in bufs[::97])
+    for step in (0, 1 << 40, 2**63 - 1):                # the step is the caller's
+        blob[16:24] = torch.from_numpy(np.frombuffer(np.int64(step).tobytes(), np.uint8).copy()).cuda()
+        assert fo.checkpoint_unpack("sgd", blob, bufs) == step
+    assert all((b.rho == i * 97 % 50 + 1).all() for i, b in enumerate(bufs[::97]))
