@@ -131,12 +131,16 @@ _raw_current_device = getattr(torch._C, "_cuda_getDevice", None)
 _cuda_initialized = torch.cuda.is_initialized
 
 
-def _stream(stream):
+def _stream_handle(stream):
     if stream is None:
         if _raw_current_stream is not None and _raw_current_device is not None and _cuda_initialized():
             return _raw_current_stream(_raw_current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _stream(stream):
+    return C.c_void_p(_stream_handle(stream))
 
 
 def _check(status, where):
@@ -280,20 +284,20 @@ def _as_list(tensors):
 def adamw_step(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step(tl.address, tl.n, hp, _stream(stream)), "flashoptim_adamw_step")
+    _check(load_library().flashoptim_adamw_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_adamw_step")
 
 
 def adamw_step_exact(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step_exact(tl.address, tl.n, hp, _stream(stream)),
+    _check(load_library().flashoptim_adamw_step_exact(tl.address, tl.n, hp, _stream_handle(stream)),
            "flashoptim_adamw_step_exact")
 
 
 def adamw_step_noalloc(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step_noalloc(tl.address, tl.n, hp, _stream(stream)),
+    _check(load_library().flashoptim_adamw_step_noalloc(tl.address, tl.n, hp, _stream_handle(stream)),
            "flashoptim_adamw_step_noalloc")
 
 
@@ -308,13 +312,13 @@ def shard_range(numel, world, rank):
 def sgd_step(tensors, momentum, stream=None):
     tl = _as_list(tensors)
     hp = _SgdHp(momentum)
-    _check(load_library().flashoptim_sgd_step(tl.address, tl.n, hp, _stream(stream)), "flashoptim_sgd_step")
+    _check(load_library().flashoptim_sgd_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_sgd_step")
 
 
 def lion_step(tensors, beta1, beta2, stream=None):
     tl = _as_list(tensors)
     hp = _LionHp(beta1, beta2)
-    _check(load_library().flashoptim_lion_step(tl.address, tl.n, hp, _stream(stream)), "flashoptim_lion_step")
+    _check(load_library().flashoptim_lion_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_lion_step")
 
 
 def stream_probe(kind, tensors, stream=None):
