@@ -141,15 +141,15 @@ __device__ __forceinline__ float recip_of_fp16(float s) {
     return fmaf(e, r0, r0);
 }
 // FP16 scale of a group from its FP32 absmax: saturate at 65504, round to nearest even.
-// Returns the FP16 bits; *r is the correctly rounded reciprocal of the scale as the decoder
-// will read it (0 when the scale is 0, so that every code of the group becomes 0).
-__device__ __forceinline__ uint32_t group_scale(float absmax, float* r) {
+// Returns the FP16 bits; *s is the scale as the decoder will read it.
+__device__ __forceinline__ uint32_t group_scale(float absmax, float* s) {
     const float a = fminf(absmax, 65504.0f);
     const _Float16 h = (_Float16)a;
-    const float s = (float)h;
-    *r = (s == 0.0f) ? 0.0f : recip_of_fp16(s);
+    *s = (float)h;
     return (uint32_t)__builtin_bit_cast(uint16_t, h);
 }
+// The correctly rounded reciprocal of a group's scale; 0 when the scale is 0, so that every code of the group becomes 0.
+__device__ __forceinline__ float recip_of_scale(float s) { return (s == 0.0f) ? 0.0f : recip_of_fp16(s); }
 
 // Correctly rounded square root for 2^-96 <= x <= FLT_MAX: the hardware reciprocal-square-root
 // estimate (1 ulp) and one Newton correction, each step one FMA.  That this sequence returns the
@@ -827,13 +827,15 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
     // epilogue, part 2: group scales (DPP steps join the lanes of a group).  The square root
     // is monotone, so the group maximum of sqrt(v) is the square root of the maximum of v.
     amax_m = group_max<VEC>(amax_m);
-    float r_m, r_v = 0.0f, kr255 = 0.0f;
-    y.ms = group_scale(amax_m, &r_m);
+    float s_m_new, s_v_new, r_v = 0.0f, kr255 = 0.0f;
+    y.ms = group_scale(amax_m, &s_m_new);
+    const float r_m = recip_of_scale(s_m_new);
     if (HAS_V) {
         // the group's maximum lies between the extremes of the wavefront's lanes: in the short root's range if they are
         amax_v = group_max<VEC>(amax_v);
         const float root_max = fast ? sqrt_rn_midrange(amax_v) : sqrtf(amax_v);
-        y.vs = group_scale(root_max, &r_v);
+        y.vs = group_scale(root_max, &s_v_new);
+        r_v = recip_of_scale(s_v_new);
         // 255 * sqrt(1 / rbc2) * r_v to within one rounding: the constant comes from the host as the two halves of
         // its double-precision value
         kr255 = fmaf(c.k255_hi, r_v, c.k255_lo * r_v);
@@ -1466,12 +1468,33 @@ __global__ __launch_bounds__(kThreads) void sweep_kernel(uint64_t first, uint64_
 //
 // The companded codes are decided from an estimate, as in the step kernels: with their exact form (an IEEE division
 // or square root per element) throughout, 150 M elements of m / v took 120 / 125 us, with the estimate 117 / 118
-// (6.5 TB/s).  Momentum: m_code_bracket.  Variance: y* = v_sqrt_f32(v) * RN(255 r), where the hardware root is
+// (6.5 TB/s).  Momentum: below.  Variance: y* = v_sqrt_f32(v) * RN(255 r), where the hardware root is
 // within one ulp (flashoptim_selftest, section 1).  In units of 2^-24 the estimate is off by 2 (root) + 1 (255 r) and
 // the exact argument of Round() by 3 (root, * r, * 255): 6 * 2^-24 * 255.5 < 9.2e-5, and the fused multiply-add that
 // forms y* -+ w rounds by at most 2^-17 = 7.7e-6, so w = 1.1e-4 decides.  A subnormal v has y below 1e-9 for every FP16
 // scale, far from a tie.
 constexpr float kTieWindowCodecV = 1.1e-4f;
+
+// The momentum codes' estimate without the reciprocal of the scale: y = 254 f(m / s) with f(x) = x / (1 + |x|), which is
+// 254 m / (s + |m|).  Errors relative to 254 f, in units of 2^-24.  The exact chain: r and m1 (1 each, times the sensitivity
+// 1 / (1 + |x|) of f), den, m2 and the product with 127 (1 each).  The estimate: s + |m| (1), v_rcp_f32 (1 ulp: 2).  At
+// |x| = 1, where it is largest, 7 * 2^-24 * 127 = 5.3e-5 (beyond |x| = 1.008 the clamp holds).  The two fused multiply-adds
+// round by half an ulp of a value below 1, times 254, and of one below 256: 7.6e-6 each.  So 6.9e-5 decides.
+// den0 is the scale, or infinity in place of 0: p is then 1/2 and the code 0.  |m| has to stay below kCodeEstimateHi, so that
+// the reciprocal is a normal number; callers take the exact form otherwise.
+// Eight instructions per element become seven, and a lane's four elements share five less: the quantisation error of 16 M
+// elements 25.3 -> 24.9 us, momentum codes of 2^24 and fewer elements up to 1 %.  (Not in the steps, for which the registers
+// that hold m1 are there anyway: AdamW over 2 M elements 6.57 -> 6.46 us and lists of 25 M and more 0.2 % faster, but flat 3.4
+// to 4.1 M elements, where every workgroup is resident at once, 1-3 % slower.)
+constexpr float kTieWindowCodecM = 8.0e-5f;
+constexpr float kCodeEstimateHi = 1.2676506002282294e30f;      // 2^100
+__device__ __forceinline__ float code_den0(float s) { return s == 0.0f ? __builtin_inff() : s; }
+__device__ __forceinline__ void m_code_bracket_of_scale(float m, float den0, float* lo, float* hi) {
+    const float rc = __builtin_amdgcn_rcpf(den0 + fabsf(m));
+    const float p = __builtin_amdgcn_fmed3f(fmaf(m, rc, 0.5f), 0.0f, 1.0f);
+    *lo = fmaf(p, 254.0f, 1.0f - kTieWindowCodecM);
+    *hi = fmaf(p, 254.0f, 1.0f + kTieWindowCodecM);
+}
 
 // quantize_lane: the codes of a lane, one byte each, and the FP16 scale bits of its group.  All eight lanes of
 // a group must call it together; elements past the end are zero and do not raise the maximum.
@@ -1484,12 +1507,13 @@ __device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], u
     for (int i = 0; i < kCodecVec; ++i) a = fmaxf(a, VARIANCE ? x[i] : fabsf(x[i]));
     a = group_max<kCodecVec>(a);
     if (VARIANCE && !LINEAR) a = sqrtf(a);
-    float r;
-    const uint32_t sbits = group_scale(a, &r);
+    float s;
+    const uint32_t sbits = group_scale(a, &s);
     uint32_t c[kCodecVec];
     if (!LINEAR) {
         uint32_t lo_w = 0, hi_w = 0;
-        const float r255 = 255.0f * r;
+        const float r255 = VARIANCE ? 255.0f * recip_of_scale(s) : 0.0f, den0 = code_den0(s);
+        const bool beyond = !VARIANCE && a > kCodeEstimateHi;
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) {
             float lo, hi;
@@ -1498,18 +1522,20 @@ __device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], u
                 lo = fmaf(root, r255, -kTieWindowCodecV);
                 hi = fmaf(root, r255, kTieWindowCodecV);
             } else {
-                m_code_bracket(x[i], r, &lo, &hi);
+                m_code_bracket_of_scale(x[i], den0, &lo, &hi);
             }
             lo_w = put_u8(lo, i, lo_w);
             hi_w = put_u8(hi, i, hi_w);
         }
         w[0] = VARIANCE ? lo_w : lo_w ^ 0x80808080u;
-        if (any_lane(lo_w != hi_w)) {
+        if (any_lane((lo_w != hi_w) | beyond)) {
+            const float r = recip_of_scale(s);
 #pragma unroll
             for (int i = 0; i < kCodecVec; ++i) c[i] = VARIANCE ? v_code_exact(x[i], r) : m_code_exact(x[i], r);
             w[0] = pack_low_bytes(c[0], c[1], c[2], c[3]);
         }
     } else {
+        const float r = recip_of_scale(s);
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) {
             c[i] = VARIANCE ? round_to_int_bits(__builtin_amdgcn_fmed3f((x[i] * r) * 255.0f, 0.0f, 255.0f))
@@ -1892,8 +1918,8 @@ hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs
 //              codecs' variance codes) within 1 ulp of sqrtf(d), for every d in [1, 4): every mantissa, and for the
 //              root either parity of the exponent;
 //   section 2: sqrt_rn_midrange(x) == sqrtf(x) for EVERY FP32 value x of its range [2^-96, FLT_MAX];
-//   section 3: momentum codes: wherever the two conversions of m_code_bracket agree, they agree with
-//              m_code_exact, for every m' in [2^-13, 2) of either sign;
+//   section 3: momentum codes: wherever the two conversions of m_code_bracket agree, they agree with m_code_exact, for every
+//              m' in [2^-13, 2) of either sign, and so do those of m_code_bracket_of_scale, with two scales;
 //   section 4: variance codes: same for v_code_bracket against v_code_exact, over every FP32 value of
 //              four binades of v, for the bias-correction pair and group scale the host passes.
 //   section 5: div_rn_midrange(n, d) == n / d on 2^30 pseudo-random operand pairs with magnitudes
@@ -1950,6 +1976,12 @@ __device__ __forceinline__ void selftest_one(int section, uint64_t gid, const St
             const uint32_t exact = m_code_exact(m1, 1.0f) & 0xffu;
             checked = (a == b);
             failed = (a ^ 0x80u) != exact;
+            for (int k = 0; k < 2; ++k) {
+                const float s = k ? 0x1.7fcp-14f : 1.0f, m = m1 * s;
+                m_code_bracket_of_scale(m, s, &lo, &hi);
+                const uint32_t low = put_u8(lo, 0, 0);
+                failed |= low == put_u8(hi, 0, 0) && (low ^ 0x80u) != (m_code_exact(m, recip_of_fp16(s)) & 0xffu);
+            }
         }
     } else if (section == 5 || section == 6) {
         if (gid < kSelftestDivCount) {
