@@ -296,8 +296,9 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
  *                    as a step call (see above), and every replay writes the step it was captured with.
  * checkpoint_unpack: scatters `blob` (DEVICE memory) back into the tensors' buffers and
  *                    returns the stored step in *step_out (host).  The header and table
- *                    are validated against (kind, list) first; this reads the header back to
- *                    the host and therefore waits for prior work on `stream`. */
+ *                    are validated against (kind, list) on the device, ahead of the copy, which
+ *                    writes nothing if they differ; the call waits for that verdict and the step,
+ *                    and therefore for prior work on `stream`, but not for the copy. */
 int64_t flashoptim_checkpoint_size(int kind, const int64_t* numels, int64_t n_tensors);
 int flashoptim_checkpoint_pack(int kind, const flashoptim_tensor* tensors, int64_t n_tensors, int64_t step,
                                void* blob, int64_t blob_bytes, void* stream);

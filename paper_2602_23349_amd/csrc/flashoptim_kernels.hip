@@ -13,17 +13,15 @@
 // pair in 10^9); the state codes and scales are unaffected, the master weight can differ by one ulp.
 //
 // The step is bandwidth-bound by definition (12.25 algorithmic bytes per parameter
-// for AdamW), but an exactly rounded body costs on the order of a hundred VALU
-// issue slots per parameter, which at 8 TB/s is of the same order as the chip's
-// non-packed FP32 rate.  The design choices below are about keeping VALU work per
-// element low without changing a single rounding:
+// for AdamW), but an exactly rounded body, written down as the definitions have it, costs
+// well over a hundred VALU instructions per parameter, which at 8 TB/s is more than the chip's
+// non-packed FP32 rate admits.  The design choices below are about keeping VALU work per
+// element low without changing a single rounding (AdamW: 64 instructions per element):
 //   * decoding a state code is a function of one byte: rho/127, code/255 and
 //     phi_m^-1(code/127) come from three 256-entry LDS tables that each workgroup
 //     fills once with the same IEEE divisions the definition uses;
-//   * the 2^l scalings of Algorithm 1 are LDS tables of exact powers of two indexed by the
-//     exponent field of theta' (the decoder multiplies once: exact, or one rounding when
-//     the result is subnormal - the same rounding the two-factor form of Algorithm 1
-//     performs; the encoder multiplies by two exact factors);
+//   * the 2^l scalings of Algorithm 1 are floats made of the exponent bits of theta', one or two integer
+//     operations each (wavefronts with a weight below 2^-110, zeros included, take a general form);
 //   * Round(x) to an 8-bit integer is one FP32 addition of 1.5 * 2^23, whose low
 //     mantissa byte is the round-half-even integer in two's complement;
 //   * BF16 rounding uses the hardware v_cvt_pk_bf16_f32 (two elements per issue);
@@ -46,12 +44,14 @@
 // Work decomposition.  A lane owns 8 consecutive elements per tile: BF16 streams move as
 // 128-bit and byte streams as 64-bit accesses, and a quantisation group (32 elements) is a
 // lane quad, so the group absmax needs two DPP quad permutes and no LDS.  A workgroup (256
-// lanes, or 512) handles one tile of consecutive elements of one
+// lanes; 512 for SGD and Lion over 2^27 elements and more) handles one tile of consecutive elements of one
 // tensor; a small two-level table maps the workgroup index to (tensor, tile) so that one call covers a
 // whole parameter list, issued as a few consecutive launches.  Stream addresses are a scalar 64-bit
 // tile base plus a 32-bit lane offset.  A lane owns 4 elements, and a group is 8 lanes, where FP32 streams are
 // moved (ablation variants, codecs, conversions: a 128-bit FP32 access per lane then covers whole cache lines)
-// and where a launch is small (fewer than 2^20 elements: more wavefronts, each with half the work).
+// and where a launch is small (fewer than 2^20 elements: more wavefronts, each with half the work).  Where a workgroup
+// shares nothing (plain FP32 steps, split and reconstruct, large compressions) it is a single wavefront.  Large launches hold
+// fewer workgroups to a compute unit than fit (step_resident) and store past the caches (step_through).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
