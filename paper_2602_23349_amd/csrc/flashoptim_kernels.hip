@@ -16,7 +16,7 @@
 // for AdamW), but an exactly rounded body, written down as the definitions have it, costs
 // well over a hundred VALU instructions per parameter, which at 8 TB/s is more than the chip's
 // non-packed FP32 rate admits.  The design choices below are about keeping VALU work per
-// element low without changing a single rounding (AdamW: 64 instructions per element):
+// element low without changing a single rounding (AdamW: 65 instructions per element):
 //   * decoding a state code is a function of one byte: rho/127, code/255 and
 //     phi_m^-1(code/127) come from three 256-entry LDS tables that each workgroup
 //     fills once with the same IEEE divisions the definition uses;
@@ -1483,9 +1483,9 @@ constexpr float kTieWindowCodecV = 1.1e-4f;
 // den0 is the scale, or infinity in place of 0: p is then 1/2 and the code 0.  |m| has to stay below kCodeEstimateHi, so that
 // the reciprocal is a normal number; callers take the exact form otherwise.
 // Eight instructions per element become seven, and a lane's four elements share five less: the quantisation error of 16 M
-// elements 25.3 -> 24.9 us, momentum codes of 2^24 and fewer elements up to 1 %.  (Not in the steps, for which the registers
-// that hold m1 are there anyway: AdamW over 2 M elements 6.57 -> 6.46 us and lists of 25 M and more 0.2 % faster, but flat 3.4
-// to 4.1 M elements, where every workgroup is resident at once, 1-3 % slower.)
+// elements 25.3 -> 24.9 us, of 100 M 80.9 -> 78.6.  (Not in the steps: AdamW over 2 M elements 6.57 -> 6.46 us and the
+// Llama-3.1-8B list 0 to 0.6 % faster, but flat 3.4 to 4.1 M elements, where every workgroup is resident at once, up to 3 %
+// slower.)
 constexpr float kTieWindowCodecM = 8.0e-5f;
 constexpr float kCodeEstimateHi = 1.2676506002282294e30f;      // 2^100
 __device__ __forceinline__ float code_den0(float s) { return s == 0.0f ? __builtin_inff() : s; }
