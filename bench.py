@@ -222,14 +222,15 @@ def read_traffic(kind, workload, entry="exact"):
                                              "recorded_not_measured_in_this_run": True}
 
 
-def kernel_label(kind, release, exact, ckpt=False):
-    """The step kernel's name as rocprofv3 prints it: <KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT>."""
+def kernel_label(kind, release, exact, ckpt=False, numel=1 << 27):
+    """The step kernel's name as rocprofv3 prints it: <KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT>, for a call over
+    2^20 elements and more."""
     if ckpt:
         return "fo::copy_kernel"
     k = ["adamw", "sgd", "lion"].index(kind)
     tf = lambda b: "true" if b else "false"
     # SGD, Lion and every ablation variant are instantiated with EXACT = true (they have no division to shorten)
-    return f"fo::step_kernel<{k}, 8, {256 if k == 0 else 512}, {tf(release)}, true, true, {tf(exact or k != 0)}>"
+    return f"fo::step_kernel<{k}, 8, {256 if k == 0 or numel < 1 << 27 else 512}, {tf(release)}, true, true, {tf(exact or k != 0)}>"
 
 
 def time_calls(torch, stream, fn, steps, warmup=2):
@@ -444,7 +445,7 @@ def small_list_measurements(fo, W, torch, stream, steps=200):
                     "entry_point": "flashoptim_adamw_step_exact" if kind == "adamw" else f"flashoptim_{kind}_step",
                     "ms_per_step": ms, "params_per_s": n / (ms * 1e-3), "achieved": g, "unit": "GB/s",
                     "frac": g / HBM_PEAK_GBPS, "same_traffic_without_arithmetic": pg, "frac_of_that": g / pg,
-                    "kernel": kernel_label(kind, len(specs) == 1, True)})
+                    "kernel": kernel_label(kind, len(specs) == 1, True, numel=n)})
         del bufs, tl
     return out
 
