@@ -209,15 +209,14 @@ __device__ __forceinline__ uint32_t m_code_exact(float m, float r) {
     return round_to_int_bits(y);
 }
 
-// The same code decided from an estimate.  m1 and den are formed exactly as above; the quotient uses
-// v_rcp_f32 (1 ulp), so y* = 254 * (m1 * rc) differs from the exact y by at most
-// (2 + 1 + 1 + 1) * 2^-24 * 128 < 3.9e-5 wherever the clamp is not active.  The function returns
-// y* + 128 -+ w, each formed by ONE fused multiply-add (its rounding, half an ulp of a value below 256,
-// adds 7.7e-6, and 128 -+ w itself is off by at most 3.9e-6): if both round to the same integer no
-// rounding tie lies within 4.7e-5 of y* on either side and that integer is the exact code plus 128.  The
-// integers come from v_cvt_pk_u8_f32 (round-half-even, saturating at 0 and 255, one byte of a word per
-// instruction): its saturation at 255 is the upper clamp of the code (+127); the lower clamp (-127) is
-// the clamp of p at -1/2.
+// The same code decided from an estimate.  m1 and den are formed exactly as above; the quotient uses v_rcp_f32 (1 ulp), so
+// 254 * (m1 * rc) differs from the exact y by at most (2 + 1 + 1) * 2^-24 * 128 < 3.1e-5 wherever the clamp is not active.
+// p = m1 * rc + 1/2 is one fused multiply-add, whose rounding (half an ulp of a value below 1, times 254) adds 7.6e-6 and
+// whose clamp to [0, 1] costs nothing.  The function returns y* + 128 -+ w = 254 p + (1 -+ w), each ONE fused multiply-add
+// (half an ulp of a value below 256: 7.7e-6): if both round to the same integer no rounding tie lies within 4.7e-5 of y* on
+// either side and that integer is the exact code plus 128.  The integers come from v_cvt_pk_u8_f32 (round-half-even,
+// saturating at 0 and 255, one byte of a word per instruction): its saturation at 255 is the upper clamp of the code (+127);
+// the lower clamp (-127) is the clamp of p at 0.
 constexpr float kTieWindowM = 6.0e-5f;
 __device__ __forceinline__ void m_code_bracket(float m, float r, float* lo, float* hi) {
     const float m1 = m * r;
