@@ -68,11 +68,11 @@ constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, b
     if (!through) return kNoLimit;
     return split ? (kind == 0 ? 4 : 5) : quant ? (kind == 0 ? 6 : 7) : kind == 0 ? 11 : 14;
 }
-// Layout conversions, in us with no limit -> with it.  To FP32: 5 M elements 16.5 -> 16.1, GPT-2 348.9 -> 344.5, 300 M 861 -> 842;
-// 2 M 5.9 with no limit, 7.4.  From FP32, in the shape of single wavefronts: GPT-2 337 -> 323, 300 M 825 -> 777 (21 of them 321
-// and 793, 16 330 and 790).
+// Layout conversions.  To FP32, 7 / 6 / 5 workgroups of 256 lanes: GPT-2 344.1 / 342.1 / 347.4 us, 300 M elements 838 / 832 /
+// 828, 5 M 15.8 / 15.8 / 15.9; under 2^22 elements no limit (2 M 6.5).  From FP32, 18 single wavefronts: GPT-2 323 (with no limit
+// 337, 21 of them 321, 16 330), 300 M 777 (825, 793, 790).
 constexpr int convert_resident(bool compress, bool through, int64_t elems) {
-    return compress ? (through ? 18 : kNoLimit) : elems < ((int64_t)1 << 22) ? kNoLimit : 7;
+    return compress ? (through ? 18 : kNoLimit) : elems < ((int64_t)1 << 22) ? kNoLimit : 6;
 }
 // The dynamic LDS, in bytes, with which exactly `resident` workgroups that use `used` bytes fit into a compute unit's
 // 160 KB (given out in units of 1280 bytes).
@@ -197,8 +197,8 @@ hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape 
                        int64_t n_blocks, hipStream_t s);
 // Lanes per workgroup and elements per tile of the layout conversions.  Compressing stages nothing: calls whose stores go
 // through take single wavefronts, 18 to a compute unit (GPT-2 344.8 -> 322.6 us, 300 M elements 816 -> 777, 25 M 70.0 -> 69.8);
-// smaller ones 256 lanes (5 M 15.0 us, as single wavefronts 15.5).  Decompressing stages three tables (without them, as single
-// wavefronts, GPT-2 342 -> 360 us with no limit and 346 with 14 to a unit).
+// smaller ones 256 lanes (5 M 15.0 us, as single wavefronts 15.5).  Decompressing takes 256 (GPT-2 340.0 us, 128 lanes 343.9, single
+// wavefronts 346.9; 300 M 834, 862 and 842).
 constexpr int convert_threads(bool compress, bool through) { return compress && through ? 64 : 256; }
 constexpr int convert_chunk(bool compress, bool through) { return convert_threads(compress, through) * 4; }
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s);

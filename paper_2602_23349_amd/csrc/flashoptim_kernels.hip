@@ -1548,7 +1548,7 @@ __device__ __forceinline__ uint32_t quantize_lane(const float (&x)[kCodecVec], u
 // Decoders of Algorithms 2 and 3 (and of the linear baseline).  What is multiplied by the group scale
 // is a function of the code byte alone: q / 255, q / 127, phi_m^-1(q / 127).  dequantize_byte forms it (the second division has
 // a denominator in [0.99, 2] and a numerator that is 0 or at least 1 / 127); where a workgroup decodes enough to stage a
-// copy of the table of these divisions (the quantisation error, the conversions) dequantize_one reads it there.  The dequantiser
+// copy of the table of these divisions (the quantisation error) dequantize_one reads it there.  The dequantiser
 // with the table took 6.2 us for 5 M momentum codes (5.0 without), 30.9 (31.0) for 38 M and 77.5 (77.0) for 100 M; variance
 // codes, 38 M, 31.3 (30.5).
 template <bool VARIANCE, bool LINEAR>
@@ -1806,8 +1806,9 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
 //
 // Migration between a standard FP32 optimizer state (theta, m, v: 12 B/param for AdamW) and
 // the compressed layout: COMPRESS applies C, Q_m, Q_v (Algorithms 1-3) in one pass over a list;
-// the other direction applies the inverses (its per-code factors from staged tables of the defining
-// divisions).  Tile look-up of the step kernels, lane layout and arithmetic of the standalone codecs.
+// the other direction applies the inverses, the codes' factors formed as in the standalone decoders (with three staged tables of
+// 256 factors per tile and 7 workgroups to a compute unit, now 6: 2 M elements 6.8 -> 6.5 us, 5 M 16.4 -> 15.8, 25 M 71.3 -> 70.3,
+// GPT-2 342.7 -> 340.0, 300 M 843 -> 834).  Tile look-up of the step kernels, lane layout and arithmetic of the standalone codecs.
 // One access of a lane to each stream: tiles of convert_chunk() elements.
 
 template <bool HAS_V, bool THROUGH, bool FULL>
@@ -1840,7 +1841,7 @@ __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0)
 }
 
 template <bool HAS_V, bool THROUGH, bool FULL>
-__device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0, float (&tab)[3][256]) {
+__device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0) {
     uint32_t pw[kCodecVec / 2], rw[kCodecVec / 4], mw[kCodecVec / 4], vw[kCodecVec / 4];
     const LanePos L = lane_pos_at<FULL>(tile0, T.numel);
     load_u16(pw, T.param, L);
@@ -1852,19 +1853,16 @@ __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile
         load_u8(vw, T.v_q, L);
         sv = load_scale(T.v_scale, L);
     }
-    tab[0][threadIdx.x] = g_decode_tables.rho[threadIdx.x];
-    tab[1][threadIdx.x] = g_decode_tables.m[threadIdx.x];
-    stage_table(tab[2], g_decode_tables.v);
     float f[kCodecVec];
 #pragma unroll
-    for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_q(half_of(pw, i), tab[0][byte_of(rw, i)]);
+    for (int i = 0; i < kCodecVec; ++i) f[i] = reconstruct_q(half_of(pw, i), code_over_127(byte_of(rw, i)));
     store_f32<THROUGH>(T.theta32, L, f);
 #pragma unroll
-    for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<false, false>(tab[1], byte_of(mw, i), sm);
+    for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_byte<false, false>(byte_of(mw, i), sm);
     store_f32<THROUGH>(T.m32, L, f);
     if (HAS_V) {
 #pragma unroll
-        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_one<true, false>(tab[2], byte_of(vw, i), sv);
+        for (int i = 0; i < kCodecVec; ++i) f[i] = dequantize_byte<true, false>(byte_of(vw, i), sv);
         store_f32<THROUGH>(T.v32, L, f);
     }
 }
@@ -1880,16 +1878,14 @@ __global__ __launch_bounds__(convert_threads(COMPRESS, THROUGH)) void convert_ke
         if (full) compress_tile<HAS_V, THROUGH, true>(T, tile0);
         else compress_tile<HAS_V, THROUGH, false>(T, tile0);
     } else {
-        __shared__ float tab[3][256];        // rho / 127, phi_m^-1(q / 127), q / 255
-        if (full) decompress_tile<HAS_V, THROUGH, true>(T, tile0, tab);
-        else decompress_tile<HAS_V, THROUGH, false>(T, tile0, tab);
+        if (full) decompress_tile<HAS_V, THROUGH, true>(T, tile0);
+        else decompress_tile<HAS_V, THROUGH, false>(T, tile0);
     }
 }
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     const dim3 grid((unsigned)n_blocks), block(convert_threads(compress, a.through));
-    const unsigned lds = lds_to_hold(convert_resident(compress, a.through, n_blocks * convert_chunk(compress, a.through)),
-                                     compress ? 0 : 3 * 256 * sizeof(float));
+    const unsigned lds = lds_to_hold(convert_resident(compress, a.through, n_blocks * convert_chunk(compress, a.through)), 0);
 #define FO_CONV(HV, CP, DR)                                                                                   \
     do {                                                                                                      \
         if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, lds, s, a);        \
