@@ -15,6 +15,7 @@
 #include <cstring>
 #include <list>
 #include <mutex>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -732,26 +733,38 @@ void give_space(CallSpace& w) {
     else destroy_space(w);
 }
 
-// Waits for the work that uses `w` (launched with result `e`).  For up to 2 ms the host watches the flag, which it sees
-// some microseconds before the runtime reports the stream idle (2^24 momentum values: 31.5 -> 27.9 us a call); longer work,
-// and work that never sets the flag (on a failed stream), is waited for through the stream.  If anything
-// failed the workspace is freed, which waits for whatever may still use it.
-int wait_space(CallSpace& w, hipError_t e, hipStream_t stream) {
+// Waits for the flag of the work that uses `w` (launched with result `e`).  For up to 2 ms the host watches it without a pause: it
+// sees it some microseconds before the runtime reports the stream idle (2^24 momentum values: 31.5 -> 27.9 us a call).  Longer
+// work is waited for through the stream if the flag ends it (`last`).  Otherwise the host goes on watching the flag, with pauses,
+// and now and then asks whether the stream has failed or run dry without it: waiting for the stream would be waiting for
+// what is enqueued behind the flag as well (unpack's copy, 14 ms for 41 GB).  If anything failed the workspace is freed, which waits for
+// whatever may still use it.
+int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last) {
+    const volatile uint32_t* f = w.flag();
+    auto is_set = [&] {
+        if (*f != w.seq) return false;
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return true;
+    };
     if (e == hipSuccess) {
-        const volatile uint32_t* f = w.flag();
         const auto t0 = std::chrono::steady_clock::now();
         for (uint32_t k = 1;; ++k) {
-            if (*f == w.seq) {
-                std::atomic_thread_fence(std::memory_order_acquire);
-                return FLASHOPTIM_OK;
-            }
+            if (is_set()) return FLASHOPTIM_OK;
             if (k % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
         }
-        e = hipStreamSynchronize(stream);
-        std::atomic_thread_fence(std::memory_order_acquire);
-        if (e == hipSuccess && *f != w.seq) e = hipErrorUnknown;        // (never: the kernel that sets it has run)
+        for (uint32_t k = 1;; ++k) {
+            if (last) {
+                e = hipStreamSynchronize(stream);
+            } else {
+                std::this_thread::sleep_for(std::chrono::microseconds(20));
+                e = k % 256 == 0 ? hipStreamQuery(stream) : hipErrorNotReady;
+                if (k % 256 == 0) (void)hipGetLastError();      // ("not ready" is no error of a later launch's)
+            }
+            if ((e == hipSuccess || e == hipErrorNotReady) && is_set()) return FLASHOPTIM_OK;
+            if (e == hipSuccess) e = hipErrorUnknown;           // (never: the kernel that sets it has run)
+            if (e != hipErrorNotReady) break;
+        }
     }
-    if (e == hipSuccess) return FLASHOPTIM_OK;
     g_last_hip_error = (int)e;
     (void)hipGetLastError();
     destroy_space(w);
@@ -1119,7 +1132,7 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
     rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, reinterpret_cast<double*>(w.host), w.flag(), w.seq,
-                                       stream), stream);
+                                       stream), stream, true);
     if (rc != FLASHOPTIM_OK) return rc;
     std::memcpy(sums, w.host, 2 * sizeof(double));
     give_space(w);
@@ -1176,7 +1189,7 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
         destroy_space(w);       // (the check may be on its way: freeing waits for it)
         return rc;
     }
-    rc = wait_space(w, hipSuccess, stream);
+    rc = wait_space(w, hipSuccess, stream, false);
     if (rc != FLASHOPTIM_OK) return rc;
     int64_t found[2];
     std::memcpy(found, w.host, sizeof(found));

@@ -204,6 +204,26 @@ def test_calls_that_return_values_wait_for_a_stream_that_stays_busy():
             assert torch.equal(a.rho, b.rho) and torch.equal(a.v_q, b.v_q)
 
 
+def test_unpack_behind_other_work_does_not_wait_for_its_copy():
+    # 16 GB each way, which takes the copy some 5 ms, behind 20 ms of other work: past the time for which the host watches the
+    # check's flag without a pause
+    bufs = [fo.ParamBuffers(1 << 30, "sgd", with_grad=False) for _ in range(4)]
+    for i, b in enumerate(bufs):
+        b.rho.fill_(i + 1)
+    blob = torch.empty(fo.checkpoint_size("sgd", [b.numel for b in bufs]), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("sgd", bufs, 12, blob)
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 12       # the list's tables
+    for b in bufs:
+        b.rho.zero_()
+    torch.cuda.synchronize()
+    mon = _busy_stream(0.02)
+    step = fo.checkpoint_unpack("sgd", blob, bufs, stream=mon.stream)
+    copying = not mon.stream.query()
+    mon.stream.synchronize()
+    assert step == 12 and copying
+    assert all(bool((b.rho == i + 1).all()) for i, b in enumerate(bufs))
+
+
 @pytest.mark.parametrize("n_tensors", [4092, 4093, 9000])
 def test_unpacking_a_long_list_waits_for_its_own_stream_only(n_tensors):
     # a header of more than 64 KB (4092 tensors) is read in parts, through the same workspace as a shorter one
