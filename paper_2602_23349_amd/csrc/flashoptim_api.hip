@@ -118,8 +118,6 @@ struct Plan {
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
     uint32_t n_segs = 0, coarse_shift = 0;      // copies only
     void* d_header = nullptr;      // copies only: the blob's header and table, all but the step
-    uint32_t* d_verdict = nullptr; // unpacking only: whether the blob's header was found to be this one, a word per call in
-    uint32_t verdicts = 0;         // turn: a refused call's copy may be still to run when a later call's check does
     void* h_mem = nullptr;         // pinned source of d_mem's upload, kept until the plan is freed
     size_t bytes = 0;              // of each
     bool uploaded = false;         // an upload has been enqueued (one that was captured runs with the graph, if at all)
@@ -158,8 +156,6 @@ Plan* find_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>&
     return nullptr;
 }
 
-constexpr uint32_t kVerdictWords = 64;      // (a power of two)
-
 // What a plan puts on the device.
 struct PlanSource {
     const void* table;
@@ -190,8 +186,8 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     const size_t index_bytes = src.index.size() * sizeof(uint32_t);
     const size_t index_at = (size_t)align64((int64_t)src.table_bytes);
     const size_t header_at = index_at + (size_t)align64((int64_t)index_bytes);
-    const size_t verdict_at = header_at + (size_t)align64((int64_t)src.header.size());
-    p.bytes = verdict_at + kVerdictWords * sizeof(uint32_t);
+    const size_t all = header_at + (size_t)align64((int64_t)src.header.size());
+    p.bytes = all > 0 ? all : 64;
     hipError_t e = hipMalloc(&p.d_mem, p.bytes);
     if (e == hipSuccess) e = hipHostMalloc(&p.h_mem, p.bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
@@ -203,7 +199,6 @@ int make_plan(const PlanTag& tag, uint64_t hash, const std::vector<TensorDev>& t
     p.d_table = p.d_mem;
     p.d_index = static_cast<uint8_t*>(p.d_mem) + index_at;
     p.d_header = static_cast<uint8_t*>(p.d_mem) + header_at;
-    p.d_verdict = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.d_mem) + verdict_at);
     uint8_t* h = static_cast<uint8_t*>(p.h_mem);
     std::memset(h, 0, p.bytes);
     if (src.table_bytes) std::memcpy(h, src.table, src.table_bytes);
@@ -675,18 +670,22 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
 //
 // The calls that return values to the host (quantisation error, unpack's header check) let a kernel write them to
 // pinned memory and wait for a flag that it sets last; the quantisation error also needs device memory for the
-// workgroups' partial sums.  Both are kept from call to call (allocating and freeing them cost ~20 us a call, and freeing
-// waits for every stream of the device); a call takes a workspace out of the pool for as long as it runs, so calls of
-// several threads and streams never share one, and a workspace goes back only once its kernels have set the flag or
-// their stream has been waited for.
+// workgroups' partial sums, and unpack a word by which its check admits its copy.  They are kept from call to call
+// (allocating and freeing them cost ~20 us a call, and freeing waits for every stream of the device); a call takes a
+// workspace out of the pool for as long as it runs, so calls of several threads and streams never share one, and a
+// workspace goes back only once its kernels have set the flag or their stream has been waited for.  One kernel may
+// still be to run then: the copy of an unpack that was admitted, which reads the word and stands any later use of it
+// (verdict_word in flashoptim_launch.h).
 struct CallSpace {
     int device = 0;
-    double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs
+    double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs, and the word behind them
     uint8_t* host = nullptr;        // pinned and coherent: kSpaceHost bytes and the flag behind them
-    uint32_t seq = 0;               // the value that marks the end of the workspace's current use
+    uint64_t seq = 0;               // the workspace's uses so far: the ticket of the current one; its low half marks its end
 
     uint32_t* flag() const;
+    uint64_t* verdict() const { return reinterpret_cast<uint64_t*>(partial + fo::kNmseMaxBlocks); }
 };
+constexpr size_t kSpaceDevice = fo::kNmseMaxBlocks * sizeof(double2) + 64;
 constexpr size_t kSpaceHost = 64;               // two values of eight bytes
 constexpr size_t kFlagStride = 64;              // bytes: the flag has a cache line of its own
 uint32_t* CallSpace::flag() const { return reinterpret_cast<uint32_t*>(host + kSpaceHost); }
@@ -695,9 +694,15 @@ constexpr int kMaxIdleSpaces = 16;              // 32 KB of device memory and 12
 CallSpace g_space_idle[kMaxIdleSpaces];         // than that give back at once is freed
 int g_space_n_idle = 0;
 
+// Frees a workspace, after everything on its device: a copy that was admitted may still read its word.
 void destroy_space(CallSpace& w) {
+    int cur = 0;
+    (void)hipGetDevice(&cur);
+    (void)hipSetDevice(w.device);
+    if (w.partial) (void)hipDeviceSynchronize();
     if (w.partial) (void)hipFree(w.partial);
     if (w.host) (void)hipHostFree(w.host);
+    (void)hipSetDevice(cur);
     w = CallSpace();
 }
 
@@ -713,7 +718,7 @@ int take_space(CallSpace& w) {
             return FLASHOPTIM_OK;
         }
     }
-    hipError_t e = hipMalloc((void**)&w.partial, fo::kNmseMaxBlocks * sizeof(double2));
+    hipError_t e = hipMalloc((void**)&w.partial, kSpaceDevice);
     if (e == hipSuccess) e = hipHostMalloc((void**)&w.host, kSpaceHost + kFlagStride, hipHostMallocCoherent);
     if (e != hipSuccess) {
         destroy_space(w);
@@ -742,7 +747,7 @@ void give_space(CallSpace& w) {
 int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last) {
     const volatile uint32_t* f = w.flag();
     auto is_set = [&] {
-        if (*f != w.seq) return false;
+        if (*f != (uint32_t)w.seq) return false;
         std::atomic_thread_fence(std::memory_order_acquire);
         return true;
     };
@@ -837,10 +842,10 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         a.header_dst = reinterpret_cast<uint4*>(blob);
         a.step = step;
     } else {
-        uint32_t* verdict = plan->d_verdict + plan->verdicts++ % kVerdictWords;
-        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), verdict,
+        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), check->verdict(),
                                        reinterpret_cast<int64_t*>(check->host), check->flag(), check->seq, stream));
-        a.verdict = verdict;
+        a.verdict = check->verdict();
+        a.ticket = check->seq;
     }
     FO_HIP(fo::launch_copy(a, stream));
     return FLASHOPTIM_OK;
@@ -1131,8 +1136,8 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     CallSpace w;
     rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
-    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, reinterpret_cast<double*>(w.host), w.flag(), w.seq,
-                                       stream), stream, true);
+    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, reinterpret_cast<double*>(w.host), w.flag(),
+                                       (uint32_t)w.seq, stream), stream, true);
     if (rc != FLASHOPTIM_OK) return rc;
     std::memcpy(sums, w.host, 2 * sizeof(double));
     give_space(w);
@@ -1193,8 +1198,15 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     if (rc != FLASHOPTIM_OK) return rc;
     int64_t found[2];
     std::memcpy(found, w.host, sizeof(found));
+    if (!found[0]) {
+        // the copy that was not admitted has to have run before the workspace's next use can write its word
+        const hipError_t e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) destroy_space(w);
+        FO_HIP(e);
+        give_space(w);
+        return FLASHOPTIM_ERR_BAD_BLOB;
+    }
     give_space(w);
-    if (!found[0]) return FLASHOPTIM_ERR_BAD_BLOB;
     *step_out = found[1];
     return FLASHOPTIM_OK;
 }

@@ -190,7 +190,8 @@ struct CopyArgs {
     uint4* header_dst;
     uint32_t header_n16;
     int64_t step;
-    const uint32_t* verdict;    // unpacking: 1 if the blob belongs to this list (nullptr: no such condition)
+    const uint64_t* verdict;    // unpacking: the word that says whether the blob belongs to this list (nullptr: no such
+    uint64_t ticket;            // condition), and the ticket of this call (verdict_admits)
 };
 
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
@@ -221,10 +222,10 @@ hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, do
 hipError_t launch_copy(CopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
-// Compares the header and table at `blob` with the expected ones, the step apart: *verdict (device) and out[0] (pinned) become
-// 1 or 0, out[1] the blob's step; *flag (pinned) becomes seq once they are there.
-hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint32_t* verdict, int64_t* out,
-                               uint32_t* flag, uint32_t seq, hipStream_t s);
+// Compares the header and table at `blob` with the expected ones, the step apart: *verdict (device) becomes verdict_word of the
+// result, out[0] (pinned) 1 or 0, out[1] the blob's step; *flag (pinned) becomes the ticket's low half once they are there.
+hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint64_t* verdict, int64_t* out,
+                               uint32_t* flag, uint64_t ticket, hipStream_t s);
 // New values for `count` entries of a step's table, from entry `first` on.  Only the fields of the entries that change
 // travel, in the order of the masks below, so that as many entries as possible go with one launch.
 enum : uint32_t { kUpdateGrad = 1, kUpdateLr = 2, kUpdateWd = 4 };

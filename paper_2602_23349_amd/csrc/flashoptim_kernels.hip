@@ -2080,12 +2080,12 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 // small tensors (8000 of them beside 16 GB: one after the other 6025 us a pack, so 5589).
 //
 // header: the blob's header and table when packing; the workgroup behind the last piece writes them to header_dst.
-// verdict: when unpacking, what check_header_kernel has found; nothing is written unless it is 1.
+// verdict: when unpacking, what check_header_kernel has found; nothing is written unless it admits this copy.
 constexpr int kCopyThreads = kCopyPiece / 16;
 static_assert(kHeaderStepAt % 16 == 0, "the step is the low half of one 16-byte access");
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     const uint32_t b = blockIdx.x + a.piece_offset;
-    const uint32_t go = a.verdict ? *a.verdict : 1u;        // (looked up beside the piece)
+    const bool go = !a.verdict || verdict_admits(*a.verdict, a.ticket);      // (looked up beside the piece)
     if (b == a.n_pieces) {
         for (uint32_t i = threadIdx.x; i < a.header_n16; i += kCopyThreads) {
             uint4 v = a.header[i];
@@ -2108,7 +2108,7 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
         }
     }
     const CopySegment sg = a.segs[t];
-    if (go == 0) return;
+    if (!go) return;
     const int64_t o = (int64_t)(b - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
     if (o + 16 <= sg.bytes) {
         const uint4 v = ld128(sg.src + o);
@@ -2167,8 +2167,8 @@ hipError_t launch_table_update(const TableUpdate& u, TensorDev* table, hipStream
 // itself, the copy was launched only once it had: a pack and an unpack of ResNet-50, 131 MB each: 101.1 us, so 91.3.)
 constexpr int kCheckThreads = 1024;
 __global__ __launch_bounds__(kCheckThreads) void check_header_kernel(const uint4* expected, const uint4* blob, uint32_t n16,
-                                                                     uint32_t* verdict, int64_t* out, uint32_t* flag,
-                                                                     uint32_t seq) {
+                                                                     uint64_t* verdict, int64_t* out, uint32_t* flag,
+                                                                     uint64_t ticket) {
     __shared__ uint32_t differs;
     if (threadIdx.x == 0) differs = 0;
     __syncthreads();
@@ -2182,15 +2182,15 @@ __global__ __launch_bounds__(kCheckThreads) void check_header_kernel(const uint4
     __syncthreads();
     if (threadIdx.x != 0) return;
     const uint4 step = blob[kHeaderStepAt / 16];
-    *verdict = differs == 0;
+    *verdict = verdict_word(ticket, differs == 0);
     out[0] = differs == 0;
     out[1] = (int64_t)((uint64_t)step.y << 32 | step.x);
-    __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
+    __hip_atomic_store(flag, (uint32_t)ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
 }
-hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint32_t* verdict, int64_t* out,
-                               uint32_t* flag, uint32_t seq, hipStream_t s) {
+hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint64_t* verdict, int64_t* out,
+                               uint32_t* flag, uint64_t ticket, hipStream_t s) {
     hipLaunchKernelGGL(check_header_kernel, dim3(1), dim3(kCheckThreads), 0, s, (const uint4*)expected, (const uint4*)blob,
-                       (uint32_t)(bytes / 16), verdict, out, flag, seq);
+                       (uint32_t)(bytes / 16), verdict, out, flag, ticket);
     return hipGetLastError();
 }
 

@@ -30,5 +30,12 @@ constexpr int64_t launch_span(int64_t total, int64_t first, int threads) {
     return total - first < most ? total - first : most;
 }
 
+// The word of device memory by which the check of an unpack admits the copy behind it on the same stream.  Calls use a word one
+// after the other, with ascending tickets from 1 on (whatever it holds before the first).  A copy that was not admitted has run
+// before the call after it begins; one that was admitted may run at any later time, whatever calls on other streams have written by
+// then: a refusal leaves the word high enough for all of them.
+constexpr uint64_t verdict_word(uint64_t ticket, bool admitted) { return admitted ? ticket : ticket - 1; }
+constexpr bool verdict_admits(uint64_t word, uint64_t ticket) { return word >= ticket; }
+
 }  // namespace fo
 #endif

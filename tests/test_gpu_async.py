@@ -224,6 +224,26 @@ def test_unpack_behind_other_work_does_not_wait_for_its_copy():
     assert all(bool((b.rho == i + 1).all()) for i, b in enumerate(bufs))
 
 
+def test_refused_unpack_has_run_when_it_returns():
+    # the word by which the check refuses its copy serves later calls, so the copy may not run behind them
+    bufs = [fo.ParamBuffers(1 << 30, "sgd", with_grad=False) for _ in range(2)]
+    blob = torch.empty(fo.checkpoint_size("sgd", [b.numel for b in bufs]), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("sgd", bufs, 12, blob)
+    blob[8] ^= 1
+    for b in bufs:
+        b.rho.fill_(7)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        with pytest.raises(fo.FlashOptimError) as err:
+            fo.checkpoint_unpack("sgd", blob, bufs, stream=side)
+        assert side.query() and err.value.status == -5
+    blob[8] ^= 1
+    assert all(bool((b.rho == 7).all()) for b in bufs)
+    assert fo.checkpoint_unpack("sgd", blob, bufs) == 12
+    assert not any(bool(b.rho.any()) for b in bufs)
+
+
 @pytest.mark.parametrize("n_tensors", [4092, 4093, 9000])
 def test_unpacking_a_long_list_waits_for_its_own_stream_only(n_tensors):
     # a header of more than 64 KB (4092 tensors) is read in parts, through the same workspace as a shorter one

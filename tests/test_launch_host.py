@@ -50,3 +50,27 @@ def test_launches_stay_below_the_work_item_limit_and_cover_every_workgroup(tmp_p
         first, n = spans[::2], spans[1::2]
         assert all(0 < k and k * threads < 2**32 for k in n), line
         assert len(n) == -(-total // most) and sum(n) == total and first == [sum(n[:i]) for i in range(len(n))], line
+
+
+def test_every_copy_runs_as_its_own_check_decided(tmp_path):
+    # five unpacks with one word, admitted or refused in every combination, the copies of admitted ones held back by their
+    # streams for as long as one likes: every order in which checks and copies can run
+    out = _run(tmp_path, """
+    long long orders = 0, wrong = 0;
+    auto go = [&](auto& self, unsigned admitted, int next, unsigned pending, uint64_t word) -> void {
+        if (next == 5 && !pending) { ++orders; return; }
+        for (int k = 0; k < next; ++k)
+            if (pending >> k & 1) {
+                wrong += fo::verdict_admits(word, k + 1) != (bool)(admitted >> k & 1);
+                self(self, admitted, next, pending & ~(1u << k), word);
+            }
+        if (next < 5 && !(pending & ~admitted))
+            self(self, admitted, next + 1, pending | 1u << next, fo::verdict_word(next + 1, admitted >> next & 1));
+    };
+    const uint64_t before[] = {0, ~(uint64_t)0};
+    for (uint64_t first : before)
+        for (unsigned admitted = 0; admitted < 32; ++admitted) go(go, admitted, 0, 0, first);
+    std::printf("%lld %lld\\n", orders, wrong);
+    """)
+    orders, wrong = (int(x) for x in out[0].split())
+    assert orders > 5000 and wrong == 0
