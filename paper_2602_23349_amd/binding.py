@@ -80,12 +80,12 @@ def load_library():
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python paper_2602_23349_amd/build.py`")
     L = C.CDLL(_LIB_PATH)
     vp, i64, i32 = C.c_void_p, C.c_int64, C.c_int
-    L.flashoptim_adamw_step.argtypes = [vp, i64, C.POINTER(_AdamWHp), vp]
-    L.flashoptim_adamw_step_exact.argtypes = [vp, i64, C.POINTER(_AdamWHp), vp]
-    L.flashoptim_adamw_step_noalloc.argtypes = [vp, i64, C.POINTER(_AdamWHp), vp]
+    L.flashoptim_adamw_step.argtypes = [C.POINTER(_Tensor), i64, C.POINTER(_AdamWHp), vp]
+    L.flashoptim_adamw_step_exact.argtypes = [C.POINTER(_Tensor), i64, C.POINTER(_AdamWHp), vp]
+    L.flashoptim_adamw_step_noalloc.argtypes = [C.POINTER(_Tensor), i64, C.POINTER(_AdamWHp), vp]
     L.flashoptim_shard_range.argtypes = [i64, i64, i64, C.POINTER(i64), C.POINTER(i64)]
-    L.flashoptim_sgd_step.argtypes = [vp, i64, C.POINTER(_SgdHp), vp]
-    L.flashoptim_lion_step.argtypes = [vp, i64, C.POINTER(_LionHp), vp]
+    L.flashoptim_sgd_step.argtypes = [C.POINTER(_Tensor), i64, C.POINTER(_SgdHp), vp]
+    L.flashoptim_lion_step.argtypes = [C.POINTER(_Tensor), i64, C.POINTER(_LionHp), vp]
     L.flashoptim_adamw_step_ex.argtypes = [C.POINTER(_TensorEx), i64, C.POINTER(_AdamWHp), C.c_uint, vp]
     L.flashoptim_sgd_step_ex.argtypes = [C.POINTER(_TensorEx), i64, C.POINTER(_SgdHp), C.c_uint, vp]
     L.flashoptim_lion_step_ex.argtypes = [C.POINTER(_TensorEx), i64, C.POINTER(_LionHp), C.c_uint, vp]
@@ -197,7 +197,6 @@ class TensorList:
         self.buffers = list(buffers)
         self.n = len(self.buffers)
         self.array = (_Tensor * max(self.n, 1))()
-        self.address = C.addressof(self.array)      # (ctypes converts an integer in less time than an array)
         for i, b in enumerate(self.buffers):
             d = self.array[i]
             d.param, d.rho, d.grad = _ptr(b.param), _ptr(b.rho), _ptr(b.grad)
@@ -218,7 +217,6 @@ class TensorList:
         out = TensorList.__new__(TensorList)
         out.buffers, out.n = [self.buffers[i]], 1
         out.array = (_Tensor * 1)()
-        out.address = C.addressof(out.array)
         C.memmove(out.array, C.byref(self.array[i]), C.sizeof(_Tensor))
         return out
 
@@ -284,20 +282,20 @@ def _as_list(tensors):
 def adamw_step(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_adamw_step")
+    _check(load_library().flashoptim_adamw_step(tl.array, tl.n, hp, _stream_handle(stream)), "flashoptim_adamw_step")
 
 
 def adamw_step_exact(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step_exact(tl.address, tl.n, hp, _stream_handle(stream)),
+    _check(load_library().flashoptim_adamw_step_exact(tl.array, tl.n, hp, _stream_handle(stream)),
            "flashoptim_adamw_step_exact")
 
 
 def adamw_step_noalloc(tensors, beta1, beta2, eps, step, stream=None):
     tl = _as_list(tensors)
     hp = _AdamWHp(beta1, beta2, eps, int(step))
-    _check(load_library().flashoptim_adamw_step_noalloc(tl.address, tl.n, hp, _stream_handle(stream)),
+    _check(load_library().flashoptim_adamw_step_noalloc(tl.array, tl.n, hp, _stream_handle(stream)),
            "flashoptim_adamw_step_noalloc")
 
 
@@ -312,13 +310,13 @@ def shard_range(numel, world, rank):
 def sgd_step(tensors, momentum, stream=None):
     tl = _as_list(tensors)
     hp = _SgdHp(momentum)
-    _check(load_library().flashoptim_sgd_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_sgd_step")
+    _check(load_library().flashoptim_sgd_step(tl.array, tl.n, hp, _stream_handle(stream)), "flashoptim_sgd_step")
 
 
 def lion_step(tensors, beta1, beta2, stream=None):
     tl = _as_list(tensors)
     hp = _LionHp(beta1, beta2)
-    _check(load_library().flashoptim_lion_step(tl.address, tl.n, hp, _stream_handle(stream)), "flashoptim_lion_step")
+    _check(load_library().flashoptim_lion_step(tl.array, tl.n, hp, _stream_handle(stream)), "flashoptim_lion_step")
 
 
 def stream_probe(kind, tensors, stream=None):

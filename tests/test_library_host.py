@@ -169,3 +169,24 @@ def test_shard_range_arithmetic():
     for bad in ((10, 0, 0), (10, 2, 2), (10, 2, -1), (-1, 2, 0)):
         with pytest.raises(fo.FlashOptimError):
             fo.shard_range(*bad)
+
+
+@pytest.mark.parametrize("name", ["adamw_step", "adamw_step_exact", "adamw_step_noalloc", "sgd_step", "lion_step"])
+def test_step_calls_read_the_list_that_they_are_given(name):
+    # descriptors of the ablation entry points are 24 bytes longer: refused, and not read with the wrong stride
+    L = fo.load_library()
+    hp = {"s": B._SgdHp, "l": B._LionHp}.get(name[0], B._AdamWHp)()
+    with pytest.raises(C.ArgumentError):
+        getattr(L, "flashoptim_" + name)((B._TensorEx * 2)(), 2, hp, None)
+    # a list steps with the descriptors that its array holds now
+    hyper = {"s": (0.9,), "l": (0.9, 0.99)}.get(name[0], (0.9, 0.999, 1e-8, 1))
+    for tl in (fo.TensorList([fo.ParamBuffers(0, "adamw", device="cpu")]), fo.TensorList([fo.ParamBuffers(0, "adamw", device="cpu")]).slice(0)):
+        getattr(fo, name)(tl, *hyper, stream=0)
+        tl.array = (B._Tensor * 1)()
+        tl.array[0].numel = -1
+        with pytest.raises(fo.FlashOptimError) as err:
+            getattr(fo, name)(tl, *hyper, stream=0)
+        assert err.value.status == -3
+        tl.array = (B._TensorEx * 1)()
+        with pytest.raises(C.ArgumentError):
+            getattr(fo, name)(tl, *hyper, stream=0)
