@@ -59,11 +59,12 @@ constexpr int chunk_elems(bool split, bool quant, StepShape shape) {
 //   Weight split only, 256 lanes: AdamW 4 (897 -> 832, 96.6 -> 93.8), SGD and Lion 5 (25 M 62.6 -> 62.1, 124 M 313.9 -> 303.6).
 //   State quantisation only: AdamW 6 of 256 lanes (before, all of 512: 488 -> 484, 58.5 -> 56.9), SGD and Lion 7 (25 M 47.8
 //       -> 47.6, 300 M 568 -> 546).
-// Not held back: compressed steps under 2^22 elements (AdamW over 3 M 8.75 us, with the limit 8.92; SGD over 4 M 8.40, 8.56),
-// and the ablation variants where stores do not go through (plain FP32 SGD over 5 M elements 15.3 us, with 18 wavefronts 16.4).
+// Not held back: compressed steps of up to 2^22 elements, which are one generation of eight workgroups to a unit (2^22 elements in
+// the caches: AdamW 9.58 us, with the limit 10.48, SGD 7.60, 7.96, Lion 7.29, 8.22; AdamW over 3 M 8.75, 8.92), and the
+// ablation variants where stores do not go through (plain FP32 SGD over 5 M elements 15.3 us, with 18 wavefronts 16.4).
 constexpr int kNoLimit = 0;
 constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, bool direct, int64_t elems, bool through) {
-    if (split && quant && elems < ((int64_t)1 << 22)) return kNoLimit;
+    if (split && quant && elems <= ((int64_t)1 << 22)) return kNoLimit;
     if (split && quant) return shape == StepShape::kWide ? 3 : kind == 0 && !direct && elems < ((int64_t)1 << 27) ? 7 : 6;
     if (!through) return kNoLimit;
     return split ? (kind == 0 ? 4 : 5) : quant ? (kind == 0 ? 6 : 7) : kind == 0 ? 11 : 14;

@@ -74,3 +74,27 @@ def test_every_copy_runs_as_its_own_check_decided(tmp_path):
     """)
     orders, wrong = (int(x) for x in out[0].split())
     assert orders > 5000 and wrong == 0
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="needs the HIP headers")
+def test_one_generation_of_workgroups_is_not_held_back(tmp_path):
+    # 256 compute units with eight workgroups of 256 lanes each: 2048 of them, or 2^22 elements (k_proj and v_proj of a Llama layer)
+    src, exe = tmp_path / "resident.cpp", tmp_path / "resident"
+    src.write_text("""#include <cstdio>
+#include "flashoptim_device.h"
+int main() {
+    for (int kind = 0; kind < 3; ++kind)
+        for (bool direct : {false, true})
+            for (long long blocks : {1, 2047, 2048, 2049, 100000}) {
+                const long long elems = blocks * fo::chunk_elems(true, true, fo::StepShape::kUsual);
+                std::printf("%lld %d\\n", blocks, fo::step_resident(kind, true, true, fo::StepShape::kUsual, direct, elems, false));
+            }
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+    assert len(lines) == 30
+    for line in lines:
+        blocks, resident = (int(x) for x in line.split())
+        assert resident == 0 if blocks <= 2048 else resident in (6, 7), line
