@@ -116,7 +116,7 @@ struct Plan {
     void* d_table = nullptr;       // TensorDev[] or CopySegment[]
     void* d_index = nullptr;       // uint32 coarse table: workgroup -> tensor (steps, conversions) or segment (copies)
     int64_t n_chunks = 0;          // workgroups of a launch over this plan
-    uint32_t n_segs = 0, coarse_shift = 0;      // copies only
+    uint32_t coarse_shift = 0;     // copies only
     void* d_header = nullptr;      // copies only: the blob's header and table, all but the step
     void* h_mem = nullptr;         // pinned source of d_mem's upload, kept until the plan is freed
     size_t bytes = 0;              // of each
@@ -425,6 +425,7 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
             while ((int64_t)live[ti].first_tile + live[ti].n_tiles <= b) ++ti;
             coarse[j] = (uint32_t)ti;
         }
+        coarse.push_back((uint32_t)live.size() - 1);
         const std::vector<uint8_t> no_header;
         rc = make_plan(tag, hash, live, {live.data(), live.size() * sizeof(TensorDev), coarse, no_header},
                        total_chunks, &plan);
@@ -438,7 +439,6 @@ int launch_live(int kind, bool split, bool quant, std::vector<TensorDev>& live, 
     a.tensors = static_cast<TensorDev*>(plan->d_table);
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = shift;
-    a.n_tensors = (uint32_t)live.size();
     const hipError_t e = launch_op(op, kind, false, split, quant, shape, a, plan->n_chunks, ce, stream);
     if (e != hipSuccess) plan->table_known = false;        // the launches that were accepted may have written a rate
     FO_HIP(e);
@@ -820,11 +820,11 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
             while ((int64_t)segs[si].first_piece + segs[si].n_pieces <= b) ++si;
             coarse[j] = (uint32_t)si;
         }
+        coarse.push_back(segs.empty() ? 0 : (uint32_t)segs.size() - 1);
         const std::vector<uint8_t> header = build_header(kind, t, n, 0, total_bytes);
         const int rc = make_plan(tag, hash, list, {segs.data(), segs.size() * sizeof(CopySegment), coarse, header},
                                  n_pieces, &plan);
         if (rc != FLASHOPTIM_OK) return rc;
-        plan->n_segs = (uint32_t)segs.size();
         plan->coarse_shift = shift;
     }
     const int rc = upload_tables(*plan, stream);
@@ -834,7 +834,6 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
     a.segs = static_cast<const CopySegment*>(plan->d_table);
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = plan->coarse_shift;
-    a.n_segs = plan->n_segs;
     a.n_pieces = (uint32_t)plan->n_chunks;
     if (pack) {
         a.header = static_cast<const uint4*>(plan->d_header);
@@ -860,7 +859,7 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
 constexpr int64_t kShardUnit = 256;     // elements: a shard that starts on a multiple has every stream 16-byte aligned
 constexpr int kNoAllocMaxTensors = 1024;
 constexpr size_t kScratchTableBytes = kNoAllocMaxTensors * sizeof(TensorDev);                 // 106,496
-constexpr size_t kScratchBytes = kScratchTableBytes + fo::kCoarseMaxEntries * sizeof(uint32_t);   // + 65,536
+constexpr size_t kScratchBytes = kScratchTableBytes + (fo::kCoarseMaxEntries + 1) * sizeof(uint32_t);   // + 65,540
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::atomic<unsigned char*> g_scratch_ptr[kMaxDevices];
@@ -895,19 +894,14 @@ static_assert(sizeof(TableBatch) <= 4096, "kernel arguments");
 __global__ __launch_bounds__(64) void noalloc_fill_table(TableBatch b, TensorDev* table) {
     if (threadIdx.x < b.count) table[b.first + threadIdx.x] = b.t[threadIdx.x];
 }
-// coarse[j] = the tensor that holds tile j << shift: the last one whose first tile is not beyond it
-// (every tensor of the table has at least one tile, so first_tile increases strictly).
+// coarse[j] = the tensor that holds tile j << shift: the last one whose first tile is not beyond it (every tensor of the
+// table has at least one tile, so first_tile increases strictly).  The last of the n_coarse entries is the last tensor.
 __global__ __launch_bounds__(256) void noalloc_fill_coarse(const TensorDev* table, uint32_t n_tensors,
                                                            uint32_t* coarse, uint32_t n_coarse, uint32_t shift) {
     const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_coarse) return;
-    const uint32_t b = j << shift;
-    uint32_t lo = 0, hi = n_tensors - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (table[mid].first_tile <= b) lo = mid; else hi = mid - 1;
-    }
-    coarse[j] = lo;
+    coarse[j] = j + 1 == n_coarse ? n_tensors - 1
+                                  : fo::entry_of(j << shift, 0, n_tensors - 1, [&](uint32_t i) { return table[i].first_tile; });
 }
 
 }  // namespace
@@ -1394,14 +1388,13 @@ int flashoptim_adamw_step_noalloc(const flashoptim_tensor* tensors, int64_t n_te
         FO_HIP(hipGetLastError());
     }
     const uint32_t shift = fo::coarse_shift(total_tiles);
-    const uint32_t n_coarse = (uint32_t)fo::coarse_entries(total_tiles, shift);
+    const uint32_t n_coarse = (uint32_t)fo::coarse_entries(total_tiles, shift) + 1;
     hipLaunchKernelGGL(noalloc_fill_coarse, dim3((n_coarse + 255) / 256), dim3(256), 0, stream, table,
                        (uint32_t)n_live, coarse, n_coarse, shift);
     FO_HIP(hipGetLastError());
     a.tensors = table;
     a.coarse = coarse;
     a.coarse_shift = shift;
-    a.n_tensors = (uint32_t)n_live;
     a.table_lr_mask = ~0u;
     FO_HIP(launch_op(kOpStepExact, FLASHOPTIM_ADAMW, false, true, true, shape, a, total_tiles, ce, stream));
     return FLASHOPTIM_OK;

@@ -154,7 +154,6 @@ struct StepArgs {
     TensorDev* tensors;         // device table (multi-tensor launch)
     const uint32_t* coarse;     // device table: tensor index per 2^coarse_shift workgroups (flashoptim_launch.h)
     uint32_t coarse_shift;
-    uint32_t n_tensors;
     uint32_t block_offset;      // tile index of this launch's workgroup 0 (a list or tensor is covered by several launches)
     // A new learning rate that all tensors of a multi-tensor step share travels here instead of in an update of the table,
     // so that a schedule, which changes it with every step, has no launch in front of every step (AdamW, with and without
@@ -182,7 +181,6 @@ struct CopyArgs {
     const CopySegment* segs;
     const uint32_t* coarse;     // segment index per 2^coarse_shift pieces, as in StepArgs
     uint32_t coarse_shift;
-    uint32_t n_segs;
     uint32_t n_pieces;
     uint32_t piece_offset;      // index of this launch's workgroup 0
     // packing: the blob's header and table (nullptr: none), which one further workgroup writes to header_dst with `step`

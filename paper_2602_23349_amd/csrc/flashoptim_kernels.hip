@@ -890,7 +890,7 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
 
 // ------------------------------------------------------------ step kernels --
 // The tensor and the tile within it that workgroup blockIdx.x handles.  Every load is wave-uniform
-// (scalar).  The search loop ends at the last tensor at the latest.
+// (scalar).
 // *index (multi-tensor launches): the tensor's index in the table.
 template <bool DIRECT>
 __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, uint32_t* index = nullptr) {
@@ -899,16 +899,10 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
         T = a.single;
         return (int64_t)b;
     }
-    uint32_t t = a.coarse[b >> a.coarse_shift];
+    const uint32_t* entry = a.coarse + (b >> a.coarse_shift);
+    uint32_t t = entry[0];
+    if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.tensors[i].first_tile; });
     T = a.tensors[t];
-    // (an empty asm statement that takes every field: the descriptor is loaded as a whole, instead of its range first and,
-    // after the test, the rest)
-    asm("" : "+s"(T.n_tiles) : "s"(T.param), "s"(T.rho), "s"(T.grad), "s"(T.m_q), "s"(T.m_scale), "s"(T.v_q), "s"(T.v_scale),
-        "s"(T.theta32), "s"(T.m32), "s"(T.v32), "s"(T.numel), "s"(T.lr), "s"(T.wd));
-    while (b - T.first_tile >= T.n_tiles && t + 1 < a.n_tensors) {
-        ++t;
-        T = a.tensors[t];
-    }
     if (index) *index = t;
     return (int64_t)(b - T.first_tile);
 }
@@ -2075,9 +2069,7 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 // More per lane is slower, less so in fewer lanes (pack of GPT-2's 638 MB / of a Llama layer / of two layers with
 // embedding and head, in us: 512 lanes x 16 accesses 225 / 387 / 2749; 1024 x 8 217 / 378 / 2659; 1024 x 1 201 / 355 /
 // 2520, 6.1 TB/s).  Pieces are found as the step kernels find their tiles, through a coarse table and the segments
-// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.  Within a coarse entry by
-// bisection: beside a large tensor an entry spans hundreds of pieces, and as many segments where a list has thousands of
-// small tensors (8000 of them beside 16 GB: one after the other 6025 us a pack, so 5589).
+// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
 //
 // header: the blob's header and table when packing; the workgroup behind the last piece writes them to header_dst.
 // verdict: when unpacking, what check_header_kernel has found; nothing is written unless it admits this copy.
@@ -2098,15 +2090,9 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
         return;
     }
     // the last segment that begins at piece b or before, among those of this coarse entry
-    const uint32_t j = b >> a.coarse_shift;
-    uint32_t t = a.coarse[j];
-    if (a.coarse_shift) {
-        uint32_t last = j < (a.n_pieces - 1) >> a.coarse_shift ? a.coarse[j + 1] : a.n_segs - 1;
-        while (t < last) {
-            const uint32_t mid = (t + last + 1) >> 1;
-            if (a.segs[mid].first_piece <= b) t = mid; else last = mid - 1;
-        }
-    }
+    const uint32_t* entry = a.coarse + (b >> a.coarse_shift);
+    uint32_t t = entry[0];
+    if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.segs[i].first_piece; });
     const CopySegment sg = a.segs[t];
     if (!go) return;
     const int64_t o = (int64_t)(b - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;

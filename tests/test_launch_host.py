@@ -98,3 +98,43 @@ int main() {
     for line in lines:
         blocks, resident = (int(x) for x in line.split())
         assert resident == 0 if blocks <= 2048 else resident in (6, 7), line
+
+
+def test_look_up_finds_every_workgroup_in_few_steps(tmp_path):
+    # lists of many small entries beside large ones, and every shift that their coarse tables could have
+    out = _run(tmp_path, """
+    const int n = 3000;
+    static uint32_t begin[n + 1], size[n], coarse[70000];
+    uint32_t seed = 1, wrong = 0, over = 0, looked = 0;
+    for (int list = 0; list < 6; ++list) {
+        for (int i = 0; i < n; ++i) {
+            seed = seed * 1664525u + 1013904223u;
+            size[i] = list == 0 ? 1 : list == 1 ? (i == n - 1 ? 60000 : 1) : list == 2 ? (i ? 1 : 60000) : list == 3 ? 1 + (seed >> 28) :
+                      list == 4 ? (i % 1000 == 500 ? 5000 : 1 + (seed >> 31)) : 1 + (i & 1) * 9;
+        }
+        begin[0] = 0;
+        for (int i = 0; i < n; ++i) begin[i + 1] = begin[i] + size[i];
+        const uint32_t total = begin[n];
+        for (uint32_t shift = 0; shift < 18; ++shift) {
+            const uint32_t entries = (uint32_t)fo::coarse_entries(total, shift);
+            for (uint32_t j = 0, t = 0; j < entries; ++j) {
+                while (begin[t + 1] <= j << shift) ++t;
+                coarse[j] = t;
+            }
+            coarse[entries] = n - 1;
+            uint32_t most = 0;                               // halvings of a whole entry
+            while ((1u << most) <= (shift < 12 ? 1u << shift : (uint32_t)n)) ++most;
+            for (uint32_t b = 0, t = 0; b < total; ++b) {
+                uint32_t reads = 0;
+                while (begin[t + 1] <= b) ++t;
+                const uint32_t got = fo::entry_of(b, coarse[b >> shift], coarse[(b >> shift) + 1], [&](uint32_t i) { ++reads; return begin[i]; });
+                wrong += got != t;
+                over += reads > most;
+                ++looked;
+            }
+        }
+    }
+    std::printf("%u %u %u\\n", looked, wrong, over);
+    """)
+    looked, wrong, over = (int(x) for x in out[0].split())
+    assert looked > 1000000 and wrong == 0 and over == 0
