@@ -1908,7 +1908,9 @@ hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs
 //              root either parity of the exponent;
 //   section 2: sqrt_rn_midrange(x) == sqrtf(x) for EVERY FP32 value x of its range [2^-96, FLT_MAX];
 //   section 3: momentum codes: wherever the two conversions of m_code_bracket agree, they agree with m_code_exact, for every
-//              m' in [2^-13, 2) of either sign, and so do those of m_code_bracket_of_scale, with two scales;
+//              m' in [2^-13, 2) of either sign, and so do those of m_code_bracket_of_scale, with two scales (a value for
+//              which any of the three decides on a wrong code fails, whether the others decide or not; otherwise
+//              it counts as checked if all three decide);
 //   section 4: variance codes: same for v_code_bracket against v_code_exact, over every FP32 value of
 //              four binades of v, for the bias-correction pair and group scale the host passes.
 //   section 5: div_rn_midrange(n, d) == n / d on 2^30 pseudo-random operand pairs with magnitudes
@@ -1960,17 +1962,20 @@ __device__ __forceinline__ void selftest_one(int section, uint64_t gid, const St
             const uint32_t mag = 0x39000000u + (uint32_t)(gid >> 1);     // 2^-13 ... 2
             const float m1 = u2f(sign | mag);
             float lo, hi;
+            checked = true;
+            const auto compare = [&](uint32_t exact) {
+                const uint32_t a = put_u8(lo, 0, 0);
+                if (a != put_u8(hi, 0, 0)) checked = false;
+                else if ((a ^ 0x80u) != (exact & 0xffu)) failed = true;
+            };
             m_code_bracket(m1, 1.0f, &lo, &hi);
-            const uint32_t a = put_u8(lo, 0, 0), b = put_u8(hi, 0, 0);
-            const uint32_t exact = m_code_exact(m1, 1.0f) & 0xffu;
-            checked = (a == b);
-            failed = (a ^ 0x80u) != exact;
+            compare(m_code_exact(m1, 1.0f));
             for (int k = 0; k < 2; ++k) {
                 const float s = k ? 0x1.7fcp-14f : 1.0f, m = m1 * s;
                 m_code_bracket_of_scale(m, s, &lo, &hi);
-                const uint32_t low = put_u8(lo, 0, 0);
-                failed |= low == put_u8(hi, 0, 0) && (low ^ 0x80u) != (m_code_exact(m, recip_of_fp16(s)) & 0xffu);
+                compare(m_code_exact(m, recip_of_fp16(s)));
             }
+            checked |= failed;
         }
     } else if (section == 5 || section == 6) {
         if (gid < kSelftestDivCount) {
