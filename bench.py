@@ -224,13 +224,20 @@ def read_traffic(kind, workload, entry="exact"):
 
 def kernel_label(kind, release, exact, ckpt=False, numel=1 << 27):
     """The step kernel's name as rocprofv3 prints it: <KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT>, for a call over
-    2^20 elements and more."""
+    `numel` elements."""
     if ckpt:
         return "fo::copy_kernel"
     k = ["adamw", "sgd", "lion"].index(kind)
     tf = lambda b: "true" if b else "false"
     # SGD, Lion and every ablation variant are instantiated with EXACT = true (they have no division to shorten)
-    return f"fo::step_kernel<{k}, 8, {256 if k == 0 or numel < 1 << 27 else 512}, {tf(release)}, true, true, {tf(exact or k != 0)}>"
+    vec, threads = 4 if numel < 1 << 20 else 8, 256 if k == 0 or numel < 1 << 27 else 512
+    return f"fo::step_kernel<{k}, {vec}, {threads}, {tf(release)}, true, true, {tf(exact or k != 0)}>"
+
+
+def kernel_labels(kind, release, exact, ckpt, numels):
+    """The kernels of a step over tensors of these sizes: one call over all of them, or (release) one for each."""
+    calls = numels if release and not ckpt else [sum(numels)]
+    return " and ".join(dict.fromkeys(kernel_label(kind, release, exact, ckpt, n) for n in calls))
 
 
 def time_calls(torch, stream, fn, steps, warmup=2):
@@ -617,7 +624,7 @@ def main():
                      "traffic": (traffic / launches) if (traffic and launches) else None,
                      "traffic_per_step": traffic,
                      "traffic_source": traffic_source,
-                     "kernel": (kernel_label(kind, release, exact, ckpt) if args.variant == "flash" else
+                     "kernel": (kernel_labels(kind, release, exact, ckpt, [s.numel for s in specs]) if args.variant == "flash" else
                                 "fo::step_kernel<...> (ablation variant)"),
                      "algorithmic_bytes_per_step": algo_bytes,
                      "algorithmic_bytes_per_launch": (algo_bytes / launches) if launches else None,

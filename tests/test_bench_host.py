@@ -50,6 +50,15 @@ def test_kernel_label_names_the_real_template_arguments():
     assert bench.kernel_label("adamw", True, False) == "fo::step_kernel<0, 8, 256, true, true, true, false>"
     assert bench.kernel_label("lion", False, False) == "fo::step_kernel<2, 8, 512, false, true, true, true>"
     assert bench.kernel_label("adamw", False, True, ckpt=True) == "fo::copy_kernel"
+    # the launch shape follows the elements of a call: all of a list's, or (gradient release) each tensor's own
+    assert bench.kernel_label("sgd", False, True, numel=124439808) == "fo::step_kernel<1, 8, 256, false, true, true, true>"
+    assert bench.kernel_label("sgd", False, True, numel=4096) == "fo::step_kernel<1, 4, 256, false, true, true, true>"
+    layer = [4096, 4096 * 14336, 128256 * 4096]
+    assert bench.kernel_labels("lion", False, True, False, layer) == "fo::step_kernel<2, 8, 512, false, true, true, true>"
+    assert bench.kernel_labels("lion", False, True, False, layer[:2]) == "fo::step_kernel<2, 8, 256, false, true, true, true>"
+    assert bench.kernel_labels("lion", True, True, False, layer) == " and ".join(
+        f"fo::step_kernel<2, {shape}, true, true, true, true>" for shape in ("4, 256", "8, 256", "8, 512"))
+    assert bench.kernel_labels("adamw", False, True, True, layer) == "fo::copy_kernel"
 
 
 @pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="a GPU is present")
