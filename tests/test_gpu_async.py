@@ -246,7 +246,7 @@ def test_refused_unpack_has_run_when_it_returns():
 
 @pytest.mark.parametrize("n_tensors", [4092, 4093, 9000])
 def test_unpacking_a_long_list_waits_for_its_own_stream_only(n_tensors):
-    # a header of more than 64 KB (4092 tensors) is read in parts, through the same workspace as a shorter one
+    # headers and tables of 64 KB and more (4092 tensors), which one workgroup compares
     bufs = [fo.ParamBuffers(33 + i % 40, "sgd", with_grad=False) for i in range(n_tensors)]
     for i, b in enumerate(bufs):
         b.rho.fill_(i % 100)

@@ -122,9 +122,11 @@ def test_steps_around_the_one_from_which_the_momentum_needs_no_correction(beta1,
 
 
 # The first sizes whose stores go through to memory (176160768 bytes of arrays at 7, 6 and 14 bytes an element), and the
-# limits below which a launch's workgroups are not held back.
+# limits up to which a launch's workgroups are not held back; from 2^27 elements on SGD and Lion take 512 lanes, here with a ragged
+# last tile.
 @pytest.mark.parametrize("kind,n", [("adamw", 25165824), ("adamw", 25165823), ("sgd", 29360128), ("lion", 29360127),
-                                    ("adamw", 1 << 22), ("sgd", (1 << 22) - 1), ("lion", 1 << 22)])
+                                    ("adamw", 1 << 22), ("sgd", (1 << 22) - 1), ("lion", 1 << 22), ("sgd", (1 << 22) + 1),
+                                    ("sgd", (1 << 27) + 77), ("lion", (1 << 27) + 4095), ("lion", (1 << 27) - 1)])
 def test_launch_rules_on_both_sides_of_their_limits(kind, n):
     rng = np.random.default_rng(n)
     small = 1000
@@ -178,6 +180,10 @@ def test_ablation_launch_rules_on_both_sides_of_their_limits(kind, split, quant,
             assert np.array_equal(b.m_q.cpu().numpy(), st.mq) and np.array_equal(bits16(b.m_scale), st.ms)
         else:
             assert np.array_equal(f32(b.m), st.m32.view(np.uint32))
+        if kind == "adamw" and quant:
+            assert np.array_equal(b.v_q.cpu().numpy(), st.vq) and np.array_equal(bits16(b.v_scale), st.vs)
+        elif kind == "adamw":
+            assert np.array_equal(f32(b.v), st.v32.view(np.uint32))
 
 
 @pytest.mark.parametrize("n", [(1 << 23) - 1, (1 << 23) + 1])
@@ -271,3 +277,38 @@ def test_unpacking_checks_every_word_of_the_table(n_tensors):
         blob[16:24] = torch.from_numpy(np.frombuffer(np.int64(step).tobytes(), np.uint8).copy()).cuda()
         assert fo.checkpoint_unpack("sgd", blob, bufs) == step
     assert all((b.rho == i * 97 % 50 + 1).all() for i, b in enumerate(bufs[::97]))
+
+
+# Lists whose coarse table spans several tiles and tensors with one entry: the tensor of a tile is searched for.
+@pytest.mark.parametrize("order", ["small first", "large first", "large among small"])
+def test_tiles_of_long_lists(order):
+    rng = np.random.default_rng(3)
+    sizes = [1 + i * 37 % 3000 for i in range(3000)]
+    sizes.insert({"small first": 3000, "large first": 0, "large among small": 1234}[order], 40000001)
+    total = sum(sizes)
+    cut = np.cumsum([0] + sizes)
+    x = np.resize(rng.normal(0, 0.02, 1000003).astype(np.float32), total)
+    m = np.resize(rng.normal(0, 1e-4, 1000033).astype(np.float32), total)
+    g = np.resize((rng.normal(0, 1e-4, 1000037).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16), total)
+    bufs, states = [], []
+    for a, k in zip(cut, sizes):
+        b = fo.ParamBuffers(k, "sgd")
+        b.theta, b.m = torch.from_numpy(x[a:a + k]).cuda(), torch.from_numpy(m[a:a + k]).cuda()
+        b.grad.copy_(to_dev_u16(g[a:a + k], torch.bfloat16))
+        b.lr, b.weight_decay = 1e-3, 0.01
+        st = oracle.TensorState(np.zeros(k, np.float32), "sgd")
+        st.thp, st.rho = oracle.split(x[a:a + k])
+        st.mq, st.ms = oracle.quantize_momentum(m[a:a + k])
+        bufs.append(b)
+        states.append(st)
+    fo.compress_state("sgd", bufs)
+    for i, (b, st) in enumerate(zip(bufs, states)):
+        _same(b, st, f"compress, tensor {i}")
+        b.theta, b.m = torch.zeros_like(b.theta), torch.zeros_like(b.m)
+    fo.decompress_state("sgd", bufs)
+    for i, (b, st) in enumerate(zip(bufs, states)):
+        assert np.array_equal(b.theta.cpu().numpy().view(np.uint32), oracle.reconstruct(st.thp, st.rho).view(np.uint32)), i
+        assert np.array_equal(b.m.cpu().numpy().view(np.uint32), oracle.dequantize_momentum(st.mq, st.ms).view(np.uint32)), i
+    _step("sgd", bufs, states, [g[a:a + k] for a, k in zip(cut, sizes)], 1, HP)
+    for i, (b, st) in enumerate(zip(bufs, states)):
+        _same(b, st, f"step, tensor {i}")
