@@ -145,7 +145,7 @@ int flashoptim_lion_step(const flashoptim_tensor* tensors, int64_t n_tensors,
  * For code under HIP stream capture, tight serving loops and harnesses that forbid allocation: the same step
  * as flashoptim_adamw_step_exact, same arguments, same results bit for bit, but the call allocates nothing
  * (no hipMalloc / hipFree / hipHostMalloc, no host-to-device copy): the two device tables of a multi-tensor
- * launch are written by small kernels, from kernel arguments, into a fixed 172,032-byte device array that
+ * launch are written by small kernels, from kernel arguments, into a fixed 172,036-byte device array that
  * each GPU holds from library load to process end.
  * Every table entry a call's launches read is written by that call first, so nothing left behind by an earlier
  * call (a longer list, larger tensors) is ever seen.
@@ -298,7 +298,8 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
  *                    returns the stored step in *step_out (host).  The header and table
  *                    are validated against (kind, list) on the device, ahead of the copy, which
  *                    writes nothing if they differ; the call waits for that verdict and the step,
- *                    and therefore for prior work on `stream`, but not for the copy. */
+ *                    and therefore for prior work on `stream`, but not for the copy (refused: until
+ *                    the copy, which then does nothing, has run too). */
 int64_t flashoptim_checkpoint_size(int kind, const int64_t* numels, int64_t n_tensors);
 int flashoptim_checkpoint_pack(int kind, const flashoptim_tensor* tensors, int64_t n_tensors, int64_t step,
                                void* blob, int64_t blob_bytes, void* stream);

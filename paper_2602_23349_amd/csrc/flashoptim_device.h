@@ -11,7 +11,7 @@
 namespace fo {
 
 constexpr int kGroup = 32;                         // quantisation group (Algorithms 2, 3)
-constexpr int kThreads = 256;                      // lanes per workgroup (codecs, conversions, sweep, self-test)
+constexpr int kThreads = 256;                      // lanes per workgroup (quantisers, sweep, self-test)
 // Launch shapes of the step kernels: consecutive elements per lane and lanes per workgroup.  One workgroup handles one
 // tile of chunk_elems() consecutive elements.
 //   kUsual: eight elements per lane and 256 lanes.
@@ -20,8 +20,10 @@ constexpr int kThreads = 256;                      // lanes per workgroup (codec
 //       flat tensor of 2^18 elements AdamW 3.9 -> 3.5 us, SGD 3.5 -> 2.8; 25 tensors of odd sizes below 2^16, SGD 4.9 -> 3.8;
 //       at 2^20 elements the two are equal, from 2^22 on the larger tile wins by 2-8 %).
 //   kWide: SGD and Lion over kWideElems elements or more, eight elements per lane and 512 lanes, three workgroups to a compute
-//       unit (below); against kUsual, six to a unit: four Llama layers with embedding and head SGD 3067 -> 3026 us, one layer
-//       343.3 -> 340.7, Lion 338.7 -> 340.9; GPT-2 SGD 197.3 with kUsual, 199.4 with kWide, 24 M elements 39.4, 40.0.
+//       unit (below); against kUsual, six to a unit, SGD: a Llama layer 345.0 -> 339.8 us, flat 2^27 209.5 -> 206.5, 400 M 632.8 ->
+//       621.3, four layers 1394 -> 1394, with embedding and head 3058 -> 3045; GPT-2 201.9 with kUsual, 203.5 with kWide, 24 M
+//       elements 39.4, 40.0.  Lion goes with SGD and is as fast either way: a layer 348.8 -> 343.2, 2^27 209.7 -> 212.6, 400 M
+//       629.1 -> 636.1, four layers with embedding and head 3054 -> 3048.
 // The ablation variants (weights not split, states not quantized, or both) move FP32 arrays: four elements per lane,
 // so that a wavefront's 128-bit FP32 access covers whole cache lines (with eight, each of two accesses covered half
 // of every line: the plain FP32 AdamW step over a decoder layer of Llama-3.1-8B, 218 M parameters, took 1034 us
@@ -49,9 +51,10 @@ constexpr int chunk_elems(bool split, bool quant, StepShape shape) {
 // while have fewer on average: the compressed steps want more of them than the FP32 ones.)  A launch is held to fewer by the
 // LDS it asks for beyond what it uses.  The lines are where the best counts lie, in us with no limit -> with it:
 //   AdamW, 6 of 256 lanes: Llama layer 442 -> 428, four layers with embedding and head 3994 -> 3867, flat 16 M 34.8 -> 34.5;
-//       7 for lists of fewer than 2^27 elements, whose workgroups spend a larger part of their time on looking up their
-//       tile (GPT-2 245.5 -> 244.2, and 244.7 with 6; ResNet-50 53.9 -> 53.8, and 54.1; 60 tensors of 60 M 118.9 -> 118.6,
-//       and 119.2).  With 5: 4 layers 3856, GPT-2 248.1, ResNet-50 54.7.
+//       7 for lists of fewer than 2^27 elements, whose workgroups spend a larger part of their time on looking up their tile
+//       (no more than two runs of one build differ by, but the same way in every list: with 6 -> 7 GPT-2 254.4 -> 253.5,
+//       ResNet-50 54.1 -> 54.0, 60 tensors of 60 M 123.9 -> 122.4, 24 of 72 M 147.9 -> 146.3).  With 5: 4 layers 3856, GPT-2
+//       248.1 (6: 244.7), ResNet-50 54.7.
 //   SGD and Lion, 6 of 256 lanes or 3 of 512; before, four of 512 (all that fit): Llama layer 346 -> 341 / 345 -> 341, flat
 //       400 M SGD 659 -> 637, GPT-2 200.8 -> 197.3 / 194.5 -> 194.1, ResNet-50 SGD 42.7 -> 42.2.
 //   Plain FP32 steps, single wavefronts: AdamW 11 (Llama layer 896 -> 845, flat 25 M 104.2 -> 97.7, 300 M 1247 -> 1155; 32
@@ -62,6 +65,10 @@ constexpr int chunk_elems(bool split, bool quant, StepShape shape) {
 // Not held back: compressed steps of up to 2^22 elements, which are one generation of eight workgroups to a unit (2^22 elements in
 // the caches: AdamW 9.58 us, with the limit 10.48, SGD 7.60, 7.96, Lion 7.29, 8.22; AdamW over 3 M 8.75, 8.92), and the
 // ablation variants where stores do not go through (plain FP32 SGD over 5 M elements 15.3 us, with 18 wavefronts 16.4).
+// A held launch leaves little of a unit's LDS to kernels on other streams (six workgroups: 2.5 KB).  No cost of that was found: two
+// Llama layers of release calls on one stream beside bf16 products on another, until both are done, no limit -> limit: AdamW and
+// ten products of 4096^3 2.02 -> 2.00 ms, three of 8192^3 3.37 -> 3.36, forty of 2048^3 2.00 -> 1.97; SGD 1.77 -> 1.77,
+// 3.13 -> 3.13, 1.67 -> 1.69.
 constexpr int kNoLimit = 0;
 constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, bool direct, int64_t elems, bool through) {
     if (split && quant && elems <= ((int64_t)1 << 22)) return kNoLimit;

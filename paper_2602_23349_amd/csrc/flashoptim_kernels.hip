@@ -560,6 +560,9 @@ __device__ __forceinline__ void pack_elements(uint32_t (&w)[N / 2], const uint16
     for (int j = 0; j < N / 2; ++j) w[j] = (uint32_t)e[2 * j] | ((uint32_t)e[2 * j + 1] << 16);
 }
 
+// Missing weights are 1, so that SGD and Lion wavefronts that have some keep to the short forms of Algorithm 1.  (In AdamW the
+// root of a missing element's variance, 0, is NaN on the short path, and so is its new weight: the wavefront takes the general
+// form of the split, with the same bits.)
 template <int VEC, bool HAS_V, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_tail(LaneIO<VEC>& x, const TensorDev& T, int64_t off, int cnt) {
     x = LaneIO<VEC>{};
@@ -928,7 +931,8 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a,
         __syncthreads();
     }
     StepConsts c = a.c;
-    // One scalar load, behind the streaming loads: nothing writes the word while a step runs, so it counts as constant.
+    // One scalar load, behind the streaming loads.  The word counts as constant: the check that writes it may run beside a step on
+    // another stream, but only once per device, and the results are the same with either value.
     if (KIND == 0) c.sqrt_min = *(const __attribute__((address_space(4))) float*)a.sqrt_min_word;
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
@@ -1237,7 +1241,7 @@ __device__ __forceinline__ void pack_u16(uint32_t (&w)[kCodecVec / 2], const uin
 }
 
 // C and C^-1 for a correction of N = 127 (INT8) or N = 32767 (INT16) levels per side,
-// written out plainly (Algorithm 1; the fused kernels use table-driven forms of the N = 127 case).
+// written out plainly (Algorithm 1; for N = 127 the step kernels use the short forms above where they apply).
 template <int N>
 __device__ __forceinline__ int split_rho(float theta, uint32_t b) {
     const int E = (int)((b >> 7) & 0xffu);
@@ -1353,7 +1357,7 @@ __global__ __launch_bounds__(kWaveThreads) void split_kernel(const float* theta,
 template <int N, typename RHO, bool THROUGH, bool FULL>
 __device__ __forceinline__ void reconstruct_tile(const uint16_t* param, const RHO* rho, float* theta, int64_t n,
                                                  int64_t tile0) {
-    static_assert(sizeof(RHO) != 1 || N == 127, "rho_over_127");
+    static_assert(sizeof(RHO) != 1 || N == 127, "code_over_127 is for INT8 corrections");
     uint32_t pw[kCodecVec / 2], rw[sizeof(RHO) == 1 ? kCodecVec / 4 : kCodecVec / 2];
     const LanePos L = lane_pos_at<FULL>(tile0, n);
     load_u16(pw, param, L);
