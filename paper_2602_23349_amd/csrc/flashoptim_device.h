@@ -106,7 +106,8 @@ constexpr int step_array_bytes(int kind, bool split, bool quant) {      // per e
 constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
     return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
 }
-constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25); }      // (of the whole call)
+// (Of the whole call.  Beyond 2^38 elements the single wavefronts that go with it would be more than a 31-bit index counts.)
+constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25) && elems < ((int64_t)1 << 38); }
 constexpr bool codec_through(int64_t elems) { return elems >= ((int64_t)1 << 23); }
 
 constexpr int kCopyPiece = 16 * 1024;        // checkpoint copy: bytes per workgroup

@@ -138,3 +138,28 @@ def test_look_up_finds_every_workgroup_in_few_steps(tmp_path):
     """)
     looked, wrong, over = (int(x) for x in out[0].split())
     assert looked > 1000000 and wrong == 0 and over == 0
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="needs the HIP headers")
+def test_conversions_of_every_accepted_size_have_tiles_enough(tmp_path):
+    # a tensor may have up to 2^40 - 1 elements, and a launch's tiles are numbered with 31 bits
+    src, exe = tmp_path / "tiles.cpp", tmp_path / "tiles"
+    src.write_text("""#include <cstdio>
+#include "flashoptim_device.h"
+int main() {
+    for (int k = 0; k <= 40; ++k)
+        for (long long d : {-1, 0, 1}) {
+            const long long n = (1LL << k) + d;
+            if (n < 1 || n >= 1LL << 40) continue;
+            for (bool compress : {false, true}) {
+                const long long tile = fo::convert_chunk(compress, fo::convert_through(n));
+                std::printf("%lld %lld\\n", n, (n + tile - 1) / tile);
+            }
+        }
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+    assert len(lines) > 200 and int(lines[-1].split()[0]) == 2**40 - 1
+    assert all(int(line.split()[1]) <= 0x7fffffff for line in lines)
