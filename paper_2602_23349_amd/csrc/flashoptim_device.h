@@ -106,6 +106,17 @@ constexpr int step_array_bytes(int kind, bool split, bool quant) {      // per e
 constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
     return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
 }
+// Whether the tiles of a launch are dealt out among wavefronts (wave_part): where stores go through and there is more than one
+// wavefront to a workgroup, but not for the compressed AdamW step.  That one is bound by the package's power and its instructions; dealt
+// out it is slower (four Llama layers with embedding and head 3855 -> 3902 us, a layer 447 -> 454, GPT-2 254.5 -> 259.5), though on a
+// card with some power to spare two layers took 868 -> 848.  The others, in one piece -> dealt out, in us: SGD two Llama layers 689 ->
+// 657, flat 400 M 629 -> 606, GPT-2 198.6 -> 187.9, 24 tensors of 72 M 112.7 -> 110.0; Lion 688 -> 662, 620 -> 603, 199.4 -> 187.3,
+// 113.0 -> 110.3; weight split only, a layer, AdamW 822 -> 782, SGD 532 -> 507, Lion 534 -> 513, 25 M 94.9 -> 90.2, 62.7 -> 60.1, 62.9 -> 60.4; state
+// quantisation only, a layer 497 -> 490, 405 -> 396, 404 -> 396, 25 M the same.  Launches whose stores do not go through are 1-2 %
+// slower dealt out (SGD over 10 M elements 16.8 -> 17.0 us).
+constexpr bool step_dealt(int kind, bool split, bool quant, bool through) {
+    return through && (split || quant) && !(kind == 0 && split && quant);
+}
 // (Of the whole call.  Beyond 2^38 elements the single wavefronts that go with it would be more than a 31-bit index counts.)
 constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25) && elems < ((int64_t)1 << 38); }
 constexpr bool codec_through(int64_t elems) { return elems >= ((int64_t)1 << 23); }

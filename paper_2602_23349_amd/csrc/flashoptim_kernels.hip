@@ -910,18 +910,26 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
     return (int64_t)(b - T.first_tile);
 }
 
-// One tile of one tensor.  FULL: every lane of the workgroup holds VEC elements (all tiles of a
+// First element, in its tensor, of what this wavefront handles of a workgroup of WAVES with tile `tile`, where the tiles of whole
+// groups are dealt out (wave_part).  Wave-uniform.
+template <int WAVES, int WAVE_ELEMS>
+__device__ __forceinline__ int64_t wave_start(int64_t tile, int64_t numel) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    return wave_part(tile, wave, WAVES, numel / (WAVES * WAVE_ELEMS)) * WAVE_ELEMS;
+}
+
+// The elements from tile0 on, `rem` of them in the tensor; lane_el is the first one of the lane, counted from there.
+// FULL: every lane of the workgroup holds VEC elements (all tiles of a
 // tensor but possibly its last); the code then has no per-lane case distinction at all.
 // (Variants in which a workgroup loads two or four such tiles up front and then updates them in
 // turn - fewer look-ups, more bytes in flight per workgroup - ran at the same rate.)
 template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool THROUGH, bool FULL>
 __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a, StepTables& tab,
-                                          const TableEntries& entries, int64_t tile0, int tile_cnt, int tid) {
+                                          const TableEntries& entries, int64_t tile0, uint32_t lane_el, int rem, int tid) {
     constexpr bool HAS_V = (KIND == 0);
     const bool leader = (tid & (kGroup / VEC - 1)) == 0;
-    const uint32_t lane_el = (uint32_t)tid * VEC;              // first element of the lane inside its tile
-    // the number of the tile's elements that fall to this lane
-    const int left = tile_cnt - (int)lane_el;
+    // the number of them that fall to this lane
+    const int left = rem - (int)lane_el;
     const int cnt = FULL ? VEC : (left >= VEC ? VEC : (left > 0 ? left : 0));
     LaneIO<VEC> x, y;
     if (FULL || cnt == VEC) load_full<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0, lane_el);
@@ -955,15 +963,19 @@ __device__ __forceinline__ void step_workgroup(const StepArgs& a) {
     TensorDev T;
     uint32_t index = 0;
     const int64_t chunk = locate_tile<DIRECT>(a, T, &index);
-    const int64_t tile0 = chunk * (int64_t)kTile;              // first element of the tile (wave-uniform)
-    const int64_t rem = T.numel - tile0;                       // elements from there to the tensor's end
+    // first element of the tile, or where tiles are dealt out of this wavefront's part of them (wave-uniform)
+    constexpr bool DEALT = step_dealt(KIND, SPLIT, QUANT, THROUGH);
+    const int64_t tile0 = DEALT ? wave_start<THREADS / 64, 64 * VEC>(chunk, T.numel) : chunk * (int64_t)kTile;
+    const uint32_t lane_el = (uint32_t)(DEALT ? tid & 63 : tid) * VEC;
+    const int64_t rem = T.numel - chunk * (int64_t)kTile;      // elements from the tile's first one to the tensor's end
     const float table_lr = T.lr;
     if (!DIRECT) T.lr = u2f((f2u(table_lr) & a.table_lr_mask) | a.shared_lr_bits);      // (integers: stays on the scalar unit)
     if (rem >= kTile) {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, true>(T, a, tab, entries, tile0, kTile, tid);
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, true>(T, a, tab, entries, tile0, lane_el, kTile, tid);
     } else {
-        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, false>(T, a, tab, entries, tile0,
-                                                                                  rem > 0 ? (int)rem : 0, tid);
+        // (less than a tile, so within an int; negative for a wavefront behind the tensor's end)
+        step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, false>(T, a, tab, entries, tile0, lane_el,
+                                                                                  (int)(T.numel - tile0), tid);
     }
     // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
     if (!DIRECT && chunk == 0 && f2u(T.lr) != f2u(table_lr) && tid == 0) a.tensors[index].lr = T.lr;
@@ -1052,17 +1064,15 @@ hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape 
 template <int KIND, int VEC, int THREADS, bool DIRECT>
 __global__ __launch_bounds__(THREADS) void probe_kernel(StepArgs a) {
     constexpr bool HAS_V = (KIND == 0);
-    constexpr int kTile = THREADS * VEC;
     const int tid = (int)threadIdx.x;
     TensorDev T;
     const int64_t chunk = locate_tile<DIRECT>(a, T);
     const bool leader = (tid & (kGroup / VEC - 1)) == 0;
-    const uint32_t lane_el = (uint32_t)tid * VEC;
-    const int64_t tile0 = chunk * (int64_t)kTile;
-    const int64_t rem = T.numel - tile0;
-    const int tile_cnt = rem >= kTile ? kTile : (int)rem;
-    const int left = tile_cnt - (int)lane_el;
-    const int cnt = left >= VEC ? VEC : (left > 0 ? left : 0);
+    const bool dealt = step_dealt(KIND, true, true, a.through);
+    const int64_t tile0 = dealt ? wave_start<THREADS / 64, 64 * VEC>(chunk, T.numel) : chunk * (int64_t)(THREADS * VEC);
+    const uint32_t lane_el = (uint32_t)(dealt ? tid & 63 : tid) * VEC;
+    const int64_t left = T.numel - tile0 - (int64_t)lane_el;
+    const int cnt = left >= VEC ? VEC : (left > 0 ? (int)left : 0);
     LaneIO<VEC> x;
     if (cnt == VEC) load_full<VEC, HAS_V, true, true>(x, T, tile0, lane_el);
     else load_tail<VEC, HAS_V, true, true>(x, T, tile0 + lane_el, cnt);

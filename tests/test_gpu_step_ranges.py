@@ -145,6 +145,25 @@ def test_launch_rules_on_both_sides_of_their_limits(kind, n):
             _same(b, st, f"{kind} {sizes}")
 
 
+# Tensors of whole groups of tiles and of a tile or an element more or less, beside one that makes the launch large enough for
+# them to be dealt out (32 tiles of 2048 elements).
+@pytest.mark.parametrize("kind", ["sgd", "lion"])
+def test_tiles_around_a_group_that_is_dealt_out(kind):
+    rng = np.random.default_rng(11)
+    sizes = [32 * 2048 * k + d for k in (1, 2) for d in (-2048, -1, 0, 1, 2048, 2049)] + [29360128 + 31 * 2048 + 7]
+    bufs, states, grads = [], [], []
+    for n in sizes:
+        thp = rng.normal(0, 0.02, n).astype(np.float32).view(np.uint32) >> 16
+        states.append(_state(rng, n, kind, thp))
+        bufs.append(upload_state(states[-1]))
+        bufs[-1].lr, bufs[-1].weight_decay = 1e-3, 0.01
+        grads.append((rng.normal(0, 1e-4, n).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+        bufs[-1].grad.copy_(to_dev_u16(grads[-1], torch.bfloat16))
+    _step(kind, bufs, states, grads, 1, HP)
+    for b, st in zip(bufs, states):
+        _same(b, st, f"{kind} numel {st.n}")
+
+
 @pytest.mark.parametrize("kind,split,quant,n", [("adamw", False, False, 12582912), ("sgd", False, False, 17616077),
                                                 ("adamw", True, False, 13550829), ("lion", True, False, 19573419),
                                                 ("adamw", False, True, 22020096), ("sgd", False, True, 25165824)])

@@ -163,3 +163,30 @@ int main() {
     lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
     assert len(lines) > 200 and int(lines[-1].split()[0]) == 2**40 - 1
     assert all(int(line.split()[1]) <= 0x7fffffff for line in lines)
+
+
+@pytest.mark.parametrize("waves", [1, 2, 4, 8, 16])
+def test_dealt_out_tiles_cover_every_part_once(tmp_path, waves):
+    # tensors of 0 to 200 whole tiles, with and without a ragged one behind them: the parts of the whole tiles are all dealt out once,
+    # the ragged tile and those of the last, incomplete group keep theirs
+    out = _run(tmp_path, f"""
+    const int waves = {waves};
+    long long wrong = 0, spread = 0;
+    for (int full = 0; full <= 200; ++full)
+        for (int ragged = 0; ragged < 2; ++ragged) {{
+            static int seen[201 * 16];
+            for (int i = 0; i < (full + ragged) * waves; ++i) seen[i] = 0;
+            for (int t = 0; t < full + ragged; ++t)
+                for (int w = 0; w < waves; ++w) {{
+                    const long long p = fo::wave_part(t, w, waves, full);
+                    if (p < 0 || p >= (full + ragged) * waves) {{ ++wrong; continue; }}
+                    ++seen[p];
+                    if (t >= full - full % fo::kTileGroup) wrong += p != (long long)t * waves + w;
+                    else if (w > 0) spread += p - fo::wave_part(t, w - 1, waves, full) == fo::kTileGroup;
+                }}
+            for (int i = 0; i < (full + ragged) * waves; ++i) wrong += seen[i] != 1;
+        }}
+    std::printf("%lld %lld\\n", wrong, spread);
+    """)
+    wrong, spread = (int(x) for x in out[0].split())
+    assert wrong == 0 and (spread > 0) == (waves > 1)
