@@ -76,11 +76,18 @@ constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, b
     if (!through) return kNoLimit;
     return split ? (kind == 0 ? 4 : 5) : quant ? (kind == 0 ? 6 : 7) : kind == 0 ? 11 : 14;
 }
-// Layout conversions.  To FP32, 7 / 6 / 5 workgroups of 256 lanes: GPT-2 344.1 / 342.1 / 347.4 us, 300 M elements 838 / 832 /
-// 828, 5 M 15.8 / 15.8 / 15.9; under 2^22 elements no limit (2 M 6.5).  From FP32, 18 single wavefronts: GPT-2 323 (with no limit
-// 337, 21 of them 321, 16 330), 300 M 777 (825, 793, 790).
-constexpr int convert_resident(bool compress, bool through, int64_t elems) {
-    return compress ? (through ? 18 : kNoLimit) : elems < ((int64_t)1 << 22) ? kNoLimit : 6;
+// Layout conversions, in us.
+//   To FP32, 256 lanes, tiles dealt out (below): of AdamW's state 4 (with 4 / 5 / 6 / 8, flat 300 M 798 / 808 / 814 / 820, a Llama layer
+//       571 / 579 / 580 / 589, GPT-2 326.5 / 329.2 / 328.4 / 334.0, flat 40 M 105.8 / 106.8 / 107.3 / 108.7), but 6 for lists of fewer than
+//       2^26 elements (60 tensors of 60 M 159.6 / 157.7 / 156.1 / 157.0); of the others' 6 (GPT-2 257 / 235 / 228 / 226, flat 300 M 591 / 546 /
+//       545 / 543).  In one piece: 7 / 6 / 5 workgroups 5 M 15.8 / 15.8 / 15.9; under 2^22 elements no limit (2 M 6.5).
+//   From FP32, single wavefronts: 20 for lists (with 18 / 20 / 22, AdamW GPT-2 321.9 / 318.9 / 329.0, a layer 563.7 / 559.8 / 581.8, 60 tensors of
+//       60 M 157.4 / 154.8 / 155.9; SGD 229.8 / 222.7 / 224.1, 404.9 / 392.9 / 397.2, 113.9 / 110.9 / 108.8), 18 for a single tensor (AdamW 300 M
+//       766.7 / 785.6 / 803.4, 200 M 510 / 525 / 541, 40 M 104.4 / 105.0 / 107.1; SGD 532 / 537 / 548, 354 / 356 / 368, 74.2 / 73.6 / 74.4).
+constexpr int convert_resident(bool compress, bool has_v, bool direct, bool through, int64_t elems) {
+    if (compress) return !through ? kNoLimit : direct ? 18 : 20;
+    if (elems < ((int64_t)1 << 22)) return kNoLimit;
+    return through && has_v && (direct || elems >= ((int64_t)1 << 26)) ? 4 : 6;
 }
 // The dynamic LDS, in bytes, with which exactly `resident` workgroups that use `used` bytes fit into a compute unit's
 // 160 KB (given out in units of 1280 bytes).
@@ -117,6 +124,10 @@ constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
 constexpr bool step_dealt(int kind, bool split, bool quant, bool through) {
     return through && (split || quant) && !(kind == 0 && split && quant);
 }
+// Conversions to FP32 are dealt out where their stores go through (in one piece -> dealt out, with the limits above on both sides, AdamW
+// GPT-2 341.0 -> 326.5 us, a Llama layer 609.6 -> 571.0, flat 300 M 822 -> 798, 40 M 110.0 -> 105.8; SGD 237.5 -> 228.0, 413.1 -> 399.7,
+// 561 -> 545, 76.6 -> 73.4).  Those from FP32 are single wavefronts.  The quantisers and dequantisers are 1 to 5 % slower dealt out.
+constexpr bool convert_dealt(bool compress, bool through) { return !compress && through; }
 // (Of the whole call.  Beyond 2^38 elements the single wavefronts that go with it would be more than a 31-bit index counts.)
 constexpr bool convert_through(int64_t elems) { return elems >= ((int64_t)1 << 25) && elems < ((int64_t)1 << 38); }
 constexpr bool codec_through(int64_t elems) { return elems >= ((int64_t)1 << 23); }
@@ -215,7 +226,7 @@ struct CopyArgs {
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
                        int64_t n_blocks, hipStream_t s);
 // Lanes per workgroup and elements per tile of the layout conversions.  Compressing stages nothing: calls whose stores go
-// through take single wavefronts, 18 to a compute unit (GPT-2 344.8 -> 322.6 us, 300 M elements 816 -> 777, 25 M 70.0 -> 69.8);
+// through take single wavefronts (GPT-2 344.8 -> 322.6 us, 300 M elements 816 -> 777, 25 M 70.0 -> 69.8);
 // smaller ones 256 lanes (5 M 15.0 us, as single wavefronts 15.5).  Decompressing takes 256 (GPT-2 340.0 us, 128 lanes 343.9, single
 // wavefronts 346.9; 300 M 834, 862 and 842).
 constexpr int convert_threads(bool compress, bool through) { return compress && through ? 64 : 256; }

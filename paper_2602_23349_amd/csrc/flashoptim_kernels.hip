@@ -1153,16 +1153,17 @@ constexpr int kWaveThreads = 64;                          // split and reconstru
 constexpr int kWaveTile = kWaveThreads * kCodecVec;
 
 struct LanePos {
-    int64_t tile0;       // first element of the pass (wave-uniform)
-    uint32_t lane_el;    // first element of the lane inside the pass
+    int64_t tile0;       // first element of the pass, or of the wavefront's part of it (wave-uniform)
+    uint32_t lane_el;    // first element of the lane, from there on
     int cnt;             // elements of the lane that exist: kCodecVec, or fewer at the ragged end
 };
 // FULL: every element of the pass exists (known at compile time, so that no case distinction is left).
-template <bool FULL>
+// DEALT: tile0 is where the wavefront's part begins.
+template <bool FULL, bool DEALT = false>
 __device__ __forceinline__ LanePos lane_pos_at(int64_t tile0, int64_t n) {
     LanePos L;
     L.tile0 = tile0;
-    L.lane_el = (uint32_t)threadIdx.x * kCodecVec;
+    L.lane_el = (uint32_t)(DEALT ? threadIdx.x & 63 : threadIdx.x) * kCodecVec;
     const int64_t left = n - tile0 - (int64_t)L.lane_el;
     L.cnt = (FULL || left >= kCodecVec) ? kCodecVec : (left > 0 ? (int)left : 0);
     return L;
@@ -1851,7 +1852,7 @@ __device__ __forceinline__ void compress_tile(const TensorDev& T, int64_t tile0)
 template <bool HAS_V, bool THROUGH, bool FULL>
 __device__ __forceinline__ void decompress_tile(const TensorDev& T, int64_t tile0) {
     uint32_t pw[kCodecVec / 2], rw[kCodecVec / 4], mw[kCodecVec / 4], vw[kCodecVec / 4];
-    const LanePos L = lane_pos_at<FULL>(tile0, T.numel);
+    const LanePos L = lane_pos_at<FULL, convert_dealt(false, THROUGH)>(tile0, T.numel);
     load_u16(pw, T.param, L);
     load_u8(rw, T.rho, L);
     load_u8(mw, T.m_q, L);
@@ -1880,8 +1881,10 @@ __global__ __launch_bounds__(convert_threads(COMPRESS, THROUGH)) void convert_ke
     constexpr int kTile = convert_chunk(COMPRESS, THROUGH);
     static_assert(kTile == convert_threads(COMPRESS, THROUGH) * kCodecVec, "one access of a lane to each stream");
     TensorDev T;
-    const int64_t tile0 = locate_tile<DIRECT>(a, T) * (int64_t)kTile;
-    const bool full = T.numel - tile0 >= kTile;
+    const int64_t tile = locate_tile<DIRECT>(a, T);
+    const bool full = T.numel - tile * kTile >= kTile;
+    const int64_t tile0 = convert_dealt(COMPRESS, THROUGH) ? wave_start<kTile / (64 * kCodecVec), 64 * kCodecVec>(tile, T.numel)
+                                                           : tile * kTile;
     if constexpr (COMPRESS) {
         if (full) compress_tile<HAS_V, THROUGH, true>(T, tile0);
         else compress_tile<HAS_V, THROUGH, false>(T, tile0);
@@ -1893,7 +1896,8 @@ __global__ __launch_bounds__(convert_threads(COMPRESS, THROUGH)) void convert_ke
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
     const dim3 grid((unsigned)n_blocks), block(convert_threads(compress, a.through));
-    const unsigned lds = lds_to_hold(convert_resident(compress, a.through, n_blocks * convert_chunk(compress, a.through)), 0);
+    const int64_t elems = n_blocks * convert_chunk(compress, a.through);
+    const unsigned lds = lds_to_hold(convert_resident(compress, has_v, direct, a.through, elems), 0);
 #define FO_CONV(HV, CP, DR)                                                                                   \
     do {                                                                                                      \
         if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, lds, s, a);        \

@@ -250,6 +250,34 @@ def test_conversions_on_both_sides_of_their_limits(n):
     assert np.array_equal(f.m.cpu().numpy().view(np.uint32), oracle.dequantize_momentum(q, s).view(np.uint32))
 
 
+# To FP32, tensors of whole groups of tiles and of a tile or an element more or less, beside one that makes the call large enough for
+# them to be dealt out (32 tiles of 1024 elements).
+@pytest.mark.parametrize("kind", ["adamw", "sgd"])
+def test_decompressing_around_a_group_that_is_dealt_out(kind):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    bufs = []
+    for n in [32 * 1024 * k + d for k in (1, 2) for d in (-1024, -1, 0, 1, 1024, 1025)] + [(1 << 25) + 31 * 1024 + 7]:
+        f = fo.ParamBuffers(n, kind, with_grad=False, split_weights=False, quantize_states=False)
+        c = fo.ParamBuffers(n, kind, with_grad=False)
+        c.param.normal_(0, 0.02, generator=g)
+        for q, lo, hi in ((c.rho, -127, 128), (c.m_q, -127, 128), (c.v_q, 0, 256)):
+            if q is not None:
+                q.random_(lo, hi, generator=g)
+        for s in (c.m_scale, c.v_scale):
+            if s is not None:
+                s.uniform_(1e-5, 1e-3, generator=g)
+        c.theta, c.m, c.v = f.theta, f.m, f.v
+        bufs.append(c)
+    fo.decompress_state(kind, bufs)
+    bits = lambda t: t.cpu().numpy().view(np.uint32)
+    for c in bufs:
+        got = download(c)
+        assert np.array_equal(bits(c.theta), oracle.reconstruct(got["thp"], got["rho"]).view(np.uint32)), c.numel
+        assert np.array_equal(bits(c.m), oracle.dequantize_momentum(got["mq"], got["ms"]).view(np.uint32)), c.numel
+        if kind == "adamw":
+            assert np.array_equal(bits(c.v), oracle.dequantize_variance(got["vq"], got["vs"]).view(np.uint32)), c.numel
+
+
 @pytest.mark.parametrize("n", [1 << 25, (1 << 25) - 1])       # single wavefronts, and 256 lanes
 def test_compressing_a_list_on_both_sides_of_its_limit(n):
     sizes = [1, 31, 255, 256, 257, 1023, 1025, 4097]
