@@ -669,28 +669,29 @@ int check_elementwise(const void* a, const void* b, const void* c, int64_t n) {
 // ------------------------------------------------------------ workspaces of waiting calls --
 //
 // The calls that return values to the host (quantisation error, unpack's header check) let a kernel write them to
-// pinned memory and wait for a flag that it sets last; the quantisation error also needs device memory for the
-// workgroups' partial sums, and unpack a word by which its check admits its copy.  They are kept from call to call
-// (allocating and freeing them cost ~20 us a call, and freeing waits for every stream of the device); a call takes a
+// pinned memory, which they watch; unpack also needs a word of device memory by which its check admits its copy.  They are kept from
+// call to call (allocating and freeing them cost ~20 us a call, and freeing waits for every stream of the device); a call takes a
 // workspace out of the pool for as long as it runs, so calls of several threads and streams never share one, and a
-// workspace goes back only once its kernels have set the flag or their stream has been waited for.  One kernel may
-// still be to run then: the copy of an unpack that was admitted, which reads the word and stands any later use of it
+// workspace goes back only once its kernels have written all that they write there or their stream has been waited for.  One kernel
+// may still be to run then: the copy of an unpack that was admitted, which reads the word and stands any later use of it
 // (verdict_word in flashoptim_launch.h).
 struct CallSpace {
     int device = 0;
-    double2* partial = nullptr;     // fo::kNmseMaxBlocks pairs, and the word behind them
-    uint8_t* host = nullptr;        // pinned and coherent: kSpaceHost bytes and the flag behind them
-    uint64_t seq = 0;               // the workspace's uses so far: the ticket of the current one; its low half marks its end
+    uint64_t* verdict = nullptr;    // device memory: the word
+    uint8_t* host = nullptr;        // pinned and coherent: kSpaceHost bytes, the flag and the quantisation error's words behind them
+    uint64_t seq = 0;               // the workspace's uses so far: the ticket of the current one
 
+    uint32_t ticket() const { return (uint32_t)seq; }      // (never 0)
     uint32_t* flag() const;
-    uint64_t* verdict() const { return reinterpret_cast<uint64_t*>(partial + fo::kNmseMaxBlocks); }
+    uint64_t* words() const;
 };
-constexpr size_t kSpaceDevice = fo::kNmseMaxBlocks * sizeof(double2) + 64;
 constexpr size_t kSpaceHost = 64;               // two values of eight bytes
 constexpr size_t kFlagStride = 64;              // bytes: the flag has a cache line of its own
+constexpr size_t kSpaceWords = (size_t)fo::kNmseMaxBlocks * fo::kNmseWords * sizeof(uint64_t);
 uint32_t* CallSpace::flag() const { return reinterpret_cast<uint32_t*>(host + kSpaceHost); }
+uint64_t* CallSpace::words() const { return reinterpret_cast<uint64_t*>(host + kSpaceHost + kFlagStride); }
 std::mutex g_space_mu;
-constexpr int kMaxIdleSpaces = 16;              // 32 KB of device memory and 128 bytes of pinned memory each; what more calls
+constexpr int kMaxIdleSpaces = 16;              // 32 KB of pinned memory and 64 bytes of device memory each; what more calls
 CallSpace g_space_idle[kMaxIdleSpaces];         // than that give back at once is freed
 int g_space_n_idle = 0;
 
@@ -699,8 +700,8 @@ void destroy_space(CallSpace& w) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(w.device);
-    if (w.partial) (void)hipDeviceSynchronize();
-    if (w.partial) (void)hipFree(w.partial);
+    if (w.verdict) (void)hipDeviceSynchronize();
+    if (w.verdict) (void)hipFree(w.verdict);
     if (w.host) (void)hipHostFree(w.host);
     (void)hipSetDevice(cur);
     w = CallSpace();
@@ -715,18 +716,22 @@ int take_space(CallSpace& w) {
             w = g_space_idle[i];
             g_space_idle[i] = g_space_idle[--g_space_n_idle];
             ++w.seq;
+            if (w.ticket() == 0) {      // tickets start over: no word may hold one that comes again
+                std::memset(w.host, 0, kSpaceHost + kFlagStride + kSpaceWords);
+                ++w.seq;
+            }
             return FLASHOPTIM_OK;
         }
     }
-    hipError_t e = hipMalloc((void**)&w.partial, kSpaceDevice);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&w.host, kSpaceHost + kFlagStride, hipHostMallocCoherent);
+    hipError_t e = hipMalloc((void**)&w.verdict, 64);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&w.host, kSpaceHost + kFlagStride + kSpaceWords, hipHostMallocCoherent);
     if (e != hipSuccess) {
         destroy_space(w);
         g_last_hip_error = (int)e;
         (void)hipGetLastError();
         return FLASHOPTIM_ERR_HIP;
     }
-    *w.flag() = 0;
+    std::memset(w.host, 0, kSpaceHost + kFlagStride + kSpaceWords);
     w.seq = 1;
     return FLASHOPTIM_OK;
 }
@@ -738,23 +743,23 @@ void give_space(CallSpace& w) {
     else destroy_space(w);
 }
 
-// Waits for the flag of the work that uses `w` (launched with result `e`).  For up to 2 ms the host watches it without a pause: it
-// sees it some microseconds before the runtime reports the stream idle (2^24 momentum values: 31.5 -> 27.9 us a call).  Longer
-// work is waited for through the stream if the flag ends it (`last`).  Otherwise the host goes on watching the flag, with pauses,
-// and now and then asks whether the stream has failed or run dry without it: waiting for the stream would be waiting for
-// what is enqueued behind the flag as well (unpack's copy, 14 ms for 41 GB).  If anything failed the workspace is freed, which waits for
-// whatever may still use it.
-int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last) {
-    const volatile uint32_t* f = w.flag();
-    auto is_set = [&] {
-        if (*f != (uint32_t)w.seq) return false;
+// Waits until is_set() finds in the pinned memory of `w` what the work that uses it (launched with result `e`) writes there.  For up
+// to 2 ms the host watches it without a pause: it sees it some microseconds before the runtime reports the stream idle (2^24 momentum
+// values, when that was written: 31.5 -> 27.9 us a call).  Longer work is waited for through the stream if nothing is behind it (`last`).  Otherwise the
+// host goes on watching, with pauses, and now and then asks whether the stream has failed or run dry without it: waiting for the
+// stream would be waiting for what is enqueued behind as well (unpack's copy, 14 ms for 41 GB).  If anything failed the workspace is
+// freed, which waits for whatever may still use it.
+template <typename F>
+int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last, F is_set) {
+    auto done = [&] {
+        if (!is_set()) return false;
         std::atomic_thread_fence(std::memory_order_acquire);
         return true;
     };
     if (e == hipSuccess) {
         const auto t0 = std::chrono::steady_clock::now();
         for (uint32_t k = 1;; ++k) {
-            if (is_set()) return FLASHOPTIM_OK;
+            if (done()) return FLASHOPTIM_OK;
             if (k % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
         }
         for (uint32_t k = 1;; ++k) {
@@ -765,7 +770,7 @@ int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last) {
                 e = k % 256 == 0 ? hipStreamQuery(stream) : hipErrorNotReady;
                 if (k % 256 == 0) (void)hipGetLastError();      // ("not ready" is no error of a later launch's)
             }
-            if ((e == hipSuccess || e == hipErrorNotReady) && is_set()) return FLASHOPTIM_OK;
+            if ((e == hipSuccess || e == hipErrorNotReady) && done()) return FLASHOPTIM_OK;
             if (e == hipSuccess) e = hipErrorUnknown;           // (never: the kernel that sets it has run)
             if (e != hipErrorNotReady) break;
         }
@@ -841,9 +846,9 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
         a.header_dst = reinterpret_cast<uint4*>(blob);
         a.step = step;
     } else {
-        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), check->verdict(),
+        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), check->verdict,
                                        reinterpret_cast<int64_t*>(check->host), check->flag(), check->seq, stream));
-        a.verdict = check->verdict();
+        a.verdict = check->verdict;
         a.ticket = check->seq;
     }
     FO_HIP(fo::launch_copy(a, stream));
@@ -1130,10 +1135,30 @@ int flashoptim_quantization_nmse(int state, int linear, const float* x, int64_t 
     CallSpace w;
     rc = take_space(w);
     if (rc != FLASHOPTIM_OK) return rc;
-    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.partial, reinterpret_cast<double*>(w.host), w.flag(),
-                                       (uint32_t)w.seq, stream), stream, true);
+    // the workgroups' pairs are added up in their order, each as soon as it is there
+    const int blocks = fo::nmse_blocks(n);
+    const volatile uint64_t* words = w.words();
+    const uint32_t ticket = w.ticket();
+    double err = 0.0, ref = 0.0;
+    int next = 0;
+    rc = wait_space(w, fo::launch_nmse(state == 1, linear == 1, x, n, w.words(), ticket, stream), stream, true, [&] {
+        for (; next < blocks; ++next) {
+            uint64_t pair[fo::kNmseWords];
+            for (int k = 0; k < fo::kNmseWords; ++k) pair[k] = words[next * fo::kNmseWords + k];
+            if (!fo::nmse_ready(pair, ticket)) return false;
+            // (what the device has written is in no cache of the host's: 16 lines ahead)
+            if (next + 32 < blocks) __builtin_prefetch(const_cast<const uint64_t*>(words) + (next + 32) * fo::kNmseWords);
+            const uint64_t bits[2] = {fo::nmse_sum(pair, 0), fo::nmse_sum(pair, 1)};
+            double d[2];
+            std::memcpy(d, bits, sizeof(d));
+            err += d[0];
+            ref += d[1];
+        }
+        return true;
+    });
     if (rc != FLASHOPTIM_OK) return rc;
-    std::memcpy(sums, w.host, 2 * sizeof(double));
+    sums[0] = err;
+    sums[1] = ref;
     give_space(w);
     return FLASHOPTIM_OK;
 }
@@ -1188,7 +1213,8 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
         destroy_space(w);       // (the check may be on its way: freeing waits for it)
         return rc;
     }
-    rc = wait_space(w, hipSuccess, stream, false);
+    const volatile uint32_t* flag = w.flag();
+    rc = wait_space(w, hipSuccess, stream, false, [&] { return *flag == w.ticket(); });
     if (rc != FLASHOPTIM_OK) return rc;
     int64_t found[2];
     std::memcpy(found, w.host, sizeof(found));

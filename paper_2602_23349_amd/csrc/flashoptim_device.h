@@ -243,11 +243,10 @@ hipError_t launch_sweep(int bits, bool directional, uint64_t first, uint64_t str
 hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s);
 hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                              hipStream_t s);
-constexpr int kNmseMaxBlocks = 256 * 8;    // eight resident workgroups per compute unit
-// partial: device memory for kNmseMaxBlocks pairs; sums: two doubles of pinned memory; *flag (pinned) becomes seq once
-// they are there
-hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
-                       uint32_t* flag, uint32_t seq, hipStream_t s);
+constexpr int kNmseThreads = 512, kNmseMaxBlocks = 1024;
+int nmse_blocks(int64_t n);
+// words: kNmseWords words of pinned memory for each of the nmse_blocks(n) workgroups, its sums with this call's ticket (nmse_word)
+hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, uint64_t* words, uint32_t ticket, hipStream_t s);
 hipError_t launch_copy(CopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);

@@ -1313,14 +1313,6 @@ __device__ __forceinline__ float reconstruct_directional(uint32_t b, int rho) {
     return base + ldexpf(q, half_ulp_log2(b) - ((rho != 0 && finer_side(b, rho < 0)) ? 1 : 0));
 }
 
-// Copies one 256-entry decode table into LDS, one entry per lane of a 256-lane workgroup, and waits for
-// it.  Every lane of the workgroup must call it.
-__device__ __forceinline__ void stage_table(float* lds, const float* table) {
-    static_assert(kThreads == 256, "one table entry per lane");
-    lds[threadIdx.x] = table[threadIdx.x];
-    __syncthreads();
-}
-
 // The rho half of C without the tables: the same three operations as split_rho, of which the clamp is the
 // identity for a finite theta' (|e| <= half an ULP under round-to-nearest), with Round() as one addition.
 // For N = 127 the product with N is exact (at most 16 + 7 significant bits).  A non-finite theta' gives 0.
@@ -1641,10 +1633,11 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(const uint8_t* q, 
 }
 
 // Quantisation error of a buffer (Section 4.5): sum (Q^-1(Q(x)) - x)^2 and sum x^2, in double.  A workgroup walks
-// over tiles blockIdx.x, blockIdx.x + gridDim.x, ... and writes its pair of partial sums; a second kernel of one
-// workgroup adds the pairs up in a fixed order and writes the result to memory that the host reads.
-// (With one pair of FP64 atomics per wavefront on the two totals, 2^24 elements took 206 us, nearly all of it
-// those 16,384 updates of two addresses.)
+// over tiles blockIdx.x, blockIdx.x + gridDim.x, ... and leaves its pair of partial sums in pinned memory, where the host, which
+// waits for the result anyway, adds the pairs up in the order of the workgroups.  A whole call, momentum / variance, with a second kernel of
+// one workgroup that added up 2048 pairs and set a flag -> now, us: 200,000 values 12.4 -> 10.1, 1 M 13.1 -> 11.3, 5 M 16.6 / 16.9 -> 15.4 / 15.5,
+// 2^24 23.9 / 24.9 -> 21.3 / 22.6, 38.6 M 37.4 / 39.0 -> 34.8 / 36.7, 100 M 74.0 / 78.6 -> 71.9 / 77.5 (of which 5.6 TB/s are left, less the 10 us
+// that the smallest call takes, 6.5).  What bounds the smallest is the launch and the way to the host and back; the largest, HBM.
 template <int THREADS>
 __device__ __forceinline__ void block_sum_pair(double& a, double& b) {
     __shared__ double part[2][THREADS / 64];
@@ -1661,19 +1654,21 @@ __device__ __forceinline__ void block_sum_pair(double& a, double& b) {
 #pragma unroll
     for (int k = 0; k < THREADS / 64; ++k) { a += part[0][k]; b += part[1][k]; }
 }
-
-template <bool VARIANCE, bool LINEAR, bool FULL>
-__device__ __forceinline__ void nmse_tile(const float* x, int64_t n, int64_t tile0, const float* tab, double& err,
-                                          double& ref) {
-    float v[kCodecPasses][kCodecVec];
+constexpr int kNmsePasses = 2;
+constexpr int kNmsePass = kNmseThreads * kCodecVec, kNmseTile = kNmsePass * kNmsePasses;
+// (elements past the end are zero: their code decodes to zero and they add nothing)
+template <bool FULL>
+__device__ __forceinline__ void nmse_load(float (&v)[kNmsePasses][kCodecVec], const float* x, int64_t n, int64_t tile0) {
 #pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) load_f32(v[r], x, lane_pos_at<FULL>(tile0 + r * kCodecPass, n));
+    for (int r = 0; r < kNmsePasses; ++r) load_f32(v[r], x, lane_pos_at<FULL>(tile0 + r * kNmsePass, n));
+}
+template <bool VARIANCE, bool LINEAR>
+__device__ __forceinline__ void nmse_add(const float (&v)[kNmsePasses][kCodecVec], const float* tab, double& err, double& ref) {
 #pragma unroll
-    for (int r = 0; r < kCodecPasses; ++r) {
+    for (int r = 0; r < kNmsePasses; ++r) {
         uint32_t w[kCodecVec / 4];
         const uint32_t sbits = quantize_lane<VARIANCE, LINEAR>(v[r], w);
         const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
-        // (elements past the end are zero: their code decodes to zero and they add nothing)
 #pragma unroll
         for (int i = 0; i < kCodecVec; ++i) {
             const double xi = (double)v[r][i];
@@ -1684,38 +1679,27 @@ __device__ __forceinline__ void nmse_tile(const float* x, int64_t n, int64_t til
     }
 }
 template <bool VARIANCE, bool LINEAR>
-__global__ __launch_bounds__(kThreads) void nmse_kernel(const float* x, int64_t n, double2* partial) {
+__global__ __launch_bounds__(kNmseThreads) void nmse_kernel(const float* x, int64_t n, uint64_t* words, uint32_t ticket) {
+    static_assert(kNmseThreads >= 256, "a lane for every entry of the table");
     __shared__ float tab[256];
-    stage_table(tab, decode_table<VARIANCE, LINEAR>());
+    const uint32_t i = threadIdx.x & 255;
+    const float entry = decode_table<VARIANCE, LINEAR>()[i];
     double err = 0.0, ref = 0.0;
-    for (int64_t tile0 = (int64_t)blockIdx.x * kCodecTile; tile0 < n; tile0 += (int64_t)gridDim.x * kCodecTile) {
-        if (n - tile0 >= kCodecTile) nmse_tile<VARIANCE, LINEAR, true>(x, n, tile0, tab, err, ref);
-        else nmse_tile<VARIANCE, LINEAR, false>(x, n, tile0, tab, err, ref);
+    float v[kNmsePasses][kCodecVec];
+    for (int64_t tile0 = (int64_t)blockIdx.x * kNmseTile; tile0 < n; tile0 += (int64_t)gridDim.x * kNmseTile) {
+        if (n - tile0 >= kNmseTile) nmse_load<true>(v, x, n, tile0);
+        else nmse_load<false>(v, x, n, tile0);
+        if (tile0 == (int64_t)blockIdx.x * kNmseTile) {      // (the table's way to LDS, behind the first tile's loads)
+            tab[i] = entry;
+            __syncthreads();
+        }
+        nmse_add<VARIANCE, LINEAR>(v, tab, err, ref);
     }
-    block_sum_pair<kThreads>(err, ref);
-    if (threadIdx.x == 0) partial[blockIdx.x] = make_double2(err, ref);
-}
-// One workgroup with all of its loads in flight, and one lane that orders the flag behind its own two stores (2^24
-// momentum values, a whole call: 27.4 us with eight rounds of loads and a system-wide fence by every lane, 25.6 now).
-constexpr int kTotalThreads = 512;
-constexpr int kTotalPairs = kNmseMaxBlocks / kTotalThreads;
-static_assert(kTotalPairs * kTotalThreads == kNmseMaxBlocks, "every lane adds the same number of pairs");
-__global__ __launch_bounds__(kTotalThreads) void nmse_total_kernel(const double2* partial, int n_partial, double* sums,
-                                                                   uint32_t* flag, uint32_t seq) {
-    double2 p[kTotalPairs];
-#pragma unroll
-    for (int k = 0; k < kTotalPairs; ++k) {
-        const int i = (int)threadIdx.x + k * kTotalThreads;
-        p[k] = i < n_partial ? partial[i] : make_double2(0.0, 0.0);
-    }
-    double err = 0.0, ref = 0.0;
-#pragma unroll
-    for (int k = 0; k < kTotalPairs; ++k) { err += p[k].x; ref += p[k].y; }
-    block_sum_pair<kTotalThreads>(err, ref);
-    if (threadIdx.x == 0) {
-        sums[0] = err;
-        sums[1] = ref;
-        __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
+    block_sum_pair<kNmseThreads>(err, ref);
+    if (threadIdx.x < kNmseWords) {
+        const uint64_t sum = (uint64_t)__double_as_longlong(threadIdx.x < 2 ? err : ref);
+        const uint64_t word = nmse_word((uint32_t)(threadIdx.x & 1 ? sum >> 32 : sum), ticket);
+        __hip_atomic_store(&words[(uint64_t)blockIdx.x * kNmseWords + threadIdx.x], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -1733,11 +1717,6 @@ static hipError_t for_each_launch(int64_t n, int tile, int threads, F launch) {
     }
     return hipSuccess;
 }
-static inline unsigned nmse_blocks(int64_t n) {
-    const int64_t tiles = (n + kCodecTile - 1) / kCodecTile;
-    return (unsigned)(tiles < kNmseMaxBlocks ? tiles : kNmseMaxBlocks);
-}
-
 template <int N, typename RHO>
 static hipError_t launch_split_n(const float* theta, uint16_t* param, RHO* rho, int64_t n, hipStream_t s) {
     return for_each_launch(n, kWaveTile, kWaveThreads, [=](dim3 blocks, int64_t at, int64_t count) {
@@ -1798,17 +1777,18 @@ hipError_t launch_dequantize(bool variance, bool linear, const void* q, const ui
         });
     });
 }
-hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, double2* partial, double* sums,
-                       uint32_t* flag, uint32_t seq, hipStream_t s) {
-    const hipError_t e = dispatch_codec(variance, linear, false, [=](auto V, auto L, auto) {
-        hipLaunchKernelGGL((nmse_kernel<decltype(V)::value, decltype(L)::value>), dim3(nmse_blocks(n)), dim3(kThreads), 0, s,
-                           x, n, partial);
+// Three workgroups to a compute unit, four for long arrays: the host reads as many pairs, which takes it some microseconds, and more
+// in flight pays only where there is much to read (768 / 1024 / 2048 workgroups, 5 M values 15.4 / 16.5 / 21; variance, 100 M, 79.6 / 77.5).
+int nmse_blocks(int64_t n) {
+    const int64_t tiles = (n + kNmseTile - 1) / kNmseTile, most = n < ((int64_t)1 << 25) ? 768 : kNmseMaxBlocks;
+    return (int)(tiles < most ? tiles : most);
+}
+hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, uint64_t* words, uint32_t ticket, hipStream_t s) {
+    return dispatch_codec(variance, linear, false, [=](auto V, auto L, auto) {
+        hipLaunchKernelGGL((nmse_kernel<decltype(V)::value, decltype(L)::value>), dim3((unsigned)nmse_blocks(n)), dim3(kNmseThreads), 0, s,
+                           x, n, words, ticket);
         return hipGetLastError();
     });
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nmse_total_kernel, dim3(1), dim3(kTotalThreads), 0, s, partial, (int)nmse_blocks(n), sums, flag,
-                       seq);
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------ layout conversion --

@@ -64,5 +64,17 @@ constexpr int64_t launch_span(int64_t total, int64_t first, int threads) {
 constexpr uint64_t verdict_word(uint64_t ticket, bool admitted) { return admitted ? ticket : ticket - 1; }
 constexpr bool verdict_admits(uint64_t word, uint64_t ticket) { return word >= ticket; }
 
+// How a workgroup hands its two sums to a host that watches: as four words of memory that the host reads, each half a sum and the ticket
+// of the call.  A word is written at once, so that whoever finds the ticket in all four has both sums; nothing has to be ordered,
+// fenced or cleared.  A call's ticket differs from those that the words can hold from calls before it.
+constexpr int kNmseWords = 4;
+constexpr uint64_t nmse_word(uint32_t half, uint32_t ticket) { return (uint64_t)ticket << 32 | half; }
+constexpr bool nmse_ready(const uint64_t (&w)[kNmseWords], uint32_t ticket) {
+    return (uint32_t)(w[0] >> 32) == ticket && (uint32_t)(w[1] >> 32) == ticket && (uint32_t)(w[2] >> 32) == ticket &&
+           (uint32_t)(w[3] >> 32) == ticket;
+}
+// The bits of sum 0 or 1.
+constexpr uint64_t nmse_sum(const uint64_t (&w)[kNmseWords], int i) { return (w[2 * i] & 0xffffffffu) | w[2 * i + 1] << 32; }
+
 }  // namespace fo
 #endif

@@ -101,6 +101,19 @@ def test_nmse_at_the_edges_of_a_tile_and_of_the_grid(state, n):
     assert err == pytest.approx(float(((df(q, s).astype(np.float64) - x64) ** 2).sum()), rel=1e-9, abs=0.0)
 
 
+# tiles of 4096 values, 768 workgroups of one tile each, and the size from which there are 1024 workgroups
+@pytest.mark.parametrize("n", [4095, 4097, 768 * 4096 - 3, 768 * 4096 + 1, (1 << 25) - 1, (1 << 25) + 4097])
+def test_nmse_of_a_single_launch_whose_pairs_the_host_adds_up(n):
+    x = (np.random.default_rng(n).standard_normal(n) * 1e-3).astype(np.float32)
+    err, ref = fo.quantization_nmse("momentum", True, _dev(x))
+    q, s = oracle.quantize_momentum(x, linear=True)
+    x64 = x.astype(np.float64)
+    # as above: n * 2^-53 < 4e-9 for the longest
+    assert ref == pytest.approx(float(np.dot(x64, x64)), rel=4e-9)
+    assert err == pytest.approx(float(((oracle.dequantize_momentum(q, s, linear=True).astype(np.float64) - x64) ** 2).sum()), rel=4e-9, abs=0.0)
+    assert (err, ref) == fo.quantization_nmse("momentum", True, _dev(x))          # added up in a fixed order
+
+
 def test_nmse_calls_of_several_threads_do_not_share_their_sums():
     import threading
     xs = [torch.full((4096 * (i + 1) + i,), float(i + 1), device="cuda") for i in range(6)]

@@ -190,3 +190,30 @@ def test_dealt_out_tiles_cover_every_part_once(tmp_path, waves):
     """)
     wrong, spread = (int(x) for x in out[0].split())
     assert wrong == 0 and (spread > 0) == (waves > 1)
+
+
+def test_a_pair_of_sums_is_read_only_when_all_of_it_is_there(tmp_path):
+    # the four words of a pair written in any order over those of any earlier call, read in between
+    out = _run(tmp_path, """
+    const uint64_t sums[] = {0, ~0ull, 0x3ff0000000000000ull, 0x00000001ffffffffull, 0xfedcba9876543210ull};
+    const uint32_t tickets[] = {0, 1, 4, 6, 0xffffffff};
+    long long wrong = 0, ready = 0;
+    for (uint64_t a : sums)
+        for (uint64_t b : sums)
+            for (uint32_t before : tickets)
+                for (unsigned written = 0; written < 16; ++written) {
+                    uint64_t w[fo::kNmseWords];
+                    for (int k = 0; k < 4; ++k) {
+                        const uint64_t sum = k < 2 ? a : b, old = k < 2 ? b : a;
+                        w[k] = written >> k & 1 ? fo::nmse_word((uint32_t)(k & 1 ? sum >> 32 : sum), 5)
+                                                : fo::nmse_word((uint32_t)(k & 1 ? old >> 32 : old), before);
+                    }
+                    const bool all = fo::nmse_ready(w, 5);
+                    wrong += all != (written == 15);
+                    if (all) wrong += fo::nmse_sum(w, 0) != a || fo::nmse_sum(w, 1) != b;
+                    ready += all;
+                }
+    std::printf("%lld %lld\\n", wrong, ready);
+    """)
+    wrong, ready = (int(x) for x in out[0].split())
+    assert wrong == 0 and ready == 125
