@@ -3,6 +3,8 @@ tensor (the gradient-release call), and an ordinary multi-tensor call whose tabl
 whose descriptors have not changed since - under HIP stream capture: the captured graph is replayed several
 times, with eager work and synchronisations in between, and every replay must leave the same bits as the same
 calls made eagerly."""
+import gc
+
 import pytest
 import torch
 
@@ -10,6 +12,14 @@ import paper_2602_23349_amd as fo
 import workloads as W
 
 pytestmark = pytest.mark.gpu
+
+# An exception that a test has caught keeps the test's frame, and with it the graph that the test captured, alive in a reference cycle
+# until the garbage collector runs.  If that happened within the next test's capture, the destructor of that graph would call into the
+# runtime there, fail and end the process.
+@pytest.fixture(autouse=True)
+def nothing_left_to_collect():
+    gc.collect()
+
 
 B1, B2, EPS = 0.9, 0.999, 1e-8
 ARRAYS = ("param", "rho", "m_q", "m_scale", "v_q", "v_scale")
