@@ -911,7 +911,7 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, 
 }
 
 // First element, in its tensor, of what this wavefront handles of a workgroup of WAVES with tile `tile`, where the tiles of whole
-// groups are dealt out (wave_part).  Wave-uniform.
+// groups are dealt out (wave_part).  Wave-uniform.  (Copies: bytes of a segment.)
 template <int WAVES, int WAVE_ELEMS>
 __device__ __forceinline__ int64_t wave_start(int64_t tile, int64_t numel) {
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -2068,16 +2068,23 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 // are 16-byte aligned on both sides), the ragged end byte by byte, and - when packing - zero-fills the padding up to
 // pad_bytes.  Bound: HBM.
 //
-// One access per lane and 1024 lanes: pieces of 16 KB that are read and written at once and make room for the next.
-// More per lane is slower, less so in fewer lanes (pack of GPT-2's 638 MB / of a Llama layer / of two layers with
-// embedding and head, in us: 512 lanes x 16 accesses 225 / 387 / 2749; 1024 x 8 217 / 378 / 2659; 1024 x 1 201 / 355 /
-// 2520, 6.1 TB/s).  Pieces are found as the step kernels find their tiles, through a coarse table and the segments
-// themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
+// One access per lane and 1024 lanes: pieces of 16 KB that are read and written at once and make room for the next, the
+// pieces of large segments dealt out among the wavefronts of a group of workgroups (wave_part; a part is 1 KB).  In us, a pack and an unpack of
+// ResNet-50 / GPT-2 / a Llama layer (SGD) / two layers with embedding: 89.2 / 407 / 555 / 3209 with every piece in one piece, 89.0 / 383 / 522 /
+// 2917 (6.75 TB/s) dealt out; as pieces of 8 KB and 512 lanes 88.4 / 382 / 525 / 2925, of 4 KB 88.9 / 382 / 524 / 2938.  More accesses per lane are
+// slower (in one piece, pack of GPT-2 512 lanes x 16 accesses 225, 1024 x 8 217, 1024 x 1 201).  Pieces are found as the step kernels find their
+// tiles, through a coarse table and the segments themselves: a table with an entry per piece would be 20 MB for the 41 GB of Llama-3.1-8B.
 //
 // header: the blob's header and table when packing; the workgroup behind the last piece writes them to header_dst.
 // verdict: when unpacking, what check_header_kernel has found; nothing is written unless it admits this copy.
 constexpr int kCopyThreads = kCopyPiece / 16;
 static_assert(kHeaderStepAt % 16 == 0, "the step is the low half of one 16-byte access");
+// The lane's offset in the segment of piece b.
+__device__ __forceinline__ int64_t copy_offset(const CopySegment& sg, uint32_t b) {
+    const int64_t piece = b - sg.first_piece;
+    if (sg.n_pieces < kTileGroup) return piece * kCopyPiece + (int64_t)threadIdx.x * 16;      // (nothing to deal out, sooner found)
+    return wave_start<kCopyThreads / 64, 64 * 16>(piece, sg.bytes) + (int64_t)(threadIdx.x & 63) * 16;
+}
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     const uint32_t b = blockIdx.x + a.piece_offset;
     const bool go = !a.verdict || verdict_admits(*a.verdict, a.ticket);      // (looked up beside the piece)
@@ -2098,7 +2105,7 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.segs[i].first_piece; });
     const CopySegment sg = a.segs[t];
     if (!go) return;
-    const int64_t o = (int64_t)(b - sg.first_piece) * kCopyPiece + (int64_t)threadIdx.x * 16;
+    const int64_t o = copy_offset(sg, b);
     if (o + 16 <= sg.bytes) {
         const uint4 v = ld128(sg.src + o);
         st128(sg.dst + o, v.x, v.y, v.z, v.w);

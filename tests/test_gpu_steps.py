@@ -404,6 +404,8 @@ def test_checkpoint_pack_unpack_small_lists():
     # a copy of more pieces than the coarse table has entries, with short sections between long ones
     ("adamw", [65535, 65536, 65537, 131071, 131072, 131073, 131088, 53_000_000]),
     ("sgd", [3]),
+    # sections around 32 and 64 pieces of 16 KB, which are dealt out in groups
+    ("sgd", [262143, 262144, 262145, 262152, 507904, 524287, 524288, 524289, 540672, 540673, 1048592]),
 ])
 def test_checkpoint_at_the_edges_of_a_piece(kind, sizes):
     rng = np.random.default_rng(len(sizes))
