@@ -840,14 +840,25 @@ int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, boo
     a.coarse = static_cast<const uint32_t*>(plan->d_index);
     a.coarse_shift = plan->coarse_shift;
     a.n_pieces = (uint32_t)plan->n_chunks;
+    int64_t* found = pack ? nullptr : reinterpret_cast<int64_t*>(check->host);
     if (pack) {
         a.header = static_cast<const uint4*>(plan->d_header);
         a.header_n16 = (uint32_t)(header_size(n) / 16);
         a.header_dst = reinterpret_cast<uint4*>(blob);
         a.step = step;
+    } else if (a.n_pieces > 0 && fo::checked_copy(total_bytes, header_size(n))) {
+        fo::CheckedCopyArgs c(a);
+        c.header = static_cast<const uint4*>(plan->d_header);
+        c.header_n16 = (uint32_t)(header_size(n) / 16);
+        c.ticket = check->seq;
+        c.found = reinterpret_cast<const uint4*>(blob);
+        c.out = found;
+        c.flag = check->flag();
+        FO_HIP(fo::launch_checked_copy(c, stream));
+        return FLASHOPTIM_OK;
     } else {
-        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), check->verdict,
-                                       reinterpret_cast<int64_t*>(check->host), check->flag(), check->seq, stream));
+        FO_HIP(fo::launch_check_header(plan->d_header, blob, (size_t)header_size(n), check->verdict, found,
+                                       check->flag(), check->seq, stream));
         a.verdict = check->verdict;
         a.ticket = check->seq;
     }

@@ -222,6 +222,14 @@ struct CopyArgs {
     const uint64_t* verdict;    // unpacking: the word that says whether the blob belongs to this list (nullptr: no such
     uint64_t ticket;            // condition), and the ticket of this call (verdict_admits)
 };
+// Unpacking a blob with a short table: every workgroup compares `header`, what the list expects, with `found`, the blob's own.  The first
+// tells the host: out[0] becomes 1 or 0 and out[1] the blob's step, then *flag (all pinned) the ticket's low half.
+struct CheckedCopyArgs : CopyArgs {
+    explicit CheckedCopyArgs(const CopyArgs& a) : CopyArgs(a) {}
+    const uint4* found;
+    int64_t* out;
+    uint32_t* flag;
+};
 
 hipError_t launch_step(int kind, bool direct, bool split, bool quant, StepShape shape, bool exact, const StepArgs& a,
                        int64_t n_blocks, hipStream_t s);
@@ -248,6 +256,14 @@ int nmse_blocks(int64_t n);
 // words: kNmseWords words of pinned memory for each of the nmse_blocks(n) workgroups, its sums with this call's ticket (nmse_word)
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, uint64_t* words, uint32_t ticket, hipStream_t s);
 hipError_t launch_copy(CopyArgs a, hipStream_t s);
+// The blobs whose unpacking takes that way: their header and table are an access per lane, and the launch that it saves is worth what the
+// barrier costs.  Smaller ones are bound by the wait for the verdict, which a kernel of its own reaches sooner.  In us, a kernel ahead of the
+// copy -> checked by every workgroup, a pack and an unpack: 5 MB 15.8 -> 16.8, 15 MB 20.4 -> 20.7, 33 MB 26.6 -> 24.3, 103 MB 68.5 -> 64.1, 205 MB
+// 133.9 -> 130.0; an unpack: ResNet-50's 131 MB 46.3 -> 45.1, 512 MB 163.0 -> 163.3, GPT-2's 638 MB 193.6 -> 195.9, 1.5 GB 456 -> 462.
+constexpr bool checked_copy(int64_t blob_bytes, int64_t header_bytes) {
+    return blob_bytes >= (int64_t)24 << 20 && blob_bytes <= (int64_t)256 << 20 && header_bytes <= kCopyPiece;
+}
+hipError_t launch_checked_copy(CheckedCopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s);
 // Compares the header and table at `blob` with the expected ones, the step apart: *verdict (device) becomes verdict_word of the

@@ -2079,11 +2079,33 @@ hipError_t launch_selftest(unsigned long long* counters, int section, const Step
 // verdict: when unpacking, what check_header_kernel has found; nothing is written unless it admits this copy.
 constexpr int kCopyThreads = kCopyPiece / 16;
 static_assert(kHeaderStepAt % 16 == 0, "the step is the low half of one 16-byte access");
+// Whether 16 bytes of a blob's header or table, number i, are not what the list expects.  The step is the caller's.
+__device__ __forceinline__ bool header_differs(uint4 x, uint4 y, uint32_t i) {
+    const uint32_t d = (x.z ^ y.z) | (x.w ^ y.w);
+    return (i == kHeaderStepAt / 16 ? d : d | (x.x ^ y.x) | (x.y ^ y.y)) != 0;
+}
+// What unpacking found, for the host that watches the flag.
+__device__ __forceinline__ void report_header(const uint4* blob, bool ok, int64_t* out, uint32_t* flag, uint64_t ticket) {
+    const uint4 step = blob[kHeaderStepAt / 16];
+    out[0] = ok;
+    out[1] = (int64_t)((uint64_t)step.y << 32 | step.x);
+    __hip_atomic_store(flag, (uint32_t)ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
+}
+// The segment that holds piece b: the last one that begins there or before, among those of its coarse entry.
+__device__ __forceinline__ CopySegment locate_piece(const CopyArgs& a, uint32_t b) {
+    const uint32_t* entry = a.coarse + (b >> a.coarse_shift);
+    uint32_t t = entry[0];
+    if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.segs[i].first_piece; });
+    return a.segs[t];
+}
 // The lane's offset in the segment of piece b.
 __device__ __forceinline__ int64_t copy_offset(const CopySegment& sg, uint32_t b) {
     const int64_t piece = b - sg.first_piece;
     if (sg.n_pieces < kTileGroup) return piece * kCopyPiece + (int64_t)threadIdx.x * 16;      // (nothing to deal out, sooner found)
     return wave_start<kCopyThreads / 64, 64 * 16>(piece, sg.bytes) + (int64_t)(threadIdx.x & 63) * 16;
+}
+__device__ __forceinline__ void copy_end(const CopySegment& sg, int64_t o) {
+    for (int k = 0; k < 16 && o + k < sg.pad_bytes; ++k) sg.dst[o + k] = (o + k < sg.bytes) ? sg.src[o + k] : (uint8_t)0;
 }
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
     const uint32_t b = blockIdx.x + a.piece_offset;
@@ -2099,32 +2121,57 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CopyArgs a) {
         }
         return;
     }
-    // the last segment that begins at piece b or before, among those of this coarse entry
-    const uint32_t* entry = a.coarse + (b >> a.coarse_shift);
-    uint32_t t = entry[0];
-    if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.segs[i].first_piece; });
-    const CopySegment sg = a.segs[t];
+    const CopySegment sg = locate_piece(a, b);
     if (!go) return;
     const int64_t o = copy_offset(sg, b);
     if (o + 16 <= sg.bytes) {
         const uint4 v = ld128(sg.src + o);
         st128(sg.dst + o, v.x, v.y, v.z, v.w);
     } else {
-        for (int k = 0; k < 16 && o + k < sg.pad_bytes; ++k) sg.dst[o + k] = (o + k < sg.bytes) ? sg.src[o + k] : (uint8_t)0;
+        copy_end(sg, o);
     }
+}
+// The same when every workgroup checks the header for itself: its two loads stand beside that of the piece, and nothing is stored
+// before all lanes have compared.  The workgroup that reports, for which the host waits, does so before it looks for its piece.
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(CheckedCopyArgs a) {
+    const uint32_t b = blockIdx.x + a.piece_offset, i = threadIdx.x;
+    bool differs = false;
+    if (i < a.header_n16) differs = header_differs(a.header[i], a.found[i], i);
+    CopySegment sg;
+    int64_t o = 0;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    const auto load = [&] {
+        sg = locate_piece(a, b);
+        o = copy_offset(sg, b);
+        if (o + 16 <= sg.bytes) v = ld128(sg.src + o);
+    };
+    if (b != 0) load();
+    const bool ok = __syncthreads_or(differs) == 0;
+    if (b == 0) {
+        if (i == 0) report_header(a.found, ok, a.out, a.flag, a.ticket);
+        load();
+    }
+    if (!ok) return;
+    if (o + 16 <= sg.bytes) st128(sg.dst + o, v.x, v.y, v.z, v.w);
+    else copy_end(sg, o);
 }
 
 // Consecutive launches of as many pieces as one may have: 2^22 - 1, or 64 GiB.
-hipError_t launch_copy(CopyArgs a, hipStream_t s) {
-    const int64_t total = (int64_t)a.n_pieces + (a.header ? 1 : 0);
+template <typename ARGS>
+static hipError_t launch_pieces(ARGS a, int64_t total, hipStream_t s) {
     for (int64_t first = 0, n; first < total; first += n) {
         n = launch_span(total, first, kCopyThreads);
         a.piece_offset = (uint32_t)first;
-        hipLaunchKernelGGL(copy_kernel, dim3((unsigned)n), dim3(kCopyThreads), 0, s, a);
+        copy_kernel<<<dim3((unsigned)n), dim3(kCopyThreads), 0, s>>>(a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+hipError_t launch_copy(CopyArgs a, hipStream_t s) { return launch_pieces(a, (int64_t)a.n_pieces + (a.header ? 1 : 0), s); }
+hipError_t launch_checked_copy(CheckedCopyArgs a, hipStream_t s) {
+    if (a.n_pieces == 0 || a.header_n16 > (uint32_t)kCopyThreads) return hipErrorInvalidValue;     // (nobody would report, or compare)
+    return launch_pieces(a, a.n_pieces, s);
 }
 
 // Small transfers between pinned host memory and device memory by a kernel instead of a copy command (16-byte
@@ -2168,20 +2215,13 @@ __global__ __launch_bounds__(kCheckThreads) void check_header_kernel(const uint4
     __shared__ uint32_t differs;
     if (threadIdx.x == 0) differs = 0;
     __syncthreads();
-    uint32_t d = 0;
-    for (uint32_t i = threadIdx.x; i < n16; i += kCheckThreads) {
-        const uint4 x = expected[i], y = blob[i];
-        d |= (x.z ^ y.z) | (x.w ^ y.w);
-        if (i != kHeaderStepAt / 16) d |= (x.x ^ y.x) | (x.y ^ y.y);
-    }
+    bool d = false;
+    for (uint32_t i = threadIdx.x; i < n16; i += kCheckThreads) d |= header_differs(expected[i], blob[i], i);
     if (d) atomicOr(&differs, 1u);
     __syncthreads();
     if (threadIdx.x != 0) return;
-    const uint4 step = blob[kHeaderStepAt / 16];
     *verdict = verdict_word(ticket, differs == 0);
-    out[0] = differs == 0;
-    out[1] = (int64_t)((uint64_t)step.y << 32 | step.x);
-    __hip_atomic_store(flag, (uint32_t)ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);     // behind this lane's two stores
+    report_header(blob, differs == 0, out, flag, ticket);
 }
 hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint64_t* verdict, int64_t* out,
                                uint32_t* flag, uint64_t ticket, hipStream_t s) {

@@ -326,6 +326,50 @@ def test_unpacking_checks_every_word_of_the_table(n_tensors):
     assert all((b.rho == i * 97 % 50 + 1).all() for i, b in enumerate(bufs[::97]))
 
 
+# Blobs of 24 to 256 MB whose table is an access per lane or less are checked by every workgroup of the copy: both sides of these limits, and
+# every word of the longest and of a short table.
+@pytest.mark.parametrize("n_tensors,n", [(1020, 26_000), (1021, 26_000), (3, 9_000_000), (3, 1_900_000), (3, 2_200_000)])
+def test_unpacking_checks_every_word_within_the_copy(n_tensors, n):
+    sizes = [n + i % 7 for i in range(n_tensors)]
+    off = np.cumsum([0] + [(k + 255) // 256 * 256 for k in sizes])
+    arena = fo.ParamBuffers(int(off[-1]), "sgd", with_grad=False)
+    bufs = fo.TensorList([arena.shard(int(o), k) for o, k in zip(off, sizes)])
+    blob = torch.zeros(fo.checkpoint_size("sgd", sizes), dtype=torch.uint8, device="cuda")
+    arena.rho.fill_(3)
+    fo.checkpoint_pack("sgd", bufs, 5, blob)
+    arena.rho.zero_()
+    table = 64 + 16 * n_tensors
+    for at in sorted({0, 4, 8, 12, 24, 32, 40, 48, 56, 63, 64, table // 2 // 4 * 4, table - 16, table - 5, table - 1}):
+        blob[at] ^= 0x10
+        with pytest.raises(fo.FlashOptimError) as err:
+            fo.checkpoint_unpack("sgd", blob, bufs)
+        assert err.value.status == -5, at
+        blob[at] ^= 0x10
+    assert not arena.rho.any()
+    for step in (0, 1 << 40, 2**63 - 1):                # the step is the caller's
+        blob[16:24] = torch.from_numpy(np.frombuffer(np.int64(step).tobytes(), np.uint8).copy()).cuda()
+        assert fo.checkpoint_unpack("sgd", blob, bufs) == step
+    assert all((arena.rho[int(o):int(o) + k] == 3).all() for o, k in zip(off, sizes))
+
+
+@pytest.mark.parametrize("n", [65_000_000, 67_000_000])      # blobs of 264 and 272 MB: checked in the copy, and ahead of it
+def test_unpacking_on_both_sides_of_the_limit_of_its_blob(n):
+    b = fo.ParamBuffers(n, "lion", with_grad=False)
+    for x, lo, hi in ((b.rho, -127, 128), (b.m_q, -127, 128), (b.param.view(torch.int16), -32768, 32768), (b.m_scale.view(torch.int16), 0, 31744)):
+        x.random_(lo, hi)
+    arrays = lambda t: [t.param.view(torch.int16), t.rho, t.m_q, t.m_scale.view(torch.int16)]
+    blob = torch.zeros(fo.checkpoint_size("lion", [n]), dtype=torch.uint8, device="cuda")
+    fo.checkpoint_pack("lion", [b], 12, blob)
+    f = fo.ParamBuffers(n, "lion", with_grad=False)
+    blob[24] ^= 1
+    with pytest.raises(fo.FlashOptimError):
+        fo.checkpoint_unpack("lion", blob, [f])
+    assert not any(x.any() for x in arrays(f))
+    blob[24] ^= 1
+    assert fo.checkpoint_unpack("lion", blob, [f]) == 12
+    assert all(torch.equal(x, y) for x, y in zip(arrays(f), arrays(b)))
+
+
 # Lists whose coarse table spans several tiles and tensors with one entry: the tensor of a tile is searched for.
 @pytest.mark.parametrize("order", ["small first", "large first", "large among small"])
 def test_tiles_of_long_lists(order):
