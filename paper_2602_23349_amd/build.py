@@ -13,10 +13,12 @@ HEADERS = [os.path.join(CSRC, "flashoptim_device.h"), os.path.join(CSRC, "flasho
            os.path.join(ROOT, "include", "flashoptim.h")]
 
 # Exact arithmetic is part of the contract: no FMA contraction, IEEE division and square root,
-# subnormals kept.  Packed FP32 instructions are disabled.
+# subnormals kept.  Packed FP32 instructions are disabled.  The command processor loads a kernel's first arguments into
+# registers before its wavefronts start (up to 14 words), instead of every wavefront by a load that it waits for.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt", "-fno-gpu-flush-denormals-to-zero",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
 

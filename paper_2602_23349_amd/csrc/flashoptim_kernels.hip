@@ -62,6 +62,14 @@
 
 namespace fo {
 
+// A launch.  (Through hipLaunchKernel itself: with <<<>>> the host takes 0.15-0.2 us more of the 3 that a launch costs it.)
+template <typename... P>
+static hipError_t launch(void (*kernel)(P...), unsigned blocks, unsigned threads, unsigned lds, hipStream_t s,
+                         const std::decay_t<P>&... p) {
+    void* args[] = {const_cast<void*>(static_cast<const void*>(&p))...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(blocks), dim3(threads), args, lds, s);
+}
+
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
 
@@ -892,22 +900,94 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
 }
 
 // ------------------------------------------------------------ step kernels --
-// The tensor and the tile within it that workgroup blockIdx.x handles.  Every load is wave-uniform
-// (scalar).
-// *index (multi-tensor launches): the tensor's index in the table.
+// The tensor that holds workgroup b of a list.  Every load is wave-uniform (scalar).
+__device__ __forceinline__ uint32_t locate_tensor(const TensorDev* tensors, const uint32_t* coarse, uint32_t shift, uint32_t b) {
+    const uint32_t* entry = coarse + (b >> shift);
+    const uint32_t t = entry[0];
+    return shift ? entry_of(b, t, entry[1], [&](uint32_t i) { return tensors[i].first_tile; }) : t;
+}
+// The tensor and the tile within it that workgroup blockIdx.x handles.
 template <bool DIRECT>
-__device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T, uint32_t* index = nullptr) {
+__device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T) {
     const uint32_t b = blockIdx.x + a.block_offset;
     if (DIRECT) {
         T = a.single;
         return (int64_t)b;
     }
-    const uint32_t* entry = a.coarse + (b >> a.coarse_shift);
-    uint32_t t = entry[0];
-    if (a.coarse_shift) t = entry_of(b, t, entry[1], [&](uint32_t i) { return a.tensors[i].first_tile; });
-    T = a.tensors[t];
-    if (index) *index = t;
+    T = a.tensors[locate_tensor(a.tensors, a.coarse, a.coarse_shift, b)];
     return (int64_t)(b - T.first_tile);
+}
+
+// What a step's kernels take.  The first arguments are those that its streaming loads wait for, fourteen words that the command
+// processor has in registers before a wavefront starts; the others come by loads of their own, which the kernels wait for behind the
+// streaming loads.  Only what a kind reads is passed (a byte costs the host 2.6 ns).  With one struct of 200 bytes for all, launched by
+// <<<>>>, -> without -> with preloaded arguments, us a call: AdamW over 2^20 elements 4.72 -> 4.71 -> 4.56, 2^21 6.30 -> 6.28 -> 6.12, 25 odd sizes
+// 4.33 -> 4.10 -> 4.05; SGD 2^21 4.26 -> 4.23 -> 4.05, 2^22 6.21 -> 6.34 -> 5.95, ten tensors of 5 M 9.37 -> 9.29 -> 9.06, ResNet-50 40.9 -> 40.8 -> 40.5.
+template <bool DIRECT, bool HAS_V>
+struct TensorArgs {};       // (of a list: everything is in the table)
+template <>
+struct TensorArgs<true, false> {
+    uint16_t* m_scale;
+    float lr, wd;
+    explicit TensorArgs(const TensorDev& d) : m_scale(d.m_scale), lr(d.lr), wd(d.wd) {}
+};
+template <>
+struct TensorArgs<true, true> : TensorArgs<true, false> {
+    uint16_t* v_scale;
+    explicit TensorArgs(const TensorDev& d) : TensorArgs<true, false>(d), v_scale(d.v_scale) {}
+};
+template <bool HAS_V>
+struct TensorArgs<false, HAS_V> {
+    explicit TensorArgs(const TensorDev&) {}
+};
+template <int KIND>
+struct KindConsts;
+template <>
+struct KindConsts<0> {
+    const float* sqrt_min_word;
+    float beta1, beta2, omb1, omb2, rbc1, rbc2, eps, k255_hi, k255_lo, v_max, m_max;
+    explicit KindConsts(const StepArgs& a)
+        : sqrt_min_word(a.sqrt_min_word), beta1(a.c.beta1), beta2(a.c.beta2), omb1(a.c.omb1), omb2(a.c.omb2), rbc1(a.c.rbc1),
+          rbc2(a.c.rbc2), eps(a.c.eps), k255_hi(a.c.k255_hi), k255_lo(a.c.k255_lo), v_max(a.c.v_max), m_max(a.c.m_max) {}
+    // sqrt_min is one more scalar load.  The word counts as constant: the check that writes it may run beside a step on another
+    // stream, but only once per device, and the results are the same with either value.
+    __device__ __forceinline__ StepConsts get() const {
+        return {beta1, beta2, omb1, omb2, rbc1, rbc2, eps, k255_hi, k255_lo, v_max, m_max,
+                *(const __attribute__((address_space(4))) float*)sqrt_min_word};
+    }
+};
+template <>
+struct KindConsts<1> {
+    float momentum;
+    explicit KindConsts(const StepArgs& a) : momentum(a.c.beta1) {}
+    __device__ __forceinline__ StepConsts get() const { return {momentum}; }
+};
+template <>
+struct KindConsts<2> {
+    float beta1, beta2, omb1, omb2;
+    explicit KindConsts(const StepArgs& a) : beta1(a.c.beta1), beta2(a.c.beta2), omb1(a.c.omb1), omb2(a.c.omb2) {}
+    __device__ __forceinline__ StepConsts get() const { return {beta1, beta2, omb1, omb2}; }
+};
+// The kernel is overloaded by the type of its last argument, one overload for each way of doing the same step: AdamW with and
+// without a bias correction of the momentum that is not 1 (an instruction per element less is 0.3-0.9 % of a step's time:
+// GPT-2 253.0 -> 251.9 us, Llama layer 445.6 -> 441.9), and either kind of stores (a branch in the kernel instead costs plain
+// FP32 steps over a few million elements 1 %).
+template <int KIND, bool DIRECT, bool M_HAT, bool THROUGH>
+struct VariantArgs : TensorArgs<DIRECT, KIND == 0>, KindConsts<KIND> {
+    explicit VariantArgs(const StepArgs& a) : TensorArgs<DIRECT, KIND == 0>(a.single), KindConsts<KIND>(a) {}
+};
+// The first arguments.  Of one tensor, the arrays that the variant has, the element count (low half, high half) and the first
+// workgroup's tile; of a list, p0 the table, p1 the coarse table, u0 its shift, u1 and u3 what makes the rate (StepArgs).
+struct HotArgs {
+    const void *p0, *p1, *p2, *p3, *p4;
+    uint32_t u0, u1, block_offset, u3;
+};
+template <bool DIRECT, bool SPLIT, bool QUANT>
+static HotArgs hot_args(const StepArgs& a) {
+    const TensorDev& d = a.single;
+    if (!DIRECT) return {a.tensors, a.coarse, nullptr, nullptr, nullptr, a.coarse_shift, a.table_lr_mask, a.block_offset, a.shared_lr_bits};
+    return {SPLIT ? d.param : (const void*)d.theta32, SPLIT ? d.rho : nullptr, d.grad, QUANT ? d.m_q : (const void*)d.m32,
+            QUANT ? d.v_q : (const void*)d.v32, (uint32_t)d.numel, (uint32_t)((uint64_t)d.numel >> 32), a.block_offset, 0};
 }
 
 // First element, in its tensor, of what this wavefront handles of a workgroup of WAVES with tile `tile`, where the tiles of whole
@@ -924,7 +1004,7 @@ __device__ __forceinline__ int64_t wave_start(int64_t tile, int64_t numel) {
 // (Variants in which a workgroup loads two or four such tiles up front and then updates them in
 // turn - fewer look-ups, more bytes in flight per workgroup - ran at the same rate.)
 template <int KIND, int VEC, int THREADS, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool THROUGH, bool FULL>
-__device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a, StepTables& tab,
+__device__ __forceinline__ void step_tile(const TensorDev& T, const KindConsts<KIND>& consts, StepTables& tab,
                                           const TableEntries& entries, int64_t tile0, uint32_t lane_el, int rem, int tid) {
     constexpr bool HAS_V = (KIND == 0);
     const bool leader = (tid & (kGroup / VEC - 1)) == 0;
@@ -938,10 +1018,7 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a,
         store_table_entries<THREADS, HAS_V, SPLIT, QUANT>(tab, entries, tid);
         __syncthreads();
     }
-    StepConsts c = a.c;
-    // One scalar load, behind the streaming loads.  The word counts as constant: the check that writes it may run beside a step on
-    // another stream, but only once per device, and the results are the same with either value.
-    if (KIND == 0) c.sqrt_min = *(const __attribute__((address_space(4))) float*)a.sqrt_min_word;
+    const StepConsts c = consts.get();       // (behind the streaming loads)
     // All lanes of a group run the update together (a lane with cnt == 0 may share its group
     // with lanes that hold elements); lanes past the end compute on zeros and store nothing.
     update_lane<KIND, VEC, SPLIT, QUANT, EXACT, M_HAT, FULL>(x, y, tab, c, T.lr, T.wd, cnt);
@@ -954,22 +1031,42 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const StepArgs& a,
 // iteration's stores).  Order of issue: decode-table loads, the (tensor, tile) look-up, the
 // streaming loads; then the tables go to LDS.
 template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT, bool M_HAT, bool THROUGH>
-__device__ __forceinline__ void step_workgroup(const StepArgs& a) {
+__device__ __forceinline__ void step_workgroup(const HotArgs& h, const VariantArgs<KIND, DIRECT, M_HAT, THROUGH>& a) {
     constexpr int kTile = THREADS * VEC;       // elements per workgroup
     __shared__ StepTables tab;
     const int tid = (int)threadIdx.x;
     TableEntries entries;
     if constexpr (SPLIT || QUANT) load_table_entries<THREADS, KIND == 0, SPLIT, QUANT>(entries, tid);
+    const uint32_t b = blockIdx.x + h.block_offset;
     TensorDev T;
-    uint32_t index = 0;
-    const int64_t chunk = locate_tile<DIRECT>(a, T, &index);
+    TensorDev* entry = nullptr;
+    if constexpr (DIRECT) {
+        T = TensorDev{};
+        T.param = T.theta32 = (float*)h.p0;
+        T.rho = (int8_t*)h.p1;
+        T.grad = h.p2;
+        T.m_q = (int8_t*)h.p3;
+        T.m32 = (float*)h.p3;
+        T.v_q = (uint8_t*)h.p4;
+        T.v32 = (float*)h.p4;
+        T.numel = (int64_t)((uint64_t)h.u1 << 32 | h.u0);
+        T.m_scale = a.m_scale;
+        if constexpr (KIND == 0) T.v_scale = a.v_scale;
+        T.lr = a.lr;
+        T.wd = a.wd;
+    } else {
+        TensorDev* tensors = (TensorDev*)h.p0;
+        entry = tensors + locate_tensor(tensors, (const uint32_t*)h.p1, h.u0, b);
+        T = *entry;
+    }
+    const int64_t chunk = DIRECT ? (int64_t)b : (int64_t)(b - T.first_tile);
     // first element of the tile, or where tiles are dealt out of this wavefront's part of them (wave-uniform)
     constexpr bool DEALT = step_dealt(KIND, SPLIT, QUANT, THROUGH);
     const int64_t tile0 = DEALT ? wave_start<THREADS / 64, 64 * VEC>(chunk, T.numel) : chunk * (int64_t)kTile;
     const uint32_t lane_el = (uint32_t)(DEALT ? tid & 63 : tid) * VEC;
     const int64_t rem = T.numel - chunk * (int64_t)kTile;      // elements from the tile's first one to the tensor's end
     const float table_lr = T.lr;
-    if (!DIRECT) T.lr = u2f((f2u(table_lr) & a.table_lr_mask) | a.shared_lr_bits);      // (integers: stays on the scalar unit)
+    if (!DIRECT) T.lr = u2f((f2u(table_lr) & h.u1) | h.u3);    // (integers: stays on the scalar unit)
     if (rem >= kTile) {
         step_tile<KIND, VEC, THREADS, SPLIT, QUANT, EXACT, M_HAT, THROUGH, true>(T, a, tab, entries, tile0, lane_el, kTile, tid);
     } else {
@@ -978,21 +1075,16 @@ __device__ __forceinline__ void step_workgroup(const StepArgs& a) {
                                                                                   (int)(T.numel - tile0), tid);
     }
     // (only with a mask of 0: no workgroup of this launch uses what the others read of the entry's rate)
-    if (!DIRECT && chunk == 0 && f2u(T.lr) != f2u(table_lr) && tid == 0) a.tensors[index].lr = T.lr;
+    if (!DIRECT && chunk == 0 && f2u(T.lr) != f2u(table_lr) && tid == 0) entry->lr = T.lr;
 }
 
-// The kernel is overloaded by the type of its arguments, one overload for each way of doing the same step: AdamW with and
-// without a bias correction of the momentum that is not 1 (an instruction per element less is 0.3-0.9 % of a step's time:
-// GPT-2 253.0 -> 251.9 us, Llama layer 445.6 -> 441.9), and either kind of stores (a branch in the kernel instead costs plain
-// FP32 steps over a few million elements 1 %).
-template <bool M_HAT, bool THROUGH>
-struct VariantArgs : StepArgs {
-    explicit VariantArgs(const StepArgs& a) : StepArgs(a) {}
-};
-#define FO_STEP_KERNEL(M_HAT, THROUGH)                                                                     \
-    template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT>             \
-    __global__ __launch_bounds__(THREADS) void step_kernel(VariantArgs<M_HAT, THROUGH> a) {                \
-        step_workgroup<KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT, M_HAT, THROUGH>(a);                \
+#define FO_STEP_KERNEL(M_HAT, THROUGH)                                                                                      \
+    template <int KIND, int VEC, int THREADS, bool DIRECT, bool SPLIT, bool QUANT, bool EXACT>                              \
+    __global__ __launch_bounds__(THREADS) void step_kernel(const void* p0, const void* p1, const void* p2, const void* p3,  \
+                                                           const void* p4, uint32_t u0, uint32_t u1, uint32_t block_offset, \
+                                                           uint32_t u3, VariantArgs<KIND, DIRECT, M_HAT, THROUGH> a) {      \
+        const HotArgs h = {p0, p1, p2, p3, p4, u0, u1, block_offset, u3};                                                   \
+        step_workgroup<KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT, M_HAT, THROUGH>(h, a);                              \
     }
 FO_STEP_KERNEL(true, true)
 FO_STEP_KERNEL(true, false)
@@ -1000,16 +1092,21 @@ FO_STEP_KERNEL(false, true)
 FO_STEP_KERNEL(false, false)
 #undef FO_STEP_KERNEL
 
-template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT, bool THROUGH>
-static hipError_t launch_through(bool direct, const StepArgs& args, int64_t n_blocks, hipStream_t s) {
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT, bool THROUGH, bool DIRECT>
+static hipError_t launch_direct(const StepArgs& a, unsigned n_blocks, unsigned lds, hipStream_t s) {
     constexpr int VEC = step_vec(SPLIT, QUANT, SHAPE), THREADS = step_threads(SPLIT, QUANT, SHAPE);
-    const dim3 grid((unsigned)n_blocks), block(THREADS);
-    const int resident = step_resident(KIND, SPLIT, QUANT, SHAPE, direct, n_blocks * (THREADS * VEC), THROUGH);
+    typedef VariantArgs<KIND, DIRECT, M_HAT, THROUGH> args_t;
+    void (*kernel)(const void*, const void*, const void*, const void*, const void*, uint32_t, uint32_t, uint32_t, uint32_t, args_t) =
+        step_kernel<KIND, VEC, THREADS, DIRECT, SPLIT, QUANT, EXACT>;
+    const HotArgs h = hot_args<DIRECT, SPLIT, QUANT>(a);
+    return launch(kernel, n_blocks, THREADS, lds, s, h.p0, h.p1, h.p2, h.p3, h.p4, h.u0, h.u1, h.block_offset, h.u3, args_t(a));
+}
+template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT, bool THROUGH>
+static hipError_t launch_through(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
+    const int resident = step_resident(KIND, SPLIT, QUANT, SHAPE, direct, n_blocks * chunk_elems(SPLIT, QUANT, SHAPE), THROUGH);
     const unsigned lds = lds_to_hold(resident, SPLIT || QUANT ? sizeof(StepTables) : 0);
-    const VariantArgs<M_HAT, THROUGH> a(args);
-    if (direct) step_kernel<KIND, VEC, THREADS, true, SPLIT, QUANT, EXACT><<<grid, block, lds, s>>>(a);
-    else step_kernel<KIND, VEC, THREADS, false, SPLIT, QUANT, EXACT><<<grid, block, lds, s>>>(a);
-    return hipGetLastError();
+    return direct ? launch_direct<KIND, SPLIT, QUANT, EXACT, SHAPE, M_HAT, THROUGH, true>(a, (unsigned)n_blocks, lds, s)
+                  : launch_direct<KIND, SPLIT, QUANT, EXACT, SHAPE, M_HAT, THROUGH, false>(a, (unsigned)n_blocks, lds, s);
 }
 template <int KIND, bool SPLIT, bool QUANT, bool EXACT, StepShape SHAPE, bool M_HAT>
 static hipError_t launch_m_hat(bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
@@ -1703,25 +1800,24 @@ __global__ __launch_bounds__(kNmseThreads) void nmse_kernel(const float* x, int6
     }
 }
 
-// launch(blocks, first, n) for every launch that the tiles of n elements take, `tile` of them to a workgroup of `threads` lanes:
+// launch_part(blocks, first, n) for every launch that the tiles of n elements take, `tile` of them to a workgroup of `threads` lanes:
 // the n elements from `first` on.  (One launch holds fewer than 2^32 work-items.)
 template <typename F>
-static hipError_t for_each_launch(int64_t n, int tile, int threads, F launch) {
+static hipError_t for_each_launch(int64_t n, int tile, int threads, F launch_part) {
     const int64_t tiles = (n + tile - 1) / tile;
     for (int64_t t = 0, k; t < tiles; t += k) {
         k = launch_span(tiles, t, threads);
         const int64_t first = t * tile, left = n - first;
-        launch(dim3((unsigned)k), first, left < k * tile ? left : k * tile);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_part((unsigned)k, first, left < k * tile ? left : k * tile);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 template <int N, typename RHO>
 static hipError_t launch_split_n(const float* theta, uint16_t* param, RHO* rho, int64_t n, hipStream_t s) {
-    return for_each_launch(n, kWaveTile, kWaveThreads, [=](dim3 blocks, int64_t at, int64_t count) {
-        if (codec_through(n)) hipLaunchKernelGGL((split_kernel<N, RHO, true>), blocks, dim3(kWaveThreads), 0, s, theta + at, param + at, rho + at, count);
-        else hipLaunchKernelGGL((split_kernel<N, RHO, false>), blocks, dim3(kWaveThreads), 0, s, theta + at, param + at, rho + at, count);
+    return for_each_launch(n, kWaveTile, kWaveThreads, [=](unsigned blocks, int64_t at, int64_t count) {
+        return launch(codec_through(n) ? split_kernel<N, RHO, true> : split_kernel<N, RHO, false>, blocks, kWaveThreads, 0, s, theta + at,
+                      param + at, rho + at, count);
     });
 }
 hipError_t launch_split(int bits, const float* theta, void* param, void* rho, int64_t n, hipStream_t s) {
@@ -1730,9 +1826,9 @@ hipError_t launch_split(int bits, const float* theta, void* param, void* rho, in
 }
 template <int N, typename RHO>
 static hipError_t launch_reconstruct_n(const uint16_t* param, const RHO* rho, float* theta, int64_t n, hipStream_t s) {
-    return for_each_launch(n, kWaveTile, kWaveThreads, [=](dim3 blocks, int64_t at, int64_t count) {
-        if (codec_through(n)) hipLaunchKernelGGL((reconstruct_kernel<N, RHO, true>), blocks, dim3(kWaveThreads), 0, s, param + at, rho + at, theta + at, count);
-        else hipLaunchKernelGGL((reconstruct_kernel<N, RHO, false>), blocks, dim3(kWaveThreads), 0, s, param + at, rho + at, theta + at, count);
+    return for_each_launch(n, kWaveTile, kWaveThreads, [=](unsigned blocks, int64_t at, int64_t count) {
+        return launch(codec_through(n) ? reconstruct_kernel<N, RHO, true> : reconstruct_kernel<N, RHO, false>, blocks, kWaveThreads, 0, s,
+                      param + at, rho + at, theta + at, count);
     });
 }
 hipError_t launch_reconstruct(int bits, const void* param, const void* rho, float* theta, int64_t n, hipStream_t s) {
@@ -1762,18 +1858,18 @@ static hipError_t dispatch_codec(bool variance, bool linear, bool through, F f) 
 }
 hipError_t launch_quantize(bool variance, bool linear, const float* x, void* q, uint16_t* scale, int64_t n, hipStream_t s) {
     return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
-        return for_each_launch(n, kCodecTile, kThreads, [=](dim3 blocks, int64_t at, int64_t count) {
-            hipLaunchKernelGGL((quantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s, x + at,
-                               (uint8_t*)q + at, scale + at / kGroup, count);
+        return for_each_launch(n, kCodecTile, kThreads, [=](unsigned blocks, int64_t at, int64_t count) {
+            return launch(quantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>, blocks, kThreads, 0, s, x + at,
+                          (uint8_t*)q + at, scale + at / kGroup, count);
         });
     });
 }
 hipError_t launch_dequantize(bool variance, bool linear, const void* q, const uint16_t* scale, float* x, int64_t n,
                              hipStream_t s) {
     return dispatch_codec(variance, linear, codec_through(n), [=](auto V, auto L, auto T) {
-        return for_each_launch(n, kCodecTile, kThreads, [=](dim3 blocks, int64_t at, int64_t count) {
-            hipLaunchKernelGGL((dequantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>), blocks, dim3(kThreads), 0, s,
-                               (const uint8_t*)q + at, scale + at / kGroup, x + at, count);
+        return for_each_launch(n, kCodecTile, kThreads, [=](unsigned blocks, int64_t at, int64_t count) {
+            return launch(dequantize_kernel<decltype(V)::value, decltype(L)::value, decltype(T)::value>, blocks, kThreads, 0, s,
+                          (const uint8_t*)q + at, scale + at / kGroup, x + at, count);
         });
     });
 }
@@ -1785,9 +1881,7 @@ int nmse_blocks(int64_t n) {
 }
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, uint64_t* words, uint32_t ticket, hipStream_t s) {
     return dispatch_codec(variance, linear, false, [=](auto V, auto L, auto) {
-        hipLaunchKernelGGL((nmse_kernel<decltype(V)::value, decltype(L)::value>), dim3((unsigned)nmse_blocks(n)), dim3(kNmseThreads), 0, s,
-                           x, n, words, ticket);
-        return hipGetLastError();
+        return launch(nmse_kernel<decltype(V)::value, decltype(L)::value>, (unsigned)nmse_blocks(n), kNmseThreads, 0, s, x, n, words, ticket);
     });
 }
 
@@ -1875,14 +1969,11 @@ __global__ __launch_bounds__(convert_threads(COMPRESS, THROUGH)) void convert_ke
 }
 
 hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs& a, int64_t n_blocks, hipStream_t s) {
-    const dim3 grid((unsigned)n_blocks), block(convert_threads(compress, a.through));
+    const unsigned threads = convert_threads(compress, a.through);
     const int64_t elems = n_blocks * convert_chunk(compress, a.through);
     const unsigned lds = lds_to_hold(convert_resident(compress, has_v, direct, a.through, elems), 0);
-#define FO_CONV(HV, CP, DR)                                                                                   \
-    do {                                                                                                      \
-        if (a.through) hipLaunchKernelGGL((convert_kernel<HV, CP, DR, true>), grid, block, lds, s, a);        \
-        else hipLaunchKernelGGL((convert_kernel<HV, CP, DR, false>), grid, block, lds, s, a);                 \
-    } while (0)
+#define FO_CONV(HV, CP, DR) \
+    return launch(a.through ? convert_kernel<HV, CP, DR, true> : convert_kernel<HV, CP, DR, false>, (unsigned)n_blocks, threads, lds, s, a)
     if (has_v) {
         if (compress) { if (direct) FO_CONV(true, true, true); else FO_CONV(true, true, false); }
         else { if (direct) FO_CONV(true, false, true); else FO_CONV(true, false, false); }
@@ -1891,7 +1982,6 @@ hipError_t launch_convert(bool has_v, bool compress, bool direct, const StepArgs
         else { if (direct) FO_CONV(false, false, true); else FO_CONV(false, false, false); }
     }
 #undef FO_CONV
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ self-test --
@@ -2159,11 +2249,11 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(CheckedCopyArgs a) {
 // Consecutive launches of as many pieces as one may have: 2^22 - 1, or 64 GiB.
 template <typename ARGS>
 static hipError_t launch_pieces(ARGS a, int64_t total, hipStream_t s) {
+    void (*kernel)(ARGS) = copy_kernel;
     for (int64_t first = 0, n; first < total; first += n) {
         n = launch_span(total, first, kCopyThreads);
         a.piece_offset = (uint32_t)first;
-        copy_kernel<<<dim3((unsigned)n), dim3(kCopyThreads), 0, s>>>(a);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch(kernel, (unsigned)n, kCopyThreads, 0, s, a);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -2181,8 +2271,7 @@ __global__ __launch_bounds__(256) void move_kernel(const uint4* src, uint4* dst,
 }
 hipError_t launch_move(const void* src, void* dst, size_t bytes, hipStream_t s) {
     const uint32_t n16 = (uint32_t)((bytes + 15) / 16), blocks = (n16 + 255) / 256;
-    hipLaunchKernelGGL(move_kernel, dim3(blocks < 64 ? blocks : 64), dim3(256), 0, s, (const uint4*)src, (uint4*)dst, n16);
-    return hipGetLastError();
+    return launch(move_kernel, blocks < 64 ? blocks : 64, 256, 0, s, (const uint4*)src, (uint4*)dst, n16);
 }
 
 // Table entries from kernel arguments.  Against a pinned buffer that a kernel reads and reports as read, which the host
@@ -2201,8 +2290,7 @@ __global__ __launch_bounds__(256) void table_update_kernel(TableUpdate u, Tensor
     }
 }
 hipError_t launch_table_update(const TableUpdate& u, TensorDev* table, hipStream_t s) {
-    hipLaunchKernelGGL(table_update_kernel, dim3(1), dim3(256), 0, s, u, table);
-    return hipGetLastError();
+    return launch(table_update_kernel, 1, 256, 0, s, u, table);
 }
 
 // Whether a blob's header and table are what this list would have written, but for the step: *verdict tells the copy that
@@ -2225,9 +2313,8 @@ __global__ __launch_bounds__(kCheckThreads) void check_header_kernel(const uint4
 }
 hipError_t launch_check_header(const void* expected, const void* blob, size_t bytes, uint64_t* verdict, int64_t* out,
                                uint32_t* flag, uint64_t ticket, hipStream_t s) {
-    hipLaunchKernelGGL(check_header_kernel, dim3(1), dim3(kCheckThreads), 0, s, (const uint4*)expected, (const uint4*)blob,
-                       (uint32_t)(bytes / 16), verdict, out, flag, ticket);
-    return hipGetLastError();
+    return launch(check_header_kernel, 1, kCheckThreads, 0, s, (const uint4*)expected, (const uint4*)blob, (uint32_t)(bytes / 16), verdict,
+                  out, flag, ticket);
 }
 
 }  // namespace fo
