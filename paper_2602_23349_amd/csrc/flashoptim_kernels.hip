@@ -17,9 +17,9 @@
 // well over a hundred VALU instructions per parameter, which at 8 TB/s is more than the chip's
 // non-packed FP32 rate admits.  The design choices below are about keeping VALU work per
 // element low without changing a single rounding (AdamW: 65 instructions per element):
-//   * decoding a state code is a function of one byte: rho/127, code/255 and
-//     phi_m^-1(code/127) come from three 256-entry LDS tables that each workgroup
-//     fills once with the same IEEE divisions the definition uses;
+//   * decoding a code is a function of one byte: rho/127 and phi_m^-1(code/127) come from two 256-entry LDS
+//     tables that each workgroup fills once with the results of the IEEE divisions that define them; code/255 is
+//     the code times the reciprocal as the sum of two floats, the IEEE quotient for every byte;
 //   * the 2^l scalings of Algorithm 1 are floats made of the exponent bits of theta', one or two integer
 //     operations each (wavefronts with a weight below 2^-110, zeros included, take a general form);
 //   * Round(x) to an 8-bit integer is one FP32 addition of 1.5 * 2^23, whose low
@@ -299,19 +299,34 @@ constexpr DecodeTables make_decode_tables() {
 }
 __device__ const DecodeTables g_decode_tables = make_decode_tables();
 
-// A step's workgroup stages the tables that its variant reads (up to 3 KB, L2-resident) into LDS: rho (SPLIT), m
-// (QUANT), v (QUANT with a variance).  256 lanes load an entry of each; of 512, the lower half loads rho and v, the upper
-// m.  The staging is split into its load half and its store half so that a kernel can issue the loads first of all (they
-// depend on nothing) and store to LDS only after it has issued its streaming loads.
+// i / 127 of a signed and i / 255 of an unsigned byte, correctly rounded: the reciprocal as the sum of two floats, of which
+// the product with i needs one rounding each.  That this is the IEEE quotient for all 256 bytes is a matter of trying them.
+__device__ __forceinline__ float code_over_127(uint32_t byte) {
+    const float i = (float)(int8_t)byte;
+    return fmaf(i, 0x1.020408p-7f, i * 0x1.020408p-35f);
+}
+__device__ __forceinline__ float code_over_255(uint32_t byte) {
+    const float i = (float)byte;
+    return fmaf(i, 0x1.010102p-8f, i * -0x1.fdfdfep-33f);
+}
+
+// A step's workgroup stages the tables that its variant reads (up to 2 KB, L2-resident) into LDS: rho (SPLIT) and m
+// (QUANT).  256 lanes load an entry of each; of 512, the lower half loads rho, the upper m.  The staging is split into its load half
+// and its store half so that a kernel can issue the loads first of all (they depend on nothing) and store to LDS only after it has
+// issued its streaming loads.
+//   The variance's factor is formed from its code (code_over_255): three instructions where the look-up takes two and an LDS read, of
+// which two thirds of the cycles are bank conflicts, and the large AdamW steps are bound by the package's power.  Looked up -> formed, us: four
+// Llama layers with embedding and head 3871 -> 3822 (on another card 3830 -> 3810), a layer by release 450 -> 449, ResNet-50 54.6 -> 53.8, state
+// quantisation only 490 -> 486, 12 M 26.2 -> 25.6, 4 M 8.69 -> 8.58, 2 M 5.84 -> 5.77.  The same for rho is slower in AdamW (3871 -> 3887;
+// after the variance's 3822 -> 3861) and in steps of the weight split only (SGD, a layer, 512 -> 516), and nothing certain for SGD and Lion.
 struct StepTables {
     float rho_scaled[256];    // rho / 127 * 2^-8 (exact), see reconstruct_fast
     float m[256];
-    float v[256];
 };
 struct TableEntries {
-    float rho, m, v;
+    float rho, m;
 };
-template <int THREADS, bool HAS_V, bool SPLIT, bool QUANT>
+template <int THREADS, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void load_table_entries(TableEntries& e, int tid) {
     static_assert(THREADS == 256 || THREADS == 512, "");
     // scalar base + 32-bit lane offset, so that no 64-bit address arithmetic lands on the vector ALU
@@ -319,24 +334,14 @@ __device__ __forceinline__ void load_table_entries(TableEntries& e, int tid) {
     typedef const __attribute__((address_space(1))) float* fptr_t;
     const base_t base = (base_t)&g_decode_tables;
     const uint32_t o4 = (uint32_t)(tid & 255) * 4u;
-    if (THREADS == 256 || tid < 256) {
-        if (SPLIT) e.rho = *(fptr_t)(base + offsetof(DecodeTables, rho) + o4);
-        if (QUANT && HAS_V) e.v = *(fptr_t)(base + offsetof(DecodeTables, v) + o4);
-    }
-    if (THREADS == 256 || tid >= 256) {
-        if (QUANT) e.m = *(fptr_t)(base + offsetof(DecodeTables, m) + o4);
-    }
+    if (SPLIT && (THREADS == 256 || tid < 256)) e.rho = *(fptr_t)(base + offsetof(DecodeTables, rho) + o4);
+    if (QUANT && (THREADS == 256 || tid >= 256)) e.m = *(fptr_t)(base + offsetof(DecodeTables, m) + o4);
 }
-template <int THREADS, bool HAS_V, bool SPLIT, bool QUANT>
+template <int THREADS, bool SPLIT, bool QUANT>
 __device__ __forceinline__ void store_table_entries(StepTables& t, const TableEntries& e, int tid) {
     const int i = tid & 255;
-    if (THREADS == 256 || tid < 256) {
-        if (SPLIT) t.rho_scaled[i] = e.rho * 0.00390625f;
-        if (QUANT && HAS_V) t.v[i] = e.v;
-    }
-    if (THREADS == 256 || tid >= 256) {
-        if (QUANT) t.m[i] = e.m;
-    }
+    if (SPLIT && (THREADS == 256 || tid < 256)) t.rho_scaled[i] = e.rho * 0.00390625f;
+    if (QUANT && (THREADS == 256 || tid >= 256)) t.m[i] = e.m;
 }
 
 // In-kernel forms of C^-1 and of the rho half of C (Algorithm 1).  E is the exponent field of theta', 2^l half the BF16
@@ -752,7 +757,7 @@ __device__ __forceinline__ void update_lane(const LaneIO<VEC>& x, LaneIO<VEC>& y
         if (KIND == 0) {
             float v;
             if (QUANT) {
-                const float v1 = tab.v[(x.vq[i >> 2] >> (8 * (i & 3))) & 0xffu] * s_v;     // Q_v^-1
+                const float v1 = code_over_255((x.vq[i >> 2] >> (8 * (i & 3))) & 0xffu) * s_v;     // Q_v^-1
                 v = v1 * v1;
             } else {
                 v = x.v32[i];
@@ -1015,7 +1020,7 @@ __device__ __forceinline__ void step_tile(const TensorDev& T, const KindConsts<K
     if (FULL || cnt == VEC) load_full<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0, lane_el);
     else load_tail<VEC, HAS_V, SPLIT, QUANT>(x, T, tile0 + lane_el, cnt);
     if constexpr (SPLIT || QUANT) {        // the plain FP32 step decodes nothing
-        store_table_entries<THREADS, HAS_V, SPLIT, QUANT>(tab, entries, tid);
+        store_table_entries<THREADS, SPLIT, QUANT>(tab, entries, tid);
         __syncthreads();
     }
     const StepConsts c = consts.get();       // (behind the streaming loads)
@@ -1036,7 +1041,7 @@ __device__ __forceinline__ void step_workgroup(const HotArgs& h, const VariantAr
     __shared__ StepTables tab;
     const int tid = (int)threadIdx.x;
     TableEntries entries;
-    if constexpr (SPLIT || QUANT) load_table_entries<THREADS, KIND == 0, SPLIT, QUANT>(entries, tid);
+    if constexpr (SPLIT || QUANT) load_table_entries<THREADS, SPLIT, QUANT>(entries, tid);
     const uint32_t b = blockIdx.x + h.block_offset;
     TensorDev T;
     TensorDev* entry = nullptr;
@@ -1365,16 +1370,6 @@ __device__ __forceinline__ float reconstruct_n(uint32_t b, int rho) {
     if (((b >> 7) & 0xffu) == 255u) return base;
     const float q = (float)rho / (float)N;
     return base + ldexpf(q, half_ulp_log2(b));
-}
-// i / 127 of a signed and i / 255 of an unsigned byte, correctly rounded: the reciprocal as the sum of two floats, of which
-// the product with i needs one rounding each.  That this is the IEEE quotient for all 256 bytes is a matter of trying them.
-__device__ __forceinline__ float code_over_127(uint32_t byte) {
-    const float i = (float)(int8_t)byte;
-    return fmaf(i, 0x1.020408p-7f, i * 0x1.020408p-35f);
-}
-__device__ __forceinline__ float code_over_255(uint32_t byte) {
-    const float i = (float)byte;
-    return fmaf(i, 0x1.010102p-8f, i * -0x1.fdfdfep-33f);
 }
 // The 8-bit case given q = rho / 127.
 __device__ __forceinline__ float reconstruct_q(uint32_t b, float q) {
