@@ -16,7 +16,7 @@
 // for AdamW), but an exactly rounded body, written down as the definitions have it, costs
 // well over a hundred VALU instructions per parameter, which at 8 TB/s is more than the chip's
 // non-packed FP32 rate admits.  The design choices below are about keeping VALU work per
-// element low without changing a single rounding (AdamW: 65 instructions per element):
+// element low without changing a single rounding (AdamW: 64 to 68 instructions per element):
 //   * decoding a code is a function of one byte: rho/127 and phi_m^-1(code/127) come from two 256-entry LDS
 //     tables that each workgroup fills once with the results of the IEEE divisions that define them; code/255 is
 //     the code times the reciprocal as the sum of two floats, the IEEE quotient for every byte;
@@ -314,7 +314,7 @@ __device__ __forceinline__ float code_over_255(uint32_t byte) {
 // (QUANT).  256 lanes load an entry of each; of 512, the lower half loads rho, the upper m.  The staging is split into its load half
 // and its store half so that a kernel can issue the loads first of all (they depend on nothing) and store to LDS only after it has
 // issued its streaming loads.
-//   The variance's factor is formed from its code (code_over_255): three instructions where the look-up takes two and an LDS read, of
+//   The variance's factor is formed from its code (code_over_255): three instructions where the look-up takes one and an LDS read, of
 // which two thirds of the cycles are bank conflicts, and the large AdamW steps are bound by the package's power.  Looked up -> formed, us: four
 // Llama layers with embedding and head 3871 -> 3822 (on another card 3830 -> 3810), a layer by release 450 -> 449, ResNet-50 54.6 -> 53.8, state
 // quantisation only 490 -> 486, 12 M 26.2 -> 25.6, 4 M 8.69 -> 8.58, 2 M 5.84 -> 5.77.  The same for rho is slower in AdamW (3871 -> 3887;
