@@ -317,8 +317,8 @@ __device__ __forceinline__ float code_over_255(uint32_t byte) {
 //   The variance's factor is formed from its code (code_over_255): three instructions where the look-up takes one and an LDS read, of
 // which two thirds of the cycles are bank conflicts, and the large AdamW steps are bound by the package's power.  Looked up -> formed, us: four
 // Llama layers with embedding and head 3871 -> 3822 (on another card 3830 -> 3810), a layer by release 450 -> 449, ResNet-50 54.6 -> 53.8, state
-// quantisation only 490 -> 486, 12 M 26.2 -> 25.6, 4 M 8.69 -> 8.58, 2 M 5.84 -> 5.77.  The same for rho is slower in AdamW (3871 -> 3887;
-// after the variance's 3822 -> 3861) and in steps of the weight split only (SGD, a layer, 512 -> 516), and nothing certain for SGD and Lion.
+// quantisation only 490 -> 486, 12 M 26.2 -> 25.6, 4 M 8.69 -> 8.58, 2 M 5.84 -> 5.77.  The same for rho, after that, gains 0.5 % in large
+// Lion steps (GPT-2 192.4 -> 191.5) and loses elsewhere: four layers 3769 -> 3788, AdamW over 4 M 8.66 -> 8.91, SGD over 5 M 8.97 -> 9.78.
 struct StepTables {
     float rho_scaled[256];    // rho / 127 * 2^-8 (exact), see reconstruct_fast
     float m[256];
