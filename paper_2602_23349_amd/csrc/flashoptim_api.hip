@@ -358,15 +358,13 @@ hipError_t launch_segment(LiveOp op, int kind, bool direct, bool split, bool qua
 // back-to-back launches on the same stream, each covering at most kSegmentElems elements.
 hipError_t launch_op(LiveOp op, int kind, bool direct, bool split, bool quant, fo::StepShape shape, StepArgs a, int64_t blocks,
                      int64_t tile_elems, hipStream_t stream) {
-    const int64_t seg = fo::kSegmentElems / tile_elems > 0 ? fo::kSegmentElems / tile_elems : 1;
-    for (int64_t first = 0; first < blocks; first += seg) {
+    const auto launch_part = [&](int64_t first, int64_t n, bool through) {
         a.block_offset = (uint32_t)first;
-        const int64_t n = blocks - first < seg ? blocks - first : seg;
-        if (op != kOpCompress && op != kOpDecompress) a.through = fo::step_through(kind, split, quant, n * tile_elems);
-        const hipError_t e = launch_segment(op, kind, direct, split, quant, shape, a, n, stream);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+        a.through = through;
+        return launch_segment(op, kind, direct, split, quant, shape, a, n, stream);
+    };
+    if (op != kOpCompress && op != kOpDecompress) return fo::for_each_step_segment(kind, split, quant, blocks, tile_elems, launch_part);
+    return fo::for_each_segment(blocks, tile_elems, [&](int64_t first, int64_t n) { return launch_part(first, n, a.through); });
 }
 
 // Launches one operation over the live tensors (already validated and converted).

@@ -95,7 +95,7 @@ constexpr unsigned lds_to_hold(int resident, unsigned used) {
     return resident == kNoLimit ? 0u : (128u / (unsigned)resident) * 1280u - used;
 }
 
-// Whether the stores of a launch go through to memory at device scope, or stay non-temporal only.  Lines that are passed on
+// Whether the stores of a call go through to memory at device scope, or stay non-temporal only.  Lines that are passed on
 // as they are written leave the DRAM fewer, larger turns from reading to writing and the end of the kernel nothing to write
 // back.  But lists whose arrays fit the 256 MB memory-side cache with room to spare are faster where their lines may wait.
 // In us, non-temporal -> through:
@@ -113,7 +113,7 @@ constexpr int step_array_bytes(int kind, bool split, bool quant) {      // per e
 constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
     return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
 }
-// Whether the tiles of a launch are dealt out among wavefronts (wave_part): where stores go through and there is more than one
+// Whether the tiles of a call are dealt out among wavefronts (wave_part): where stores go through and there is more than one
 // wavefront to a workgroup, but not for the compressed AdamW step.  That one is bound by the package's power and its instructions; dealt
 // out it is slower (four Llama layers with embedding and head 3855 -> 3902 us, a layer 447 -> 454, GPT-2 254.5 -> 259.5), though on a
 // card with some power to spare two layers took 868 -> 848.  The others, in one piece -> dealt out, in us: SGD two Llama layers 689 ->
@@ -180,6 +180,23 @@ struct StepConsts {
 #define FO_SEGMENT_ELEMS (1 << 28)
 #endif
 constexpr int64_t kSegmentElems = FO_SEGMENT_ELEMS;
+// launch_part(first, n) for each of these launches: the tiles first .. first + n - 1 of the call's `tiles`, up to the first that fails.
+template <typename F>
+hipError_t for_each_segment(int64_t tiles, int64_t tile_elems, F launch_part) {
+    const int64_t most = kSegmentElems / tile_elems > 0 ? kSegmentElems / tile_elems : 1;
+    for (int64_t first = 0; first < tiles; first += most) {
+        const hipError_t e = launch_part(first, tiles - first < most ? tiles - first : most);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+// The same for a step, launch_part(first, n, through).  One decision for the whole call: it is also that on which wavefront handles
+// what (step_dealt), and of the tiles that wave_part deals out together some may lie in one launch and some in the next.
+template <typename F>
+hipError_t for_each_step_segment(int kind, bool split, bool quant, int64_t tiles, int64_t tile_elems, F launch_part) {
+    const bool through = step_through(kind, split, quant, tiles * tile_elems);
+    return for_each_segment(tiles, tile_elems, [&](int64_t first, int64_t n) { return launch_part(first, n, through); });
+}
 struct StepArgs {
     TensorDev* tensors;         // device table (multi-tensor launch)
     const uint32_t* coarse;     // device table: tensor index per 2^coarse_shift workgroups (flashoptim_launch.h)
@@ -193,7 +210,7 @@ struct StepArgs {
     uint32_t table_lr_mask;
     uint32_t shared_lr_bits;
     TensorDev single;           // the one tensor of a direct launch
-    bool through;               // stores go through to memory (step_through per launch, convert_through per call)
+    bool through;               // stores go through to memory (step_through, convert_through; the same for all launches of a call)
     StepConsts c;
     const float* sqrt_min_word; // AdamW steps: device word that holds StepConsts::sqrt_min for this device
 };

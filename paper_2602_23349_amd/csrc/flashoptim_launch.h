@@ -40,7 +40,9 @@ constexpr uint32_t entry_of(uint32_t b, uint32_t first, uint32_t last, Begin beg
 // wavefronts of one workgroup handle; consecutive workgroups run on different XCDs.  With a tile in one piece, each XCD asks for pieces
 // of 2 to 16 KB of a stream at a time.  Memory is faster the finer consecutive bytes are spread over the XCDs (a stream's addresses go
 // round its channels every few KB), so the tiles of a whole group of kTileGroup are dealt out: first the first wavefronts of all its
-// workgroups, then the second ones, and so on.  In a tensor's last, incomplete group every tile is in one piece.  The traffic of a step
+// workgroups, then the second ones, and so on.  In a tensor's last, incomplete group every tile is in one piece.  Only if all workgroups
+// of a group go by this is every part of it handled once: whether they do is decided per call, not per launch, since a launch may end within a
+// group (for_each_step_segment).  The traffic of a step
 // without arithmetic over 2^30 elements, 256 lanes, in TB/s, in one piece -> groups of 8 / 16 / 32 / 64 / 128 tiles: AdamW 5.9 -> 6.3 / 6.5 /
 // 6.6 / 6.65 / 6.3; plain FP32 AdamW 5.75 -> 6.3 (8), 6.8 (64), as single wavefronts 6.76.  The steps themselves: step_dealt.  What it
 // costs: a line of scales serves several parts, each on another XCD, and every L2 fetches it (SGD: 1.85 % of the traffic; two or four consecutive

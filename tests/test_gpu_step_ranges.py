@@ -164,6 +164,47 @@ def test_tiles_around_a_group_that_is_dealt_out(kind):
         _same(b, st, f"{kind} numel {st.n}")
 
 
+# A launch holds 2^28 elements; the second one of this list is far below the size from which stores go through, and a group of tiles
+# that are dealt out lies across the cut.  Every element of every array.
+@pytest.mark.parametrize("kind,split,quant", [("sgd", True, True), ("lion", True, True), ("adamw", True, False), ("adamw", False, True)])
+def test_tiles_that_are_dealt_out_across_two_launches(kind, split, quant):
+    arrays = [("param", "thp"), ("rho", "rho"), ("theta", "theta32"), ("m_q", "mq"), ("m_scale", "ms"), ("v_q", "vq"), ("v_scale", "vs"),
+              ("m", "m32"), ("v", "v32")]
+    rng = np.random.default_rng(28)
+    theta = rng.normal(0, 0.02, 1000003).astype(np.float32)
+    grad = (rng.normal(0, 1e-4, 1000003).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    bufs, states, grads = [], [], []
+    for n in (17 * 4096, (1 << 28) + 200000):
+        st = oracle.TensorState(np.resize(theta, n), kind, split_weights=split, quantize_states=quant)
+        b = fo.ParamBuffers(n, kind, split_weights=split, quantize_states=quant)
+        for x, y in arrays:
+            if getattr(b, x) is not None:
+                getattr(b, x).view(torch.uint8).copy_(torch.from_numpy(getattr(st, y).view(np.uint8)))
+        grads.append(np.resize(grad, n))
+        b.grad.copy_(to_dev_u16(grads[-1], torch.bfloat16))
+        b.lr, b.weight_decay = 1e-3, 0.01
+        bufs.append(b)
+        states.append(st)
+    lr, wd = np.float32(1e-3), np.float32(0.01)
+    if kind == "adamw":
+        fo.adamw_step_ex(bufs, HP["beta1"], HP["beta2"], HP["eps"], 1)
+    elif kind == "sgd":
+        fo.sgd_step(bufs, HP["momentum"])
+    else:
+        fo.lion_step(bufs, HP["beta1"], HP["beta2"])
+    for b, st, g in zip(bufs, states, grads):
+        if kind == "adamw":
+            oracle.adamw_step(st, g, lr, wd, HP["beta1"], HP["beta2"], HP["eps"], 1, 16)
+        elif kind == "sgd":
+            oracle.sgd_step(st, g, lr, wd, HP["momentum"], 16)
+        else:
+            oracle.lion_step(st, g, lr, wd, HP["beta1"], HP["beta2"], 16)
+        for x, y in arrays:
+            if getattr(b, x) is not None:
+                got, want = getattr(b, x).view(torch.uint8).cpu().numpy(), getattr(st, y).view(np.uint8)
+                assert np.array_equal(got, want), f"{x}: {int((got != want).sum())} bytes of {want.size}, numel {st.n}"
+
+
 @pytest.mark.parametrize("kind,split,quant,n", [("adamw", False, False, 12582912), ("sgd", False, False, 17616077),
                                                 ("adamw", True, False, 13550829), ("lion", True, False, 19573419),
                                                 ("adamw", False, True, 22020096), ("sgd", False, True, 25165824)])

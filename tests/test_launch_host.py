@@ -217,3 +217,58 @@ def test_a_pair_of_sums_is_read_only_when_all_of_it_is_there(tmp_path):
     """)
     wrong, ready = (int(x) for x in out[0].split())
     assert wrong == 0 and ready == 125
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="needs the HIP headers")
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("split,quant", [(1, 1), (1, 0), (0, 1), (0, 0)])
+def test_every_part_of_a_list_is_handled_once_whatever_launch_it_is_in(tmp_path, kind, split, quant):
+    # tensors of 0 to 31 tiles and a remainder ahead of a large one, so that its groups of tiles lie across the cut at 2^28 elements; the
+    # last launch a few tiles, just below, at and above the size from which stores go through, or nearly whole; a third launch
+    src, exe = tmp_path / "parts.cpp", tmp_path / "parts"
+    src.write_text("""#include <cstdio>
+#include <vector>
+#include "flashoptim_device.h"
+int main() {
+    const int kind = %d;
+    const bool split = %d, quant = %d;
+    const long long limit = (fo::kThroughBytes + fo::step_array_bytes(kind, split, quant) - 1) / fo::step_array_bytes(kind, split, quant);
+    long long launches = 0, wrong = 0, across = 0;
+    for (long long ahead : {1LL, 4096LL, 17 * 4096LL + 1, 31 * 4096LL, 70000LL})
+        for (long long behind : {1000LL, 200000LL, limit - 8192, limit, limit + 8192, (1LL << 28) - 100000, (1LL << 28) + 50000}) {
+            const std::vector<long long> numel = {ahead, (1LL << 28) + behind - ahead - 77, 77};
+            const fo::StepShape shape = fo::step_shape(kind, split, quant, (1LL << 28) + behind);
+            const int tile_elems = fo::chunk_elems(split, quant, shape), waves = fo::step_threads(split, quant, shape) / 64;
+            std::vector<std::vector<unsigned char>> seen;
+            std::vector<long long> first_tile;
+            long long tiles = 0;
+            for (long long n : numel) {
+                const long long k = (n + tile_elems - 1) / tile_elems;
+                first_tile.push_back(tiles);
+                seen.emplace_back(k * waves, 0);
+                tiles += k;
+            }
+            const hipError_t e = fo::for_each_step_segment(kind, split, quant, tiles, tile_elems, [&](int64_t first, int64_t n, bool through) {
+                ++launches;
+                size_t t = 0;
+                for (int64_t b = first; b < first + n; ++b) {
+                    while (t + 1 < numel.size() && first_tile[t + 1] <= b) ++t;
+                    const long long tile = b - first_tile[t], full = numel[t] / tile_elems;
+                    across += b == first && first > 0 && tile %% fo::kTileGroup != 0;
+                    for (int w = 0; w < waves; ++w) {
+                        const long long part = fo::step_dealt(kind, split, quant, through) ? fo::wave_part(tile, w, waves, full) : tile * waves + w;
+                        if (part < 0 || part >= (long long)seen[t].size()) ++wrong; else ++seen[t][part];
+                    }
+                }
+                return hipSuccess;
+            });
+            wrong += e != hipSuccess;
+            for (const auto& s : seen) for (unsigned char c : s) wrong += c != 1;
+        }
+    std::printf("%%lld %%lld %%lld\\n", launches, across, wrong);
+}
+""" % (kind, split, quant))
+    subprocess.run(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    launches, across, wrong = (int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    assert launches == 5 * (6 * 2 + 3) and across > launches // 4 and wrong == 0
