@@ -114,15 +114,16 @@ constexpr bool step_through(int kind, bool split, bool quant, int64_t elems) {
     return elems * step_array_bytes(kind, split, quant) >= kThroughBytes;
 }
 // Whether the tiles of a call are dealt out among wavefronts (wave_part): where stores go through and there is more than one
-// wavefront to a workgroup, but not for the compressed AdamW step.  That one is bound by the package's power and its instructions; dealt
-// out it is slower (four Llama layers with embedding and head 3855 -> 3902 us, a layer 447 -> 454, GPT-2 254.5 -> 259.5), though on a
-// card with some power to spare two layers took 868 -> 848.  The others, in one piece -> dealt out, in us: SGD two Llama layers 689 ->
+// wavefront to a workgroup, but not for AdamW with quantised states, compressed or not.  That one is bound by the package's power and its
+// instructions; dealt out it is slower (compressed, four Llama layers with embedding and head 3855 -> 3902 us, a layer 447 -> 454, GPT-2 254.5 ->
+// 259.5, though on a card with some power to spare two layers took 868 -> 848; state quantisation only, the whole Llama list 17785 -> 18105, a
+// layer 484.3 -> 489.6, GPT-2 277.7 -> 278.8).  The others, in one piece -> dealt out, in us: SGD two Llama layers 689 ->
 // 657, flat 400 M 629 -> 606, GPT-2 198.6 -> 187.9, 24 tensors of 72 M 112.7 -> 110.0; Lion 688 -> 662, 620 -> 603, 199.4 -> 187.3,
 // 113.0 -> 110.3; weight split only, a layer, AdamW 822 -> 782, SGD 532 -> 507, Lion 534 -> 513, 25 M 94.9 -> 90.2, 62.7 -> 60.1, 62.9 -> 60.4; state
-// quantisation only, a layer 497 -> 490, 405 -> 396, 404 -> 396, 25 M the same.  Launches whose stores do not go through are 1-2 %
-// slower dealt out (SGD over 10 M elements 16.8 -> 17.0 us).
+// quantisation only, SGD the whole list 14695 -> 14681, a layer 399.2 -> 399.5, GPT-2 230.7 -> 227.6, Lion 14743 -> 14680, 400.6 -> 399.1, 232.3 ->
+// 228.1.  Calls whose stores do not go through are 1-2 % slower dealt out (SGD over 10 M elements 16.8 -> 17.0 us).
 constexpr bool step_dealt(int kind, bool split, bool quant, bool through) {
-    return through && (split || quant) && !(kind == 0 && split && quant);
+    return through && (split || quant) && !(kind == 0 && quant);
 }
 // Conversions to FP32 are dealt out where their stores go through (in one piece -> dealt out, with the limits above on both sides, AdamW
 // GPT-2 341.0 -> 326.5 us, a Llama layer 609.6 -> 571.0, flat 300 M 822 -> 798, 40 M 110.0 -> 105.8; SGD 237.5 -> 228.0, 413.1 -> 399.7,

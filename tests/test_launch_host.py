@@ -272,3 +272,23 @@ int main() {
                     os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     launches, across, wrong = (int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
     assert launches == 5 * (6 * 2 + 3) and across > launches // 4 and wrong == 0
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="needs the HIP headers")
+def test_which_steps_deal_their_tiles_out(tmp_path):
+    # AdamW with quantised states, bound by power, is slower that way; a single wavefront has nothing to deal out
+    src, exe = tmp_path / "dealt.cpp", tmp_path / "dealt"
+    src.write_text("""#include <cstdio>
+#include "flashoptim_device.h"
+int main() {
+    for (int kind = 0; kind < 3; ++kind)
+        for (int k = 0; k < 4; ++k)
+            if (fo::step_dealt(kind, k & 1, k & 2, true)) std::printf("%d%s%s ", kind, k & 1 ? "s" : "", k & 2 ? "q" : "");
+    for (int kind = 0; kind < 3; ++kind)
+        for (int k = 0; k < 4; ++k) if (fo::step_dealt(kind, k & 1, k & 2, false)) return 1;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    assert out.split() == ["0s", "1s", "1q", "1sq", "2s", "2q", "2sq"]
