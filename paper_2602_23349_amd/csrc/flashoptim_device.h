@@ -274,12 +274,16 @@ int nmse_blocks(int64_t n);
 // words: kNmseWords words of pinned memory for each of the nmse_blocks(n) workgroups, its sums with this call's ticket (nmse_word)
 hipError_t launch_nmse(bool variance, bool linear, const float* x, int64_t n, uint64_t* words, uint32_t ticket, hipStream_t s);
 hipError_t launch_copy(CopyArgs a, hipStream_t s);
-// The blobs whose unpacking takes that way: their header and table are an access per lane, and the launch that it saves is worth what the
-// barrier costs.  Smaller ones are bound by the wait for the verdict, which a kernel of its own reaches sooner.  In us, a kernel ahead of the
-// copy -> checked by every workgroup, a pack and an unpack: 5 MB 15.8 -> 16.8, 15 MB 20.4 -> 20.7, 33 MB 26.6 -> 24.3, 103 MB 68.5 -> 64.1, 205 MB
-// 133.9 -> 130.0; an unpack: ResNet-50's 131 MB 46.3 -> 45.1, 512 MB 163.0 -> 163.3, GPT-2's 638 MB 193.6 -> 195.9, 1.5 GB 456 -> 462.
+// The blobs whose unpacking takes that way: every workgroup, for 16 KB of its own, reads header and table twice (the list's and the blob's), so
+// they are short (252 tensors), and the launch that it saves is worth what the barrier costs.  Smaller ones are bound by the wait for the
+// verdict, which a kernel of its own reaches sooner.  In us, a kernel ahead of the copy -> checked by every workgroup, a pack and an unpack, few tensors:
+// 5 MB 15.8 -> 16.8, 15 MB 20.4 -> 20.7, 33 MB 26.6 -> 24.3, 103 MB 68.5 -> 64.1, 205 MB 133.9 -> 130.0; an unpack: ResNet-50's 131 MB 46.3 -> 45.1,
+// 512 MB 163.0 -> 163.3, GPT-2's 638 MB 193.6 -> 195.9, 1.5 GB 456 -> 462.  An unpack of 28 / 101 / 244 MB by the tensors in its table: 60 of them
+// 13.7 -> 12.6, 35.3 -> 34.4, 79.4 -> 77.9; 200 15.0 -> 13.9, 35.9 -> 35.5, 80.4 -> 80.1; 252 14.2 -> 14.4, 37.1 -> 37.3, 81.6 -> 81.2; 330 16.4 -> 15.2,
+// 36.4 -> 37.3, 82.2 -> 81.6; 500 14.9 -> 16.0, 38.7 -> 40.2, 82.1 -> 83.8; 1020 25.2 -> 25.0, 48.0 -> 49.0, 84.6 -> 97.0.
+constexpr int64_t kCheckedHeader = 4096;
 constexpr bool checked_copy(int64_t blob_bytes, int64_t header_bytes) {
-    return blob_bytes >= (int64_t)24 << 20 && blob_bytes <= (int64_t)256 << 20 && header_bytes <= kCopyPiece;
+    return blob_bytes >= (int64_t)24 << 20 && blob_bytes <= (int64_t)256 << 20 && header_bytes <= kCheckedHeader;
 }
 hipError_t launch_checked_copy(CheckedCopyArgs a, hipStream_t s);
 // Moves `bytes` (rounded up to 16: both buffers must have room) from pinned host memory to device memory.

@@ -292,3 +292,19 @@ int main() {
                     os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
     assert out.split() == ["0s", "1s", "1q", "1sq", "2s", "2q", "2sq"]
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"), reason="needs the HIP headers")
+def test_long_tables_are_not_read_by_every_workgroup_of_a_copy(tmp_path):
+    # a header of 64 bytes and 16 for each tensor, in units of 64: 252 tensors are 4096 bytes
+    src, exe = tmp_path / "checked.cpp", tmp_path / "checked"
+    src.write_text("""#include <cstdio>
+#include "flashoptim_device.h"
+int main() {
+    for (long long n : {1, 252, 253, 1020})
+        for (long long mb : {23, 24, 256, 257}) std::printf("%d", fo::checked_copy(mb << 20, 64 + (16 * n + 63) / 64 * 64));
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2602_23349_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout == "0110" "0110" "0000" "0000"
