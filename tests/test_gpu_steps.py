@@ -111,6 +111,14 @@ def test_stream_probe_changes_nothing_in_the_large_shape(kind, monkeypatch):
 
 
 @pytest.mark.parametrize("kind", ["adamw", "sgd", "lion"])
+def test_stream_probe_changes_nothing_where_its_tiles_are_dealt_out(kind, monkeypatch):
+    # (29.4 M elements are enough for every kind; whole groups of 32 tiles of 2048 elements and a part of one, then a ragged tile)
+    specs = W.odd_sizes()[:4] + [W.ParamSpec("big", (29360128 + 5 * 2048 + 77,), "matrix"), W.ParamSpec("group", (32 * 2048 + 1,), "matrix")]
+    monkeypatch.setattr(W, "odd_sizes", lambda: specs)
+    test_stream_probe_changes_nothing(kind)
+
+
+@pytest.mark.parametrize("kind", ["adamw", "sgd", "lion"])
 def test_stream_probe_changes_nothing(kind):
     # the measurement aid moves a step's bytes and must leave every array as it was, ragged ends
     # and single-tensor (table-free) lists included
