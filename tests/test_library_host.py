@@ -190,3 +190,19 @@ def test_step_calls_read_the_list_that_they_are_given(name):
         tl.array = (B._TensorEx * 1)()
         with pytest.raises(C.ArgumentError):
             getattr(fo, name)(tl, *hyper, stream=0)
+
+
+def test_library_is_stale_once_a_source_a_header_or_its_flags_are_newer(tmp_path, monkeypatch):
+    # (the flags, which the exact arithmetic rests on, stand in build.py itself)
+    from paper_2602_23349_amd import build as hip_build
+    lib = str(tmp_path / "lib.so")
+    monkeypatch.setattr(hip_build, "LIB", lib)
+    assert hip_build.stale()
+    open(lib, "w").close()
+    newer = None
+    monkeypatch.setattr(hip_build.os.path, "getmtime", lambda p: 2.0 if p == newer else 1.0)
+    assert not hip_build.stale()
+    for newer in hip_build.SOURCES + hip_build.HEADERS + [os.path.abspath(hip_build.__file__)]:
+        assert hip_build.stale(), newer
+    newer = lib
+    assert not hip_build.stale()
