@@ -785,7 +785,7 @@ int wait_space(CallSpace& w, hipError_t e, hipStream_t stream, bool last, F is_s
 // plan holds them on the device.  When packing they go with the copy, and the step is an argument of the kernel: nothing is
 // staged per call, calls behind any amount of earlier work never wait, and a captured one can be replayed.  When unpacking
 // (check: the workspace that the host will wait for) a kernel compares them with the blob's ahead of the copy, which does
-// nothing unless they agree.
+// nothing unless they agree, or the workgroups of the copy do so themselves (checked_copy).
 int run_copy(int kind, const flashoptim_tensor* t, int64_t n, uint8_t* blob, bool pack, int64_t total_bytes, int64_t step,
              hipStream_t stream, CallSpace* check = nullptr) {
     // the identity: every tensor, those without elements included (they lengthen the header and move the sections)
@@ -1228,7 +1228,8 @@ int flashoptim_checkpoint_unpack(int kind, const void* blob, int64_t blob_bytes,
     int64_t found[2];
     std::memcpy(found, w.host, sizeof(found));
     if (!found[0]) {
-        // the copy that was not admitted has to have run before the workspace's next use can write its word
+        // The copy that was not admitted has to have run before the workspace's next use can write its word.  (One that checks the blob
+        // itself has no word; it is waited for all the same, so that a refused call leaves nothing to run.)
         const hipError_t e = hipStreamSynchronize(stream);
         if (e != hipSuccess) destroy_space(w);
         FO_HIP(e);

@@ -79,11 +79,15 @@ constexpr int step_resident(int kind, bool split, bool quant, StepShape shape, b
 // Layout conversions, in us.
 //   To FP32, 256 lanes, tiles dealt out (below): of AdamW's state 4 (with 4 / 5 / 6 / 8, flat 300 M 798 / 808 / 814 / 820, a Llama layer
 //       571 / 579 / 580 / 589, GPT-2 326.5 / 329.2 / 328.4 / 334.0, flat 40 M 105.8 / 106.8 / 107.3 / 108.7), but 6 for lists of fewer than
-//       2^26 elements (60 tensors of 60 M 159.6 / 157.7 / 156.1 / 157.0); of the others' 6 (GPT-2 257 / 235 / 228 / 226, flat 300 M 591 / 546 /
+//       2^26 elements (60 tensors of 60 M 159.6 / 157.7 / 156.1 / 157.0), where the two are within 1 % of each other on either side (with 4 / 6, 60
+//       uneven tensors of 40 M 108.7 / 107.4, 60 M 161.1 / 159.4, 72 M 191.3 / 191.4, 90 M 238.5 / 237.0; 20 of them 107.6 / 107.1, 160.4 / 159.9,
+//       190.0 / 191.4, 240.6 / 240.8); of the others' 6 (GPT-2 257 / 235 / 228 / 226, flat 300 M 591 / 546 /
 //       545 / 543).  In one piece: 7 / 6 / 5 workgroups 5 M 15.8 / 15.8 / 15.9; under 2^22 elements no limit (2 M 6.5).
 //   From FP32, single wavefronts: 20 for lists (with 18 / 20 / 22, AdamW GPT-2 321.9 / 318.9 / 329.0, a layer 563.7 / 559.8 / 581.8, 60 tensors of
 //       60 M 157.4 / 154.8 / 155.9; SGD 229.8 / 222.7 / 224.1, 404.9 / 392.9 / 397.2, 113.9 / 110.9 / 108.8), 18 for a single tensor (AdamW 300 M
-//       766.7 / 785.6 / 803.4, 200 M 510 / 525 / 541, 40 M 104.4 / 105.0 / 107.1; SGD 532 / 537 / 548, 354 / 356 / 368, 74.2 / 73.6 / 74.4).
+//       766.7 / 785.6 / 803.4, 200 M 510 / 525 / 541, 40 M 104.4 / 105.0 / 107.1; SGD 532 / 537 / 548, 354 / 356 / 368, 74.2 / 73.6 / 74.4), of which
+//       those of SGD and Lion up to 60 M would be 1 % faster with 20 (34 M 62.9 / 62.1, 60 M 108.5 / 107.3, 100 M 178.7 / 179.1; AdamW 34 M 89.1 /
+//       88.5, 60 M 154.5 / 156.8).
 constexpr int convert_resident(bool compress, bool has_v, bool direct, bool through, int64_t elems) {
     if (compress) return !through ? kNoLimit : direct ? 18 : 20;
     if (elems < ((int64_t)1 << 22)) return kNoLimit;

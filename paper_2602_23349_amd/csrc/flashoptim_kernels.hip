@@ -316,7 +316,8 @@ __device__ __forceinline__ float code_over_255(uint32_t byte) {
 // issued its streaming loads.
 //   The variance's factor is formed from its code (code_over_255): three instructions where the look-up takes one and an LDS read, of
 // which two thirds of the cycles are bank conflicts, and the large AdamW steps are bound by the package's power.  Looked up -> formed, us: four
-// Llama layers with embedding and head 3871 -> 3822 (on another card 3830 -> 3810), a layer by release 450 -> 449, ResNet-50 54.6 -> 53.8, state
+// Llama layers with embedding and head 3871 -> 3822, 3830 -> 3810 and, with the changes just before it, 3874 -> 3858 on three cards, the last
+// within what two runs differ by; a layer by release 450 -> 449, ResNet-50 54.6 -> 53.8, state
 // quantisation only 490 -> 486, 12 M 26.2 -> 25.6, 4 M 8.69 -> 8.58, 2 M 5.84 -> 5.77.  The same for rho, after that, gains 0.5 % in large
 // Lion steps (GPT-2 192.4 -> 191.5) and loses elsewhere: four layers 3769 -> 3788, AdamW over 4 M 8.66 -> 8.91, SGD over 5 M 8.97 -> 9.78.
 struct StepTables {
@@ -928,6 +929,8 @@ __device__ __forceinline__ int64_t locate_tile(const StepArgs& a, TensorDev& T) 
 // streaming loads.  Only what a kind reads is passed (a byte costs the host 2.6 ns).  With one struct of 200 bytes for all, launched by
 // <<<>>>, -> without -> with preloaded arguments, us a call: AdamW over 2^20 elements 4.72 -> 4.71 -> 4.56, 2^21 6.30 -> 6.28 -> 6.12, 25 odd sizes
 // 4.33 -> 4.10 -> 4.05; SGD 2^21 4.26 -> 4.23 -> 4.05, 2^22 6.21 -> 6.34 -> 5.95, ten tensors of 5 M 9.37 -> 9.29 -> 9.06, ResNet-50 40.9 -> 40.8 -> 40.5.
+// (Where the host sets the pace, its differ more from run to run than this: AdamW over 2^20 elements on another machine 5.07 -> 5.01.  The kernel alone
+// takes 4.6 there, 5.0 before.)
 template <bool DIRECT, bool HAS_V>
 struct TensorArgs {};       // (of a list: everything is in the table)
 template <>
@@ -1870,7 +1873,9 @@ hipError_t launch_dequantize(bool variance, bool linear, const void* q, const ui
     });
 }
 // Three workgroups to a compute unit, four for long arrays: the host reads as many pairs, which takes it some microseconds, and more
-// in flight pays only where there is much to read (768 / 1024 / 2048 workgroups, 5 M values 15.4 / 16.5 / 21; variance, 100 M, 79.6 / 77.5).
+// in flight pays only where there is much to read.  With 768 / 1024 workgroups, momentum (variance), us: 5 M values 15.4 / 16.5, with 2048 21; 12 M
+// 19.2 / 19.2 (20.9 / 20.8), 20 M 24.4 / 24.5 (25.9 / 25.8), 28 M 29.6 / 28.8 (31.9 / 30.6), 34 M 33.7 / 32.9 (36.3 / 35.1), 45 M 39.9 / 39.3 (43.0 /
+// 41.6), 60 M 49.1 / 48.3 (54.8 / 52.4), 100 M 77.1 / 76.1 (83.7 / 81.8).  They are equal up to 20 M; from there to the line at 2^25 it costs up to 4 %.
 int nmse_blocks(int64_t n) {
     const int64_t tiles = (n + kNmseTile - 1) / kNmseTile, most = n < ((int64_t)1 << 25) ? 768 : kNmseMaxBlocks;
     return (int)(tiles < most ? tiles : most);

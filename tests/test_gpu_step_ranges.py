@@ -368,7 +368,7 @@ def test_unpacking_checks_every_word_of_the_table(n_tensors):
 
 
 # Blobs of 24 to 256 MB whose header and table are 4 KB or less (252 tensors) are checked by every workgroup of the copy: both sides of these
-# limits, and every word of a long and of a short table.
+# limits, and words all over a long and a short table.
 @pytest.mark.parametrize("n_tensors,n", [(252, 110_000), (253, 110_000), (1020, 26_000), (1021, 26_000), (3, 9_000_000), (3, 1_900_000), (3, 2_200_000)])
 def test_unpacking_checks_every_word_within_the_copy(n_tensors, n):
     sizes = [n + i % 7 for i in range(n_tensors)]
